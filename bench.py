@@ -6,9 +6,9 @@ Workload: the polydisperse microstructure (256^3 unit cell, 60 seeded RSA
 spheres with radii U(10, 24) voxels, stiffness contrast 20) at the state of
 its first load increment (macroscopic stretch 1.0025 along e1).  One "step"
 is one CG iteration of the linear system of the first Newton correction
-(eq. (30) with the tangent at F = Fbar): the matvec (fused contraction and
-N2 transform, N1 pass, N0 pass with the projection, inverse passes of the
-potential) and the CG updates and FP64 reductions.  Warmup iterations run
+(eq. (30) with the tangent at F = Fbar): the matvec (contraction and its
+divergence, N2 and N1 passes, N0 pass with the projection, inverse passes)
+and the CG updates and FP64 reductions.  Warmup iterations run
 first, untimed; then exactly --steps iterations are timed between two
 device synchronisations.  The system is assembled before the warmup.
 
@@ -17,7 +17,7 @@ The mixed form's figures are reported alongside, together with one complete
 Newton solve of the increment in each form (end-to-end time to Newton 1e-8,
 CG 1e-10, and the mixed form's field error against the FP64 solution).
 The roofline object refers to the kernel class with the largest time in the
-warmup (the fused front kernel); its average launch duration comes from HIP
+warmup (the contraction and divergence kernel); its average launch duration comes from HIP
 events taken by the kernel launches themselves during the timed iterations.
 
     python bench.py [--gpus 1] [--steps 40] [--warmup 5] [--n 256] [--no-cpu]
@@ -41,8 +41,19 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 
 # Algorithmic bytes per voxel and launch for each kernel class of the
-# mechanics CG iteration, in words of the working precision (9-component
-# fields; the spectrum occupies the same bytes as the real field).
+# mechanics CG iteration, in words of the working precision (the spectrum
+# occupies the same bytes as the real field): 63 in all.
+WORDS_MOVED = {
+    "front": 18,      # read pi (3) + state (12); write the divergence q (3)
+    "r2c": 6,         # N2 pass of q: read 3, write 3
+    "axis": 6,        # N1 pass: read 3, write 3
+    "zproj": 12,      # N0 pass: read q (3) + residual (3), write residual (3) + z (3)
+    "axis3": 6,       # inverse N1 pass: read 3, write 3
+    "c2r3": 15,       # inverse N2 pass and CG vectors: read z (3) + pi (3) + xi (3), write pi (3) + xi (3)
+}
+# The iteration that carried nine components through the N2 and N1 passes and
+# the residual in real space (81 words): the model of profiles that name no
+# model of their own, and the unit of the older records.
 WORDS_PER_VOXEL = {
     "front": 36,      # read rho, pi, xi (9) + state (12); write xi, pi (6), spectrum (9)
     "axis": 15,       # N1 pass of the 9-component spectrum: read 9, write 6 (2 merged fields per row)
@@ -149,7 +160,7 @@ def run_cg_form(work, form, steps, warmup, solve=True):
         plan.cg_iterate(warmup)
     torch.cuda.synchronize()
     prof_all = plan.profile_end()
-    timed = [k for k in WORDS_PER_VOXEL if prof_all[k][1] > 0]
+    timed = [k for k in WORDS_MOVED if prof_all[k][1] > 0]
     dominant = max(timed, key=lambda k: prof_all[k][0]) if timed else "front"
     plan.profile_begin(passes=[dominant])
     torch.cuda.synchronize()
@@ -160,7 +171,7 @@ def run_cg_form(work, form, steps, warmup, solve=True):
     prof = plan.profile_end()
     print(f"[{form}] {steps} CG iterations (after {warmup} warmup) in {elapsed * 1e3:.2f} ms, "
           f"err_res before the correction {err0:.3e}, ||r||/||b|| {it['relres']:.3e}", flush=True)
-    out = dict(elapsed=elapsed, cg_iters=steps, prof=prof, prof_all=prof_all, relres=it["relres"], err0=err0)
+    out = dict(elapsed=elapsed, cg_iters=steps, words=WORDS_MOVED, prof=prof, prof_all=prof_all, relres=it["relres"], err0=err0)
     if solve:
         F.zero_()
         F[0] = 1.0
@@ -209,7 +220,7 @@ def run_ramp_form(work, form, steps, warmup, first=1):
               f"cg {[s['lin_history'] for s in st['newton']]}", flush=True)
     torch.cuda.synchronize()
     prof_all = plan.profile_end()
-    timed = [k for k in WORDS_PER_VOXEL if prof_all[k][1] > 0]
+    timed = [k for k in WORDS_MOVED if prof_all[k][1] > 0]
     dominant = max(timed, key=lambda k: prof_all[k][0]) if timed else "front"
     plan.profile_begin(passes=[dominant])
     cg_iters = 0
@@ -228,7 +239,8 @@ def run_ramp_form(work, form, steps, warmup, first=1):
     prof = plan.profile_end()
     Pm = plan.homogenized_stress()
     plan.close()
-    return dict(elapsed=elapsed, cg_iters=cg_iters, newton_iters=newton_iters, prof=prof, prof_all=prof_all,
+    return dict(elapsed=elapsed, cg_iters=cg_iters, newton_iters=newton_iters, words=WORDS_MOVED, prof=prof,
+                prof_all=prof_all,
                 P11=float(Pm[0, 0]))
 
 
@@ -244,6 +256,8 @@ def measured_traffic(kernel, word_bytes):
         return None
     rec = json.load(open(path))
     h = hashlib.sha256()
+    if not all(os.path.exists(os.path.join(ROOT, f)) for f in rec["source_files"]):
+        return None
     for f in rec["source_files"]:
         h.update(open(os.path.join(ROOT, f), "rb").read())
     if h.hexdigest() != rec["source_sha256"]:
@@ -257,22 +271,23 @@ def roofline(res, N, word_bytes):
     (res["prof_all"]) when there were any."""
     prof = res["prof"]
     warm = res.get("prof_all")
-    cands = {k: prof[k] for k in WORDS_PER_VOXEL if prof[k][1] > 0}
+    words = res.get("words", WORDS_PER_VOXEL)
+    cands = {k: prof[k] for k in words if prof[k][1] > 0}
     name = max(cands, key=lambda k: cands[k][0])
     ms, launches = cands[name]
     avg_s = ms / 1e3 / launches
-    bytes_per_launch = WORDS_PER_VOXEL[name] * word_bytes * N
+    bytes_per_launch = words[name] * word_bytes * N
     achieved = bytes_per_launch / avg_s / 1e9
     traffic = measured_traffic(name, word_bytes) if N == 256 ** 3 else None
     return dict(kernel=name, bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS, unit="GB/s",
                 frac=round(achieved / HBM_PEAK_GBS, 4), traffic=traffic,
                 avg_launch_us=round(avg_s * 1e6, 2), launches=launches,
                 bytes_per_launch=bytes_per_launch,
-                per_class=per_class(warm if warm and any(n > 0 for _, n in warm.values()) else prof, N,
-                                    word_bytes))
+                per_class=per_class(warm if warm and any(n > 0 for _, n in warm.values()) else prof, N, word_bytes,
+                                    words))
 
 
-def per_class(prof, N, word_bytes):
+def per_class(prof, N, word_bytes, words=WORDS_MOVED):
     """Per kernel class: total ms, counted launches, mean us per launch and,
     for the CG-iteration classes, algorithmic GB/s."""
     out = {}
@@ -281,8 +296,8 @@ def per_class(prof, N, word_bytes):
             continue
         avg = ms / n
         d = {"ms": round(ms, 2), "launches": int(n), "avg_us": round(1e3 * avg, 1)}
-        if k in WORDS_PER_VOXEL:
-            d["GB/s"] = round(WORDS_PER_VOXEL[k] * word_bytes * N / (avg * 1e-3) / 1e9, 1)
+        if k in words:
+            d["GB/s"] = round(words[k] * word_bytes * N / (avg * 1e-3) / 1e9, 1)
         out[k] = d
     return out
 

@@ -75,12 +75,12 @@ k_newton_gate(const KrylovScalars* __restrict__ ks, NewtonCtl* __restrict__ nc, 
 // the item's partial sums of (G*P) : (G*P).  Converged items and items out of
 // iterations finish; the others count the iteration about to be taken.
 __global__ void __launch_bounds__(1024)
-k_newton_check(const double* __restrict__ partials, int nparts, NewtonCtl* __restrict__ nc, int* __restrict__ idle,
+k_newton_check(const double* __restrict__ partials, Parts parts, NewtonCtl* __restrict__ nc, int* __restrict__ idle,
                int st_noconv) {
   __shared__ double red[16];
   const int b = blockIdx.x;
   if (idle[b]) return;
-  const double s = sum_partials(partials + (long)b * nparts, nparts, red);
+  const double s = sum_parts(partials + (long)b * parts.stride(), parts, red);
   if (threadIdx.x != 0) return;
   NewtonCtl& c = nc[b];
   const double err = sqrt(s) / c.den;
@@ -104,12 +104,12 @@ k_newton_check(const double* __restrict__ partials, int nparts, NewtonCtl* __res
 // Start the item's CG on the right-hand side whose partial sums of b.b are
 // given (rr0 = rr = b.b, iteration 0; tol2 and maxit stay as set).
 __global__ void __launch_bounds__(1024)
-k_newton_cg_start(const double* __restrict__ partials, int nparts, KrylovScalars* __restrict__ ks,
+k_newton_cg_start(const double* __restrict__ partials, Parts parts, KrylovScalars* __restrict__ ks,
                   NewtonCtl* __restrict__ nc, const int* __restrict__ idle) {
   __shared__ double red[16];
   const int b = blockIdx.x;
   if (idle[b]) return;
-  const double s = sum_partials(partials + (long)b * nparts, nparts, red);
+  const double s = sum_parts(partials + (long)b * parts.stride(), parts, red);
   if (threadIdx.x != 0) return;
   KrylovScalars& k = ks[b];
   k.rr0 = s;
@@ -119,19 +119,6 @@ k_newton_cg_start(const double* __restrict__ partials, int nparts, KrylovScalars
   k.beta = 0.0;
   k.done = (s == 0.0) ? 1 : 0;
   nc[b].started = 1;
-}
-
-// Per-item field kernels: grid.y = item, n values per item; masked by idle.
-// F += dF (dF in type T).
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_items_axpy(double* __restrict__ F, const T* __restrict__ dF, const int* __restrict__ idle, long n) {
-  const int b = blockIdx.y;
-  if (idle[b]) return;
-  F += (long)b * n;
-  dF += (long)b * n;
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) F[i] += (double)dF[i];
 }
 
 }  // namespace fg

@@ -1,0 +1,880 @@
+// Kernels of the CG on the operator of eq. (30) in divergence form.
+//
+// With D the corner-stencil gradient (fg_potential.hpp) every vector of the
+// CG is a discrete gradient (r = D z, p = D pi, x = D xi), and the projection
+// of a field Y is G*Y = D (D^T D)^+ D^T Y: its 3-component divergence
+// s = D^T Y carries everything the projection needs.  The CG on G K is then
+//   z_k = (D^T D)^+ s_k,  pi_k = z_k + beta pi_{k-1},  q = D^T K : (D pi_k),
+//   alpha = r.r / p.Kp,   s_{k+1} = s_k - alpha q,     xi += alpha pi_k,
+//   r.r = |D z|^2 = sum_q |s^(q)|^2 / (N |r(q)|^2)   (Parseval),
+// the same scalars and iterates as the 9-component CG of Alg. 1, with three
+// components through the transforms instead of nine, and with the residual
+// kept where it is needed, in the spectrum (s^ is read and written by the N0
+// pass; no real-space residual update).  Passes of one iteration (words per
+// voxel, 64 in all):
+//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     15
+//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6
+//   k_r2c_edges  N2 pass of q                                                6.6
+//   k_n1         N1 pass into the block layout (+ alpha)                     6
+//   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12
+//   k_n1         inverse N1 pass                                             6
+// (the iteration that carried nine components through the N2 and N1 passes
+// and the residual in real space moved 81).
+#pragma once
+#include "fg_fft.hpp"
+#include "fg_fft3.hpp"
+#include "fg_potential.hpp"
+#include "fg_tangent.hpp"
+
+namespace fg {
+
+// W consecutive voxels of one plane in one 16-byte (or 8-byte) access.
+template <typename R, int W> struct FrontPack;
+template <> struct FrontPack<double, 2> { using type = double2; };
+template <> struct FrontPack<float, 2> { using type = float2; };
+template <> struct FrontPack<float, 4> { using type = float4; };
+template <typename R, typename PV> __device__ __forceinline__ R pk_get(const PV& v, int w) {
+  return reinterpret_cast<const R*>(&v)[w];
+}
+template <typename R, typename PV> __device__ __forceinline__ void pk_set(PV& v, int w, R a) {
+  reinterpret_cast<R*>(&v)[w] = a;
+}
+// nontemporal load of a W-vector (streams read once: the tangent state and
+// the solution potential), so that they do not push the stencil's neighbour
+// lines of rho and pi out of the caches
+template <typename R, int W, typename PV> __device__ __forceinline__ PV pk_load_nt(const PV* p) {
+  typedef R nvw __attribute__((ext_vector_type(W)));
+  const nvw a = __builtin_nontemporal_load(reinterpret_cast<const nvw*>(p));
+  PV v;
+#pragma unroll
+  for (int w = 0; w < W; ++w) pk_set<R>(v, w, a[w]);
+  return v;
+}
+
+// Per-item mask of a launch: items with a nonzero word are left alone.
+struct Gate {
+  const int* p = nullptr;
+  int stride = 0;
+  __device__ __forceinline__ bool operator()(long item) const { return p && p[item * stride] != 0; }
+  static Gate done(const KrylovScalars* ks) { return Gate{&ks->done, (int)(sizeof(KrylovScalars) / sizeof(int))}; }
+  static Gate flags(const int* f) { return Gate{f, f ? 1 : 0}; }
+};
+
+// Layout of a spectral component after the N1 pass: blocks of B adjacent kx
+// columns (128 bytes) of one ky, the N0 lines of a block together: element
+// (i0, ky, kx) at ((kx / B) N1 + ky) bstr + i0 B + kx % B.  The N0 pass then
+// reads and writes whole contiguous blocks, and the N1 passes still touch
+// whole 128-byte lines.  The kx = 0 column (two real columns packed in one,
+// see k_n0) lives in a compact array of its own, [component][ky][i0].
+struct BlockLayout {
+  int B;
+  long bstr;  // complex values from one block to the next
+  long cstr;  // complex values of a component
+  __host__ __device__ __forceinline__ long at(int n1, int ky, int kx) const {
+    const int b = kx / B;
+    return ((long)b * n1 + ky) * bstr + (kx - b * B);
+  }
+};
+template <typename R> constexpr int block_cols(int M) {
+  int b = 1;
+  while (M % (2 * b) == 0 && 2 * b * (int)sizeof(cplx<R>) <= 128) b *= 2;
+  return b;
+}
+// Blocks of a power-of-two size are kept one line apart from each other.
+template <typename R> inline BlockLayout block_layout(int n0, int n1, int M) {
+  BlockLayout l;
+  l.B = block_cols<R>(M);
+  l.bstr = (long)n0 * l.B + (n0 >= 64 ? l.B : 0);
+  l.cstr = (M / l.B) * (long)n1 * l.bstr;
+  return l;
+}
+
+// ---------------------------------------------------------------------------
+// Source of the tensor field whose divergence is taken: the tangent of either
+// law applied to D pi, or a stored 9-component field.
+constexpr int kSrcField = 2;
+
+// Lines (i1) and lanes along N2 of a wave's patch: 8 x 8 lanes of W voxels,
+// one 128-byte line of each plane per patch row.
+constexpr int kPatch = 8;
+
+// What the patches of k_cg_op cannot add up themselves, per component of q:
+//   col  the step across the upper N2 edge of a patch: [line][patch] holds the
+//        contribution of patch `patch` to the last node before it
+//   row  the step across the upper line edge of a block of 8 lines:
+//        [i0][block][x] holds the contribution of block `block` to the line
+//        before it, and [i0][block][patch] in cor that of the corner.
+// k_r2c_edges adds them while it loads q.
+struct EdgeLayout {
+  int W8;         // voxels of a patch along N2
+  int np, nb;     // patches per line, blocks per plane
+  long col, row, cor, comp;  // offsets of the arrays in a component, values per component
+};
+template <typename R> inline EdgeLayout edge_layout(int n0, int n1, int n2) {
+  EdgeLayout e;
+  e.W8 = kPatch * ((sizeof(R) == 4 && n2 % 4 == 0) ? 4 : 2);
+  e.np = (n2 + e.W8 - 1) / e.W8;
+  e.nb = (n1 + kPatch - 1) / kPatch;
+  e.row = 0;
+  e.col = (long)n0 * e.nb * n2;
+  e.cor = e.col + (long)n0 * n1 * e.np;
+  e.comp = (e.cor + (long)n0 * e.nb * e.np + 31) / 32 * 32;
+  return e;
+}
+
+template <typename R> struct OpArgs {
+  R* q;                // out: 3 N per item
+  R* edge;             // out: 3 el.comp per item
+  const R* pi;         // direction potential, 3 N per item (unused by kSrcField)
+  const R* st;         // tangent state, or the 9-component field
+  double* partials;    // p.Kp per workgroup (unused by kSrcField)
+  Gate gate;
+  EdgeLayout el;
+  int n0, n1, n2;
+  int K;       // node planes per wave
+  int nseg;    // plane runs
+  int groups;  // workgroups per item
+  R q0, q1, q2;
+};
+
+constexpr int kOpThreads = 256;
+
+// q = D^T Y with Y = K : (D pi) (or a stored field).  A wave owns a patch of
+// 8 lines x 8 W voxels of a run of K node planes and marches along i0: node
+// plane m takes the voxel planes m and m + 1, so the previous plane's Y stays
+// in registers.  Inside the patch a node's contributions come from the lanes
+// of the next voxels and of the next line; what crosses the patch's edges is
+// stored apart (EdgeLayout), so nothing is computed twice, no workgroup
+// barrier is needed and the waves run freely.
+template <typename R, int W, int SRC>
+__global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
+  using PV = typename FrontPack<R, W>::type;
+  __shared__ double red[16];
+  const unsigned lb = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int item = (int)(lb / (unsigned)a.groups);
+  if (a.gate(item)) return;
+  const int grp = (int)(lb - (unsigned)item * (unsigned)a.groups);
+  // patches fastest along N2, then lines, then plane runs
+  const long wv = (long)grp * (kOpThreads / 64) + threadIdx.x / 64;
+  const int lane = threadIdx.x & 63;
+  const int l = lane >> 3, gx = lane & 7;
+  const int patch = (int)(wv % a.el.np);
+  const long rest = wv / a.el.np;
+  const int blk = (int)(rest % a.el.nb);
+  const int seg = (int)(rest / a.el.nb);
+  const bool live = seg < a.nseg;
+  const int i1 = blk * kPatch + l, x = patch * a.el.W8 + gx * W;
+  const bool active = live && i1 < a.n1 && x < a.n2;
+  const long N = (long)a.n0 * a.n1 * a.n2;
+  const R* pi = a.pi + (long)item * 3 * N;
+  const R* st = a.st + (long)item * (SRC == kSrcField ? 9 : state_words(SRC)) * N;
+  R* q = a.q + (long)item * 3 * N;
+  R* edge = a.edge + (long)item * 3 * a.el.comp;
+  // the next voxels (line) of the patch are in the lane one (eight) above
+  const bool lastx = gx == kPatch - 1 || x + W >= a.n2;
+  const bool lastl = l == kPatch - 1 || i1 + 1 >= a.n1;
+  const int ps = seg * a.K, pe = live ? min(a.n0, ps + a.K) : ps - 1;
+  double acc = 0.0;
+  R Yp[9][W];
+#pragma unroll
+  for (int k = 0; k < 9; ++k)
+#pragma unroll
+    for (int w = 0; w < W; ++w) Yp[k][w] = R(0);
+  const int xm = (x == 0) ? a.n2 - 1 : x - 1;
+  const int i1m = (i1 == 0) ? a.n1 - 1 : i1 - 1;
+  auto plane_sums = [&](int i0, R (&cs)[3][3][W]) {
+    const R* r0 = pi + ((long)i0 * a.n1 + i1) * a.n2;
+    const R* r1 = pi + ((long)i0 * a.n1 + i1m) * a.n2;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      R u[2][W + 1];
+      const PV v0 = *reinterpret_cast<const PV*>(r0 + c * N + x);
+      const PV v1 = *reinterpret_cast<const PV*>(r1 + c * N + x);
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        u[0][w + 1] = pk_get<R>(v0, w);
+        u[1][w + 1] = pk_get<R>(v1, w);
+      }
+      // the corner x - 1 from the lane below where there is one
+      u[0][0] = __shfl_up(u[0][W], 1);
+      u[1][0] = __shfl_up(u[1][W], 1);
+      if (gx == 0) {
+        u[0][0] = r0[c * N + xm];
+        u[1][0] = r1[c * N + xm];
+      }
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const R a0 = u[0][w + 1] + u[0][w], a1 = u[1][w + 1] + u[1][w];
+        cs[c][0][w] = a0 + a1;
+        cs[c][1][w] = a0 - a1;
+        cs[c][2][w] = (u[0][w + 1] + u[1][w + 1]) - (u[0][w] + u[1][w]);
+      }
+    }
+  };
+  R pp[3][3][W];
+  if constexpr (SRC != kSrcField) {
+    if (active) plane_sums(ps == 0 ? a.n0 - 1 : ps - 1, pp);
+  }
+  constexpr int NS = (SRC == kSrcField) ? 1 : (SRC == kLawSVK) ? 17 : 12;
+  for (int v = ps; v <= pe; ++v) {
+    const int i0 = (v == a.n0) ? 0 : v;
+    const long line = (long)i0 * a.n1 + i1;
+    R Yc[9][W];
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+      for (int w = 0; w < W; ++w) Yc[k][w] = R(0);
+    if (active) {
+      const R* sp = st + line * a.n2 + x;
+      if constexpr (SRC == kSrcField) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          const PV y = *reinterpret_cast<const PV*>(sp + k * N);
+#pragma unroll
+          for (int w = 0; w < W; ++w) Yc[k][w] = pk_get<R>(y, w);
+        }
+      } else {
+        PV A[NS];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) A[k] = pk_load_nt<R, W>(reinterpret_cast<const PV*>(sp + k * N));
+        R X[W][9];
+        R cs[3][3][W];
+        plane_sums(i0, cs);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int w = 0; w < W; ++w) {
+            X[w][3 * c] = a.q0 * (cs[c][0][w] - pp[c][0][w]);
+            X[w][3 * c + 1] = a.q1 * (cs[c][1][w] + pp[c][1][w]);
+            X[w][3 * c + 2] = a.q2 * (cs[c][2][w] + pp[c][2][w]);
+            pp[c][0][w] = cs[c][0][w];
+            pp[c][1][w] = cs[c][1][w];
+            pp[c][2][w] = cs[c][2][w];
+          }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          R A0[9], Y0[9];
+#pragma unroll
+          for (int k = 0; k < 9; ++k) A0[k] = pk_get<R>(A[k], w);
+          if constexpr (SRC == kLawSVK) {
+            R S0[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) S0[k] = pk_get<R>(A[9 + k], w);
+            svk_apply<R>(A0, S0, pk_get<R>(A[15], w), pk_get<R>(A[16], w), X[w], Y0);
+          } else {
+            tangent_apply<R>(A0, pk_get<R>(A[9], w), pk_get<R>(A[10], w), pk_get<R>(A[11], w), X[w], Y0);
+          }
+          double d = 0.0;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) {
+            d += (double)X[w][k] * (double)Y0[k];
+            Yc[k][w] = Y0[k];
+          }
+          if (v < pe) acc += d;
+        }
+      }
+    }
+    if (v > ps) {  // node plane v - 1 is complete
+      const long nline = (long)(v - 1) * a.n1 + i1;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        R f0[W], f1[W], c0[W], c1[W];  // to node i2 / node i2 - 1, of node line i1 (0) and i1 - 1 (1)
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          // no contraction: the contributions of equal neighbours cancel
+          // exactly (a uniform field has zero divergence, not rounding)
+#pragma clang fp contract(off)
+          const R d0 = a.q0 * (Yp[3 * i][w] - Yc[3 * i][w]);
+          const R s1 = a.q1 * (Yp[3 * i + 1][w] + Yc[3 * i + 1][w]);
+          const R s2 = a.q2 * (Yp[3 * i + 2][w] + Yc[3 * i + 2][w]);
+          const R u0 = d0 + s1, u1 = d0 - s1;
+          f0[w] = u0 + s2;
+          c0[w] = u0 - s2;
+          f1[w] = u1 + s2;
+          c1[w] = u1 - s2;
+        }
+        const R n0 = __shfl_down(c0[0], 1), n1 = __shfl_down(c1[0], 1);
+        const R cl = __shfl_down(c1[0], kPatch);
+        R Tp[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const R cp = (w + 1 < W) ? c0[w + 1 < W ? w + 1 : w] : (lastx ? R(0) : n0);
+          const R cm = (w + 1 < W) ? c1[w + 1 < W ? w + 1 : w] : (lastx ? R(0) : n1);
+          Tp[w] = f0[w] + cp;
+          f1[w] += cm;  // the whole contribution to node line i1 - 1
+        }
+        PV out;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const R t = __shfl_down(f1[w], kPatch);
+          pk_set<R>(out, w, Tp[w] + (lastl ? R(0) : t));
+        }
+        if (active) {
+          *reinterpret_cast<PV*>(q + i * N + nline * a.n2 + x) = out;
+          R* ec = edge + i * a.el.comp;
+          if (l == 0) {
+            PV r;
+#pragma unroll
+            for (int w = 0; w < W; ++w) pk_set<R>(r, w, f1[w]);
+            const long b = (long)(v - 1) * a.el.nb + blk;
+            *reinterpret_cast<PV*>(ec + a.el.row + b * a.n2 + x) = r;
+            if (gx == 0) ec[a.el.cor + b * a.el.np + patch] = c1[0];
+          }
+          if (gx == 0) ec[a.el.col + nline * a.el.np + patch] = c0[0] + (lastl ? R(0) : cl);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+      for (int w = 0; w < W; ++w) Yp[k][w] = Yc[k][w];
+  }
+  if constexpr (SRC != kSrcField) {
+    const double s = block_sum(acc, red);
+    if (threadIdx.x == 0) a.partials[(long)item * a.groups + grp] = s;
+  }
+}
+
+// N2 transform of the 3-component fields q of k_cg_op with the patch edges
+// added on load.  grid: line blocks of 3 N0 N1 lines per item, blockIdx.y =
+// item.
+template <typename R, int M>
+__global__ void __launch_bounds__(XBLOCK)
+k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, cplx<R>* __restrict__ out, int n0,
+            int n1, SpecTables<R> tb, Gate gate) {
+  using C = cplx<R>;
+  using LS = Line<M>;
+  constexpr int LPB = XBLOCK / LS::T, N2 = 2 * M;
+  constexpr int PAD = (M >= 16) ? 1 : 0;
+  constexpr int NP = (N2 + 15) / 16;  // most patches of a line
+  __shared__ C lds[LPB * (M + PAD)];
+  __shared__ C stw[M], spost[M];
+  __shared__ R ecl[LPB][NP], ecr[LPB][NP];
+  const int item = blockIdx.y;
+  if (gate(item)) return;
+  for (int k = threadIdx.x; k < M; k += XBLOCK) {
+    stw[k] = tb.twM[k];
+    spost[k] = tb.post[k];
+  }
+  const int t = threadIdx.x % LS::T;
+  const int ll = threadIdx.x / LS::T;
+  const int nlines = n0 * n1;
+  const int lin = (int)(blockIdx.x * LPB) + ll;
+  const bool active = lin < 3 * nlines;
+  const int comp = active ? lin / nlines : 0;
+  const int line = active ? lin - comp * nlines : 0;
+  const int i0 = line / n1, i1 = line - i0 * n1;
+  const long base = ((long)item * 3 * nlines + (active ? lin : 0)) * M;
+  const C* src = reinterpret_cast<const C*>(q) + base;
+  const R* ec = edge + ((long)item * 3 + comp) * el.comp;
+  // the last line of its block takes the row stored by the next block
+  const bool lastl = i1 % kPatch == kPatch - 1 || i1 == n1 - 1;
+  const long nb = (long)i0 * el.nb + ((i1 == n1 - 1) ? 0 : i1 / kPatch + 1);
+  C* my = lds + ll * (M + PAD);
+  C v[LS::E], r[LS::E];
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) v[e] = active ? ld_stream(src + LS::idxA(t, e)) : mk<C>(R(0), R(0));
+  if (active && lastl) {
+    const C* erow = reinterpret_cast<const C*>(ec + el.row + nb * N2);
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) r[e] = erow[LS::idxA(t, e)];
+  } else {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) r[e] = mk<C>(R(0), R(0));
+  }
+  // the line's edge values through LDS (one coalesced read each)
+  if (active) {
+    for (int p = t; p < el.np; p += LS::T) {
+      ecl[ll][p] = ec[el.col + (long)line * el.np + p];
+      ecr[ll][p] = lastl ? ec[el.cor + nb * el.np + p] : R(0);
+    }
+  }
+  __syncthreads();
+  const int sh = 31 - __clz(el.W8);  // W8 is a power of two
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) {
+    const int n = LS::idxA(t, e);
+    const int xn = (2 * n + 2 == N2) ? 0 : 2 * n + 2;
+    if ((xn & (el.W8 - 1)) == 0) {
+      v[e].y += ecl[ll][xn >> sh];
+      r[e].y += ecr[ll][xn >> sh];
+    }
+    v[e] = cadd(v[e], r[e]);
+  }
+  __syncthreads();
+  line_fft_AB<M, false>(v, my, 1, t, stw);
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) my[LS::idxB(t, e)] = v[e];
+  __syncthreads();
+  auto post = [&](int k) {
+    const C zk = my[k];
+    if (k == 0) return mk<C>(zk.x + zk.y, zk.x - zk.y);  // both ends of the real line's spectrum
+    const C zm = my[M - k];
+    const C ev = cscale(cadd(zk, cconj(zm)), R(0.5));
+    const C od = cscale(mul_mi(csub(zk, cconj(zm))), R(0.5));
+    return cadd(ev, cmul(od, spost[k]));
+  };
+  if constexpr (sizeof(R) == 4 && M % (2 * LS::T) == 0) {
+    // two adjacent elements per thread: whole 128-byte lines per store
+#pragma unroll
+    for (int j = 0; j < M / (2 * LS::T); ++j) {
+      const int k = 2 * (j * LS::T + t);
+      const C x0 = post(k), x1 = post(k + 1);
+      if (active) st_stream_f4(out + base + k, make_float4(x0.x, x0.y, x1.x, x1.y));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const int k = LS::idxB(t, e);
+      const C X = post(k);
+      if (active) st_stream(out + base + k, X);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// N1 pass between the line layout (component, i0, i1, kx) and the block
+// layout: forward line -> block, inverse block -> line.  Grid (M / tile, N0,
+// 3 per item).  CPT = 2 (single precision): two adjacent columns per thread.
+template <typename R> struct N1Args {
+  cplx<R>* lines;
+  cplx<R>* blocks;
+  cplx<R>* dc;  // kx = 0 column, [component][ky][i0]
+  BlockLayout bl;
+  int M, tile;
+  const cplx<R>* tw;
+  Gate gate;
+  // forward pass of the CG: one workgroup per item forms alpha from the
+  // partial sums of p.Kp (nothing before the N0 pass reads it)
+  const double* pap;
+  int npap;
+  KrylovScalars* ks;
+};
+
+template <typename R, int L, bool INV, int CPT, bool TWL>
+__global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
+  using C = cplx<R>;
+  using LS = Line<L>;
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ double red[16];
+  C* lds = reinterpret_cast<C*>(smem_raw);
+  const int z = blockIdx.z, i0 = blockIdx.y, N0 = gridDim.y;
+  if (a.gate(z / 3)) return;
+  if constexpr (!INV) {
+    if (a.pap && blockIdx.x == 0 && i0 == 0 && z % 3 == 0) {
+      const int item = z / 3;
+      const double s = sum_partials(a.pap + (long)item * a.npap, a.npap, red);
+      if (threadIdx.x == 0) krylov_alpha(a.ks + item, s, 0);
+    }
+  }
+  const int B = a.tile;
+  const C* tw = a.tw;
+  if constexpr (TWL) {
+    C* stw = lds + L * B;
+    for (int k = threadIdx.x; k < L; k += blockDim.x) stw[k] = a.tw[k];
+    __syncthreads();
+    tw = stw;
+  }
+  const int BC = B / CPT;
+  const int cg = threadIdx.x % BC;
+  const int t = threadIdx.x / BC;
+  const int kx = blockIdx.x * B + CPT * cg;
+  C* ln = a.lines + (((long)z * N0 + i0) * L) * a.M + kx;            // + n M
+  C* bk = a.blocks + (long)z * a.bl.cstr + a.bl.at(L, 0, kx) + (long)i0 * a.bl.B;  // + ky bstr
+  C* dc = a.dc + (long)z * L * N0 + i0;                              // + ky N0
+  const bool col0 = kx == 0;
+  C v[CPT][LS::E];
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) {
+    const int n = LS::idxA(t, e);
+    if constexpr (CPT == 2) {
+      const float4 w = *reinterpret_cast<const float4*>(INV ? bk + n * a.bl.bstr : ln + (long)n * a.M);
+      v[0][e] = mk<C>(w.x, w.y);
+      v[CPT - 1][e] = mk<C>(w.z, w.w);
+      if (INV && col0) v[0][e] = dc[(long)n * N0];
+    } else {
+      if (INV && col0)
+        v[0][e] = dc[(long)n * N0];
+      else if constexpr (INV)
+        v[0][e] = bk[n * a.bl.bstr];
+      else  // the N2 pass streamed it out; double precision streams it in too (168 -> 147 us at 256^3)
+        v[0][e] = sizeof(R) == 8 ? ld_stream(ln + (long)n * a.M) : ln[(long)n * a.M];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) line_fft_AB<L, INV>(v[c], lds + CPT * cg + c, B, t, tw);
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) {
+    const int n = LS::idxB(t, e);
+    if constexpr (CPT == 2) {
+      C* dst = INV ? ln + (long)n * a.M : bk + n * a.bl.bstr;
+      if (!INV && col0) {
+        dc[(long)n * N0] = v[0][e];
+        dst[1] = v[CPT - 1][e];
+      } else {
+        *reinterpret_cast<float4*>(dst) = make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y);
+      }
+    } else if constexpr (INV) {
+      ln[(long)n * a.M] = v[0][e];
+    } else {
+      if (col0)
+        dc[(long)n * N0] = v[0][e];
+      else
+        bk[n * a.bl.bstr] = v[0][e];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// N0 pass on the block layout: forward N0 transform of q, the CG update of
+// the spectral residual, the norm, the symbol, and the inverse N0 transform.
+//   kN0Cg     s -= alpha q (stored), z = f s, partial sums of r.r
+//   kN0Start  s = sign q (stored, type RO), z = f s (type RO), r.r
+//   kN0Apply  z = f q
+//   kN0Norm   partial sums of r.r alone
+// f = 1 / (N |r|^2) with the rotated vector r of eq. (28) (0 where r = 0),
+// and r.r = sum over the full spectrum of f |s|^2 (the columns kx > 0 of the
+// half spectrum count twice).
+//
+// The kx = 0 column packs the spectra A (kx = 0) and B (kx = N2/2) of real
+// planes as A + i B: a leading slice of the launch takes its column pairs
+// (ky, -ky), separates A(k) = (P(k) + conj P(-k)) / 2 and
+// B(k) = (P(k) - conj P(-k)) / (2 i), scales each with its own symbol and
+// recombines; the other workgroups leave that column alone.
+constexpr int kN0Cg = 0, kN0Start = 1, kN0Apply = 2, kN0Norm = 3;
+
+template <typename R, typename RO> struct N0Args {
+  const cplx<R>* q;    // blocks
+  const cplx<R>* dcq;  // kx = 0 column
+  cplx<RO>* z;         // blocks (may be q)
+  cplx<RO>* dcz;
+  cplx<RO>* s;         // spectral residual, blocks
+  cplx<RO>* dcs;
+  BlockLayout bl, blo;  // of q, and of z and s
+  int N1, M, tile, kymajor;
+  SpecTables<R> tb;
+  R scale, sign;
+  Gate gate;
+  const KrylovScalars* ks;
+  double* partials;  // per workgroup: column pairs, then [component][ky][tile]; items consecutive (Parts)
+  int ndc, nmain;    // workgroups per component
+};
+
+template <typename R> constexpr size_t n0_extra_lds(int L) {
+  return (size_t)L * sizeof(cplx<R>) + 2 * (size_t)L * sizeof(R);
+}
+
+template <typename R, typename RO, int L, int CPT, int MODE>
+__global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
+  using C = cplx<R>;
+  using CO = cplx<RO>;
+  using LS = typename ZGradSel<R, L>::type;
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ double red[16];
+  const unsigned per_comp = (unsigned)(a.ndc + a.nmain), per_item = 3 * per_comp;
+  const int item = (int)(blockIdx.x / per_item);
+  if (a.gate(item)) return;
+  const unsigned rem = blockIdx.x - (unsigned)item * per_item;
+  const bool isdc = rem < 3u * (unsigned)a.ndc;
+  const int wdc = isdc ? a.ndc : a.nmain;
+  const unsigned r2i = isdc ? rem : rem - 3u * (unsigned)a.ndc;
+  const int comp = (int)(r2i / (unsigned)wdc);
+  const int idx = (int)(r2i - (unsigned)comp * wdc);
+  const long zc = 3L * item + comp;
+  const int B = a.tile;
+  C* stw = reinterpret_cast<C*>(smem_raw);
+  R* scz = reinterpret_cast<R*>(stw + L);
+  R* ssz = scz + L;
+  C* lds = reinterpret_cast<C*>(ssz + L);
+  for (int k = threadIdx.x; k < L; k += blockDim.x) {
+    stw[k] = a.tb.tw0[k];
+    scz[k] = a.tb.cz[k];
+    ssz[k] = a.tb.sz[k];
+  }
+  __syncthreads();
+  const R alpha = (MODE == kN0Cg) ? (R)a.ks[item].alpha : R(0);
+  double acc[CPT];
+#pragma unroll
+  for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
+  long part = blockIdx.x;
+  if (isdc) {
+    // threads beyond the pair's 2 T repeat the work of the first ones (equal
+    // values to equal LDS places) and store nothing
+    const int td = threadIdx.x % (2 * LS::T);
+    const int col = td % 2, t = td / 2;
+    const int ky0 = idx, ky1 = (ky0 == 0) ? 0 : a.N1 - ky0;
+    const int ky = col ? ky1 : ky0;
+    const bool store = (int)threadIdx.x < 2 * LS::T && (col == 0 || ky1 != ky0);
+    const long off = (zc * a.N1 + ky) * L;
+    C* sp = lds + 2 * L;
+    C v[1][LS::E];
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) v[0][e] = a.dcq[off + LS::idxA(t, e)];
+    LS::template fwd<false>(v[0], lds + col, 2, t, stw);
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const int kz = LS::idxB(t, e);
+      if constexpr (MODE == kN0Cg) {
+        const CO s = a.dcs[off + kz];
+        v[0][e] = mk<C>((R)s.x - alpha * v[0][e].x, (R)s.y - alpha * v[0][e].y);
+      } else if constexpr (MODE == kN0Start) {
+        v[0][e] = cscale(v[0][e], a.sign);
+      }
+      sp[col * L + kz] = v[0][e];
+    }
+    __syncthreads();
+    const R cy = a.tb.cy[ky], sy = a.tb.sy[ky], sxM = a.tb.sx[a.M];
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const int kz = LS::idxB(t, e);
+      const C P = v[0][e], Pm = sp[(1 - col) * L + (kz == 0 ? 0 : L - kz)];
+      if constexpr (MODE == kN0Cg || MODE == kN0Start) {
+        if (store) a.dcs[off + kz] = mk<CO>((RO)P.x, (RO)P.y);
+      }
+      // rotated vector at qx = 0: (sz cy, cz sy, 0); at qx = pi: (0, 0, cz cy sx)
+      const R ra = ssz[kz] * cy, rb = scz[kz] * sy, rc = scz[kz] * cy * sxM;
+      const R a2 = ra * ra + rb * rb, b2 = rc * rc;
+      const R fa = a2 > R(0) ? a.scale / a2 : R(0), fb = b2 > R(0) ? a.scale / b2 : R(0);
+      const C A = cscale(cadd(P, cconj(Pm)), R(0.5));
+      const C Bv = cscale(mul_mi(csub(P, cconj(Pm))), R(0.5));
+      if (MODE != kN0Apply && store)
+        acc[0] += (double)fa * ((double)A.x * A.x + (double)A.y * A.y) +
+               (double)fb * ((double)Bv.x * Bv.x + (double)Bv.y * Bv.y);
+      v[0][e] = cadd(cscale(A, fa), mul_pi(cscale(Bv, fb)));
+    }
+    if constexpr (MODE != kN0Norm) {
+      LS::inv(v[0], lds + col, 2, t, stw);
+      if (store) {
+#pragma unroll
+        for (int e = 0; e < LS::E; ++e) a.dcz[off + LS::idxA(t, e)] = mk<CO>((RO)v[0][e].x, (RO)v[0][e].y);
+      }
+    }
+  } else {
+    const int nkx = a.M / B;
+    const int ktile = a.kymajor ? idx / a.N1 : idx % nkx;
+    const int ky = a.kymajor ? idx - ktile * a.N1 : idx / nkx;
+    const int BC = B / CPT;
+    // (a workgroup wider than the tile, for the column pairs: repeats as above)
+    const int tm = threadIdx.x % (LS::T * BC);
+    const bool store = (int)threadIdx.x < LS::T * BC;
+    const int col0 = CPT * (tm % BC);
+    const int t = tm / BC;
+    const int kx0 = ktile * B + col0;
+    part = (long)item * per_item + 3L * a.ndc + ((long)comp * a.N1 + ky) * nkx + ktile;
+    const C* src = a.q + zc * a.bl.cstr + a.bl.at(a.N1, ky, kx0);
+    const long oo = zc * a.blo.cstr + a.blo.at(a.N1, ky, kx0);
+    const int bi = a.bl.B, bo = a.blo.B;
+    R f0[CPT], f1[CPT];
+    const R cy = a.tb.cy[ky], sy = a.tb.sy[ky];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const R cx = a.tb.cx[kx0 + c], sx = a.tb.sx[kx0 + c];
+      const R x0 = cy * cx, x1 = sy * cx, x2 = cy * sx;
+      f0[c] = x0 * x0;
+      f1[c] = x1 * x1 + x2 * x2;
+    }
+    C v[CPT][LS::E];
+    CO s[CPT][MODE == kN0Cg ? LS::E : 1];
+    if constexpr (CPT == 2) {
+      static_assert(sizeof(R) == 4 && sizeof(RO) == 4, "column pairs in single precision");
+#pragma unroll
+      for (int e = 0; e < LS::E; ++e) {
+        const float4 w = ld_stream_f4(src + (long)LS::idxA(t, e) * bi);
+        v[0][e] = mk<C>(w.x, w.y);
+        v[CPT - 1][e] = mk<C>(w.z, w.w);
+      }
+      if constexpr (MODE == kN0Cg) {
+#pragma unroll
+        for (int e = 0; e < LS::E; ++e) {
+          const float4 w = ld_stream_f4(a.s + oo + (long)LS::idxB(t, e) * bo);
+          s[0][e] = mk<CO>(w.x, w.y);
+          s[CPT - 1][e] = mk<CO>(w.z, w.w);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < LS::E; ++e) v[0][e] = ld_stream(src + (long)LS::idxA(t, e) * bi);
+      if constexpr (MODE == kN0Cg) {
+#pragma unroll
+        for (int e = 0; e < LS::E; ++e) s[0][e] = ld_stream(a.s + oo + (long)LS::idxB(t, e) * bo);
+      }
+    }
+    LS::template fwd_cols<false, CPT>(v, lds + col0, B, t, stw);
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const int kz = LS::idxB(t, e);
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        if constexpr (MODE == kN0Cg)
+          v[c][e] = mk<C>((R)s[c][e].x - alpha * v[c][e].x, (R)s[c][e].y - alpha * v[c][e].y);
+        else if constexpr (MODE == kN0Start)
+          v[c][e] = cscale(v[c][e], a.sign);
+      }
+      if constexpr (MODE == kN0Cg || MODE == kN0Start) {
+        CO* d = a.s + oo + (long)kz * bo;
+        if constexpr (CPT == 2) {
+          if (store && kx0 != 0)
+            st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
+          else if (store)
+            d[1] = v[CPT - 1][e];
+        } else {
+          if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        const R sz = ssz[kz], cz = scz[kz];
+        const R r2 = sz * sz * f0[c] + cz * cz * f1[c];
+        const R f = r2 > R(0) ? a.scale / r2 : R(0);
+        if (MODE != kN0Apply && store && kx0 + c != 0)
+          acc[c] = __fma_rn(
+              2.0 * (double)f, __fma_rn((double)v[c][e].x, (double)v[c][e].x, (double)v[c][e].y * (double)v[c][e].y),
+              acc[c]);
+        v[c][e] = cscale(v[c][e], f);
+      }
+    }
+    if constexpr (MODE != kN0Norm) {
+      LS::template inv_cols<CPT>(v, lds + col0, B, t, stw);
+#pragma unroll
+      for (int e = 0; e < LS::E; ++e) {
+        CO* d = a.z + oo + (long)LS::idxA(t, e) * bo;
+        if constexpr (CPT == 2) {
+          if (store && kx0 != 0)
+            st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
+          else if (store)
+            d[1] = v[CPT - 1][e];
+        } else {
+          if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
+        }
+      }
+    }
+  }
+  if constexpr (MODE != kN0Apply) {
+    if (isdc) {
+      const double sum = block_sum(acc[0], red);
+      if (threadIdx.x == 0) a.partials[part] = sum;
+      return;
+    }
+    // the tile's sum as a binary tree, over the threads of a column first and
+    // over the columns then: it continues over the tiles of a row in
+    // sum_parts, so r.r is the same number whatever the tile
+    const int BC = B / CPT, nth = LS::T * BC;
+    const bool in = (int)threadIdx.x < nth;
+    double v[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) v[c] = in ? acc[c] : 0.0;
+    const int wb = min(64, nth);  // threads of the tile in a wave
+    for (int off = BC; off < wb; off <<= 1) {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) v[c] += __shfl_xor(v[c], off, 64);
+    }
+    double w = v[0];
+    if (nth > 64) {  // (then BC divides 64, or a wave holds one thread of each of 64 columns)
+      double* cr = reinterpret_cast<double*>(smem_raw);  // [wave][column]
+      __syncthreads();
+      const int wid = threadIdx.x / 64, lane = threadIdx.x & 63;
+      const int cw = min(BC, 64);
+      if (in && lane < cw) {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) cr[(wid * cw + lane) * CPT + c] = v[c];
+      }
+      __syncthreads();
+      const int nw = nth / 64, cpw = BC > 64 ? BC / 64 : 1, tw = nw / cpw;  // waves of one set of columns
+      if ((int)threadIdx.x < BC) {
+        // column set of this thread: waves wid, wid + cpw, ... in tree order
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+          auto at = [&](int k) { return cr[(((int)threadIdx.x / 64 + k * cpw) * cw + lane) * CPT + c]; };
+          if (tw == 1) v[c] = at(0);
+          if (tw == 2) v[c] = at(0) + at(1);
+          if (tw == 4) v[c] = (at(0) + at(1)) + (at(2) + at(3));
+        }
+      }
+      __syncthreads();
+    }
+    w = v[0];
+    if constexpr (CPT == 2) w = v[0] + v[CPT - 1];
+    for (int off = 1; off < min(BC, 64); off <<= 1) w += __shfl_xor(w, off, 64);
+    if (BC > 64) {  // columns over several waves (short lines)
+      double* cr = reinterpret_cast<double*>(smem_raw);
+      if ((int)threadIdx.x < BC && (threadIdx.x & 63) == 0) cr[threadIdx.x / 64] = w;
+      __syncthreads();
+      if (threadIdx.x == 0) w = BC == 128 ? cr[0] + cr[1] : (cr[0] + cr[1]) + (cr[2] + cr[3]);
+    }
+    if (threadIdx.x == 0) a.partials[part] = w;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Inverse N2 pass of z fused with the CG vectors, per line of a component:
+//   xi += alpha_{k-1} pi_{k-1},  pi_k = z + beta pi_{k-1}   (k > 0),
+//   xi = 0,  pi_0 = z                                       (k = 0).
+// grid: line blocks of 3 N0 N1 lines per item, blockIdx.y = item.
+template <typename R, int M>
+__global__ void __launch_bounds__(XBLOCK)
+k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, long nlines3,
+          SpecTables<R> tb, const KrylovScalars* __restrict__ ksb) {
+  using C = cplx<R>;
+  using LS = Line<M>;
+  constexpr int LPB = XBLOCK / LS::T;
+  constexpr int PAD = (M >= 16) ? 1 : 0;
+  __shared__ C lds[LPB * (M + PAD)];
+  __shared__ C stw[M], spost[M];
+  const int item = blockIdx.y;
+  const KrylovScalars* ks = ksb + item;
+  if (ks->done) return;
+  for (int k = threadIdx.x; k < M; k += XBLOCK) {
+    stw[k] = tb.twM[k];
+    spost[k] = tb.post[k];
+  }
+  const bool first = ks->iter == 0;
+  const R alpha = (R)ks->alpha, beta = (R)ks->beta;
+  const int t = threadIdx.x % LS::T;
+  const int ll = threadIdx.x / LS::T;
+  const long lin = (long)blockIdx.x * LPB + ll;
+  const bool active = ll < LPB && lin < nlines3;
+  const long base = ((long)item * nlines3 + (active ? lin : 0)) * M;
+  C* my = lds + (ll < LPB ? ll : 0) * (M + PAD);
+  C v[LS::E];
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e)
+    v[e] = active ? (sizeof(R) == 8 ? ld_stream(in + base + LS::idxA(t, e)) : in[base + LS::idxA(t, e)])
+                  : mk<C>(R(0), R(0));
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) my[LS::idxA(t, e)] = v[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < LS::E; ++e) {
+    const int k = LS::idxA(t, e);
+    const C xk = v[e];
+    if (k == 0) {
+      v[e] = mk<C>(xk.x + xk.y, xk.x - xk.y);
+    } else {
+      const C xm = my[M - k];
+      const C s = cadd(xk, cconj(xm));
+      const C d = cmulc(csub(xk, cconj(xm)), spost[k]);  // * W^{-k}
+      v[e] = cadd(s, mul_pi(d));
+    }
+  }
+  __syncthreads();  // mirrors read before the exchange overwrites the buffer
+  line_fft_AB<M, true>(v, my, 1, t, stw);
+  if (!active) return;
+  if (first) {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const long n = base + LS::idxB(t, e);
+      pi[n] = v[e];
+      xi[n] = mk<C>(R(0), R(0));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const long n = base + LS::idxB(t, e);
+      const C p = pi[n], x = xi[n];
+      xi[n] = mk<C>(x.x + alpha * p.x, x.y + alpha * p.y);
+      pi[n] = mk<C>(v[e].x + beta * p.x, v[e].y + beta * p.y);
+    }
+  }
+}
+
+}  // namespace fg

@@ -251,6 +251,46 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
   return block_sum(acc, red);
 }
 
+// Partial sums of one item written by a pass whose tile may vary: `head`
+// plain ones, then groups of r consecutive ones each, added as a binary tree
+// (the tree continues the one in which the workgroup added its columns, so a
+// group's sum does not depend on how many columns a workgroup took).
+struct Parts {
+  int groups, head, r;  // sums in all (plain ones and groups)
+  Parts(int n = 0) : groups(n), head(n), r(1) {}
+  Parts(int g, int h, int r_) : groups(g), head(h), r(r_) {}
+  __host__ __device__ __forceinline__ int stride() const { return head + (groups - head) * r; }
+};
+
+__device__ __forceinline__ double sum_parts(const double* __restrict__ partials, const Parts ps, double* red) {
+  if (ps.r == 1) return sum_partials(partials, ps.groups, red);
+  double acc = 0.0;
+  for (int g = threadIdx.x; g < ps.groups; g += blockDim.x) {
+    if (g < ps.head) {
+      acc += partials[g];
+      continue;
+    }
+    const double* p = partials + ps.head + (long)(g - ps.head) * ps.r;
+    double st[9], v = 0.0;  // binary counter of subtree sums (r <= 256)
+    for (int i = 0; i < ps.r; ++i) {
+      v = p[i];
+      bool go = true;
+#pragma unroll
+      for (int k = 0; k < 9; ++k)
+        if (go) {
+          if ((i >> k) & 1) {
+            v = st[k] + v;
+          } else {
+            st[k] = v;
+            go = false;
+          }
+        }
+    }
+    acc += v;
+  }
+  return block_sum(acc, red);
+}
+
 // CG step length from s = p.Ap (or p.Aq): alpha = r.r / s (r.z / s
 // preconditioned), or breakdown when s <= 0.  One thread.
 __device__ __forceinline__ void krylov_alpha(KrylovScalars* ks, double s, int pcg) {

@@ -2,4 +2,6 @@
 #include "fg_fft_impl.hpp"
 namespace fg {
 FG_INSTANTIATE_LAUNCHERS(double)
+// CG start of the mixed form: double-precision pass, single-precision results
+template Parts launch_n0<double, float>(int, int, N0Args<double, float>, int, hipStream_t, hipEvent_t, hipEvent_t);
 }

@@ -4,9 +4,8 @@
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <stdexcept>
+#include <type_traits>
 
-#include "fg_cgfront.hpp"
-#include "fg_fft3.hpp"
 #include "fg_launch.hpp"
 
 namespace fg {
@@ -102,43 +101,6 @@ void launch_axis(int L, bool inv, R* data, long estride, long ystride, long zstr
 }
 
 template <typename R>
-void launch_axis_rows(int N1, R* data, int N0, int M, const SpecTables<R>& tb, const Skip& skip, hipStream_t s,
-                      int nitems, int tile, const double* pap_partials, int nparts, KrylovScalars* ks, R* dcb,
-                      hipEvent_t ev0, hipEvent_t ev1) {
-  tile &= ~kTileColumnPairs;
-  const int T = zline_threads(N1);  // threads per line of RowLine<R, N1>
-  // single precision: two adjacent columns per thread
-  constexpr int CPT = (sizeof(R) == 4) ? 2 : 1;
-  int B = tile > 0 ? tile : zgrad_tile(N1, M, (int)sizeof(cplx<R>));
-  int cpt = (B % CPT == 0) ? CPT : 1;
-  // the N1 tile is shared with launch_axis: halve it until the workgroup and
-  // its LDS (exchange buffer + twiddles) fit
-  while (B > 1 && (T * B / cpt > 256 || (size_t)N1 * (B + 1) * sizeof(cplx<R>) > 65536)) {
-    B /= 2;
-    cpt = (B % CPT == 0) ? CPT : 1;
-  }
-  const size_t shm = (size_t)N1 * (B + 1) * sizeof(cplx<R>);
-  const long plane = (long)N1 * M;
-  // planes y = i0, z = row (3 per item); components of a row n0 planes apart
-  dim3 grid((unsigned)(M / B), (unsigned)N0, (unsigned)(3 * nitems));
-  const Skip sk = skip.unit(3L * N0);
-  switch (N1) {
-#define FG_CASE(L_)                                                                                    \
-  case L_:                                                                                             \
-    if (cpt == 2)                                                                                      \
-      launch_ev((k_fft_axis_rows<R, L_, CPT>), grid, dim3(T * B / 2), shm, s, ev0, ev1, data, (long)M, plane, \
-                         3L * N0 * plane, (long)N0 * plane, B, tb, sk, pap_partials, nparts, ks, dcb); \
-    else                                                                                               \
-      launch_ev((k_fft_axis_rows<R, L_, 1>), grid, dim3(T * B), shm, s, ev0, ev1, data, (long)M, plane,  \
-                         3L * N0 * plane, (long)N0 * plane, B, tb, sk, pap_partials, nparts, ks, dcb); \
-    return;
-    FG_FOR_N1(FG_CASE)
-#undef FG_CASE
-  }
-  throw std::invalid_argument("unsupported axis length");
-}
-
-template <typename R>
 void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, const Skip& skip,
                   hipStream_t s, int nitems, int tile) {
   const int T = zline_threads(N0);
@@ -158,70 +120,6 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
                        kymajor);                                                                       \
     hipLaunchKernelGGL((k_fft_z_dc<R, L_, 0>), gdc, dim3(64 * z_dc_groups<0>()), 0, s, data, N1, M, tb, scale, \
                        0.0, 0.0, skip, (const R*)nullptr);                                            \
-    return;
-    FG_FOR_AXIS(FG_CASE)
-#undef FG_CASE
-  }
-  throw std::invalid_argument("unsupported N0");
-}
-
-// The potential-form N0 pass with the kx = 0 pairs as its leading slice
-// (N0 = 256 only; see launch_zgrad).
-template <typename R, int L>
-void launch_zgrad_fused(dim3 grid, dim3 block, size_t shm, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, R* data,
-                        int N1, int M, int B, const SpecTables<R>& tb, R scale, const Skip& sk, int kymajor,
-                        int dc_lead, const R* dcb) {
-  if constexpr (L == 256) {
-    launch_ev((k_fft_z_grad3<R, L, 1, true>), grid, block, shm, s, ev0, ev1, data, N1, M, B, tb, scale, sk, kymajor,
-              dc_lead, dcb);
-  } else {
-    throw std::logic_error("the fused kx = 0 slice is built for N0 = 256 only");
-  }
-}
-
-template <typename R>
-void launch_zgrad(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, const Skip& skip,
-                  hipStream_t s, int nitems, int tile, const R* dcb, hipEvent_t ev0, hipEvent_t ev1) {
-  const int T = zgrad_threads(N0, (int)sizeof(cplx<R>));
-  const int kymajor = (tile == 0 || (tile & kTileKyMajor)) ? 1 : 0;
-  tile &= ~kTileKyMajor;
-  // single precision: two adjacent columns per thread (one at N0 = 256)
-  constexpr int CPT = (sizeof(R) == 4) ? 2 : 1;
-  int B = tile > 0 ? tile : zgrad_tile(N0, M, (int)sizeof(cplx<R>));
-  auto cpt_of = [&](int b) { return (b % 2 == 0) ? zgrad_cpt(N0, (int)sizeof(cplx<R>)) : 1; };
-  while (B > 1 && T * B / cpt_of(B) > 256) B /= 2;  // a tile chosen for another line shape
-  const int cpt = cpt_of(B);
-  const size_t shm = (size_t)N0 * B * sizeof(cplx<R>) + zgrad_extra_lds<R>(N0);
-  dim3 grid = kymajor ? dim3((unsigned)N1, (unsigned)(M / B), (unsigned)(3 * nitems))
-                      : dim3((unsigned)(M / B), (unsigned)N1, (unsigned)(3 * nitems));
-  dim3 gdc((unsigned)(N1 / 2 + 1), (unsigned)(3 * nitems), 1);
-  const Skip sk = skip.unit(3);  // grid.z (grad) and grid.y (kx = 0): 3 rows per item
-  // N0 = 256 with one column per thread: the kx = 0 pairs run as a leading
-  // slice of the same launch when they fit in it, so that they overlap the
-  // rest instead of following it (measured at 256^3, the pass with its
-  // kx = 0 work: single precision 152 -> 143 us); the workgroups then take
-  // the larger of the two LDS sizes (in double precision 48 KiB: 3 per CU,
-  // as many as the registers allow anyway)
-  const int dc_lead = (N1 / 2 + 1) * 3 * nitems;
-  const size_t shm_dc = std::max(shm, (size_t)z_dc_lds<256, 2>() * sizeof(cplx<R>));
-  const bool fuse_dc = N0 == 256 && cpt == 1 && T * B >= 64 * z_dc_groups<2>() &&
-                       (long)dc_lead <= (long)grid.x * grid.y && shm_dc <= 65536;
-  switch (N0) {
-#define FG_CASE(L_)                                                                                    \
-  case L_:                                                                                             \
-    if (fuse_dc) {                                                                                     \
-      launch_zgrad_fused<R, L_>(dim3(grid.x, grid.y, grid.z + 1), dim3(T * B), shm_dc, s, ev0, ev1, data, N1, M, B, \
-                                tb, scale, sk, kymajor, dc_lead, dcb);                                 \
-      return;                                                                                          \
-    }                                                                                                  \
-    if (cpt == 2)                                                                                      \
-      launch_ev((k_fft_z_grad3<R, L_, CPT>), grid, dim3(T * B / 2), shm, s, ev0, nullptr, data, N1, M, B, tb, scale, \
-                         sk, kymajor, 0, nullptr);                                                     \
-    else                                                                                               \
-      launch_ev((k_fft_z_grad3<R, L_, 1>), grid, dim3(T * B), shm, s, ev0, nullptr, data, N1, M, B, tb, scale, sk, \
-                         kymajor, 0, nullptr);                                                         \
-    launch_ev((k_fft_z_dc<R, L_, 2>), gdc, dim3(64 * z_dc_groups<2>()), 0, s, nullptr, ev1, data, N1, M, tb,   \
-              scale, 0.0, 0.0, sk, dcb);                                                              \
     return;
     FG_FOR_AXIS(FG_CASE)
 #undef FG_CASE
@@ -252,23 +150,173 @@ void launch_zscalar(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R s
 }
 
 template <typename R>
-int launch_cg_front(int M, R* spec, R* pbuf, R* xbuf, const R* rbuf, const R* st, const KrylovScalars* ks,
-                    double* partials, long N, int n0, int n1, const double h[3], const SpecTables<R>& tb,
-                    hipStream_t s, int nitems, hipEvent_t ev0, hipEvent_t ev1, int law) {
-  const R q0 = (R)(0.25 / h[0]), q1 = (R)(0.25 / h[1]), q2 = (R)(0.25 / h[2]);
-  const long nlines = (long)n0 * n1;
+int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* partials, const Gate& gate, int n0, int n1,
+                 int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  OpArgs<R> a;
+  a.el = edge_layout<R>(n0, n1, n2);
+  const OpSplit sp = op_split(n0, n1, n2, a.el, nitems);
+  a.q = q;
+  a.edge = edge;
+  a.pi = pi;
+  a.st = st;
+  a.partials = partials;
+  a.gate = gate;
+  a.n0 = n0;
+  a.n1 = n1;
+  a.n2 = n2;
+  a.K = sp.K;
+  a.nseg = sp.nseg;
+  a.groups = sp.groups;
+  a.q0 = (R)(0.25 / h[0]);
+  a.q1 = (R)(0.25 / h[1]);
+  a.q2 = (R)(0.25 / h[2]);
+  auto go = [&](auto width) {
+    constexpr int W = decltype(width)::value;
+    const dim3 grid((unsigned)((long)sp.groups * nitems)), block(kOpThreads);
+    if (src == kSrcField)
+      launch_ev((k_cg_op<R, W, kSrcField>), grid, block, 0, s, ev0, ev1, a);
+    else if (src == kLawSVK)
+      launch_ev((k_cg_op<R, W, kLawSVK>), grid, block, 0, s, ev0, ev1, a);
+    else
+      launch_ev((k_cg_op<R, W, kLawNH>), grid, block, 0, s, ev0, ev1, a);
+  };
+  if constexpr (sizeof(R) == 4) {
+    if (a.el.W8 == 4 * kPatch) {
+      go(std::integral_constant<int, 4>());
+      return sp.groups;
+    }
+  }
+  go(std::integral_constant<int, 2>());
+  return sp.groups;
+}
+
+template <typename R>
+void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
+                      const SpecTables<R>& tb, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const EdgeLayout el = edge_layout<R>(n0, n1, 2 * M);
   switch (M) {
-#define FG_CASE(L_)                                                                                   \
-  case L_: {                                                                                          \
-    using FS = FrontShape<L_>;                                                                        \
-    const long blocks = nitems * ((nlines + FS::LB - 1) / FS::LB);                                    \
-    if (law == kLawSVK)                                                                            \
-      launch_ev((k_cg_front<R, L_, kLawSVK>), dim3((unsigned)blocks), dim3(FS::THREADS), 0, s, ev0, ev1, spec, \
-                pbuf, xbuf, rbuf, st, ks, partials, N, n0, n1, tb, q0, q1, q2);                         \
-    else                                                                                              \
-      launch_ev((k_cg_front<R, L_, kLawNH>), dim3((unsigned)blocks), dim3(FS::THREADS), 0, s, ev0, ev1, spec, \
-                pbuf, xbuf, rbuf, st, ks, partials, N, n0, n1, tb, q0, q1, q2);                         \
-    return (int)blocks;                                                                               \
+#define FG_CASE(L_)                                                                                              \
+  case L_: {                                                                                                     \
+    constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
+    const dim3 grid((unsigned)((3L * n0 * n1 + LPB - 1) / LPB), (unsigned)nitems);                               \
+    launch_ev((k_r2c_edges<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, q, edge, el, reinterpret_cast<cplx<R>*>(out), \
+              n0, n1, tb, gate);                                                                                 \
+    return;                                                                                                      \
+  }
+    FG_FOR_M(FG_CASE)
+#undef FG_CASE
+  }
+  throw std::invalid_argument("unsupported N2/2");
+}
+
+template <typename R>
+void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  int tile = a.tile;
+  int cpt = (sizeof(R) == 4 && (tile & kTileColumnPairs)) ? 2 : 1;
+  tile &= ~kTileColumnPairs;
+  const int T = line_threads(N1);
+  const int B = tile > 0 ? tile : column_tile_cpt(N1, a.M, (int)sizeof(cplx<R>), cpt);
+  if (B % cpt != 0) cpt = 1;
+  // single precision reads the stage twiddles from LDS where they fit beside
+  // the exchange buffer (as launch_axis)
+  const bool twl = sizeof(R) == 4 && (size_t)(N1 * B + N1) * sizeof(cplx<R>) <= 65536;
+  const size_t shm = (size_t)(N1 * B + (twl ? N1 : 0)) * sizeof(cplx<R>);
+  a.tile = B;
+  const dim3 grid((unsigned)(a.M / B), (unsigned)N0, (unsigned)(3 * nitems));
+  const dim3 block((unsigned)(T * B / cpt));
+  constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
+  constexpr bool TW = sizeof(R) == 4;
+  switch (N1) {
+#define FG_N1_GO(L_, INV_, CPT_)                                                               \
+  do {                                                                                         \
+    if (twl)                                                                                   \
+      launch_ev((k_n1<R, L_, INV_, CPT_, TW>), grid, block, (unsigned)shm, s, ev0, ev1, a);    \
+    else                                                                                       \
+      launch_ev((k_n1<R, L_, INV_, CPT_, false>), grid, block, (unsigned)shm, s, ev0, ev1, a); \
+  } while (0)
+#define FG_CASE(L_)                \
+  case L_:                         \
+    if (cpt == 2) {                \
+      if (inv)                     \
+        FG_N1_GO(L_, true, CP);    \
+      else                         \
+        FG_N1_GO(L_, false, CP);   \
+    } else {                       \
+      if (inv)                     \
+        FG_N1_GO(L_, true, 1);     \
+      else                         \
+        FG_N1_GO(L_, false, 1);    \
+    }                              \
+    return;
+    FG_FOR_N1(FG_CASE)
+#undef FG_CASE
+#undef FG_N1_GO
+  }
+  throw std::invalid_argument("unsupported N1");
+}
+
+template <typename R, typename RO>
+Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const int eb = (int)sizeof(cplx<R>);
+  const int T = zgrad_threads(N0, eb);
+  // built-in choice: the largest tile, workgroups ky fastest (consecutive
+  // blocks in memory)
+  a.kymajor = (a.tile == 0 || (a.tile & kTileKyMajor)) ? 1 : 0;
+  int B = a.tile & ~kTileKyMajor;
+  if (B == 0) B = zgrad_tile(N0, a.M, eb);
+  auto cpt_of = [&](int b) { return (b % 2 == 0) ? zgrad_cpt(N0, eb) : 1; };
+  while (B > 1 && T * B / cpt_of(B) > 256) B /= 2;  // a tile chosen for another line shape
+  const int cpt = cpt_of(B);
+  a.tile = B;
+  a.ndc = a.N1 / 2 + 1;
+  a.nmain = (a.M / B) * a.N1;
+  const size_t shm = (size_t)N0 * std::max(B, 4) * sizeof(cplx<R>) + n0_extra_lds<R>(N0);
+  const int bm = a.M & -a.M;  // a row of ky in groups of the largest power of two of columns
+  const Parts parts(3 * a.ndc + 3 * a.N1 * (a.M / bm), 3 * a.ndc, bm / B);
+  const dim3 grid((unsigned)((long)parts.stride() * nitems));
+  const dim3 block((unsigned)std::max(T * B / cpt, 2 * T));
+  constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
+  constexpr bool kSame = sizeof(R) == sizeof(RO);
+  switch (N0) {
+#define FG_N0_GO(L_, MODE_)                                                                      \
+  do {                                                                                           \
+    if (cpt == 2)                                                                                \
+      launch_ev((k_n0<R, RO, L_, CP, MODE_>), grid, block, (unsigned)shm, s, ev0, ev1, a);       \
+    else                                                                                         \
+      launch_ev((k_n0<R, RO, L_, 1, MODE_>), grid, block, (unsigned)shm, s, ev0, ev1, a);        \
+  } while (0)
+#define FG_CASE(L_)                                  \
+  case L_:                                           \
+    if (mode == kN0Cg) {                             \
+      if constexpr (kSame) FG_N0_GO(L_, kN0Cg);      \
+    } else if (mode == kN0Apply) {                   \
+      if constexpr (kSame) FG_N0_GO(L_, kN0Apply);   \
+    } else if constexpr (sizeof(R) == 8) {           \
+      if (mode == kN0Start)                          \
+        FG_N0_GO(L_, kN0Start);                      \
+      else if constexpr (kSame)                      \
+        FG_N0_GO(L_, kN0Norm);                       \
+    }                                                \
+    return parts;
+    FG_FOR_AXIS(FG_CASE)
+#undef FG_CASE
+#undef FG_N0_GO
+  }
+  throw std::invalid_argument("unsupported N0");
+}
+
+template <typename R>
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTables<R>& tb, const KrylovScalars* ks,
+                    int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  using C = cplx<R>;
+  switch (M) {
+#define FG_CASE(L_)                                                                                              \
+  case L_: {                                                                                                     \
+    constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
+    const dim3 grid((unsigned)((nlines3 + LPB - 1) / LPB), (unsigned)nitems);                                    \
+    launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, reinterpret_cast<const C*>(in),            \
+              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines3, tb, ks);                              \
+    return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
 #undef FG_CASE
@@ -277,19 +325,20 @@ int launch_cg_front(int M, R* spec, R* pbuf, R* xbuf, const R* rbuf, const R* st
 }
 
 #define FG_INSTANTIATE_LAUNCHERS(R)                                                                     \
-  template int launch_cg_front<R>(int, R*, R*, R*, const R*, const R*, const KrylovScalars*, double*, long, int, \
-                                  int, const double*, const SpecTables<R>&, hipStream_t, int, hipEvent_t,   \
-                                  hipEvent_t, int);                                                     \
+  template int launch_cg_op<R>(int, R*, R*, const R*, const R*, double*, const Gate&, int, int, int, const double*, \
+                               int, hipStream_t, hipEvent_t, hipEvent_t);                               \
+  template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
+                                    hipStream_t, hipEvent_t, hipEvent_t);                               \
+  template void launch_n1<R>(int, bool, int, N1Args<R>, int, hipStream_t, hipEvent_t, hipEvent_t);      \
+  template Parts launch_n0<R, R>(int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
+  template void launch_c2r_dir<R>(int, const R*, R*, R*, long, const SpecTables<R>&, const KrylovScalars*, int, \
+                                  hipStream_t, hipEvent_t, hipEvent_t);                                 \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
   template int launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, const C2REpi&, hipStream_t, hipEvent_t, \
                              hipEvent_t);                                                           \
   template void launch_axis<R>(int, bool, R*, long, long, long, int, int, int, const cplx<R>*, const Skip&, \
                                hipStream_t, int, hipEvent_t, hipEvent_t);                               \
-  template void launch_axis_rows<R>(int, R*, int, int, const SpecTables<R>&, const Skip&, hipStream_t, int, int,    \
-                                    const double*, int, KrylovScalars*, R*, hipEvent_t, hipEvent_t);            \
   template void launch_zproj<R>(int, R*, int, int, const SpecTables<R>&, R, const Skip&, hipStream_t, int, int); \
-  template void launch_zgrad<R>(int, R*, int, int, const SpecTables<R>&, R, const Skip&, hipStream_t, int, int, \
-                                const R*, hipEvent_t, hipEvent_t);                                       \
   template void launch_zscalar<R>(int, R*, int, int, const SpecTables<R>&, R, double, double, const Skip&, \
                                   hipStream_t);
 

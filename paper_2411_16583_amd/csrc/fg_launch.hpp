@@ -4,7 +4,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
-#include "fg_fft.hpp"
+#include "fg_cg3.hpp"
 
 namespace fg {
 
@@ -33,21 +33,46 @@ int column_tile_t(int T, int L, int M, int elem_bytes);
 int column_tile_cpt(int L, int M, int elem_bytes, int cpt);
 int line_threads(int L);
 int zline_threads(int L);  // threads per line of the fused N0 projection pass
-// threads per line and columns per thread of the potential-form N0 pass
+// threads per line and columns per thread of the N0 pass of the CG
 // (elem_bytes: bytes of one complex value of the working precision)
 int zgrad_threads(int L, int elem_bytes);
 int zgrad_cpt(int L, int elem_bytes);
-int zgrad_tile(int L, int M, int elem_bytes);  // built-in tile of launch_zgrad
+int zgrad_tile(int L, int M, int elem_bytes);  // built-in tile of launch_n0
 
-// Fused CG front on the potentials (deferred xi update, direction update,
-// p = D pi, contraction, p.Kp, N2 real-to-complex pass); h: grid spacings;
-// law: kLawNH or kLawSVK (the tangent state's layout); returns the
-// number of partials written.
+// Plane runs and workgroups of launch_cg_op for nitems fields.
+struct OpSplit {
+  int K, nseg, groups;  // planes per run, runs, workgroups (partial sums) per item
+};
+OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems);
+
+// q = D^T K : (D pi) for all items (src: the law), or D^T of the 9-component
+// fields st (src = kSrcField), as k_cg_op leaves it (q and its patch edges);
+// h: grid spacings.  Returns the number of partial sums of p.Kp per item.
 template <typename R>
-int launch_cg_front(int M, R* spec, R* pbuf, R* xbuf, const R* rbuf, const R* st, const KrylovScalars* ks,
-                    double* partials, long N, int n0, int n1, const double h[3], const SpecTables<R>& tb,
-                    hipStream_t s, int nitems = 1, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
-                    int law = 0);
+int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* partials, const Gate& gate, int n0, int n1,
+                 int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                 hipEvent_t ev1 = nullptr);
+// N2 transform of q with its patch edges added.
+template <typename R>
+void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
+                      const SpecTables<R>& tb, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                      hipEvent_t ev1 = nullptr);
+// N1 pass between the line layout and the block layout (k_n1), 3 components
+// per item; tile as for launch_axis.
+template <typename R>
+void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+               hipEvent_t ev1 = nullptr);
+// N0 pass in the block layout (k_n0) in one of its modes; returns the
+// partial sums of r.r of an item.
+template <typename R, typename RO>
+Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+              hipEvent_t ev1 = nullptr);
+// most partial sums per item that launch_n0 writes, for any tile
+inline long n0_max_parts(int N1, int M) { return 3L * ((long)M * N1 + N1 / 2 + 1); }
+// Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
+template <typename R>
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTables<R>& tb, const KrylovScalars* ks,
+                    int nitems, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 template <typename R>
 void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const Skip& skip,
@@ -61,32 +86,11 @@ template <typename R>
 void launch_axis(int L, bool inv, R* data, long estride, long ystride, long zstride, int M, int gy, int gz,
                  const cplx<R>* tw, const Skip& skip, hipStream_t s, int tile = 0, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);
-// Forward N1 pass of the potential-form projection for nitems 9-component
-// fields: per row, the two terms sharing the N0 factor are merged (slots
-// 3i, 3i + 1 written; kx = 0 column unmerged in all three slots).  tile as
-// for launch_axis (a column-pair flag is ignored).  With pap_partials (in
-// the CG), one workgroup per item also sets the item's step length from
-// the front's nparts partial sums of p.Ap (k_finalize mode 0).  With dcb,
-// the kx = 0 column of the three slots of every row is also written there,
-// contiguous along N0 (complex [9 nitems][N1][N0]), for launch_zgrad.
-template <typename R>
-void launch_axis_rows(int N1, R* data, int N0, int M, const SpecTables<R>& tb, const Skip& skip, hipStream_t s,
-                      int nitems = 1, int tile = 0, const double* pap_partials = nullptr, int nparts = 0,
-                      KrylovScalars* ks = nullptr, R* dcb = nullptr, hipEvent_t ev0 = nullptr,
-                      hipEvent_t ev1 = nullptr);
 // N0 pass fused with the projection, for nitems 9-component fields (3 rows
 // each).
 template <typename R>
 void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, const Skip& skip,
                   hipStream_t s, int nitems = 1, int tile = 0);
-// N0 pass fused with the projection in the potential form, on the output of
-// launch_axis_rows (the potential U_i written to slot 3i of each item), and
-// its kx = 0 companion (reading the kx = 0 column from dcb when given: the
-// buffer launch_axis_rows filled in the same pass).
-template <typename R>
-void launch_zgrad(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, const Skip& skip,
-                  hipStream_t s, int nitems = 1, int tile = 0, const R* dcb = nullptr, hipEvent_t ev0 = nullptr,
-                  hipEvent_t ev1 = nullptr);
 // Flag on a projection-pass tile: workgroups ordered ky fastest.
 constexpr int kTileKyMajor = 1 << 16;
 // Flag on an N1-pass tile in single precision: two adjacent columns per

@@ -17,7 +17,6 @@
 #include "fg_launch.hpp"
 #include "fg_pointwise.hpp"
 #include "fg_scalar.hpp"
-#include "fg_cgfront.hpp"
 #include "fg_fft3.hpp"
 #include "fg_batch.hpp"
 #include "fg_cggrad.hpp"
@@ -92,6 +91,20 @@ int zgrad_tile(int L, int M, int elem_bytes) {
 // precision.
 int zgrad_threads(int L, int elem_bytes) { return (elem_bytes == 8 && L == 256) ? Line<256>::T : zline_threads(L); }
 int zgrad_cpt(int L, int elem_bytes) { return (elem_bytes == 8 && L != 256) ? 2 : 1; }
+
+// Runs of 32 node planes (each computes one voxel plane more), shorter ones
+// where a grid would leave the chip short of waves.
+OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
+  const long patches = (long)el.np * el.nb;
+  OpSplit s;
+  s.K = 32;
+  // 1024 waves: one per SIMD (measured at 48 x 96 x 192 in single precision
+  // with K halved until there are 1024 / 3072 / 8000 waves: 23 / 31 / 30 us)
+  while (s.K > 1 && patches * ((n0 + s.K - 1) / s.K) * nitems < 1024) s.K /= 2;
+  s.nseg = (n0 + s.K - 1) / s.K;
+  s.groups = (int)((patches * s.nseg + kOpThreads / 64 - 1) / (kOpThreads / 64));
+  return s;
+}
 
 int zline_threads(int L) {
   if (L == 256) return Line3<256>::T;
@@ -192,11 +205,15 @@ struct fg_plan {
   double* Fu = nullptr;          // uniform tensor (9)
   double* S64 = nullptr;         // 9N doubles: stress / FP64 spectra
   void* S = nullptr;             // 9N T (aliases S64 in FP64 plans)
-  void* x = nullptr;             // 9N T
-  void* r = nullptr;             // 9N T
-  void* p = nullptr;             // 9N T
+  void* p = nullptr;             // 9N T: direction potential pi (3N); scratch outside the CG
+  void* x = nullptr;             // 3N T: solution potential xi
   void* st = nullptr;            // tangent state, state_words(law) N T
-  void* dcb = nullptr;           // kx = 0 column of the row slots, contiguous along N0 (9 n0 n1 complex per item)
+  // spectra of 3-component fields (fg_cg3.hpp): line layout, block layout
+  // and the compact kx = 0 column, and the spectral residual of the CG
+  void *ln = nullptr, *bk = nullptr, *dc = nullptr, *rs = nullptr, *rdc = nullptr;
+  double *ln64 = nullptr, *bk64 = nullptr, *dc64 = nullptr;  // the first three in double (aliases in FP64 plans)
+  void *q = nullptr, *qe = nullptr;            // divergence q (3N T) and its patch edges
+  double *q64 = nullptr, *qe64 = nullptr;
   double* sc = nullptr;          // scalar solver area, 16N doubles
   size_t part_n = 0;
 
@@ -262,9 +279,10 @@ size_t layout(fg_plan* P, char* base) {
   P->flags = carve<int>(base, off, 4);
   P->dscal = carve<double>(base, off, 64 + 16 * P->nitems);
   P->Fu = carve<double>(base, off, 16 + 9 * P->nitems);
-  // partial sums: 9 per 256-voxel block of every item, plus slack for the
-  // per-item rounding of the line passes
-  P->part_n = (size_t)9 * P->nitems * (N / 256 + 2) + 8192;
+  // partial sums of an item: 9 per 256-voxel block, a workgroup per line of
+  // k_cg_op or per column of the N0 pass at most, plus slack for the per-item
+  // rounding of the line passes
+  P->part_n = (size_t)P->nitems * std::max({9 * (N / 256 + 2), (long)n0 * n1, fg::n0_max_parts(n1, M)}) + 8192;
   P->part = carve<double>(base, off, P->part_n);
   P->part2 = carve<double>(base, off, P->part_n);
   const size_t tb = (P->prec == FG_FP64) ? sizeof(double) : sizeof(float);
@@ -274,11 +292,33 @@ size_t layout(fg_plan* P, char* base) {
   } else {
     P->S = carve<char>(base, off, 9 * NT * tb);
   }
-  P->x = carve<char>(base, off, 9 * NT * tb);
-  P->r = carve<char>(base, off, 9 * NT * tb);
   P->p = carve<char>(base, off, 9 * NT * tb);
+  P->x = carve<char>(base, off, 3 * NT * tb);
   P->st = carve<char>(base, off, (size_t)fg::state_words(P->law) * NT * tb);
-  P->dcb = carve<char>(base, off, (size_t)9 * n0 * n1 * P->nitems * sizeof(cplx<double>));
+  const size_t nit = (size_t)P->nitems;
+  const size_t cb64 = fg::block_layout<double>(n0, n1, M).cstr, cb32 = fg::block_layout<float>(n0, n1, M).cstr;
+  const size_t cb = (P->prec == FG_FP64) ? cb64 : cb32;
+  P->ln = carve<char>(base, off, 3 * NT * tb);
+  P->bk = carve<char>(base, off, 3 * nit * cb * 2 * tb);
+  P->dc = carve<char>(base, off, 3 * nit * n0 * n1 * 2 * tb);
+  P->rs = carve<char>(base, off, 3 * nit * cb * 2 * tb);
+  P->rdc = carve<char>(base, off, 3 * nit * n0 * n1 * 2 * tb);
+  const size_t ne64 = fg::edge_layout<double>(n0, n1, P->n2).comp, ne32 = fg::edge_layout<float>(n0, n1, P->n2).comp;
+  P->q = carve<char>(base, off, 3 * NT * tb);
+  P->qe = carve<char>(base, off, 3 * nit * (P->prec == FG_FP64 ? ne64 : ne32) * tb);
+  if (P->prec == FG_FP64) {
+    P->ln64 = (double*)P->ln;
+    P->bk64 = (double*)P->bk;
+    P->dc64 = (double*)P->dc;
+    P->q64 = (double*)P->q;
+    P->qe64 = (double*)P->qe;
+  } else {
+    P->ln64 = carve<double>(base, off, 3 * NT);
+    P->bk64 = carve<double>(base, off, 6 * nit * cb64);
+    P->dc64 = carve<double>(base, off, 6 * nit * n0 * n1);
+    P->q64 = carve<double>(base, off, 3 * NT);
+    P->qe64 = carve<double>(base, off, 3 * nit * ne64);
+  }
   // scalar solvers (phase field, Fick) only on single plans; batches keep
   // just the zero fields standing in for c and d
   P->sc = carve<double>(base, off, P->nitems == 1 ? 16 * N : NT);
@@ -395,17 +435,17 @@ void check_domain(fg_plan* P) {
   }
 }
 
-// Sum of nparts partials into dscal[slot].
-void reduce_to(fg_plan* P, const double* parts, int nparts, int slot) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, parts, nparts, (KrylovScalars*)nullptr,
+// Sum of the partials into dscal[slot].
+void reduce_to(fg_plan* P, const double* parts, Parts n, int slot) {
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, parts, n, (KrylovScalars*)nullptr,
                      P->dscal + slot, 2, 0);
   check_launch();
 }
 
-// Per-item sums (nparts partials per item, item-major) into the item slot
+// Per-item sums (partials item-major) into the item slot
 // array dscal[64 + 16 b + slot]... stored as dscal[64 + slot * nitems + b].
-void reduce_items(fg_plan* P, const double* parts, int nparts_per_item, int slot) {
-  hipLaunchKernelGGL(k_finalize, dim3(P->nitems), dim3(1024), 0, P->stream, parts, nparts_per_item,
+void reduce_items(fg_plan* P, const double* parts, Parts n, int slot) {
+  hipLaunchKernelGGL(k_finalize, dim3(P->nitems), dim3(1024), 0, P->stream, parts, n,
                      (KrylovScalars*)nullptr, P->dscal + 64 + (long)slot * P->nitems, 2, 0);
   check_launch();
 }
@@ -476,6 +516,34 @@ int precond1(fg_plan* P, const R* in, R* work, R* out, double a0, double a1, con
   return inv_yx<R>(P, work, out, 1, epi);
 }
 
+// Arguments of the N1 and N0 passes of 3-component fields.
+template <typename R>
+N1Args<R> n1_args(fg_plan* P, void* lines, void* blocks, void* dc, const Gate& gate) {
+  N1Args<R> a{};
+  a.lines = (cplx<R>*)lines;
+  a.blocks = (cplx<R>*)blocks;
+  a.dc = (cplx<R>*)dc;
+  a.bl = block_layout<R>(P->n0, P->n1, P->M);
+  a.M = P->M;
+  a.tile = tile_axis<R>(P);
+  a.tw = tabs<R>(P).tw1;
+  a.gate = gate;
+  return a;
+}
+template <typename R, typename RO> N0Args<R, RO> n0_args(fg_plan* P, const Gate& gate) {
+  N0Args<R, RO> a{};
+  a.bl = block_layout<R>(P->n0, P->n1, P->M);
+  a.blo = block_layout<RO>(P->n0, P->n1, P->M);
+  a.N1 = P->n1;
+  a.M = P->M;
+  a.tile = tile_zproj<R>(P);
+  a.tb = tabs<R>(P).spec();
+  a.scale = (R)(1.0 / (double)P->N);
+  a.sign = R(1);
+  a.gate = gate;
+  return a;
+}
+
 // ----------------------------------------------------------------------------
 // Mechanics.
 void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, double* pparts,
@@ -493,21 +561,47 @@ void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, doubl
   check_launch();
 }
 
-// ||G*P|| of the stress in S64 (in place), into dscal[slot]; G*P stays in S64.
-void potential64(fg_plan* P, double* field, const Skip& skip);
-
-// |G*P|^2 of the FP64 9-component fields in S64 (all items not idle) by the
-// potential route: S64 is replaced by the potential U(P) (slot 3i of each
-// item, D U = G*P) and the partial sums of |D U|^2 go to P->part; returns
-// the partials per item.  A following cg_start may reuse U.
-int residual_pot(fg_plan* P, const int* idle) {
-  potential64(P, P->S64, idle ? Skip::flags(idle) : Skip{});
-  return launch_grad_norm(P->S64, 3 * P->N, 9 * P->N, idle, P->part, P->n0, P->n1, P->n2, P->nitems, P->h,
-                          P->stream);
+// Spectrum of the divergence D^T Y of the FP64 9-component fields Y of all
+// items not masked, in the FP64 block layout (bk64, dc64): stencil and N2
+// transform, then the N1 pass.
+void divergence64(fg_plan* P, const double* Y, const Gate& gate) {
+  const SpecTables<double> tb = P->t64.spec();
+  {
+    ProfScope ps(P, FG_PASS_R2C);
+    launch_cg_op<double>(kSrcField, P->q64, P->qe64, nullptr, Y, nullptr, gate, P->n0, P->n1, P->n2, P->h, P->nitems,
+                         P->stream);
+    launch_r2c_edges<double>(P->M, P->q64, P->qe64, P->ln64, gate, P->n0, P->n1, tb, P->nitems, P->stream);
+  }
+  ProfScope ps(P, FG_PASS_AXIS);
+  launch_n1<double>(P->n1, false, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate), P->nitems, P->stream);
 }
 
-// |G*P|^2 of a single-item plan into dscal[slot] (S64 ends up holding U(P)).
-void residual_norm(fg_plan* P, int slot) { reduce_to(P, P->part, residual_pot(P, nullptr), slot); }
+// |G*Y|^2 of the FP64 9-component fields Y of all items not idle (G*Y =
+// D (D^T D)^+ D^T Y, normed in the spectrum); partial sums to P->part,
+// described by the result.  With start, the residual of a CG on
+// r_0 = sign G*Y is left ready for cg_iteration: s_0 and z_0 in the working
+// precision.
+Parts residual_pass(fg_plan* P, const double* Y, const int* idle, bool start, double sign = -1.0) {
+  const Gate gate = Gate::flags(idle);
+  divergence64(P, Y, gate);
+  ProfScope ps(P, FG_PASS_ZPROJ);
+  auto go = [&](auto out, int mode) {
+    using T = decltype(out);
+    N0Args<double, T> a = n0_args<double, T>(P, gate);
+    a.q = (const cplx<double>*)P->bk64;
+    a.dcq = (const cplx<double>*)P->dc64;
+    a.z = (cplx<T>*)P->bk;
+    a.dcz = (cplx<T>*)P->dc;
+    a.s = (cplx<T>*)P->rs;
+    a.dcs = (cplx<T>*)P->rdc;
+    a.sign = sign;
+    a.partials = P->part;
+    return launch_n0<double, T>(P->n0, mode, a, P->nitems, P->stream);
+  };
+  const Parts nb = !start ? go(double(), kN0Norm) : P->prec == FG_FP64 ? go(double(), kN0Start) : go(float(), kN0Start);
+  check_launch();
+  return nb;
+}
 
 // mean of a 9-component FP64 field into dscal[8 + k]
 void mean9(fg_plan* P, const double* field) {
@@ -537,8 +631,7 @@ int next_chunk(const KrylovScalars& h, long launched) {
 // (they return at once); excluded from the profiled launch counts.
 void note_noop_iterations(fg_plan* P, long noop) {
   if (!P->prof_on || noop <= 0) return;
-  for (int pass : {FG_PASS_FRONT, FG_PASS_AXIS, FG_PASS_ZPROJ, FG_PASS_AXIS3, FG_PASS_C2R3, FG_PASS_GRAD,
-                   FG_PASS_FINALIZE})
+  for (int pass : {FG_PASS_FRONT, FG_PASS_R2C, FG_PASS_AXIS, FG_PASS_ZPROJ, FG_PASS_AXIS3, FG_PASS_C2R3, FG_PASS_FINALIZE})
     if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
 }
 
@@ -547,143 +640,93 @@ inline dim3 item_grid(long n, int nitems) {
   return dim3((unsigned)std::min<long>(256, (n + 255) / 256), (unsigned)nitems);
 }
 
-// Inverse half of the projection in the potential form for all items: the
-// 3-component potential U (slots 0, 3, 6 of each item, spectral, written by
-// launch_zgrad) back to real space: N1 pass, then N2 complex-to-real.
-template <typename R>
-void inv_potential(fg_plan* P, R* data, const Skip& skip) {
-  const SpecTables<R> tb = tabs<R>(P).spec();
-  const long lines = (long)P->n0 * P->n1;
-  {
-    ProfScope ps(P, FG_PASS_AXIS3, true);
-    // planes y = i0, z = 3 item + c (components 3 apart)
-    launch_axis<R>(P->n1, true, data, P->M, (long)P->n1 * P->M, 3L * P->n0 * P->n1 * P->M, P->M, P->n0,
-                   3 * P->nitems, tb.tw1, skip.unit(3L * P->n0), P->stream, tile_axis<R>(P), ps.start, ps.stop);
-  }
-  ProfScope ps(P, FG_PASS_C2R3, true);
-  // sub-items (item, c) of N0 N1 lines, 3 N0 N1 lines apart, 3 per item
-  Skip sk = skip.unit(lines);
-  sk.item_stride = 3 * lines;
-  sk.sub = 3;
-  C2REpi epi{1.0, nullptr, true, nullptr, sk};
-  launch_c2r<R>(P->M, data, data, 3 * lines * P->nitems, tb, epi, P->stream, ps.start, ps.stop);
-}
-
 // One CG iteration for every item of the plan (items whose solve is done
-// skip every kernel), on the potentials rho, pi, xi of r = D rho, p = D pi,
-// x = D xi (fg_potential.hpp):
-//   xi += alpha_{k-1} pi_{k-1}; pi = rho + beta pi; Y = K:(D pi); p.Y; N2
-//   pass of Y; N1 pass (9 components in, the two terms of each row that
-//   share the N0 factor merged; alpha = r.r / p.Kp by one workgroup per
-//   item); N0 pass reducing the projection to the 3-component potential; N1
-//   and N2 inverse passes of the potential U (D U = G(K p)); rho -= alpha U,
-//   r.r = |D rho|^2; beta, convergence.
+// skip every kernel): the passes of fg_cg3.hpp.  It starts from z_k in the
+// block layout (left by residual_pass or by the iteration before).
 template <typename T>
 void cg_iteration(fg_plan* P) {
-  T* S = (T*)P->S;
   const int nit = P->nitems;
   KrylovScalars* ks = P->ks;
   const SpecTables<T> tb = tabs<T>(P).spec();
-  const Skip skip = Skip::done(ks);
+  const Gate gate = Gate::done(ks);
+  {
+    ProfScope ps(P, FG_PASS_AXIS3, true);
+    launch_n1<T>(P->n1, true, P->n0, n1_args<T>(P, P->ln, P->bk, P->dc, gate), nit, P->stream, ps.start, ps.stop);
+  }
+  {
+    ProfScope ps(P, FG_PASS_C2R3, true);
+    launch_c2r_dir<T>(P->M, (const T*)P->ln, (T*)P->p, (T*)P->x, 3L * P->n0 * P->n1, tb, ks, nit, P->stream, ps.start,
+                      ps.stop);
+  }
   int nbf;
   {
     ProfScope ps(P, FG_PASS_FRONT, true);
-    nbf = launch_cg_front<T>(P->M, S, (T*)P->p, (T*)P->x, (const T*)P->r, (const T*)P->st, ks, P->part, P->N, P->n0,
-                             P->n1, P->h, tb, P->stream, nit, ps.start, ps.stop, P->law);
+    nbf = launch_cg_op<T>(P->law, (T*)P->q, (T*)P->qe, (const T*)P->p, (const T*)P->st, P->part, gate, P->n0, P->n1,
+                          P->n2, P->h, nit, P->stream, ps.start, ps.stop);
   }
   {
-    // alpha = r.r / p.Ap is formed by the row pass (one workgroup per item)
-    ProfScope ps(P, FG_PASS_AXIS, true);
-    launch_axis_rows<T>(P->n1, S, P->n0, P->M, tb, skip, P->stream, nit, tile_axis<T>(P), P->part, nbf / nit, ks,
-                        (T*)P->dcb, ps.start, ps.stop);
+    ProfScope ps(P, FG_PASS_R2C, true);
+    launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->stream,
+                        ps.start, ps.stop);
   }
+  {
+    // alpha = r.r / p.Kp is formed by the N1 pass (one workgroup per item)
+    ProfScope ps(P, FG_PASS_AXIS, true);
+    N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
+    a.pap = P->part;
+    a.npap = nbf;
+    a.ks = ks;
+    launch_n1<T>(P->n1, false, P->n0, a, nit, P->stream, ps.start, ps.stop);
+  }
+  Parts nbz;
   {
     ProfScope ps(P, FG_PASS_ZPROJ, true);
-    launch_zgrad<T>(P->n0, S, P->n1, P->M, tb, (T)(1.0 / (double)P->N), skip, P->stream, nit, tile_zproj<T>(P),
-                    (const T*)P->dcb, ps.start, ps.stop);
-  }
-  inv_potential<T>(P, S, skip);
-  int nbg;
-  {
-    ProfScope ps(P, FG_PASS_GRAD, true);
-    nbg = launch_cg_rupd<T>((const T*)S, 3 * P->N, (T*)P->r, ks, nullptr, P->part2, P->n0, P->n1, P->n2, nit, P->h, 0,
-                            P->stream, ps.start, ps.stop);
+    N0Args<T, T> a = n0_args<T, T>(P, gate);
+    a.q = a.z = (cplx<T>*)P->bk;
+    a.dcq = a.dcz = (cplx<T>*)P->dc;
+    a.s = (cplx<T>*)P->rs;
+    a.dcs = (cplx<T>*)P->rdc;
+    a.ks = ks;
+    a.partials = P->part2;
+    nbz = launch_n0<T, T>(P->n0, kN0Cg, a, nit, P->stream, ps.start, ps.stop);
   }
   {
     ProfScope ps(P, FG_PASS_FINALIZE, true);
-    launch_ev(k_finalize, dim3(nit), dim3(1024), 0, P->stream, ps.start, ps.stop, (const double*)P->part2, nbg, ks,
+    launch_ev(k_finalize, dim3(nit), dim3(1024), 0, P->stream, ps.start, ps.stop, (const double*)P->part2, nbz, ks,
               (double*)nullptr, 1, 0);
   }
   check_launch();
 }
 
-// Potential of the 9-component FP64 fields in `field` (all items), in place:
-// N2, N1 (rows merged), N0 (projection to the potential) and the inverse N1
-// and N2 passes.  Afterwards slot 3i of each item holds the real U_i with
-// D U = G(field).
-void potential64(fg_plan* P, double* field, const Skip& skip) {
-  const SpecTables<double> tb = P->t64.spec();
-  {
-    ProfScope ps(P, FG_PASS_R2C);
-    launch_r2c<double>(P->M, field, field, 9L * P->n0 * P->n1 * P->nitems, tb, skip.unit(9L * P->n0 * P->n1),
-                       P->stream);
-  }
-  {
-    ProfScope ps(P, FG_PASS_AXIS);
-    launch_axis_rows<double>(P->n1, field, P->n0, P->M, tb, skip, P->stream, P->nitems, tile_axis<double>(P), nullptr,
-                             0, nullptr, (double*)P->dcb);
-  }
-  {
-    ProfScope ps(P, FG_PASS_ZPROJ);
-    launch_zgrad<double>(P->n0, field, P->n1, P->M, tb, 1.0 / (double)P->N, skip, P->stream, P->nitems,
-                         tile_zproj<double>(P), (const double*)P->dcb);
-  }
-  inv_potential<double>(P, field, skip);
-}
-
-// CG start on the potentials for every item not idle: rho_0 = sign U with U
-// the potential of the FP64 field `field` (overwritten; with potential_ready
-// `field` already holds U, as residual_pot leaves it), so that
-// r_0 = D rho_0 = sign G(field); xi = 0; per-block partial sums of
-// |r_0|^2 = |D rho_0|^2 into P->part.  Returns the partials per item (the
-// caller reduces them into the Krylov scalars).
-template <typename T>
-int cg_start(fg_plan* P, double* field, double sign, const int* idle, bool potential_ready = false) {
-  if (!potential_ready) potential64(P, field, idle ? Skip::flags(idle) : Skip{});
-  const long N = P->N;
-  hipLaunchKernelGGL((k_cg_start_pot<T>), item_grid(3 * N, P->nitems), dim3(256), 0, P->stream, (T*)P->r, (T*)P->x,
-                     (const double*)field, 3 * N, 9 * N, sign, idle, N);
-  const int nb = launch_cg_rupd<T>((const T*)P->r, 0, (T*)P->r, P->ks, idle, P->part, P->n0, P->n1, P->n2, P->nitems,
-                                   P->h, 2, P->stream);
-  check_launch();
-  return nb;
-}
-
-// Single-item CG start: cg_start and the Krylov scalars (rr0 = rr = |r_0|^2,
-// iter = 0, done if r_0 = 0).
-template <typename T>
-void cg_start1(fg_plan* P, double* field, double sign, bool potential_ready = false) {
-  const int nb = cg_start<T>(P, field, sign, nullptr, potential_ready);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, nb, P->ks, (double*)nullptr, 5, 0);
+// Krylov scalars of a single-item CG whose start residual_pass left the
+// partial sums of r_0.r_0 (rr0 = rr, iter = 0, done if r_0 = 0).
+void cg_begin(fg_plan* P, Parts parts) {
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, parts, P->ks, (double*)nullptr, 5, 0);
   check_launch();
 }
 
-// The CG solution x = D xi of every item not idle, in double precision, into
-// the 9-component field dst (after the last deferred update of xi).
-template <typename T>
-void cg_result(fg_plan* P, double* dst, const int* idle) {
-  const long N = P->N;
-  hipLaunchKernelGGL((k_cg_final_xi<T>), item_grid(3 * N, P->nitems), dim3(256), 0, P->stream, (T*)P->x,
-                     (const T*)P->p, (const KrylovScalars*)P->ks, idle, N);
-  launch_grad_store<T, double>((const T*)P->x, N, 9 * N, dst, 9 * N, idle, P->n0, P->n1, P->n2, P->nitems, P->h,
-                               P->stream);
+// The CG solution x = D xi of every item not idle, in double precision:
+// stored in the 9-component field dst, or added to it.
+void cg_result(fg_plan* P, double* dst, bool add, const int* idle = nullptr) {
+  auto go = [&](auto tag) {
+    using T = decltype(tag);
+    const T *xi = (const T*)P->x, *pi = (const T*)P->p;
+    if (add)
+      launch_cg_result<T, true>(xi, pi, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+    else
+      launch_cg_result<T, false>(xi, pi, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+  };
+  if (P->prec == FG_FP64)
+    go(double());
+  else
+    go(float());
   check_launch();
 }
 
 template <typename T>
 void cg_solve(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
   KrylovScalars* ks = P->ks;
-  // rho_0, xi = 0 and ks (rr0, rr, iter = 0, done) were set by cg_start1
+  // s_0, z_0 and ks (rr0, rr, iter = 0, done) were set by residual_pass and cg_begin
   {
     // only tol2 / maxit are host-set; the rest was set on the device
     P->hd[62] = (o->fixed_lin > 0) ? 0.0 : o->tol_lin * o->tol_lin;
@@ -718,16 +761,15 @@ double residual_denominator(fg_plan* P, const double Fmacro[9]) {
   FG_HIP(hipMemcpyAsync(P->Fu, Fmacro, 9 * sizeof(double), hipMemcpyHostToDevice, P->stream));
   const unsigned nbN = blocks_for(P->N);
   constitutive(P, P->Fu, P->S64, nullptr, P->part2);
-  reduce_to(P, P->part2, (int)nbN, 0);  // ||P(Fbar)||^2
-  residual_norm(P, 1);                  // ||G*P(Fbar)||^2
+  reduce_to(P, P->part2, (int)nbN, 0);                                 // ||P(Fbar)||^2
+  reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);  // ||G*P(Fbar)||^2
   sync_read(P);
   check_domain(P);
   return std::max(std::max(std::sqrt(P->hd[1]), 1e-14 * std::sqrt(P->hd[0])), 1e-300);
 }
 
 // P and the tangent state at the current F, and ||G*(P - B)|| (B = 0 when
-// null); S64 is left holding the potential U(P - B) (D U = G*(P - B)) that the
-// CG start reuses.
+// null); the CG on G*(K : dF) = -G*(P - B) is left ready to run (cg_begin).
 double newton_residual_norm(fg_plan* P, const double* B = nullptr) {
   constitutive(P, nullptr, P->S64, P->st, nullptr);
   if (B) {
@@ -735,10 +777,10 @@ double newton_residual_norm(fg_plan* P, const double* B = nullptr) {
     hipLaunchKernelGGL(k_sub_f64, dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, P->S64, B, n9);
     check_launch();
   }
-  residual_norm(P, 2);
+  cg_begin(P, residual_pass(P, P->S64, nullptr, true));
   sync_read(P);
   check_domain(P);
-  return std::sqrt(P->hd[2]);
+  return std::sqrt(P->hks[0].rr0);
 }
 double newton_residual(fg_plan* P, double den) { return newton_residual_norm(P) / den; }
 
@@ -747,7 +789,6 @@ double newton_residual(fg_plan* P, double den) { return newton_residual_norm(P) 
 // value at the entry state (Fmacro unused).
 void newton(fg_plan* P, const double Fmacro[9], const fg_solver_opts* o, fg_stats* stats,
             const double* B = nullptr) {
-  const long n9 = 9 * P->N;
   double den = B ? 0.0 : residual_denominator(P, Fmacro);
   int it = 0;
   if (stats) {
@@ -771,27 +812,18 @@ void newton(fg_plan* P, const double Fmacro[9], const fg_solver_opts* o, fg_stat
     const double tol_eff = (P->prec == FG_MIXED) ? 0.01 * o->tol_newton : o->tol_newton;
     if (err <= tol_eff) break;
     if (it >= o->max_newton) throw Status(FG_E_NOCONV, "Newton reached max_newton iterations");
-    // b = -G*P: r_0 = D rho_0 with rho_0 = -U(P), the potential the residual
-    // pass left in S64
+    // the CG on b = -G*P starts from what newton_residual_norm left
     if (P->prec == FG_FP64) {
-      cg_start1<double>(P, P->S64, -1.0, true);
       cg_solve<double>(P, o, stats);
-      cg_result<double>(P, P->S64, nullptr);
     } else {
       fg_solver_opts om = *o;
       // Inner forcing: the single-precision operator is accurate to a few
       // 1e-7 at 256^3 (FFT rounding), so CG is not asked for more than 1e-5;
       // the double-precision Newton residual refines the rest.
       if (om.fixed_lin <= 0) om.tol_lin = std::max(o->tol_lin, 1e-5);
-      cg_start1<float>(P, P->S64, -1.0, true);
       cg_solve<float>(P, &om, stats);
-      // dF = D xi evaluated in double precision: a discrete gradient, hence
-      // compatible to rounding whatever the single-precision error of xi
-      cg_result<float>(P, P->S64, nullptr);
     }
-    hipLaunchKernelGGL((k_axpy_into_f64<double>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, P->F,
-                       (const double*)P->S64, n9);
-    check_launch();
+    cg_result(P, P->F, true);  // F += dF
     if (stats) {
       if (it < 64) stats->lin_history[it] = stats->lin_iters_last;
       stats->lin_iters_total += stats->lin_iters_last;
@@ -842,17 +874,14 @@ void adjoint(fg_plan* P, const double W[9], double* gE, double* gO, const fg_sol
   launch_contract<T>(P, S, (const T*)pbuf);
   check_launch();
   static_assert(sizeof(T) == 8, "the single-precision adjoint is adjoint_mixed");
-  {
-    // b = -G*(K:W): r_0 = D rho_0 with rho_0 = -U, U the potential of K:W
-    // (D U = G*(K:W))
-    cg_start1<double>(P, (double*)S, -1.0);
-  }
+  // b = -G*(K:W)
+  cg_begin(P, residual_pass(P, (double*)S, nullptr, true));
   sync_read(P);
   check_domain(P);
   if (!P->hks[0].done) cg_solve<T>(P, o, stats);
-  // lam = D xi (zero when the right-hand side vanishes: xi = 0)
-  double* lam = (double*)P->r;
-  cg_result<double>(P, lam, nullptr);
+  // lam = D xi (zero when the right-hand side vanishes)
+  double* lam = P->sc;
+  cg_result(P, lam, false);
   const double* c = P->c ? P->c : P->zeroN;
   const double* d = P->d ? P->d : P->zeroN;
   if (gE || gO) {
@@ -866,9 +895,9 @@ void adjoint(fg_plan* P, const double W[9], double* gE, double* gO, const fg_sol
 }
 
 // Mixed form of the adjoint: the system G*(K:lam) = -G*(K:W) is refined in
-// double precision, lam_{k+1} = lam_k + G*(d_k), where d_k solves
+// double precision, lam_{k+1} = lam_k + d_k, where d_k = D xi solves
 // G*(K:d) = R_k by CG with the single-precision operator and
-//   R_k = -G*(G*(K:(W + lam_k)))
+//   R_k = -G*(K:(W + lam_k))
 // is the double-precision residual (K evaluated from F on the fly).  Stops
 // when ||R_k|| <= tol_lin ||R_0||, the criterion of the double-precision CG.
 // lam lives in the (otherwise unused) scalar-solver area.
@@ -889,21 +918,14 @@ void adjoint_mixed(fg_plan* P, const double W[9], double* gE, double* gO, const 
     hipLaunchKernelGGL(k_tangent_apply_f64, dim3(nbN), dim3(256), 0, P->stream, P->F, c, d, P->E, P->nu, P->Om,
                        (const double*)P->Fu, (const double*)lam, P->S64, P->flags, N, P->law);
     check_launch();
-    C2REpi e1{1.0, nullptr, true, nullptr, Skip{}};
-    project9<double>(P, P->S64, P->S64, P->S64, e1);
-    C2REpi e2{-1.0, nullptr, true, P->part, Skip{}};
-    const int nb = project9<double>(P, P->S64, P->S64, P->S64, e2);
-    // rr = R.R, and the inner CG starts from it (rr0 of the correction)
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, nb, P->ks, (double*)nullptr, 5, 0);
-    check_launch();
+    // the inner CG starts from R_k (rr0 = R.R)
+    cg_begin(P, residual_pass(P, P->S64, nullptr, true));
     sync_read(P);
     check_domain(P);
     rr = P->hks[0].rr0;
     if (refine == 0) rr0 = rr;
     if (rr0 == 0.0 || std::sqrt(rr / rr0) <= o->tol_lin) break;
     if (refine >= 30) throw Status(FG_E_NOCONV, "mixed adjoint: refinement did not converge");
-    // inner CG on R_k (compatible, in S64): rho_0 = U of R_k, r_0 = D rho_0
-    cg_start1<float>(P, P->S64, 1.0);
     fg_solver_opts om = *o;
     // the correction reduces R_k by 1e-5 at most (single-precision operator),
     // and by no more than what is left to reach tol_lin ||R_0||
@@ -912,12 +934,7 @@ void adjoint_mixed(fg_plan* P, const double W[9], double* gE, double* gO, const 
     fg_stats inner{};
     cg_solve<float>(P, &om, &inner);
     if (stats) stats->lin_iters_total += inner.lin_iters_last;
-    // lam += G*(d) in double precision, d = D xi
-    cg_result<float>(P, P->S64, nullptr);
-    project9<double>(P, P->S64, P->S64, P->S64, e1);
-    hipLaunchKernelGGL((k_axpy_into_f64<double>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, lam,
-                       (const double*)P->S64, n9);
-    check_launch();
+    cg_result(P, lam, true);  // lam += D xi in double precision
   }
   if (stats) {
     stats->newton_iters = refine;  // double-precision refinements
@@ -979,7 +996,7 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   auto apply_prec = [&]() {
     C2REpi epi{1.0, v.r, false, P->part, skip};
     const int nb = precond1<double>(P, v.r, v.work, v.z, a0, a1, epi);
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, nb, ks, (double*)nullptr, 4, 1);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, Parts(nb), ks, (double*)nullptr, 4, 1);
   };
   apply_prec();
   check_launch();
@@ -993,11 +1010,11 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
       else
         hipLaunchKernelGGL(k_fick_apply, dim3(nbN), dim3(256), 0, P->stream, v.p, v.w, v.A6, dt, g, v.q, P->part,
                            ks, P->N);
-      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, (int)nbN, ks, (double*)nullptr, 0,
+      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, Parts((int)nbN), ks, (double*)nullptr, 0,
                          1);
       hipLaunchKernelGGL((k_cg_update<double>), dim3(nbu), dim3(256), 0, P->stream, v.x, v.r, v.p, v.q, ks,
                          P->part2, P->N);
-      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, (int)nbu, ks, (double*)nullptr, 3,
+      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbu), ks, (double*)nullptr, 3,
                          1);
       apply_prec();
       check_launch();
@@ -1025,7 +1042,7 @@ void pff(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
                      v.a, v.r, v.x, P->gc, P->lc, P->part, P->part2, P->flags, P->N, P->law);
   check_launch();
   reduce_to(P, P->part, (int)nbN, 0);  // sum H
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, (int)nbN, P->ksc, (double*)nullptr,
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbN), P->ksc, (double*)nullptr,
                      5, 1);
   check_launch();
   sync_read(P);
@@ -1071,7 +1088,7 @@ void fick(fg_plan* P, double dt, const double* cdot, const fg_solver_opts* o, fg
     hipLaunchKernelGGL(k_fick_residual, dim3(nbN), dim3(256), 0, P->stream, P->c, v.ct, v.mu, v.A6, cdot, dt, g,
                        v.r, v.x, P->part2, N);
     check_launch();
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, (int)nbN, P->ksc,
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbN), P->ksc,
                        (double*)nullptr, 5, 1);
     check_launch();
     sync_read(P);
@@ -1304,12 +1321,6 @@ fg_status fg_newton_linear_begin(fg_plan* P, const double F_macro[9], double* er
   return run(P, [&]() {
     need_ready(P, true);
     const double err = newton_residual(P, residual_denominator(P, F_macro));
-    // b = -G*P: rho_0 = -U(P), the potential newton_residual left in S64
-    if (P->prec == FG_FP64)
-      cg_start1<double>(P, P->S64, -1.0, true);
-    else
-      cg_start1<float>(P, P->S64, -1.0, true);
-    sync_read(P);
     if (err_res) *err_res = err;
     P->lin_open = true;
   });
@@ -1349,14 +1360,7 @@ fg_status fg_cg_iterate(fg_plan* P, int n, int apply, fg_stats* stats) {
     if (k.flag == 1) throw Status(FG_E_BREAKDOWN, "CG breakdown: p.Ap <= 0");
     if (apply) {
       P->lin_open = false;
-      if (P->prec == FG_FP64)
-        cg_result<double>(P, P->S64, nullptr);
-      else
-        cg_result<float>(P, P->S64, nullptr);
-      const long n9 = 9 * P->N;
-      hipLaunchKernelGGL((k_axpy_into_f64<double>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, P->F,
-                         (const double*)P->S64, n9);
-      check_launch();
+      cg_result(P, P->F, true);  // F += dF
       FG_HIP(hipStreamSynchronize(P->stream));
     }
   });
@@ -1399,9 +1403,9 @@ fg_status fg_residual(fg_plan* P, const double F_macro[9], double* err_res) {
     const unsigned nbN = blocks_for(P->N);
     constitutive(P, P->Fu, P->S64, nullptr, P->part2);
     reduce_to(P, P->part2, (int)nbN, 0);
-    residual_norm(P, 1);
+    reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);
     constitutive(P, nullptr, P->S64, nullptr, nullptr);
-    residual_norm(P, 2);
+    reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 2);
     sync_read(P);
     check_domain(P);
     const double den = std::max(std::max(std::sqrt(P->hd[1]), 1e-14 * std::sqrt(P->hd[0])), 1e-300);
@@ -1476,17 +1480,17 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
   return run(P, [&]() {
     if (!P->ws) throw Status(FG_E_STATE, "workspace not set");
     P->lin_open = false;
-    {
-      ProfScope ps(P, FG_PASS_R2C);
-      launch_r2c<double>(P->M, x, P->S64, 9L * P->n0 * P->n1, P->t64.spec(), Skip{}, P->stream);
-    }
-    launch_axis_rows<double>(P->n1, P->S64, P->n0, P->M, P->t64.spec(), Skip{}, P->stream, 1, tile_axis<double>(P),
-                             nullptr, 0, nullptr, (double*)P->dcb);
-    launch_zgrad<double>(P->n0, P->S64, P->n1, P->M, P->t64.spec(), 1.0 / (double)P->N, Skip{}, P->stream, 1,
-                         tile_zproj<double>(P), (const double*)P->dcb);
-    inv_potential<double>(P, P->S64, Skip{});
-    launch_grad_store<double, double>((const double*)P->S64, 3 * P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1,
-                                      P->n2, 1, P->h, P->stream);
+    const Gate none{};
+    divergence64(P, x, none);
+    N0Args<double, double> a = n0_args<double, double>(P, none);
+    a.q = a.z = (cplx<double>*)P->bk64;
+    a.dcq = a.dcz = (cplx<double>*)P->dc64;
+    launch_n0<double, double>(P->n0, kN0Apply, a, 1, P->stream);
+    launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
+    launch_c2r<double>(P->M, P->ln64, P->ln64, 3L * P->n0 * P->n1, P->t64.spec(),
+                       C2REpi{1.0, nullptr, true, nullptr, Skip{}}, P->stream);
+    launch_grad_store<double, double>(P->ln64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
+                                      P->stream);
     check_launch();
   });
 }
@@ -1698,28 +1702,16 @@ void batch_tick(fg_plan* P, fg_batch::Group& g, bool newton) {
   cg_iteration<T>(P);
   if (!newton) return;
   const int nit = P->nitems;
-  const long n9 = 9 * P->N;
-  const dim3 gi = item_grid(n9, nit);
   hipLaunchKernelGGL(k_newton_gate, dim3(1), dim3(1024), 0, P->stream, (const KrylovScalars*)P->ks, g.nc, g.idle,
                      g.active, nit, (int)FG_E_BREAKDOWN, (int)FG_E_NOCONV);
-  // F += D xi, evaluated in double precision (a discrete gradient: compatible
-  // to rounding also in the mixed form)
-  cg_result<T>(P, P->S64, g.idle);
-  hipLaunchKernelGGL((k_items_axpy<double>), gi, dim3(256), 0, P->stream, P->F, (const double*)P->S64,
-                     (const int*)g.idle, n9);
+  cg_result(P, P->F, true, g.idle);  // F += D xi
   constitutive(P, nullptr, P->S64, P->st, nullptr, g.idle);
-  {
-    // err_res of eq. (31) from |D U(P)| = |G*P| and the Newton test
-    const int nb = residual_pot(P, g.idle);
-    hipLaunchKernelGGL(k_newton_check, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, g.nc,
-                       g.idle, (int)FG_E_NOCONV);
-  }
-  {
-    // b = -G*P: rho_0 = -U(P) (left in S64), xi = 0, and a fresh CG
-    const int nb = cg_start<T>(P, P->S64, -1.0, g.idle, true);
-    hipLaunchKernelGGL(k_newton_cg_start, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, P->ks, g.nc,
-                       (const int*)g.idle);
-  }
+  // err_res of eq. (31), the Newton test, and a fresh CG on b = -G*P
+  const Parts nb = residual_pass(P, P->S64, g.idle, true);
+  hipLaunchKernelGGL(k_newton_check, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, g.nc, g.idle,
+                     (int)FG_E_NOCONV);
+  hipLaunchKernelGGL(k_newton_cg_start, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, P->ks, g.nc,
+                     (const int*)g.idle);
   check_launch();
 }
 
@@ -1782,7 +1774,7 @@ void batch_prologue(fg_batch* B, fg_batch::Group& g, const double* F_macro, cons
   // ||P(Fbar)||^2 and ||G*P(Fbar)||^2 per item
   constitutive(P, P->Fu, P->S64, nullptr, P->part2);
   reduce_items(P, P->part2, (int)blocks_for(N), 0);
-  reduce_items(P, P->part, residual_pot(P, nullptr), 1);
+  reduce_items(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);
   sync_read(P);
   check_domain(P);
   const bool mixed = (P->prec == FG_MIXED);
@@ -1804,14 +1796,6 @@ void batch_prologue(fg_batch* B, fg_batch::Group& g, const double* F_macro, cons
   }
   FG_HIP(hipMemcpyAsync(g.nc, B->hnc, nit * sizeof(NewtonCtl), hipMemcpyHostToDevice, P->stream));
   FG_HIP(hipMemcpyAsync(P->ks, P->hks, nit * sizeof(KrylovScalars), hipMemcpyHostToDevice, P->stream));
-  const long n9 = 9 * N * nit;
-  if (P->prec == FG_FP64)
-    hipLaunchKernelGGL((k_fill<double>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, (double*)P->x, 0.0,
-                       n9);
-  else
-    hipLaunchKernelGGL((k_fill<float>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, (float*)P->x, 0.0f,
-                       n9);
-  check_launch();
   FG_HIP(hipStreamSynchronize(P->stream));  // pinned control blocks are reused
 }
 
@@ -2144,20 +2128,33 @@ int tile_len(const fg_plan* P, int which) { return (which & 1) ? P->n0 : P->n1; 
 
 template <typename R>
 void time_pass_impl(fg_plan* P, bool zproj, int tile, int reps, double* ms) {
-  R* S = (sizeof(R) == 8) ? (R*)P->S64 : (R*)P->S;
-  const long n = 9 * P->N * P->nitems;
-  hipLaunchKernelGGL((k_fill<R>), dim3(grid_stride_blocks(n)), dim3(256), 0, P->stream, S, (R)1e-3, n);
+  R *ln = (R*)P->ln, *bk = (R*)P->bk, *dc = (R*)P->dc;
+  if (sizeof(R) == 8) {
+    ln = (R*)P->ln64;
+    bk = (R*)P->bk64;
+    dc = (R*)P->dc64;
+  }
+  auto fill = [&](R* p, long n) {
+    hipLaunchKernelGGL((k_fill<R>), dim3(grid_stride_blocks(n)), dim3(256), 0, P->stream, p, (R)1e-3, n);
+  };
+  fill(ln, 3 * P->N * P->nitems);
+  fill(bk, 6 * block_layout<R>(P->n0, P->n1, P->M).cstr * P->nitems);
+  fill(dc, 6L * P->n0 * P->n1 * P->nitems);
   check_launch();
-  const SpecTables<R> tb = tabs<R>(P).spec();
+  const Gate none{};
   auto launch = [&]() {
     if (zproj) {
-      launch_zgrad<R>(P->n0, S, P->n1, P->M, tb, (R)(1.0 / (double)P->N), Skip{}, P->stream, P->nitems, tile);
+      N0Args<R, R> a = n0_args<R, R>(P, none);
+      a.q = a.z = (cplx<R>*)bk;
+      a.dcq = a.dcz = (cplx<R>*)dc;
+      a.tile = tile;
+      launch_n0<R, R>(P->n0, kN0Apply, a, P->nitems, P->stream);
     } else {
-      // the N1 work of a CG iteration: the forward row pass and the inverse
-      // pass of the potential
-      launch_axis_rows<R>(P->n1, S, P->n0, P->M, tb, Skip{}, P->stream, P->nitems, tile);
-      launch_axis<R>(P->n1, true, S, P->M, (long)P->n1 * P->M, 3L * P->n0 * P->n1 * P->M, P->M, P->n0,
-                     3 * P->nitems, tb.tw1, Skip{}, P->stream, tile);
+      // the N1 work of a CG iteration: the forward and the inverse pass
+      N1Args<R> a = n1_args<R>(P, ln, bk, dc, none);
+      a.tile = tile;
+      launch_n1<R>(P->n1, false, P->n0, a, P->nitems, P->stream);
+      launch_n1<R>(P->n1, true, P->n0, a, P->nitems, P->stream);
     }
   };
   hipEvent_t e0, e1;

@@ -384,14 +384,14 @@ k_cg_update(T* __restrict__ x, T* __restrict__ r, const T* __restrict__ p, const
 // mode 4: PCG: r.z -> beta = rz_new / rz.
 // mode 5: initialise a Krylov solve from rr0 = sum (b.b): rr = rr0, iter = 0.
 __global__ void __launch_bounds__(1024)
-k_finalize(const double* __restrict__ partials, int nparts, KrylovScalars* ks, double* out, int mode, int pcg) {
-  // one workgroup per batch item: nparts partials, scalars and output each
+k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, double* out, int mode, int pcg) {
+  // one workgroup per batch item: its partials, scalars and output
   __shared__ double red[16];
-  partials += (long)blockIdx.x * nparts;
+  partials += (long)blockIdx.x * parts.stride();
   if (ks) ks += blockIdx.x;
   if (out) out += blockIdx.x;
   if (ks && ks->done && mode != 5 && mode != 2) return;
-  const double s = sum_partials(partials, nparts, red);
+  const double s = sum_parts(partials, parts, red);
   if (threadIdx.x != 0) return;
   if (mode == 0) {
     krylov_alpha(ks, s, pcg);

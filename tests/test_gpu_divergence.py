@@ -1,0 +1,71 @@
+"""The divergence form of the CG (q = D^T K : (D pi) formed by patches of 8
+lines x 16 or 32 voxels whose edges are stored apart and added by the N2 pass,
+runs of node planes along N0, the block layout of the N0 pass) at the sizes
+where its splits can go wrong, against the CPU oracle.
+
+Tolerances as for the other grids: the projection 1e-13 (FP64 rounding of
+the transforms), CG iterates 1e-11 in double and 1e-5 in single precision.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import constitutive as cm
+from oracle import krylov, mechanics, spectral
+from tests.gpu_util import dt, host, plan_for, rel
+
+pytestmark = pytest.mark.gpu
+
+# partial blocks of lines (N1 = 6, 12), half and one-and-a-half patches along
+# N2 (8, 24, 48), one block exactly (8), a plane, node-plane runs that do not
+# divide N0 (48 and 96 planes), blocks padded in the block layout (N0 >= 64)
+SHAPES = [(4, 6, 8), (6, 12, 24), (8, 8, 16), (1, 12, 48), (48, 4, 12), (96, 6, 8), (64, 8, 32), (4, 24, 96)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_projection_by_divergence(shape):
+    print(f"projection by divergence {shape}", flush=True)
+    work = synth.homogeneous_workload(shape, (1.0, 0.7, 1.3))
+    plan = plan_for(work)
+    x = np.random.default_rng(11).standard_normal((3, 3) + shape)
+    y = torch.empty((9,) + shape, dtype=torch.float64, device="cuda:0")
+    plan.project_grad(dt(x.reshape((9,) + shape)), y)
+    ref = spectral.project(x, work["spacing"])
+    assert rel(host(y, (3, 3) + shape), ref, x) <= 1e-13
+    plan.close()
+
+
+# (without (4, 24, 96) in single precision: with voxels 24 times longer along
+# one axis the potentials of the modes whose gradient nearly vanishes are 3e3
+# times larger than their gradients, and their single-precision storage moves
+# the fourth iterate by 2e-5, whichever way the operator is applied)
+@pytest.mark.parametrize("law", ["neo_hookean", "svk"])
+@pytest.mark.parametrize("shape,precision,tol", [(s, "fp64", 1e-11) for s in SHAPES] +
+                         [(s, "mixed", 1e-5) for s in SHAPES[:-1]])
+def test_cg_iterates_by_divergence(shape, precision, tol, law):
+    """Four CG iterations (2, then 2 more) of the first Newton system of a
+    random two-phase cell = the oracle's 9-component CG."""
+    print(f"cg {shape} {precision} {law}", flush=True)
+    work = synth.homogeneous_workload(shape)
+    rng = np.random.default_rng(5 + shape[2])
+    phase = rng.random(shape) < 0.3
+    work["E"] = np.where(phase, 100e9, 10e9)
+    work["law"] = law
+    Fbar = np.eye(3)
+    Fbar[1, 1] += 0.004
+    Fbar[2, 1] += 0.003
+    F0 = mechanics.uniform_field(Fbar, shape)
+    c0, d0 = work["c0"], work["d0"]
+    GP, _ = mechanics.residual_rhs(F0, c0, d0, work, work["spacing"])
+    b = -spectral.project(GP, work["spacing"])
+    K = cm.tangent(F0, c0, d0, work["E"], work["nu"], work["Omega"], law=law)
+    dF, _, _ = krylov.cg(lambda X: mechanics.operator(K, X, work["spacing"]), b, 1e-10, 100, fixed_iters=4)
+    plan = plan_for(work, precision)
+    F = dt(F0)
+    plan.set_state(F, dt(c0), dt(d0))
+    plan.newton_linear_begin(Fbar)
+    plan.cg_iterate(2)
+    assert plan.cg_iterate(2, apply=True)["iters"] == 4
+    assert rel(host(F, (3, 3) + shape) - F0, dF) <= tol
+    plan.close()
