@@ -435,7 +435,7 @@ k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, 
 // ---------------------------------------------------------------------------
 // N1 pass between the line layout (component, i0, i1, kx) and the block
 // layout: forward line -> block, inverse block -> line.  Grid (M / tile, N0,
-// 3 per item).  CPT = 2 (single precision): two adjacent columns per thread.
+// components).  CPT = 2 (single precision): two adjacent columns per thread.
 template <typename R> struct N1Args {
   cplx<R>* lines;
   cplx<R>* blocks;
@@ -449,6 +449,8 @@ template <typename R> struct N1Args {
   const double* pap;
   int npap;
   KrylovScalars* ks;
+  int pcg;  // alpha = r.z / p.Ap (preconditioned CG)
+  int nc;   // components per item
 };
 
 template <typename R, int L, bool INV, int CPT, bool TWL>
@@ -459,12 +461,12 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
   __shared__ double red[16];
   C* lds = reinterpret_cast<C*>(smem_raw);
   const int z = blockIdx.z, i0 = blockIdx.y, N0 = gridDim.y;
-  if (a.gate(z / 3)) return;
+  if (a.gate(z / a.nc)) return;
   if constexpr (!INV) {
-    if (a.pap && blockIdx.x == 0 && i0 == 0 && z % 3 == 0) {
-      const int item = z / 3;
+    if (a.pap && blockIdx.x == 0 && i0 == 0 && z % a.nc == 0) {
+      const int item = z / a.nc;
       const double s = sum_partials(a.pap + (long)item * a.npap, a.npap, red);
-      if (threadIdx.x == 0) krylov_alpha(a.ks + item, s, 0);
+      if (threadIdx.x == 0) krylov_alpha(a.ks + item, s, a.pcg);
     }
   }
   const int B = a.tile;
@@ -532,15 +534,18 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
 //   kN0Start  s = sign q (stored, type RO), z = f s (type RO), r.r
 //   kN0Apply  z = f q
 //   kN0Norm   partial sums of r.r alone
-// f = 1 / (N |r|^2) with the rotated vector r of eq. (28) (0 where r = 0),
-// and r.r = sum over the full spectrum of f |s|^2 (the columns kx > 0 of the
-// half spectrum count twice).
+// SYM = kSymProj: f = 1 / (N |r|^2) with the rotated vector r of eq. (28) (0
+// where r = 0), and r.r = sum over the full spectrum of f |s|^2 (the columns
+// kx > 0 of the half spectrum count twice).  SYM = kSymLap (the scalar
+// problems' preconditioner): f = 1 / (N (a0 + a1 lambda(q))), r.r = sum of
+// |s|^2 / N and r.z = sum of f |s|^2, lambda = sum_j (2/h_j)^2 sin^2(q_j/2).
 //
 // The kx = 0 column packs the spectra A (kx = 0) and B (kx = N2/2) of real
 // planes as A + i B: a leading slice of the launch takes its column pairs
 // (ky, -ky), separates A(k) = (P(k) + conj P(-k)) / 2 and
 // B(k) = (P(k) - conj P(-k)) / (2 i), scales each with its own symbol and
 // recombines; the other workgroups leave that column alone.
+constexpr int kSymProj = 0, kSymLap = 1;
 constexpr int kN0Cg = 0, kN0Start = 1, kN0Apply = 2, kN0Norm = 3;
 
 template <typename R, typename RO> struct N0Args {
@@ -557,6 +562,9 @@ template <typename R, typename RO> struct N0Args {
   Gate gate;
   const KrylovScalars* ks;
   double* partials;  // per workgroup: column pairs, then [component][ky][tile]; items consecutive (Parts)
+  double* partials2;  // the same of r.z (kSymLap)
+  double a0, a1;      // kSymLap
+  int nc;             // components per item
   int ndc, nmain;    // workgroups per component
 };
 
@@ -564,23 +572,70 @@ template <typename R> constexpr size_t n0_extra_lds(int L) {
   return (size_t)L * sizeof(cplx<R>) + 2 * (size_t)L * sizeof(R);
 }
 
-template <typename R, typename RO, int L, int CPT, int MODE>
+// A tile's sum as a binary tree, over the threads of a column first and over
+// the columns then: it continues over the tiles of a row in sum_parts, so the
+// sum is the same number whatever the tile.  Thread t BC + g (t < T, in the
+// first T BC threads) holds the CPT columns CPT g ...; cr: T BC CPT doubles of
+// LDS.  Thread 0 has the result.
+template <int T, int CPT>
+__device__ __forceinline__ double tile_tree(double (&v)[CPT], int BC, double* cr) {
+  const int nth = T * BC;
+  const int wid = threadIdx.x / 64, lane = threadIdx.x & 63;
+  const bool in = (int)threadIdx.x < nth;
+#pragma unroll
+  for (int c = 0; c < CPT; ++c)
+    if (!in) v[c] = 0.0;
+  for (int off = BC; off < min(64, nth); off <<= 1) {
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) v[c] += __shfl_xor(v[c], off, 64);
+  }
+  __syncthreads();
+  if (nth > 64) {
+    const int cw = min(BC, 64), cpw = BC > 64 ? BC / 64 : 1, tw = nth / 64 / cpw;  // tw waves of one set of columns
+    if (in && lane < cw) {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) cr[(wid * cw + lane) * CPT + c] = v[c];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < BC) {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        auto at = [&](int k) { return cr[((wid + k * cpw) * cw + lane) * CPT + c]; };
+        if (tw == 1) v[c] = at(0);
+        if (tw == 2) v[c] = at(0) + at(1);
+        if (tw == 4) v[c] = (at(0) + at(1)) + (at(2) + at(3));
+      }
+    }
+    __syncthreads();
+  }
+  double w = v[0];
+  if constexpr (CPT == 2) w = v[0] + v[CPT - 1];
+  for (int off = 1; off < min(BC, 64); off <<= 1) w += __shfl_xor(w, off, 64);
+  if (BC > 64) {  // columns over several waves (short lines)
+    if ((int)threadIdx.x < BC && lane == 0) cr[wid] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) w = BC == 128 ? cr[0] + cr[1] : (cr[0] + cr[1]) + (cr[2] + cr[3]);
+  }
+  return w;
+}
+
+template <typename R, typename RO, int L, int CPT, int MODE, int SYM>
 __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
   using C = cplx<R>;
   using CO = cplx<RO>;
   using LS = typename ZGradSel<R, L>::type;
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ double red[16];
-  const unsigned per_comp = (unsigned)(a.ndc + a.nmain), per_item = 3 * per_comp;
+  const unsigned per_comp = (unsigned)(a.ndc + a.nmain), per_item = (unsigned)a.nc * per_comp;
   const int item = (int)(blockIdx.x / per_item);
   if (a.gate(item)) return;
   const unsigned rem = blockIdx.x - (unsigned)item * per_item;
-  const bool isdc = rem < 3u * (unsigned)a.ndc;
+  const bool isdc = rem < (unsigned)(a.nc * a.ndc);
   const int wdc = isdc ? a.ndc : a.nmain;
-  const unsigned r2i = isdc ? rem : rem - 3u * (unsigned)a.ndc;
+  const unsigned r2i = isdc ? rem : rem - (unsigned)(a.nc * a.ndc);
   const int comp = (int)(r2i / (unsigned)wdc);
   const int idx = (int)(r2i - (unsigned)comp * wdc);
-  const long zc = 3L * item + comp;
+  const long zc = (long)a.nc * item + comp;
   const int B = a.tile;
   C* stw = reinterpret_cast<C*>(smem_raw);
   R* scz = reinterpret_cast<R*>(stw + L);
@@ -593,9 +648,9 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
   }
   __syncthreads();
   const R alpha = (MODE == kN0Cg) ? (R)a.ks[item].alpha : R(0);
-  double acc[CPT];
+  double acc[CPT], acc2[CPT];  // acc2: r.z (kSymLap)
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) acc[c] = 0.0;
+  for (int c = 0; c < CPT; ++c) acc[c] = acc2[c] = 0.0;
   long part = blockIdx.x;
   if (isdc) {
     // threads beyond the pair's 2 T repeat the work of the first ones (equal
@@ -631,15 +686,30 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       if constexpr (MODE == kN0Cg || MODE == kN0Start) {
         if (store) a.dcs[off + kz] = mk<CO>((RO)P.x, (RO)P.y);
       }
-      // rotated vector at qx = 0: (sz cy, cz sy, 0); at qx = pi: (0, 0, cz cy sx)
-      const R ra = ssz[kz] * cy, rb = scz[kz] * sy, rc = scz[kz] * cy * sxM;
-      const R a2 = ra * ra + rb * rb, b2 = rc * rc;
-      const R fa = a2 > R(0) ? a.scale / a2 : R(0), fb = b2 > R(0) ? a.scale / b2 : R(0);
+      R fa, fb;
+      if constexpr (SYM == kSymProj) {
+        // rotated vector at qx = 0: (sz cy, cz sy, 0); at qx = pi: (0, 0, cz cy sx)
+        const R ra = ssz[kz] * cy, rb = scz[kz] * sy, rc = scz[kz] * cy * sxM;
+        const R a2 = ra * ra + rb * rb, b2 = rc * rc;
+        fa = a2 > R(0) ? a.scale / a2 : R(0);
+        fb = b2 > R(0) ? a.scale / b2 : R(0);
+      } else {
+        const double la = (double)(ssz[kz] * ssz[kz] + sy * sy);
+        fa = (R)((double)a.scale / (a.a0 + a.a1 * la));
+        fb = (R)((double)a.scale / (a.a0 + a.a1 * (la + (double)(sxM * sxM))));
+      }
       const C A = cscale(cadd(P, cconj(Pm)), R(0.5));
       const C Bv = cscale(mul_mi(csub(P, cconj(Pm))), R(0.5));
-      if (MODE != kN0Apply && store)
-        acc[0] += (double)fa * ((double)A.x * A.x + (double)A.y * A.y) +
-               (double)fb * ((double)Bv.x * Bv.x + (double)Bv.y * Bv.y);
+      if (MODE != kN0Apply && store) {
+        const double na = (double)A.x * A.x + (double)A.y * A.y, nb = (double)Bv.x * Bv.x + (double)Bv.y * Bv.y;
+        const double d = (double)fa * na + (double)fb * nb;
+        if constexpr (SYM == kSymProj) {
+          acc[0] += d;
+        } else {
+          acc[0] += (na + nb) * (double)a.scale;
+          acc2[0] += d;
+        }
+      }
       v[0][e] = cadd(cscale(A, fa), mul_pi(cscale(Bv, fb)));
     }
     if constexpr (MODE != kN0Norm) {
@@ -660,7 +730,7 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
     const int col0 = CPT * (tm % BC);
     const int t = tm / BC;
     const int kx0 = ktile * B + col0;
-    part = (long)item * per_item + 3L * a.ndc + ((long)comp * a.N1 + ky) * nkx + ktile;
+    part = (long)item * per_item + (long)a.nc * a.ndc + ((long)comp * a.N1 + ky) * nkx + ktile;
     const C* src = a.q + zc * a.bl.cstr + a.bl.at(a.N1, ky, kx0);
     const long oo = zc * a.blo.cstr + a.blo.at(a.N1, ky, kx0);
     const int bi = a.bl.B, bo = a.blo.B;
@@ -669,9 +739,14 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       const R cx = a.tb.cx[kx0 + c], sx = a.tb.sx[kx0 + c];
-      const R x0 = cy * cx, x1 = sy * cx, x2 = cy * sx;
-      f0[c] = x0 * x0;
-      f1[c] = x1 * x1 + x2 * x2;
+      if constexpr (SYM == kSymProj) {
+        const R x0 = cy * cx, x1 = sy * cx, x2 = cy * sx;
+        f0[c] = x0 * x0;
+        f1[c] = x1 * x1 + x2 * x2;
+      } else {
+        f0[c] = R(1);
+        f1[c] = sy * sy + sx * sx;
+      }
     }
     C v[CPT][LS::E];
     CO s[CPT][MODE == kN0Cg ? LS::E : 1];
@@ -724,12 +799,19 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         const R sz = ssz[kz], cz = scz[kz];
-        const R r2 = sz * sz * f0[c] + cz * cz * f1[c];
-        const R f = r2 > R(0) ? a.scale / r2 : R(0);
-        if (MODE != kN0Apply && store && kx0 + c != 0)
-          acc[c] = __fma_rn(
-              2.0 * (double)f, __fma_rn((double)v[c][e].x, (double)v[c][e].x, (double)v[c][e].y * (double)v[c][e].y),
-              acc[c]);
+        R f;
+        if constexpr (SYM == kSymProj) {
+          const R r2 = sz * sz * f0[c] + cz * cz * f1[c];
+          f = r2 > R(0) ? a.scale / r2 : R(0);
+        } else {
+          f = (R)((double)a.scale / (a.a0 + a.a1 * (double)(sz * sz + f1[c])));
+        }
+        if (MODE != kN0Apply && store && kx0 + c != 0) {
+          const double n = __fma_rn((double)v[c][e].x, (double)v[c][e].x, (double)v[c][e].y * (double)v[c][e].y);
+          const double w = 2.0 * (double)(SYM == kSymProj ? f : a.scale);
+          acc[c] = __fma_rn(w, n, acc[c]);
+          if constexpr (SYM == kSymLap) acc2[c] = __fma_rn(2.0 * (double)f, n, acc2[c]);
+        }
         v[c][e] = cscale(v[c][e], f);
       }
     }
@@ -750,58 +832,16 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
     }
   }
   if constexpr (MODE != kN0Apply) {
-    if (isdc) {
-      const double sum = block_sum(acc[0], red);
-      if (threadIdx.x == 0) a.partials[part] = sum;
-      return;
-    }
-    // the tile's sum as a binary tree, over the threads of a column first and
-    // over the columns then: it continues over the tiles of a row in
-    // sum_parts, so r.r is the same number whatever the tile
-    const int BC = B / CPT, nth = LS::T * BC;
-    const bool in = (int)threadIdx.x < nth;
-    double v[CPT];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) v[c] = in ? acc[c] : 0.0;
-    const int wb = min(64, nth);  // threads of the tile in a wave
-    for (int off = BC; off < wb; off <<= 1) {
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) v[c] += __shfl_xor(v[c], off, 64);
-    }
-    double w = v[0];
-    if (nth > 64) {  // (then BC divides 64, or a wave holds one thread of each of 64 columns)
-      double* cr = reinterpret_cast<double*>(smem_raw);  // [wave][column]
+    double* cr = reinterpret_cast<double*>(smem_raw);
+    auto emit = [&](double (&v)[CPT], double* out) {
+      const double sum = isdc ? block_sum(v[0], red) : tile_tree<LS::T, CPT>(v, B / CPT, cr);
+      if (threadIdx.x == 0) out[part] = sum;
+    };
+    emit(acc, a.partials);
+    if constexpr (SYM == kSymLap) {
       __syncthreads();
-      const int wid = threadIdx.x / 64, lane = threadIdx.x & 63;
-      const int cw = min(BC, 64);
-      if (in && lane < cw) {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) cr[(wid * cw + lane) * CPT + c] = v[c];
-      }
-      __syncthreads();
-      const int nw = nth / 64, cpw = BC > 64 ? BC / 64 : 1, tw = nw / cpw;  // waves of one set of columns
-      if ((int)threadIdx.x < BC) {
-        // column set of this thread: waves wid, wid + cpw, ... in tree order
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          auto at = [&](int k) { return cr[(((int)threadIdx.x / 64 + k * cpw) * cw + lane) * CPT + c]; };
-          if (tw == 1) v[c] = at(0);
-          if (tw == 2) v[c] = at(0) + at(1);
-          if (tw == 4) v[c] = (at(0) + at(1)) + (at(2) + at(3));
-        }
-      }
-      __syncthreads();
+      emit(acc2, a.partials2);
     }
-    w = v[0];
-    if constexpr (CPT == 2) w = v[0] + v[CPT - 1];
-    for (int off = 1; off < min(BC, 64); off <<= 1) w += __shfl_xor(w, off, 64);
-    if (BC > 64) {  // columns over several waves (short lines)
-      double* cr = reinterpret_cast<double*>(smem_raw);
-      if ((int)threadIdx.x < BC && (threadIdx.x & 63) == 0) cr[threadIdx.x / 64] = w;
-      __syncthreads();
-      if (threadIdx.x == 0) w = BC == 128 ? cr[0] + cr[1] : (cr[0] + cr[1]) + (cr[2] + cr[3]);
-    }
-    if (threadIdx.x == 0) a.partials[part] = w;
   }
 }
 
@@ -809,10 +849,11 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 // Inverse N2 pass of z fused with the CG vectors, per line of a component:
 //   xi += alpha_{k-1} pi_{k-1},  pi_k = z + beta pi_{k-1}   (k > 0),
 //   xi = 0,  pi_0 = z                                       (k = 0).
-// grid: line blocks of 3 N0 N1 lines per item, blockIdx.y = item.
+// grid: line blocks of the item's lines (N0 N1 per component), blockIdx.y =
+// item.
 template <typename R, int M>
 __global__ void __launch_bounds__(XBLOCK)
-k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, long nlines3,
+k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, long nlines,
           SpecTables<R> tb, const KrylovScalars* __restrict__ ksb) {
   using C = cplx<R>;
   using LS = Line<M>;
@@ -832,8 +873,8 @@ k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __r
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
   const long lin = (long)blockIdx.x * LPB + ll;
-  const bool active = ll < LPB && lin < nlines3;
-  const long base = ((long)item * nlines3 + (active ? lin : 0)) * M;
+  const bool active = ll < LPB && lin < nlines;
+  const long base = ((long)item * nlines + (active ? lin : 0)) * M;
   C* my = lds + (ll < LPB ? ll : 0) * (M + PAD);
   C v[LS::E];
 #pragma unroll

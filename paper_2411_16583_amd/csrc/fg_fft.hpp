@@ -539,54 +539,12 @@ __device__ __forceinline__ R rget(const RVec<R>& r, int j) {
   return j == 0 ? r.x : (j == 1 ? r.y : r.z);
 }
 
-// LDS bytes of k_fft_z_proj / k_fft_z_scalar beyond the L x B exchange buffer:
+// LDS bytes of k_fft_z_proj beyond the L x B exchange buffer:
 // the stage twiddles and the kz tables, staged once per workgroup (reading
 // them from LDS inside each transform keeps the compiler from holding them in
 // registers across the six transforms of a row).
 template <typename R> constexpr size_t zpass_extra_lds(int L) {
   return (size_t)L * sizeof(cplx<R>) + 2 * (size_t)L * sizeof(R);
-}
-
-// Scalar symbol variant (preconditioners of Alg. 2 / Alg. 3):
-//   Z = A * scale / (a0 + a1 lambda(q)),  lambda = sum_j (2/h_j)^2 sin^2(q_j/2).
-template <typename R>
-__device__ __forceinline__ R lap_sym(const SpecTables<R>& tb, int kz, int ky, int kx) {
-  const R a = tb.sz[kz], b = tb.sy[ky], c = tb.sx[kx];
-  return a * a + b * b + c * c;
-}
-
-template <typename R, int L>
-__global__ void __launch_bounds__(256)
-k_fft_z_scalar(R* data, int N1, int M, int B, SpecTables<R> tb, R scale, double a0, double a1,
-               Skip skip) {
-  using C = cplx<R>;
-  using LS = Line<L>;
-  extern __shared__ char smem_raw[];
-  C* lds = reinterpret_cast<C*>(smem_raw);
-  C* stw = lds + L * B;
-  if (skip(blockIdx.z)) return;
-  for (int k = threadIdx.x; k < L; k += blockDim.x) stw[k] = tb.tw0[k];
-  __syncthreads();
-  const int col = threadIdx.x % B;
-  const int t = threadIdx.x / B;
-  const int kx = blockIdx.x * B + col;
-  const int ky = blockIdx.y;
-  const long plane = (long)N1 * M;
-  C* base = reinterpret_cast<C*>(data) + (long)ky * M + kx;
-  C v[LS::E];
-#pragma unroll
-  for (int e = 0; e < LS::E; ++e) v[e] = base[LS::idxA(t, e) * plane];
-  line_fft_AB<L, false>(v, lds + col, B, t, stw);
-#pragma unroll
-  for (int e = 0; e < LS::E; ++e) {
-    const double den = a0 + a1 * (double)lap_sym(tb, LS::idxB(t, e), ky, kx);
-    v[e] = cscale(v[e], (R)((double)scale / den));
-  }
-  line_ifft_BA<L>(v, lds + col, B, t, stw);
-  if (kx != 0) {
-#pragma unroll
-    for (int e = 0; e < LS::E; ++e) base[LS::idxA(t, e) * plane] = v[e];
-  }
 }
 
 // kx = 0 column: the packed value is A + i B (A: plane kx = 0, B: plane

@@ -6,14 +6,10 @@
 #include <stdexcept>
 #include <type_traits>
 
+#include "fg_fft_sizes.hpp"
 #include "fg_launch.hpp"
 
 namespace fg {
-
-#define FG_FOR_M(X) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256)
-#define FG_FOR_AXIS(X) X(1) X(4) X(6) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256)
-// N1 passes also take 512-long lines (plane grids of 512 x 512)
-#define FG_FOR_N1(X) FG_FOR_AXIS(X) X(512)
 
 template <typename R>
 void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const Skip& skip,
@@ -128,28 +124,6 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
 }
 
 template <typename R>
-void launch_zscalar(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, double a0, double a1,
-                    const Skip& skip, hipStream_t s) {
-  const int B = column_tile(N0, M, (int)sizeof(cplx<R>));
-  const int T = line_threads(N0);
-  const size_t shm = (size_t)N0 * B * sizeof(cplx<R>) + zpass_extra_lds<R>(N0);
-  dim3 grid((unsigned)(M / B), (unsigned)N1, 1);
-  dim3 gdc((unsigned)(N1 / 2 + 1), 1, 1);
-  switch (N0) {
-#define FG_CASE(L_)                                                                                   \
-  case L_:                                                                                            \
-    hipLaunchKernelGGL((k_fft_z_scalar<R, L_>), grid, dim3(T * B), shm, s, data, N1, M, B, tb, scale, a0, \
-                       a1, skip);                                                                     \
-    hipLaunchKernelGGL((k_fft_z_dc<R, L_, 1>), gdc, dim3(64 * z_dc_groups<1>()), 0, s, data, N1, M, tb, scale, \
-                       a0, a1, skip, (const R*)nullptr);                                              \
-    return;
-    FG_FOR_AXIS(FG_CASE)
-#undef FG_CASE
-  }
-  throw std::invalid_argument("unsupported N0");
-}
-
-template <typename R>
 int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* partials, const Gate& gate, int n0, int n1,
                  int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   OpArgs<R> a;
@@ -222,7 +196,7 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
   const bool twl = sizeof(R) == 4 && (size_t)(N1 * B + N1) * sizeof(cplx<R>) <= 65536;
   const size_t shm = (size_t)(N1 * B + (twl ? N1 : 0)) * sizeof(cplx<R>);
   a.tile = B;
-  const dim3 grid((unsigned)(a.M / B), (unsigned)N0, (unsigned)(3 * nitems));
+  const dim3 grid((unsigned)(a.M / B), (unsigned)N0, (unsigned)(a.nc * nitems));
   const dim3 block((unsigned)(T * B / cpt));
   constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
   constexpr bool TW = sizeof(R) == 4;
@@ -256,7 +230,7 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
 }
 
 template <typename R, typename RO>
-Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const int eb = (int)sizeof(cplx<R>);
   const int T = zgrad_threads(N0, eb);
   // built-in choice: the largest tile, workgroups ky fastest (consecutive
@@ -272,31 +246,38 @@ Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hi
   a.nmain = (a.M / B) * a.N1;
   const size_t shm = (size_t)N0 * std::max(B, 4) * sizeof(cplx<R>) + n0_extra_lds<R>(N0);
   const int bm = a.M & -a.M;  // a row of ky in groups of the largest power of two of columns
-  const Parts parts(3 * a.ndc + 3 * a.N1 * (a.M / bm), 3 * a.ndc, bm / B);
+  const Parts parts(a.nc * (a.ndc + a.N1 * (a.M / bm)), a.nc * a.ndc, bm / B);
   const dim3 grid((unsigned)((long)parts.stride() * nitems));
   const dim3 block((unsigned)std::max(T * B / cpt, 2 * T));
   constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
   constexpr bool kSame = sizeof(R) == sizeof(RO);
   switch (N0) {
-#define FG_N0_GO(L_, MODE_)                                                                      \
+#define FG_N0_GO(L_, MODE_, SYM_)                                                                \
   do {                                                                                           \
     if (cpt == 2)                                                                                \
-      launch_ev((k_n0<R, RO, L_, CP, MODE_>), grid, block, (unsigned)shm, s, ev0, ev1, a);       \
+      launch_ev((k_n0<R, RO, L_, CP, MODE_, SYM_>), grid, block, (unsigned)shm, s, ev0, ev1, a); \
     else                                                                                         \
-      launch_ev((k_n0<R, RO, L_, 1, MODE_>), grid, block, (unsigned)shm, s, ev0, ev1, a);        \
+      launch_ev((k_n0<R, RO, L_, 1, MODE_, SYM_>), grid, block, (unsigned)shm, s, ev0, ev1, a);  \
   } while (0)
-#define FG_CASE(L_)                                  \
-  case L_:                                           \
-    if (mode == kN0Cg) {                             \
-      if constexpr (kSame) FG_N0_GO(L_, kN0Cg);      \
-    } else if (mode == kN0Apply) {                   \
-      if constexpr (kSame) FG_N0_GO(L_, kN0Apply);   \
-    } else if constexpr (sizeof(R) == 8) {           \
-      if (mode == kN0Start)                          \
-        FG_N0_GO(L_, kN0Start);                      \
-      else if constexpr (kSame)                      \
-        FG_N0_GO(L_, kN0Norm);                       \
-    }                                                \
+#define FG_CASE(L_)                                              \
+  case L_:                                                       \
+    if (sym == kSymLap) {                                        \
+      if constexpr (sizeof(R) == 8 && kSame) {                   \
+        if (mode == kN0Cg)                                       \
+          FG_N0_GO(L_, kN0Cg, kSymLap);                          \
+        else                                                     \
+          FG_N0_GO(L_, kN0Start, kSymLap);                       \
+      }                                                          \
+    } else if (mode == kN0Cg) {                                  \
+      if constexpr (kSame) FG_N0_GO(L_, kN0Cg, kSymProj);        \
+    } else if (mode == kN0Apply) {                               \
+      if constexpr (kSame) FG_N0_GO(L_, kN0Apply, kSymProj);     \
+    } else if constexpr (sizeof(R) == 8) {                       \
+      if (mode == kN0Start)                                      \
+        FG_N0_GO(L_, kN0Start, kSymProj);                        \
+      else if constexpr (kSame)                                  \
+        FG_N0_GO(L_, kN0Norm, kSymProj);                         \
+    }                                                            \
     return parts;
     FG_FOR_AXIS(FG_CASE)
 #undef FG_CASE
@@ -306,16 +287,16 @@ Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hi
 }
 
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTables<R>& tb, const KrylovScalars* ks,
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines, const SpecTables<R>& tb, const KrylovScalars* ks,
                     int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   using C = cplx<R>;
   switch (M) {
 #define FG_CASE(L_)                                                                                              \
   case L_: {                                                                                                     \
     constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
-    const dim3 grid((unsigned)((nlines3 + LPB - 1) / LPB), (unsigned)nitems);                                    \
+    const dim3 grid((unsigned)((nlines + LPB - 1) / LPB), (unsigned)nitems);                                    \
     launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, reinterpret_cast<const C*>(in),            \
-              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines3, tb, ks);                              \
+              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines, tb, ks);                              \
     return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
@@ -330,7 +311,7 @@ void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTa
   template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
                                     hipStream_t, hipEvent_t, hipEvent_t);                               \
   template void launch_n1<R>(int, bool, int, N1Args<R>, int, hipStream_t, hipEvent_t, hipEvent_t);      \
-  template Parts launch_n0<R, R>(int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
+  template Parts launch_n0<R, R>(int, int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
   template void launch_c2r_dir<R>(int, const R*, R*, R*, long, const SpecTables<R>&, const KrylovScalars*, int, \
                                   hipStream_t, hipEvent_t, hipEvent_t);                                 \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
@@ -338,8 +319,6 @@ void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTa
                              hipEvent_t);                                                           \
   template void launch_axis<R>(int, bool, R*, long, long, long, int, int, int, const cplx<R>*, const Skip&, \
                                hipStream_t, int, hipEvent_t, hipEvent_t);                               \
-  template void launch_zproj<R>(int, R*, int, int, const SpecTables<R>&, R, const Skip&, hipStream_t, int, int); \
-  template void launch_zscalar<R>(int, R*, int, int, const SpecTables<R>&, R, double, double, const Skip&, \
-                                  hipStream_t);
+  template void launch_zproj<R>(int, R*, int, int, const SpecTables<R>&, R, const Skip&, hipStream_t, int, int);
 
 }  // namespace fg

@@ -8,6 +8,11 @@
 
 namespace fg {
 
+struct Grid3 {
+  int n0, n1, n2;
+  double ih0, ih1, ih2;  // 1 / h_j
+};
+
 // Launch that takes a timing event pair itself when one is given (the
 // kernel's own start and end, no marker packets on the stream): ev0 is
 // recorded at the start of this kernel, ev1 at its end; either may be null.
@@ -65,13 +70,13 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
 // N0 pass in the block layout (k_n0) in one of its modes; returns the
 // partial sums of r.r of an item.
 template <typename R, typename RO>
-Parts launch_n0(int N0, int mode, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
               hipEvent_t ev1 = nullptr);
 // most partial sums per item that launch_n0 writes, for any tile
 inline long n0_max_parts(int N1, int M) { return 3L * ((long)M * N1 + N1 / 2 + 1); }
 // Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines3, const SpecTables<R>& tb, const KrylovScalars* ks,
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines, const SpecTables<R>& tb, const KrylovScalars* ks,
                     int nitems, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 template <typename R>
@@ -100,9 +105,10 @@ constexpr int kTileColumnPairs = 1 << 17;
 // threads and an L x tile exchange buffer (plus the pass's tables) within
 // 64 KiB.  zproj: the fused N0 projection pass (L = N0), else the N1 pass.
 bool tile_valid(bool zproj, int L, int M, int elem_bytes, int tile);
-// N0 pass fused with a scalar symbol scale / (a0 + a1 lambda(q)), 1 component.
-template <typename R>
-void launch_zscalar(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R scale, double a0, double a1,
-                    const Skip& skip, hipStream_t s);
+// q = A p of the phase-field (op = 0: coef = a) or Fick (op = 1: coef = w, A6)
+// operator with its N2 transform (k_scalar_op); returns the number of partial
+// sums of p.q.
+int launch_scalar_op(int op, int M, const double* p, const double* coef, const double* A6, double kdiff, const Grid3& g,
+                     double* spec, double* partials, const Gate& gate, const SpecTables<double>& tb, hipStream_t s);
 
 }  // namespace fg

@@ -438,7 +438,7 @@ void check_domain(fg_plan* P) {
 // Sum of the partials into dscal[slot].
 void reduce_to(fg_plan* P, const double* parts, Parts n, int slot) {
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, parts, n, (KrylovScalars*)nullptr,
-                     P->dscal + slot, 2, 0);
+                     P->dscal + slot, 2);
   check_launch();
 }
 
@@ -446,7 +446,7 @@ void reduce_to(fg_plan* P, const double* parts, Parts n, int slot) {
 // array dscal[64 + 16 b + slot]... stored as dscal[64 + slot * nitems + b].
 void reduce_items(fg_plan* P, const double* parts, Parts n, int slot) {
   hipLaunchKernelGGL(k_finalize, dim3(P->nitems), dim3(1024), 0, P->stream, parts, n,
-                     (KrylovScalars*)nullptr, P->dscal + 64 + (long)slot * P->nitems, 2, 0);
+                     (KrylovScalars*)nullptr, P->dscal + 64 + (long)slot * P->nitems, 2);
   check_launch();
 }
 inline double item_value(const fg_plan* P, int slot, int b) { return P->hd[64 + (long)slot * P->nitems + b]; }
@@ -504,22 +504,11 @@ int project9(fg_plan* P, const R* in, R* work, R* out, const C2REpi& epi) {
   return inv_yx<R>(P, work, out, 9 * P->nitems, epi);
 }
 
-// y = F^-1[ F[x] / (a0 + a1 lambda) ] for one scalar field, returns #partials.
+// Arguments of the N1 and N0 passes of nc-component fields.
 template <typename R>
-int precond1(fg_plan* P, const R* in, R* work, R* out, double a0, double a1, const C2REpi& epi) {
-  fwd_xy<R>(P, in, work, 1, epi.skip);
-  {
-    ProfScope ps(P, FG_PASS_ZSCALAR);
-    launch_zscalar<R>(P->n0, work, P->n1, P->M, tabs<R>(P).spec(), (R)(1.0 / (double)P->N), a0, a1, epi.skip,
-                      P->stream);
-  }
-  return inv_yx<R>(P, work, out, 1, epi);
-}
-
-// Arguments of the N1 and N0 passes of 3-component fields.
-template <typename R>
-N1Args<R> n1_args(fg_plan* P, void* lines, void* blocks, void* dc, const Gate& gate) {
+N1Args<R> n1_args(fg_plan* P, void* lines, void* blocks, void* dc, const Gate& gate, int nc = 3) {
   N1Args<R> a{};
+  a.nc = nc;
   a.lines = (cplx<R>*)lines;
   a.blocks = (cplx<R>*)blocks;
   a.dc = (cplx<R>*)dc;
@@ -530,8 +519,9 @@ N1Args<R> n1_args(fg_plan* P, void* lines, void* blocks, void* dc, const Gate& g
   a.gate = gate;
   return a;
 }
-template <typename R, typename RO> N0Args<R, RO> n0_args(fg_plan* P, const Gate& gate) {
+template <typename R, typename RO> N0Args<R, RO> n0_args(fg_plan* P, const Gate& gate, int nc = 3) {
   N0Args<R, RO> a{};
+  a.nc = nc;
   a.bl = block_layout<R>(P->n0, P->n1, P->M);
   a.blo = block_layout<RO>(P->n0, P->n1, P->M);
   a.N1 = P->n1;
@@ -596,7 +586,7 @@ Parts residual_pass(fg_plan* P, const double* Y, const int* idle, bool start, do
     a.dcs = (cplx<T>*)P->rdc;
     a.sign = sign;
     a.partials = P->part;
-    return launch_n0<double, T>(P->n0, mode, a, P->nitems, P->stream);
+    return launch_n0<double, T>(P->n0, mode, kSymProj, a, P->nitems, P->stream);
   };
   const Parts nb = !start ? go(double(), kN0Norm) : P->prec == FG_FP64 ? go(double(), kN0Start) : go(float(), kN0Start);
   check_launch();
@@ -688,12 +678,12 @@ void cg_iteration(fg_plan* P) {
     a.dcs = (cplx<T>*)P->rdc;
     a.ks = ks;
     a.partials = P->part2;
-    nbz = launch_n0<T, T>(P->n0, kN0Cg, a, nit, P->stream, ps.start, ps.stop);
+    nbz = launch_n0<T, T>(P->n0, kN0Cg, kSymProj, a, nit, P->stream, ps.start, ps.stop);
   }
   {
     ProfScope ps(P, FG_PASS_FINALIZE, true);
     launch_ev(k_finalize, dim3(nit), dim3(1024), 0, P->stream, ps.start, ps.stop, (const double*)P->part2, nbz, ks,
-              (double*)nullptr, 1, 0);
+              (double*)nullptr, 1);
   }
   check_launch();
 }
@@ -701,7 +691,7 @@ void cg_iteration(fg_plan* P) {
 // Krylov scalars of a single-item CG whose start residual_pass left the
 // partial sums of r_0.r_0 (rr0 = rr, iter = 0, done if r_0 = 0).
 void cg_begin(fg_plan* P, Parts parts) {
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, parts, P->ks, (double*)nullptr, 5, 0);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, parts, P->ks, (double*)nullptr, 5);
   check_launch();
 }
 
@@ -952,13 +942,17 @@ void adjoint_mixed(fg_plan* P, const double W[9], double* gE, double* gO, const 
 }
 
 // ----------------------------------------------------------------------------
-// Scalar PCG (shared by the phase-field and Fick solves).  Vectors in the
-// scalar area: x, r, z, p, q, work (spectral).  ks[1] holds the scalars; the
-// caller has set r = b, x = 0 and ks[1] (rr0) via mode 5.
+// Scalar PCG (shared by the phase-field and Fick solves), on the passes of the
+// mechanics CG with one component and the preconditioner's symbol: the
+// residual lives in the spectrum, r.r and r.z come from Parseval, and
+//   p = z + beta p, x += alpha p  ride on the inverse N2 pass of z,
+//   q = A p and p.q               on its N2 transform.
+// ksc holds the scalars; the caller has set v.r = b and ksc (rr0) via
+// mode 5.  The last step of x is left to the caller (pcg_x).
 enum class ScalarOp { PFF, FICK };
 
 struct ScalarVecs {
-  double *x, *r, *z, *p, *q, *work, *a, *w, *mu, *A6, *ct;
+  double *x, *r, *p, *s, *sdc, *a, *w, *mu, *A6, *ct;
 };
 
 ScalarVecs scalar_vecs(fg_plan* P) {
@@ -966,11 +960,10 @@ ScalarVecs scalar_vecs(fg_plan* P) {
   double* b = P->sc;
   ScalarVecs v;
   v.x = b + 0 * N;
-  v.r = b + 1 * N;
-  v.z = b + 2 * N;
-  v.p = b + 3 * N;
-  v.q = b + 4 * N;
-  v.work = b + 5 * N;
+  v.r = b + 1 * N;  // right-hand side
+  v.p = b + 2 * N;
+  v.s = b + 3 * N;  // 2N: spectral residual, block layout
+  v.sdc = b + 5 * N;  // its kx = 0 column
   v.a = b + 6 * N;
   v.w = b + 6 * N;  // Fick uses w where PFF uses a
   v.mu = b + 7 * N;
@@ -988,35 +981,46 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   ((int*)(P->hd + 61))[0] = (o->fixed_lin > 0) ? o->fixed_lin : o->max_lin;
   FG_HIP(hipMemcpyAsync(&ks->tol2, P->hd + 60, sizeof(double), hipMemcpyHostToDevice, P->stream));
   FG_HIP(hipMemcpyAsync(&ks->maxit, P->hd + 61, sizeof(int), hipMemcpyHostToDevice, P->stream));
-  const Skip skip = Skip::done(ks);
-  const unsigned nbN = blocks_for(P->N);
-  const unsigned nbu = grid_stride_blocks(P->N);
+  const Gate gate = Gate::done(ks);
+  const SpecTables<double> tb = P->t64.spec();
   const Grid3 g{P->n0, P->n1, P->n2, 1.0 / P->h[0], 1.0 / P->h[1], 1.0 / P->h[2]};
-  // z = M r, rz
-  auto apply_prec = [&]() {
-    C2REpi epi{1.0, v.r, false, P->part, skip};
-    const int nb = precond1<double>(P, v.r, v.work, v.z, a0, a1, epi);
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, Parts(nb), ks, (double*)nullptr, 4, 1);
+  auto n0_pass = [&](int mode) {
+    N0Args<double, double> a = n0_args<double, double>(P, gate, 1);
+    a.q = a.z = (cplx<double>*)P->bk64;
+    a.dcq = a.dcz = (cplx<double>*)P->dc64;
+    a.s = (cplx<double>*)v.s;
+    a.dcs = (cplx<double>*)v.sdc;
+    a.a0 = a0;
+    a.a1 = a1;
+    a.ks = ks;
+    a.partials = P->part2;
+    a.partials2 = P->part;
+    ProfScope ps(P, FG_PASS_ZSCALAR);
+    const Parts n = launch_n0<double, double>(P->n0, mode, kSymLap, a, 1, P->stream);
+    hipLaunchKernelGGL(k_pcg_finalize, dim3(1), dim3(1024), 0, P->stream, (const double*)P->part2,
+                       (const double*)P->part, n, ks, mode == kN0Start ? 1 : 0);
   };
-  apply_prec();
+  const N1Args<double> n1 = n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1);
+  // s_0 = b, z_0
+  launch_r2c<double>(P->M, v.r, P->ln64, (long)P->n0 * P->n1, tb, Skip::done(ks), P->stream);
+  launch_n1<double>(P->n1, false, P->n0, n1, 1, P->stream);
+  n0_pass(kN0Start);
   check_launch();
   int chunk = 4;
   for (int guard = 0; guard < 1000000; ++guard) {
     for (int k = 0; k < chunk; ++k) {
-      hipLaunchKernelGGL(k_pcg_dir, dim3(nbN), dim3(256), 0, P->stream, v.p, v.z, ks, P->N);
-      if (op == ScalarOp::PFF)
-        hipLaunchKernelGGL(k_pff_apply, dim3(nbN), dim3(256), 0, P->stream, v.p, v.a, P->gc * P->lc, g, v.q,
-                           P->part, ks, P->N);
-      else
-        hipLaunchKernelGGL(k_fick_apply, dim3(nbN), dim3(256), 0, P->stream, v.p, v.w, v.A6, dt, g, v.q, P->part,
-                           ks, P->N);
-      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part, Parts((int)nbN), ks, (double*)nullptr, 0,
-                         1);
-      hipLaunchKernelGGL((k_cg_update<double>), dim3(nbu), dim3(256), 0, P->stream, v.x, v.r, v.p, v.q, ks,
-                         P->part2, P->N);
-      hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbu), ks, (double*)nullptr, 3,
-                         1);
-      apply_prec();
+      launch_n1<double>(P->n1, true, P->n0, n1, 1, P->stream);
+      launch_c2r_dir<double>(P->M, P->ln64, v.p, v.x, (long)P->n0 * P->n1, tb, ks, 1, P->stream);
+      const int nb = launch_scalar_op(op == ScalarOp::FICK, P->M, v.p, op == ScalarOp::FICK ? v.w : v.a, v.A6,
+                                      op == ScalarOp::FICK ? dt : P->gc * P->lc, g, P->ln64, P->part, gate, tb,
+                                      P->stream);
+      N1Args<double> n1f = n1;
+      n1f.pap = P->part;
+      n1f.npap = nb;
+      n1f.ks = ks;
+      n1f.pcg = 1;
+      launch_n1<double>(P->n1, false, P->n0, n1f, 1, P->stream);
+      n0_pass(kN0Cg);
       check_launch();
     }
     sync_read(P);
@@ -1039,11 +1043,11 @@ void pff(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
   const unsigned nbN = blocks_for(P->N);
   const double* c = P->c ? P->c : P->zeroN;
   hipLaunchKernelGGL(k_pff_history, dim3(nbN), dim3(256), 0, P->stream, P->F, c, P->E, P->nu, P->Om, P->smax, P->H,
-                     v.a, v.r, v.x, P->gc, P->lc, P->part, P->part2, P->flags, P->N, P->law);
+                     v.a, v.r, P->gc, P->lc, P->part, P->part2, P->flags, P->N, P->law);
   check_launch();
   reduce_to(P, P->part, (int)nbN, 0);  // sum H
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbN), P->ksc, (double*)nullptr,
-                     5, 1);
+                     5);
   check_launch();
   sync_read(P);
   check_domain(P);
@@ -1055,7 +1059,9 @@ void pff(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
     stats->lin_iters_last = 0;
     stats->lin_relres = 0.0;
   }
-  FG_HIP(hipMemcpyAsync(P->d, v.x, P->N * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
+  hipLaunchKernelGGL(k_pff_result, dim3(nbN), dim3(256), 0, P->stream, P->d, (const double*)v.x, (const double*)v.p,
+                     (const KrylovScalars*)P->ksc, P->N);
+  check_launch();
 }
 
 void fick(fg_plan* P, double dt, const double* cdot, const fg_solver_opts* o, fg_stats* stats,
@@ -1086,16 +1092,17 @@ void fick(fg_plan* P, double dt, const double* cdot, const fg_solver_opts* o, fg
     check_launch();
     reduce_to(P, P->part, (int)nbN, 2);  // sum 1/w
     hipLaunchKernelGGL(k_fick_residual, dim3(nbN), dim3(256), 0, P->stream, P->c, v.ct, v.mu, v.A6, cdot, dt, g,
-                       v.r, v.x, P->part2, N);
+                       v.r, P->part2, N);
     check_launch();
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(1024), 0, P->stream, P->part2, Parts((int)nbN), P->ksc,
-                       (double*)nullptr, 5, 1);
+                       (double*)nullptr, 5);
     check_launch();
     sync_read(P);
     check_domain(P);
     const double winv = P->hd[2] / (double)N;
     if (!P->hksc[0].done) scalar_pcg(P, ScalarOp::FICK, winv, dt * abar, dt, o, stats);
-    hipLaunchKernelGGL(k_fick_update, dim3(nbN), dim3(256), 0, P->stream, P->c, v.x, v.w, P->part, N);
+    hipLaunchKernelGGL(k_fick_update, dim3(nbN), dim3(256), 0, P->stream, P->c, v.x, v.p, (const KrylovScalars*)P->ksc,
+                       v.w, P->part, N);
     check_launch();
     reduce_to(P, P->part, (int)nbN, 3);
     sync_read(P);
@@ -1485,7 +1492,7 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
     N0Args<double, double> a = n0_args<double, double>(P, none);
     a.q = a.z = (cplx<double>*)P->bk64;
     a.dcq = a.dcz = (cplx<double>*)P->dc64;
-    launch_n0<double, double>(P->n0, kN0Apply, a, 1, P->stream);
+    launch_n0<double, double>(P->n0, kN0Apply, kSymProj, a, 1, P->stream);
     launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
     launch_c2r<double>(P->M, P->ln64, P->ln64, 3L * P->n0 * P->n1, P->t64.spec(),
                        C2REpi{1.0, nullptr, true, nullptr, Skip{}}, P->stream);
@@ -2148,7 +2155,7 @@ void time_pass_impl(fg_plan* P, bool zproj, int tile, int reps, double* ms) {
       a.q = a.z = (cplx<R>*)bk;
       a.dcq = a.dcz = (cplx<R>*)dc;
       a.tile = tile;
-      launch_n0<R, R>(P->n0, kN0Apply, a, P->nitems, P->stream);
+      launch_n0<R, R>(P->n0, kN0Apply, kSymProj, a, P->nitems, P->stream);
     } else {
       // the N1 work of a CG iteration: the forward and the inverse pass
       N1Args<R> a = n1_args<R>(P, ln, bk, dc, none);

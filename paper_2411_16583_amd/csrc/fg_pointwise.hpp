@@ -296,95 +296,22 @@ k_contract(T* __restrict__ Y, const T* __restrict__ X, const T* __restrict__ st,
   for (int k = 0; k < 9; ++k) yv[k * N2v + i] = mk<V>(Y0[k], Y1[k]);
 }
 
-// 16-byte vector of the working precision (2 doubles or 4 floats).
-template <typename T> struct vec16;
-template <> struct vec16<double> {
-  using type = double2;
-  static constexpr int n = 2;
-};
-template <> struct vec16<float> {
-  using type = float4;
-  static constexpr int n = 4;
-};
-
-template <typename T, typename V> __device__ __forceinline__ T vget(const V& v, int k) {
-  if constexpr (sizeof(V) == 16 && sizeof(T) == 8) {
-    return k == 0 ? v.x : v.y;
-  } else {
-    return k == 0 ? v.x : (k == 1 ? v.y : (k == 2 ? v.z : v.w));
-  }
-}
-template <typename T, typename V> __device__ __forceinline__ void vset(V& v, int k, T a) {
-  if constexpr (sizeof(V) == 16 && sizeof(T) == 8) {
-    if (k == 0) v.x = a; else v.y = a;
-  } else {
-    if (k == 0) v.x = a; else if (k == 1) v.y = a; else if (k == 2) v.z = a; else v.w = a;
-  }
-}
-
-// x += alpha p, r -= alpha q, per-block partial sums of r.r.  16-byte
-// accesses; n must be a multiple of the vector width (the scalar fields of
-// the preconditioned solvers: N is even).
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_cg_update(T* __restrict__ x, T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ q,
-            const KrylovScalars* __restrict__ ks, double* __restrict__ partials, long n) {
-  using V = typename vec16<T>::type;
-  constexpr int W = vec16<T>::n;
-  __shared__ double red[16];
-  if (ks->done) return;
-  const T alpha = (T)ks->alpha;
-  double acc = 0.0;
-  const long nv = n / W;
-  V* xv = reinterpret_cast<V*>(x);
-  V* rv = reinterpret_cast<V*>(r);
-  const V* pv = reinterpret_cast<const V*>(p);
-  const V* qv = reinterpret_cast<const V*>(q);
-  const long stride = (long)gridDim.x * blockDim.x;
-  long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i + stride < nv; i += 2 * stride) {
-    V xa = xv[i], ra = rv[i], pa = pv[i], qa = qv[i];
-    V xb = xv[i + stride], rb = rv[i + stride], pb = pv[i + stride], qb = qv[i + stride];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      vset(xa, k, (T)(vget<T>(xa, k) + alpha * vget<T>(pa, k)));
-      const T ta = vget<T>(ra, k) - alpha * vget<T>(qa, k);
-      vset(ra, k, ta);
-      acc += (double)ta * (double)ta;
-      vset(xb, k, (T)(vget<T>(xb, k) + alpha * vget<T>(pb, k)));
-      const T tb = vget<T>(rb, k) - alpha * vget<T>(qb, k);
-      vset(rb, k, tb);
-      acc += (double)tb * (double)tb;
-    }
-    xv[i] = xa;
-    rv[i] = ra;
-    xv[i + stride] = xb;
-    rv[i + stride] = rb;
-  }
-  for (; i < nv; i += stride) {
-    V xa = xv[i], ra = rv[i], pa = pv[i], qa = qv[i];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      vset(xa, k, (T)(vget<T>(xa, k) + alpha * vget<T>(pa, k)));
-      const T ta = vget<T>(ra, k) - alpha * vget<T>(qa, k);
-      vset(ra, k, ta);
-      acc += (double)ta * (double)ta;
-    }
-    xv[i] = xa;
-    rv[i] = ra;
-  }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-// mode 0: alpha = rz / pAp (rz = rr for plain CG), breakdown check.
 // mode 1: plain CG: rr_new, iteration count, convergence, beta.
 // mode 2: store the sum into out[0] (norms).
-// mode 3: PCG: r.r (convergence) -- z not yet formed.
-// mode 4: PCG: r.z -> beta = rz_new / rz.
 // mode 5: initialise a Krylov solve from rr0 = sum (b.b): rr = rr0, iter = 0.
+__device__ __forceinline__ void krylov_test(KrylovScalars* ks, double rr) {
+  ks->iter += 1;
+  ks->rr = rr;
+  if (ks->tol2 > 0.0 && rr <= ks->tol2 * ks->rr0) {
+    ks->done = 1;
+  } else if (ks->iter >= ks->maxit) {
+    ks->done = 1;
+    ks->flag = (ks->tol2 > 0.0) ? 2 : 0;
+  }
+}
+
 __global__ void __launch_bounds__(1024)
-k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, double* out, int mode, int pcg) {
+k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, double* out, int mode) {
   // one workgroup per batch item: its partials, scalars and output
   __shared__ double red[16];
   partials += (long)blockIdx.x * parts.stride();
@@ -393,39 +320,13 @@ k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, 
   if (ks && ks->done && mode != 5 && mode != 2) return;
   const double s = sum_parts(partials, parts, red);
   if (threadIdx.x != 0) return;
-  if (mode == 0) {
-    krylov_alpha(ks, s, pcg);
-  } else if (mode == 1) {
-    const double rr = s;
-    ks->iter += 1;
+  if (mode == 1) {
     // beta is kept even when the solve stops here, so that a solve stopped
     // at a fixed iteration count can be continued
-    ks->beta = rr / ks->rr;
-    if (ks->tol2 > 0.0 && rr <= ks->tol2 * ks->rr0) {
-      ks->done = 1;
-    } else if (ks->iter >= ks->maxit) {
-      ks->done = 1;
-      ks->flag = (ks->tol2 > 0.0) ? 2 : 0;
-    }
-    ks->rr = rr;
+    ks->beta = s / ks->rr;
+    krylov_test(ks, s);
   } else if (mode == 2) {
     out[0] = s;
-  } else if (mode == 3) {
-    ks->iter += 1;
-    ks->rr = s;
-    if (ks->tol2 > 0.0 && s <= ks->tol2 * ks->rr0) {
-      ks->done = 1;
-    } else if (ks->iter >= ks->maxit) {
-      ks->done = 1;
-      ks->flag = (ks->tol2 > 0.0) ? 2 : 0;
-    }
-  } else if (mode == 4) {
-    if (ks->iter == 0) {
-      ks->beta = 0.0;
-    } else {
-      ks->beta = s / ks->rz;
-    }
-    ks->rz = s;
   } else if (mode == 5) {
     ks->rr0 = s;
     ks->rr = s;
@@ -434,6 +335,23 @@ k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, 
     ks->beta = 0.0;
     ks->done = (s == 0.0) ? 1 : 0;
   }
+}
+
+// Preconditioned CG after the N0 pass: r.r (iteration count, convergence) and
+// r.z -> beta = rz_new / rz; with start, r.z of the first residual alone.
+__global__ void __launch_bounds__(1024)
+k_pcg_finalize(const double* __restrict__ prr, const double* __restrict__ prz, Parts parts, KrylovScalars* ks,
+               int start) {
+  __shared__ double red[16];
+  if (ks->done) return;
+  const double rz = sum_parts(prz, parts, red);
+  const double rr = start ? 0.0 : sum_parts(prr, parts, red);
+  if (threadIdx.x != 0) return;
+  if (!start) {
+    ks->beta = rz / ks->rz;
+    krylov_test(ks, rr);
+  }
+  ks->rz = rz;
 }
 
 // F += x (F FP64, x in the CG precision), n = 9N.

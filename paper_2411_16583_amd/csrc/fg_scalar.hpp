@@ -9,17 +9,9 @@
 // linear maps; the constant-coefficient preconditioners go through the FFT.
 #pragma once
 #include "fg_pointwise.hpp"
+#include "fg_scalar_op.hpp"
 
 namespace fg {
-
-struct Grid3 {
-  int n0, n1, n2;
-  double ih0, ih1, ih2;  // 1 / h_j
-};
-
-__device__ __forceinline__ long vox(const Grid3& g, int i0, int i1, int i2) {
-  return ((long)i0 * g.n1 + i1) * g.n2 + i2;
-}
 
 // Eigenvalues of a symmetric 3x3 matrix (closed form, trigonometric).
 __device__ __forceinline__ void sym_eig3(double a00, double a11, double a22, double a01, double a02, double a12,
@@ -50,12 +42,11 @@ __device__ __forceinline__ void sym_eig3(double a00, double a11, double a22, dou
 //   sigma = J^-1 s^-2 F S F^T                               (SVK),
 // D_f = < sum <sigma_i>^2 / sigma_max^2 - 1 >, H <- max(H, gc/(2 lc) D_f).
 // Writes the PFF coefficient a = gc/lc + 2H, the right-hand side b = 2H (into
-// r), zeroes the solution x, and per-block partials of H (part_h) and b.b
-// (part_b).
+// r), and per-block partials of H (part_h) and b.b (part_b).
 __global__ void __launch_bounds__(256)
 k_pff_history(const double* __restrict__ F, const double* __restrict__ c, const double* __restrict__ E,
               const double* __restrict__ nu, const double* __restrict__ Om, const double* __restrict__ smax,
-              double* __restrict__ H, double* __restrict__ acoef, double* __restrict__ r, double* __restrict__ x,
+              double* __restrict__ H, double* __restrict__ acoef, double* __restrict__ r,
               double gc, double lc, double* __restrict__ part_h, double* __restrict__ part_b, int* flags, long N,
               int law) {
   __shared__ double red[16];
@@ -115,7 +106,6 @@ k_pff_history(const double* __restrict__ F, const double* __restrict__ c, const 
     H[i] = h;
     acoef[i] = gc / lc + 2.0 * h;
     r[i] = 2.0 * h;
-    x[i] = 0.0;
     hv = h;
     bb = 4.0 * h * h;
   }
@@ -123,42 +113,6 @@ k_pff_history(const double* __restrict__ F, const double* __restrict__ c, const 
   if (threadIdx.x == 0) part_h[blockIdx.x] = s;
   s = block_sum(bb, red);
   if (threadIdx.x == 0) part_b[blockIdx.x] = s;
-}
-
-// q = A(p) = a p - k Lap_h p (7-point), partial sums of p.q.
-__global__ void __launch_bounds__(256)
-k_pff_apply(const double* __restrict__ p, const double* __restrict__ acoef, double kdiff, Grid3 g,
-            double* __restrict__ q, double* __restrict__ partials, const KrylovScalars* __restrict__ ks, long N) {
-  __shared__ double red[16];
-  if (ks->done) return;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  double acc = 0.0;
-  if (i < N) {
-    const int i2 = (int)(i % g.n2);
-    const int i1 = (int)((i / g.n2) % g.n1);
-    const int i0 = (int)(i / ((long)g.n2 * g.n1));
-    const double pc = p[i];
-    const double l0 = (2.0 * pc - p[vox(g, (i0 + 1) % g.n0, i1, i2)] - p[vox(g, (i0 + g.n0 - 1) % g.n0, i1, i2)]) *
-                      g.ih0 * g.ih0;
-    const double l1 = (2.0 * pc - p[vox(g, i0, (i1 + 1) % g.n1, i2)] - p[vox(g, i0, (i1 + g.n1 - 1) % g.n1, i2)]) *
-                      g.ih1 * g.ih1;
-    const double l2 = (2.0 * pc - p[vox(g, i0, i1, (i2 + 1) % g.n2)] - p[vox(g, i0, i1, (i2 + g.n2 - 1) % g.n2)]) *
-                      g.ih2 * g.ih2;
-    const double qv = acoef[i] * pc + kdiff * (l0 + l1 + l2);
-    q[i] = qv;
-    acc = pc * qv;
-  }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-// PCG search direction p = z (first iteration) or z + beta p.
-__global__ void __launch_bounds__(256)
-k_pcg_dir(double* __restrict__ p, const double* __restrict__ z, const KrylovScalars* __restrict__ ks, long N) {
-  if (ks->done) return;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  p[i] = (ks->iter == 0) ? z[i] : z[i] + ks->beta * p[i];
 }
 
 // ---------------------------------------------------------------- Fick ----
@@ -273,53 +227,11 @@ k_fick_mu(const double* __restrict__ c, const double* __restrict__ F, const doub
   if (threadIdx.x == 0) part_winv[blockIdx.x] = s;
 }
 
-// L(v) = grad+^T ( Aplus grad+ v ) at voxel i (forward differences, their
-// adjoint for the divergence).  With div = -grad+^T and Aplus = -M c(1-c) C^-1
-// this is div[ M c(1-c) C^-1 grad v ], the operator of eq. (43).
-__device__ __forceinline__ double fick_L(const double* __restrict__ v, const double* __restrict__ A6, const Grid3& g,
-                                         long N, int i0, int i1, int i2) {
-  const int im[3] = {(i0 + g.n0 - 1) % g.n0, (i1 + g.n1 - 1) % g.n1, (i2 + g.n2 - 1) % g.n2};
-  const double ih[3] = {g.ih0, g.ih1, g.ih2};
-  const int ic[3] = {i0, i1, i2};
-  // Aplus component index for (j, k)
-  const int aidx[9] = {0, 5, 4, 5, 1, 3, 4, 3, 2};
-  auto gradp = [&](int a0, int a1, int a2, double (&gr)[3]) {
-    const double vc = v[vox(g, a0, a1, a2)];
-    gr[0] = (v[vox(g, (a0 + 1) % g.n0, a1, a2)] - vc) * g.ih0;
-    gr[1] = (v[vox(g, a0, (a1 + 1) % g.n1, a2)] - vc) * g.ih1;
-    gr[2] = (v[vox(g, a0, a1, (a2 + 1) % g.n2)] - vc) * g.ih2;
-  };
-  double gr[3];
-  gradp(i0, i1, i2, gr);
-  const long ic_lin = vox(g, i0, i1, i2);
-  double out = 0.0;
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    // flux_j(x) = sum_k A_jk(x) gr_k(x)
-    double fx = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) fx += A6[aidx[3 * j + k] * N + ic_lin] * gr[k];
-    // flux_j(x - e_j)
-    int b[3] = {ic[0], ic[1], ic[2]};
-    b[j] = im[j];
-    double gm[3];
-    gradp(b[0], b[1], b[2], gm);
-    const long bl = vox(g, b[0], b[1], b[2]);
-    double fm = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) fm += A6[aidx[3 * j + k] * N + bl] * gm[k];
-    // grad+^T w = sum_j (w_j(x - e_j) - w_j(x)) / h_j
-    out += (fm - fx) * ih[j];
-  }
-  return out;
-}
-
-// Fick residual: b = -f(c) = -(c - c_t + dt L(mu) - dt cdot_B), partials of b.b;
-// also zeroes the solution x.
+// Fick residual: b = -f(c) = -(c - c_t + dt L(mu) - dt cdot_B), partials of b.b.
 __global__ void __launch_bounds__(256)
 k_fick_residual(const double* __restrict__ c, const double* __restrict__ ct, const double* __restrict__ mu,
                 const double* __restrict__ A6, const double* __restrict__ cdot, double dt, Grid3 g,
-                double* __restrict__ b, double* __restrict__ x, double* __restrict__ partials, long N) {
+                double* __restrict__ b, double* __restrict__ partials, long N) {
   __shared__ double red[16];
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   double acc = 0.0;
@@ -327,46 +239,39 @@ k_fick_residual(const double* __restrict__ c, const double* __restrict__ ct, con
     const int i2 = (int)(i % g.n2);
     const int i1 = (int)((i / g.n2) % g.n1);
     const int i0 = (int)(i / ((long)g.n2 * g.n1));
-    const double f = c[i] - ct[i] + dt * fick_L(mu, A6, g, N, i0, i1, i2) - dt * (cdot ? cdot[i] : 0.0);
+    const double f = c[i] - ct[i] + dt * fick_L(mu, A6, g, N, neighbours(g, i0, i1, i2)) - dt * (cdot ? cdot[i] : 0.0);
     b[i] = -f;
-    x[i] = 0.0;
     acc = f * f;
   }
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// q = B(p) = p / w + dt L(p), partials of p.q.
-__global__ void __launch_bounds__(256)
-k_fick_apply(const double* __restrict__ p, const double* __restrict__ w, const double* __restrict__ A6, double dt,
-             Grid3 g, double* __restrict__ q, double* __restrict__ partials, const KrylovScalars* __restrict__ ks,
-             long N) {
-  __shared__ double red[16];
-  if (ks->done) return;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  double acc = 0.0;
-  if (i < N) {
-    const int i2 = (int)(i % g.n2);
-    const int i1 = (int)((i / g.n2) % g.n1);
-    const int i0 = (int)(i / ((long)g.n2 * g.n1));
-    const double pc = p[i];
-    const double qv = pc / w[i] + dt * fick_L(p, A6, g, N, i0, i1, i2);
-    q[i] = qv;
-    acc = pc * qv;
-  }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+// The solution of a scalar PCG with its last, deferred step:
+// x + alpha p, or 0 where the solve never iterated.
+__device__ __forceinline__ double pcg_x(const double* __restrict__ x, const double* __restrict__ p,
+                                        const KrylovScalars* __restrict__ ks, long i) {
+  return ks->iter == 0 ? 0.0 : x[i] + ks->alpha * p[i];
 }
 
-// c += dmu / w, partials of dc.dc.
+// d = solution of the phase-field solve.
 __global__ void __launch_bounds__(256)
-k_fick_update(double* __restrict__ c, const double* __restrict__ dmu, const double* __restrict__ w,
-              double* __restrict__ partials, long N) {
+k_pff_result(double* __restrict__ d, const double* __restrict__ x, const double* __restrict__ p,
+             const KrylovScalars* __restrict__ ks, long N) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < N) d[i] = pcg_x(x, p, ks, i);
+}
+
+// c += dmu / w (dmu the solution of the linear step), partials of dc.dc.
+__global__ void __launch_bounds__(256)
+k_fick_update(double* __restrict__ c, const double* __restrict__ x, const double* __restrict__ p,
+              const KrylovScalars* __restrict__ ks, const double* __restrict__ w, double* __restrict__ partials,
+              long N) {
   __shared__ double red[16];
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   double acc = 0.0;
   if (i < N) {
-    const double dc = dmu[i] / w[i];
+    const double dc = pcg_x(x, p, ks, i) / w[i];
     c[i] += dc;
     acc = dc * dc;
   }
