@@ -335,13 +335,25 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   }
 }
 
+// Element k of a real line's half spectrum from its packed transform z (k = 0
+// carries both ends); w = W_{N2}^k.
+template <typename C> __device__ __forceinline__ C r2c_post(const C* z, int k, int M, C w) {
+  using R = decltype(C::x);
+  const C zk = z[k];
+  if (k == 0) return mk<C>(zk.x + zk.y, zk.x - zk.y);
+  const C zm = z[M - k];
+  const C ev = cscale(cadd(zk, cconj(zm)), R(0.5));
+  const C od = cscale(mul_mi(csub(zk, cconj(zm))), R(0.5));
+  return cadd(ev, cmul(od, w));
+}
+
 // N2 transform of the 3-component fields q of k_cg_op with the patch edges
-// added on load.  grid: line blocks of 3 N0 N1 lines per item, blockIdx.y =
+// added on load, into the line layout or (planes) the plane layout.  grid: line blocks of 3 N0 N1 lines per item, blockIdx.y =
 // item.
 template <typename R, int M>
 __global__ void __launch_bounds__(XBLOCK)
 k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, cplx<R>* __restrict__ out, int n0,
-            int n1, SpecTables<R> tb, Gate gate) {
+            int n1, SpecTables<R> tb, Gate gate, int planes) {
   using C = cplx<R>;
   using LS = Line<M>;
   constexpr int LPB = XBLOCK / LS::T, N2 = 2 * M;
@@ -406,15 +418,22 @@ k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, 
 #pragma unroll
   for (int e = 0; e < LS::E; ++e) my[LS::idxB(t, e)] = v[e];
   __syncthreads();
-  auto post = [&](int k) {
-    const C zk = my[k];
-    if (k == 0) return mk<C>(zk.x + zk.y, zk.x - zk.y);  // both ends of the real line's spectrum
-    const C zm = my[M - k];
-    const C ev = cscale(cadd(zk, cconj(zm)), R(0.5));
-    const C od = cscale(mul_mi(csub(zk, cconj(zm))), R(0.5));
-    return cadd(ev, cmul(od, spost[k]));
-  };
-  if constexpr (sizeof(R) == 4 && M % (2 * LS::T) == 0) {
+  auto post = [&](int k) { return r2c_post(my, k, M, spost[k]); };
+  if (planes) {
+    // plane layout: the workgroup's lines of one kx together
+    C* o = out + (long)item * 3 * nlines * M;
+    const int lin0 = (int)(blockIdx.x * LPB), c0 = lin0 / nlines;
+    for (int i = threadIdx.x; i < LPB * M; i += XBLOCK) {
+      const int k = i / LPB, j = i - k * LPB;
+      if (lin0 + j >= 3 * nlines) continue;
+      int c = c0, r = lin0 + j - c0 * nlines;
+      while (r >= nlines) {
+        r -= nlines;
+        ++c;
+      }
+      o[((long)c * M + k) * nlines + r] = r2c_post(lds + j * (M + PAD), k, M, spost[k]);
+    }
+  } else if constexpr (sizeof(R) == 4 && M % (2 * LS::T) == 0) {
     // two adjacent elements per thread: whole 128-byte lines per store
 #pragma unroll
     for (int j = 0; j < M / (2 * LS::T); ++j) {
@@ -849,12 +868,12 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 // Inverse N2 pass of z fused with the CG vectors, per line of a component:
 //   xi += alpha_{k-1} pi_{k-1},  pi_k = z + beta pi_{k-1}   (k > 0),
 //   xi = 0,  pi_0 = z                                       (k = 0).
-// grid: line blocks of the item's lines (N0 N1 per component), blockIdx.y =
-// item.
+// grid: line blocks of the item's lines (nlines per component), blockIdx.y =
+// item; in: line or (planes) plane layout.  Without ks: z alone, into pi.
 template <typename R, int M>
 __global__ void __launch_bounds__(XBLOCK)
-k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, long nlines,
-          SpecTables<R> tb, const KrylovScalars* __restrict__ ksb) {
+k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, int nlines, int nc,
+          SpecTables<R> tb, const KrylovScalars* __restrict__ ksb, int planes) {
   using C = cplx<R>;
   using LS = Line<M>;
   constexpr int LPB = XBLOCK / LS::T;
@@ -863,27 +882,69 @@ k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __r
   __shared__ C stw[M], spost[M];
   const int item = blockIdx.y;
   const KrylovScalars* ks = ksb + item;
-  if (ks->done) return;
+  if (ksb && ks->done) return;
   for (int k = threadIdx.x; k < M; k += XBLOCK) {
     stw[k] = tb.twM[k];
     spost[k] = tb.post[k];
   }
-  const bool first = ks->iter == 0;
-  const R alpha = (R)ks->alpha, beta = (R)ks->beta;
+  const bool first = !ksb || ks->iter == 0;
+  const R alpha = first ? R(0) : (R)ks->alpha, beta = first ? R(0) : (R)ks->beta;
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
-  const long lin = (long)blockIdx.x * LPB + ll;
-  const bool active = ll < LPB && lin < nlines;
-  const long base = ((long)item * nlines + (active ? lin : 0)) * M;
-  C* my = lds + (ll < LPB ? ll : 0) * (M + PAD);
+  const int all = nc * nlines;  // lines of the item
+  const int lin0 = (int)blockIdx.x * LPB, lin = lin0 + ll;
+  const bool active = lin < all;
+  const long ib = (long)item * all * M;
+  const long base = ib + (long)(active ? lin : 0) * M;
+  C* my = lds + ll * (M + PAD);
   C v[LS::E];
+  if (planes) {
+    static_assert(LPB * M == LS::E * XBLOCK, "elements per thread");
+    const int c0 = lin0 / nlines;
 #pragma unroll
-  for (int e = 0; e < LS::E; ++e)
-    v[e] = active ? (sizeof(R) == 8 ? ld_stream(in + base + LS::idxA(t, e)) : in[base + LS::idxA(t, e)])
-                  : mk<C>(R(0), R(0));
+    for (int e = 0; e < LS::E; ++e) {
+      const int i = threadIdx.x + e * XBLOCK, k = i / LPB, j = i % LPB;
+      int c = c0, r = lin0 + j - c0 * nlines;
+      while (r >= nlines) {
+        r -= nlines;
+        ++c;
+      }
+      v[e] = lin0 + j < all ? in[ib + ((long)c * M + k) * nlines + r] : mk<C>(R(0), R(0));
+    }
+  } else {
 #pragma unroll
-  for (int e = 0; e < LS::E; ++e) my[LS::idxA(t, e)] = v[e];
-  __syncthreads();
+    for (int e = 0; e < LS::E; ++e)
+      v[e] = active ? (sizeof(R) == 8 ? ld_stream(in + base + LS::idxA(t, e)) : in[base + LS::idxA(t, e)])
+                    : mk<C>(R(0), R(0));
+  }
+  // the vectors are read with the spectrum where the registers allow it (one
+  // memory latency instead of two: what the pass costs on small grids)
+  constexpr bool kAhead = LS::E * sizeof(C) <= 192;
+  C po[LS::E], xo[LS::E];
+  auto vectors = [&]() {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      po[e] = pi[base + LS::idxB(t, e)];
+      xo[e] = xi[base + LS::idxB(t, e)];
+    }
+  };
+  if constexpr (kAhead) {
+    if (!first && active) vectors();
+  }
+  if (planes) {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) {
+      const int i = threadIdx.x + e * XBLOCK;
+      lds[(i % LPB) * (M + PAD) + i / LPB] = v[e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) v[e] = my[LS::idxA(t, e)];
+  } else {
+#pragma unroll
+    for (int e = 0; e < LS::E; ++e) my[LS::idxA(t, e)] = v[e];
+    __syncthreads();
+  }
 #pragma unroll
   for (int e = 0; e < LS::E; ++e) {
     const int k = LS::idxA(t, e);
@@ -905,13 +966,14 @@ k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __r
     for (int e = 0; e < LS::E; ++e) {
       const long n = base + LS::idxB(t, e);
       pi[n] = v[e];
-      xi[n] = mk<C>(R(0), R(0));
+      if (xi) xi[n] = mk<C>(R(0), R(0));
     }
   } else {
+    if constexpr (!kAhead) vectors();
 #pragma unroll
     for (int e = 0; e < LS::E; ++e) {
       const long n = base + LS::idxB(t, e);
-      const C p = pi[n], x = xi[n];
+      const C p = po[e], x = xo[e];
       xi[n] = mk<C>(x.x + alpha * p.x, x.y + alpha * p.y);
       pi[n] = mk<C>(v[e].x + beta * p.x, v[e].y + beta * p.y);
     }

@@ -188,7 +188,7 @@ __device__ __forceinline__ void line_fft_AB(C (&v)[Line<L>::E], C* lds, int ls, 
 }
 
 // Inverse DFT of a line, layout B -> layout A (mirror of line_fft_AB).
-template <int L, typename C>
+template <int L, typename C, bool WAVE = false>
 __device__ __forceinline__ void line_ifft_BA(C (&v)[Line<L>::E], C* lds, int ls, int t,
                                              const C* __restrict__ tw) {
   using LS = Line<L>;
@@ -205,7 +205,7 @@ __device__ __forceinline__ void line_ifft_BA(C (&v)[Line<L>::E], C* lds, int ls,
 #pragma unroll
       for (int n2 = 0; n2 < LS::R2; ++n2) lds[(n2 * LS::R1 + k1) * ls] = v[w * LS::R2 + n2];
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int u = 0; u < LS::U; ++u) {
       const int n2 = t + LS::T * u;
@@ -213,7 +213,7 @@ __device__ __forceinline__ void line_ifft_BA(C (&v)[Line<L>::E], C* lds, int ls,
       for (int k1 = 0; k1 < LS::R1; ++k1) v[u * LS::R1 + k1] = lds[(n2 * LS::R1 + k1) * ls];
       Dft<LS::R1, 1, true, C>::run(v + u * LS::R1);
     }
-    __syncthreads();
+    lds_sync<WAVE>();
   }
 }
 
@@ -238,7 +238,7 @@ __device__ __forceinline__ double block_sum(double v, double* red /*>= 16 double
 // Each thread keeps eight independent running sums, so that eight loads are
 // in flight per thread instead of one (the partials come from other XCDs'
 // L2 or from HBM).
-__device__ __forceinline__ double sum_partials(const double* __restrict__ partials, int nparts, double* red) {
+__device__ __forceinline__ double thread_partials(const double* __restrict__ partials, int nparts) {
   const int bd = blockDim.x;
   double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int k = threadIdx.x;
@@ -247,8 +247,10 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
     for (int u = 0; u < 8; ++u) a[u] += partials[k + u * bd];
   }
   for (; k < nparts; k += bd) a[0] += partials[k];
-  const double acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-  return block_sum(acc, red);
+  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+}
+__device__ __forceinline__ double sum_partials(const double* __restrict__ partials, int nparts, double* red) {
+  return block_sum(thread_partials(partials, nparts), red);
 }
 
 // Partial sums of one item written by a pass whose tile may vary: `head`

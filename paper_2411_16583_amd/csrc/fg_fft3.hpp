@@ -70,7 +70,7 @@ template <int L> struct Line3 {
   __device__ __forceinline__ static int pos1(int b, int k1) { return b * R1 + k1; }
   __device__ __forceinline__ static int pos2(int k1, int b2, int k2) { return (k2 * R3 + b2) * R1 + k1; }
 
-  template <bool INV, typename C>
+  template <bool INV, typename C, bool WAVE = false>
   __device__ __forceinline__ static void fwd(C (&v)[E], C* lds, int ls, int t, const C* tw) {
 #pragma unroll
     for (int u = 0; u < U1; ++u) {
@@ -81,7 +81,7 @@ template <int L> struct Line3 {
 #pragma unroll
       for (int k1 = 0; k1 < R1; ++k1) lds[pos1(b, k1) * ls] = v[u * R1 + k1];
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int w = 0; w < U2; ++w) {
       const int g = t + T * w;
@@ -92,7 +92,7 @@ template <int L> struct Line3 {
 #pragma unroll
       for (int k2 = 1; k2 < R2; ++k2) v[w * R2 + k2] = twiddle_tab<INV>(v[w * R2 + k2], tw, (R1 * b2 * k2) % L);
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int w = 0; w < U2; ++w) {
       const int g = t + T * w;
@@ -100,7 +100,7 @@ template <int L> struct Line3 {
 #pragma unroll
       for (int k2 = 0; k2 < R2; ++k2) lds[pos2(k1, b2, k2) * ls] = v[w * R2 + k2];
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int z = 0; z < U3; ++z) {
       const int g = t + T * z;
@@ -109,10 +109,10 @@ template <int L> struct Line3 {
       for (int b2 = 0; b2 < R3; ++b2) v[z * R3 + b2] = lds[pos2(k1, b2, k2) * ls];
       Dft<R3, 1, INV, C>::run(v + z * R3);
     }
-    __syncthreads();
+    lds_sync<WAVE>();
   }
 
-  template <typename C>
+  template <typename C, bool WAVE = false>
   __device__ __forceinline__ static void inv(C (&v)[E], C* lds, int ls, int t, const C* tw) {
 #pragma unroll
     for (int z = 0; z < U3; ++z) {
@@ -126,7 +126,7 @@ template <int L> struct Line3 {
         lds[pos2(k1, b2, k2) * ls] = a;
       }
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int w = 0; w < U2; ++w) {
       const int g = t + T * w;
@@ -135,7 +135,7 @@ template <int L> struct Line3 {
       for (int k2 = 0; k2 < R2; ++k2) v[w * R2 + k2] = lds[pos2(k1, b2, k2) * ls];
       Dft<R2, 1, true, C>::run(v + w * R2);  // over k2 -> n2
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int w = 0; w < U2; ++w) {
       const int g = t + T * w;
@@ -148,7 +148,7 @@ template <int L> struct Line3 {
         lds[pos1(b, k1) * ls] = a;
       }
     }
-    __syncthreads();
+    lds_sync<WAVE>();
 #pragma unroll
     for (int u = 0; u < U1; ++u) {
       const int b = t + T * u;
@@ -156,7 +156,7 @@ template <int L> struct Line3 {
       for (int k1 = 0; k1 < R1; ++k1) v[u * R1 + k1] = lds[pos1(b, k1) * ls];
       Dft<R1, 1, true, C>::run(v + u * R1);  // over k1 -> n1
     }
-    __syncthreads();
+    lds_sync<WAVE>();
   }
 
   // fwd and inv of CPT adjacent columns together (lds points at the first
@@ -314,13 +314,13 @@ template <int L> struct Line2Ops {
   static constexpr int T = LS::T, E = LS::E;
   __device__ __forceinline__ static int idxA(int t, int e) { return LS::idxA(t, e); }
   __device__ __forceinline__ static int idxB(int t, int e) { return LS::idxB(t, e); }
-  template <bool INV, typename C>
+  template <bool INV, typename C, bool WAVE = false>
   __device__ __forceinline__ static void fwd(C (&v)[E], C* lds, int ls, int t, const C* tw) {
-    line_fft_AB<L, INV>(v, lds, ls, t, tw);
+    line_fft_AB<L, INV, C, WAVE>(v, lds, ls, t, tw);
   }
-  template <typename C>
+  template <typename C, bool WAVE = false>
   __device__ __forceinline__ static void inv(C (&v)[E], C* lds, int ls, int t, const C* tw) {
-    line_ifft_BA<L>(v, lds, ls, t, tw);
+    line_ifft_BA<L, C, WAVE>(v, lds, ls, t, tw);
   }
   // columns one after the other (one element per LDS access)
   template <bool INV, int CPT, typename C>

@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <stdexcept>
+#include <string>
 #include <type_traits>
 
 #include "fg_fft_sizes.hpp"
@@ -166,7 +167,7 @@ int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* parti
 
 template <typename R>
 void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
-                      const SpecTables<R>& tb, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+                      const SpecTables<R>& tb, int nitems, int planes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const EdgeLayout el = edge_layout<R>(n0, n1, 2 * M);
   switch (M) {
 #define FG_CASE(L_)                                                                                              \
@@ -174,7 +175,7 @@ void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate
     constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
     const dim3 grid((unsigned)((3L * n0 * n1 + LPB - 1) / LPB), (unsigned)nitems);                               \
     launch_ev((k_r2c_edges<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, q, edge, el, reinterpret_cast<cplx<R>*>(out), \
-              n0, n1, tb, gate);                                                                                 \
+              n0, n1, tb, gate, planes);                                                                              \
     return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
@@ -287,16 +288,16 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
 }
 
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines, const SpecTables<R>& tb, const KrylovScalars* ks,
-                    int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, int nlines, int nc, const SpecTables<R>& tb,
+                    const KrylovScalars* ks, int nitems, int planes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   using C = cplx<R>;
   switch (M) {
 #define FG_CASE(L_)                                                                                              \
   case L_: {                                                                                                     \
     constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
-    const dim3 grid((unsigned)((nlines + LPB - 1) / LPB), (unsigned)nitems);                                    \
+    const dim3 grid((unsigned)((nc * nlines + LPB - 1) / LPB), (unsigned)nitems);                                \
     launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, reinterpret_cast<const C*>(in),            \
-              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines, tb, ks);                              \
+              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines, nc, tb, ks, planes);                   \
     return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
@@ -305,15 +306,63 @@ void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines, const SpecTab
   throw std::invalid_argument("unsupported N2/2");
 }
 
+template <typename R, typename RO>
+Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hipStream_t s, hipEvent_t ev0,
+                   hipEvent_t ev1) {
+  const int plane = a.n0 * a.n1;
+  // one plane per workgroup; several small ones where that leaves 512
+  // workgroups
+  a.P = 1;
+  while (a.M % (2 * a.P) == 0 && 2 * a.P * plane <= 1024 && (long)nc * a.M / (2 * a.P) * nitems >= 512) a.P *= 2;
+  a.groups = nc * a.M / a.P;
+  a.dn1 = FastDiv(a.n1);
+  const dim3 grid((unsigned)(a.groups * nitems));
+  // a thread per line task where 512 threads are enough
+  const int tasks = a.P * std::max(a.n0 * plane_line_threads(a.n1), a.n1 * plane_line_threads(a.n0));
+  const dim3 block((unsigned)std::min(512, (tasks + 63) / 64 * 64));
+  const unsigned shm = (unsigned)plane_lds<R>(a.n0, a.n1, a.P);
+  auto go = [&](auto kernel) {
+    if (shm > 65536) {
+      // (the attribute is per kernel and device; setting it again is cheap)
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+      if (e != hipSuccess) throw std::runtime_error(std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
+    }
+    launch_ev(kernel, grid, block, shm, s, ev0, ev1, a);
+  };
+  constexpr bool kSame = sizeof(R) == sizeof(RO);
+  if (sym == kSymLap) {
+    if constexpr (sizeof(R) == 8 && kSame) {
+      if (mode == kN0Cg)
+        go(k_plane<R, RO, kN0Cg, kSymLap>);
+      else
+        go(k_plane<R, RO, kN0Start, kSymLap>);
+    }
+  } else if (mode == kN0Cg) {
+    if constexpr (kSame) go(k_plane<R, RO, kN0Cg, kSymProj>);
+  } else if constexpr (sizeof(R) == 8) {
+    if (mode == kN0Start) {
+      go(k_plane<R, RO, kN0Start, kSymProj>);
+    } else if constexpr (kSame) {
+      if (mode == kN0Norm)
+        go(k_plane<R, RO, kN0Norm, kSymProj>);
+      else
+        go(k_plane<R, RO, kN0Apply, kSymProj>);
+    }
+  }
+  return Parts(a.groups);
+}
+
 #define FG_INSTANTIATE_LAUNCHERS(R)                                                                     \
   template int launch_cg_op<R>(int, R*, R*, const R*, const R*, double*, const Gate&, int, int, int, const double*, \
                                int, hipStream_t, hipEvent_t, hipEvent_t);                               \
   template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
-                                    hipStream_t, hipEvent_t, hipEvent_t);                               \
+                                    int, hipStream_t, hipEvent_t, hipEvent_t);                          \
   template void launch_n1<R>(int, bool, int, N1Args<R>, int, hipStream_t, hipEvent_t, hipEvent_t);      \
   template Parts launch_n0<R, R>(int, int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
-  template void launch_c2r_dir<R>(int, const R*, R*, R*, long, const SpecTables<R>&, const KrylovScalars*, int, \
-                                  hipStream_t, hipEvent_t, hipEvent_t);                                 \
+  template Parts launch_plane<R, R>(int, int, PlaneArgs<R, R>, int, int, hipStream_t, hipEvent_t, hipEvent_t); \
+  template void launch_c2r_dir<R>(int, const R*, R*, R*, int, int, const SpecTables<R>&, const KrylovScalars*, int, \
+                                  int, hipStream_t, hipEvent_t, hipEvent_t);                            \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
   template int launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, const C2REpi&, hipStream_t, hipEvent_t, \
                              hipEvent_t);                                                           \

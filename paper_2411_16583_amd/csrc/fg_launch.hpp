@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fg_cg3.hpp"
+#include "fg_plane.hpp"
 
 namespace fg {
 
@@ -60,7 +61,7 @@ int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* parti
 // N2 transform of q with its patch edges added.
 template <typename R>
 void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
-                      const SpecTables<R>& tb, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                      const SpecTables<R>& tb, int nitems, int planes, hipStream_t s, hipEvent_t ev0 = nullptr,
                       hipEvent_t ev1 = nullptr);
 // N1 pass between the line layout and the block layout (k_n1), 3 components
 // per item; tile as for launch_axis.
@@ -74,10 +75,18 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
               hipEvent_t ev1 = nullptr);
 // most partial sums per item that launch_n0 writes, for any tile
 inline long n0_max_parts(int N1, int M) { return 3L * ((long)M * N1 + N1 / 2 + 1); }
+// Whether a grid's planes fit k_plane in double precision (the working type
+// of every residual pass).
+bool plane_fits(int n0, int n1);
+// N1 and N0 passes in one (k_plane), mode and symbol as launch_n0; a: q, z, s,
+// tables, scalars and partial sums.  Returns the partial sums of an item.
+template <typename R, typename RO>
+Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                   hipEvent_t ev1 = nullptr);
 // Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, long nlines, const SpecTables<R>& tb, const KrylovScalars* ks,
-                    int nitems, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_c2r_dir(int M, const R* in, R* pi, R* xi, int nlines, int nc, const SpecTables<R>& tb,
+                    const KrylovScalars* ks, int nitems, int planes, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 template <typename R>
 void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const Skip& skip,
@@ -106,9 +115,10 @@ constexpr int kTileColumnPairs = 1 << 17;
 // 64 KiB.  zproj: the fused N0 projection pass (L = N0), else the N1 pass.
 bool tile_valid(bool zproj, int L, int M, int elem_bytes, int tile);
 // q = A p of the phase-field (op = 0: coef = a) or Fick (op = 1: coef = w, A6)
-// operator with its N2 transform (k_scalar_op); returns the number of partial
+// operator, or q = p (op = 2), with its N2 transform (k_scalar_op); returns the number of partial
 // sums of p.q.
 int launch_scalar_op(int op, int M, const double* p, const double* coef, const double* A6, double kdiff, const Grid3& g,
-                     double* spec, double* partials, const Gate& gate, const SpecTables<double>& tb, hipStream_t s);
+                     double* spec, double* partials, const Gate& gate, const SpecTables<double>& tb, int planes,
+                     hipStream_t s);
 
 }  // namespace fg

@@ -20,6 +20,7 @@
 #include "fg_fft3.hpp"
 #include "fg_batch.hpp"
 #include "fg_cggrad.hpp"
+#include "fg_plane.hpp"
 
 using namespace fg;
 
@@ -106,6 +107,13 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
   return s;
 }
 
+// The largest plane that fits LDS in double precision is 96 x 96 (one
+// workgroup per CU), with a margin for the kernel's static LDS.  One CG
+// iteration with k_plane / with the three separate passes (us): 16^3 32.7 /
+// 37.0, 64^3 54.0 / 59.5 (single precision 43.7 / 49.2), 96^3 113 / 121, 24 x
+// 96 x 48 48 / 55, plane 256 x 256 42 / 47, 48 x 96 x 192 123 / 123.
+bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= 160 * 1024 - 1024; }
+
 int zline_threads(int L) {
   if (L == 256) return Line3<256>::T;
   if (L == 128) return Line3<128>::T;
@@ -183,6 +191,7 @@ struct fg_plan {
   // [0] N1 pass FP64, [1] N0 projection pass FP64, [2] N1 pass FP32, [3] N0 projection pass FP32
   int tiles[4] = {0, 0, 0, 0};
   int tiles_gen = 0;  // bumped by fg_plan_set_tiles (a captured batch graph is then stale)
+  bool planes = false;  // the N1 and N0 passes of the CG run as one (k_plane)
   int law = ::FG_LAW_NEO_HOOKE;  // material law (fg_set_law, before the workspace)
   double h[3];
   fg_precision prec;
@@ -282,7 +291,7 @@ size_t layout(fg_plan* P, char* base) {
   // partial sums of an item: 9 per 256-voxel block, a workgroup per line of
   // k_cg_op or per column of the N0 pass at most, plus slack for the per-item
   // rounding of the line passes
-  P->part_n = (size_t)P->nitems * std::max({9 * (N / 256 + 2), (long)n0 * n1, fg::n0_max_parts(n1, M)}) + 8192;
+  P->part_n = (size_t)P->nitems * std::max({9 * (N / 256 + 2), (long)n0 * n1, 2 * fg::n0_max_parts(n1, M)}) + 8192;
   P->part = carve<double>(base, off, P->part_n);
   P->part2 = carve<double>(base, off, P->part_n);
   const size_t tb = (P->prec == FG_FP64) ? sizeof(double) : sizeof(float);
@@ -534,6 +543,18 @@ template <typename R, typename RO> N0Args<R, RO> n0_args(fg_plan* P, const Gate&
   return a;
 }
 
+template <typename R, typename RO> PlaneArgs<R, RO> plane_args(fg_plan* P, const Gate& gate) {
+  PlaneArgs<R, RO> a{};
+  a.n0 = P->n0;
+  a.n1 = P->n1;
+  a.M = P->M;
+  a.tb = tabs<R>(P).spec();
+  a.scale = (R)(1.0 / (double)P->N);
+  a.sign = R(1);
+  a.gate = gate;
+  return a;
+}
+
 // ----------------------------------------------------------------------------
 // Mechanics.
 void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, double* pparts,
@@ -552,16 +573,17 @@ void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, doubl
 }
 
 // Spectrum of the divergence D^T Y of the FP64 9-component fields Y of all
-// items not masked, in the FP64 block layout (bk64, dc64): stencil and N2
-// transform, then the N1 pass.
+// items not masked: stencil and N2 transform, in the plane layout (ln64) or,
+// after the N1 pass, in the FP64 block layout (bk64, dc64).
 void divergence64(fg_plan* P, const double* Y, const Gate& gate) {
   const SpecTables<double> tb = P->t64.spec();
   {
     ProfScope ps(P, FG_PASS_R2C);
     launch_cg_op<double>(kSrcField, P->q64, P->qe64, nullptr, Y, nullptr, gate, P->n0, P->n1, P->n2, P->h, P->nitems,
                          P->stream);
-    launch_r2c_edges<double>(P->M, P->q64, P->qe64, P->ln64, gate, P->n0, P->n1, tb, P->nitems, P->stream);
+    launch_r2c_edges<double>(P->M, P->q64, P->qe64, P->ln64, gate, P->n0, P->n1, tb, P->nitems, P->planes, P->stream);
   }
+  if (P->planes) return;
   ProfScope ps(P, FG_PASS_AXIS);
   launch_n1<double>(P->n1, false, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate), P->nitems, P->stream);
 }
@@ -577,6 +599,15 @@ Parts residual_pass(fg_plan* P, const double* Y, const int* idle, bool start, do
   ProfScope ps(P, FG_PASS_ZPROJ);
   auto go = [&](auto out, int mode) {
     using T = decltype(out);
+    if (P->planes) {
+      PlaneArgs<double, T> a = plane_args<double, T>(P, gate);
+      a.q = (const cplx<double>*)P->ln64;
+      a.z = (cplx<T>*)P->ln;
+      a.s = (cplx<T>*)P->rs;
+      a.sign = sign;
+      a.partials = P->part;
+      return launch_plane<double, T>(mode, kSymProj, a, 3, P->nitems, P->stream);
+    }
     N0Args<double, T> a = n0_args<double, T>(P, gate);
     a.q = (const cplx<double>*)P->bk64;
     a.dcq = (const cplx<double>*)P->dc64;
@@ -639,14 +670,14 @@ void cg_iteration(fg_plan* P) {
   KrylovScalars* ks = P->ks;
   const SpecTables<T> tb = tabs<T>(P).spec();
   const Gate gate = Gate::done(ks);
-  {
+  if (!P->planes) {
     ProfScope ps(P, FG_PASS_AXIS3, true);
     launch_n1<T>(P->n1, true, P->n0, n1_args<T>(P, P->ln, P->bk, P->dc, gate), nit, P->stream, ps.start, ps.stop);
   }
   {
     ProfScope ps(P, FG_PASS_C2R3, true);
-    launch_c2r_dir<T>(P->M, (const T*)P->ln, (T*)P->p, (T*)P->x, 3L * P->n0 * P->n1, tb, ks, nit, P->stream, ps.start,
-                      ps.stop);
+    launch_c2r_dir<T>(P->M, (const T*)P->ln, (T*)P->p, (T*)P->x, P->n0 * P->n1, 3, tb, ks, nit, P->planes, P->stream,
+                      ps.start, ps.stop);
   }
   int nbf;
   {
@@ -656,20 +687,30 @@ void cg_iteration(fg_plan* P) {
   }
   {
     ProfScope ps(P, FG_PASS_R2C, true);
-    launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->stream,
-                        ps.start, ps.stop);
+    launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->planes,
+                        P->stream, ps.start, ps.stop);
   }
-  {
-    // alpha = r.r / p.Kp is formed by the N1 pass (one workgroup per item)
-    ProfScope ps(P, FG_PASS_AXIS, true);
-    N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
+  Parts nbz;
+  if (P->planes) {
+    ProfScope ps(P, FG_PASS_ZPROJ, true);
+    PlaneArgs<T, T> a = plane_args<T, T>(P, gate);
+    a.q = a.z = (cplx<T>*)P->ln;
+    a.s = (cplx<T>*)P->rs;
     a.pap = P->part;
     a.npap = nbf;
     a.ks = ks;
-    launch_n1<T>(P->n1, false, P->n0, a, nit, P->stream, ps.start, ps.stop);
-  }
-  Parts nbz;
-  {
+    a.partials = P->part2;
+    nbz = launch_plane<T, T>(kN0Cg, kSymProj, a, 3, nit, P->stream, ps.start, ps.stop);
+  } else {
+    {
+      // alpha = r.r / p.Kp is formed by the N1 pass (one workgroup per item)
+      ProfScope ps(P, FG_PASS_AXIS, true);
+      N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
+      a.pap = P->part;
+      a.npap = nbf;
+      a.ks = ks;
+      launch_n1<T>(P->n1, false, P->n0, a, nit, P->stream, ps.start, ps.stop);
+    }
     ProfScope ps(P, FG_PASS_ZPROJ, true);
     N0Args<T, T> a = n0_args<T, T>(P, gate);
     a.q = a.z = (cplx<T>*)P->bk;
@@ -984,43 +1025,67 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   const Gate gate = Gate::done(ks);
   const SpecTables<double> tb = P->t64.spec();
   const Grid3 g{P->n0, P->n1, P->n2, 1.0 / P->h[0], 1.0 / P->h[1], 1.0 / P->h[2]};
-  auto n0_pass = [&](int mode) {
-    N0Args<double, double> a = n0_args<double, double>(P, gate, 1);
-    a.q = a.z = (cplx<double>*)P->bk64;
-    a.dcq = a.dcz = (cplx<double>*)P->dc64;
-    a.s = (cplx<double>*)v.s;
-    a.dcs = (cplx<double>*)v.sdc;
-    a.a0 = a0;
-    a.a1 = a1;
-    a.ks = ks;
-    a.partials = P->part2;
-    a.partials2 = P->part;
-    ProfScope ps(P, FG_PASS_ZSCALAR);
-    const Parts n = launch_n0<double, double>(P->n0, mode, kSymLap, a, 1, P->stream);
+  // the N1 and N0 passes of q (npap partial sums of p.q) and the inverse N1
+  // pass of z
+  auto passes = [&](int mode, int npap) {
+    Parts n;
+    if (P->planes) {
+      ProfScope ps(P, FG_PASS_ZSCALAR);
+      PlaneArgs<double, double> a = plane_args<double, double>(P, gate);
+      a.q = a.z = (cplx<double>*)P->ln64;
+      a.s = (cplx<double>*)v.s;
+      a.sa0 = a0;
+      a.sa1 = a1;
+      a.ks = ks;
+      a.pap = P->part;
+      a.npap = npap;
+      a.pcg = 1;
+      a.partials = P->part2;
+      a.partials2 = P->part2 + P->part_n / 2;
+      n = launch_plane<double, double>(mode, kSymLap, a, 1, 1, P->stream);
+    } else {
+      N1Args<double> f = n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1);
+      if (mode == kN0Cg) {
+        f.pap = P->part;
+        f.npap = npap;
+        f.ks = ks;
+        f.pcg = 1;
+      }
+      launch_n1<double>(P->n1, false, P->n0, f, 1, P->stream);
+      N0Args<double, double> a = n0_args<double, double>(P, gate, 1);
+      a.q = a.z = (cplx<double>*)P->bk64;
+      a.dcq = a.dcz = (cplx<double>*)P->dc64;
+      a.s = (cplx<double>*)v.s;
+      a.dcs = (cplx<double>*)v.sdc;
+      a.a0 = a0;
+      a.a1 = a1;
+      a.ks = ks;
+      a.partials = P->part2;
+      a.partials2 = P->part2 + P->part_n / 2;
+      {
+        ProfScope ps(P, FG_PASS_ZSCALAR);
+        n = launch_n0<double, double>(P->n0, mode, kSymLap, a, 1, P->stream);
+      }
+    }
     hipLaunchKernelGGL(k_pcg_finalize, dim3(1), dim3(1024), 0, P->stream, (const double*)P->part2,
-                       (const double*)P->part, n, ks, mode == kN0Start ? 1 : 0);
+                       (const double*)(P->part2 + P->part_n / 2), n, ks, mode == kN0Start ? 1 : 0);
+    if (!P->planes)
+      launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1), 1, P->stream);
   };
-  const N1Args<double> n1 = n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1);
+  auto apply = [&](int which, const double* in) {
+    return launch_scalar_op(which, P->M, in, op == ScalarOp::FICK ? v.w : v.a, v.A6,
+                            op == ScalarOp::FICK ? dt : P->gc * P->lc, g, P->ln64, P->part, gate, tb, P->planes,
+                            P->stream);
+  };
   // s_0 = b, z_0
-  launch_r2c<double>(P->M, v.r, P->ln64, (long)P->n0 * P->n1, tb, Skip::done(ks), P->stream);
-  launch_n1<double>(P->n1, false, P->n0, n1, 1, P->stream);
-  n0_pass(kN0Start);
+  apply(2, v.r);
+  passes(kN0Start, 0);
   check_launch();
   int chunk = 4;
   for (int guard = 0; guard < 1000000; ++guard) {
     for (int k = 0; k < chunk; ++k) {
-      launch_n1<double>(P->n1, true, P->n0, n1, 1, P->stream);
-      launch_c2r_dir<double>(P->M, P->ln64, v.p, v.x, (long)P->n0 * P->n1, tb, ks, 1, P->stream);
-      const int nb = launch_scalar_op(op == ScalarOp::FICK, P->M, v.p, op == ScalarOp::FICK ? v.w : v.a, v.A6,
-                                      op == ScalarOp::FICK ? dt : P->gc * P->lc, g, P->ln64, P->part, gate, tb,
-                                      P->stream);
-      N1Args<double> n1f = n1;
-      n1f.pap = P->part;
-      n1f.npap = nb;
-      n1f.ks = ks;
-      n1f.pcg = 1;
-      launch_n1<double>(P->n1, false, P->n0, n1f, 1, P->stream);
-      n0_pass(kN0Cg);
+      launch_c2r_dir<double>(P->M, P->ln64, v.p, v.x, P->n0 * P->n1, 1, tb, ks, 1, P->planes, P->stream);
+      passes(kN0Cg, apply(op == ScalarOp::FICK ? 1 : 0, v.p));
       check_launch();
     }
     sync_read(P);
@@ -1182,6 +1247,7 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
   for (int k = 0; k < 3; ++k) P->h[k] = spacing[k];
   P->nitems = nitems;
   P->prec = prec;
+  P->planes = fg::plane_fits(P->n0, P->n1);
   P->stream = (hipStream_t)stream;
   P->need = layout(P, nullptr) + kAlign;
   if (hipHostMalloc((void**)&P->hks, (nitems + 1) * sizeof(KrylovScalars), hipHostMallocDefault) != hipSuccess ||
@@ -1489,14 +1555,20 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
     P->lin_open = false;
     const Gate none{};
     divergence64(P, x, none);
-    N0Args<double, double> a = n0_args<double, double>(P, none);
-    a.q = a.z = (cplx<double>*)P->bk64;
-    a.dcq = a.dcz = (cplx<double>*)P->dc64;
-    launch_n0<double, double>(P->n0, kN0Apply, kSymProj, a, 1, P->stream);
-    launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
-    launch_c2r<double>(P->M, P->ln64, P->ln64, 3L * P->n0 * P->n1, P->t64.spec(),
-                       C2REpi{1.0, nullptr, true, nullptr, Skip{}}, P->stream);
-    launch_grad_store<double, double>(P->ln64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
+    if (P->planes) {
+      PlaneArgs<double, double> a = plane_args<double, double>(P, none);
+      a.q = a.z = (cplx<double>*)P->ln64;
+      launch_plane<double, double>(kN0Apply, kSymProj, a, 3, 1, P->stream);
+    } else {
+      N0Args<double, double> a = n0_args<double, double>(P, none);
+      a.q = a.z = (cplx<double>*)P->bk64;
+      a.dcq = a.dcz = (cplx<double>*)P->dc64;
+      launch_n0<double, double>(P->n0, kN0Apply, kSymProj, a, 1, P->stream);
+      launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
+    }
+    launch_c2r_dir<double>(P->M, P->ln64, P->q64, nullptr, P->n0 * P->n1, 3, P->t64.spec(), nullptr, 1, P->planes,
+                           P->stream);
+    launch_grad_store<double, double>(P->q64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
                                       P->stream);
     check_launch();
   });

@@ -58,7 +58,9 @@ __device__ __forceinline__ double fick_L(const double* __restrict__ v, const dou
 // Operator of a scalar PCG on p fused with the N2 transform of its result:
 //   OP = 0  q = a p - k Lap_h p (phase field, 7-point),
 //   OP = 1  q = p / w + dt L(p) (Fick; kdiff = dt),
-// and the partial sums of p.q.  A workgroup owns LPB lines (i0, i1): its
+//   OP = 2  q = p (the right-hand side),
+// and the partial sums of p.q (OP 0, 1), into the line layout or (planes) the
+// plane layout.  A workgroup owns LPB lines (i0, i1): its
 // threads evaluate the stencil voxel by voxel along the lines into LDS, then
 // T threads per line transform it there; q itself never goes to memory.
 constexpr int kScalarThreads = 256;
@@ -70,7 +72,7 @@ template <int M> constexpr int scalar_lines() {
 template <int M, int OP>
 __global__ void __launch_bounds__(kScalarThreads)
 k_scalar_op(const double* __restrict__ p, const double* __restrict__ coef, const double* __restrict__ A6, double kdiff,
-            Grid3 g, double2* __restrict__ out, double* __restrict__ partials, SpecTables<double> tb, Gate gate) {
+            Grid3 g, double2* __restrict__ out, double* __restrict__ partials, SpecTables<double> tb, Gate gate, int planes) {
   using C = double2;
   using LS = Line<M>;
   constexpr int LPB = scalar_lines<M>(), N2 = 2 * M;
@@ -95,6 +97,8 @@ k_scalar_op(const double* __restrict__ p, const double* __restrict__ coef, const
         const double l1 = (2.0 * p0 - pc[n.p[1]] - pc[n.m[1]]) * g.ih1 * g.ih1;
         const double l2 = (2.0 * p0 - pc[n.p[2]] - pc[n.m[2]]) * g.ih2 * g.ih2;
         qv = coef[n.c] * p0 + kdiff * (l0 + l1 + l2);
+      } else if constexpr (OP == 2) {
+        qv = p0;
       } else {
         qv = p0 / coef[n.c] + kdiff * fick_L(p, A6, g, N, n);
       }
@@ -120,24 +124,22 @@ k_scalar_op(const double* __restrict__ p, const double* __restrict__ coef, const
 #pragma unroll
     for (int e = 0; e < LS::E; ++e) my[LS::idxB(t, e)] = v[e];
     lds_sync<true>();
-    if (active) {
+    if (active && !planes) {
 #pragma unroll
       for (int e = 0; e < LS::E; ++e) {
         const int k = LS::idxB(t, e);
-        const C zk = my[k];
-        C X;
-        if (k == 0) {
-          X = mk<C>(zk.x + zk.y, zk.x - zk.y);  // both ends of the real line's spectrum
-        } else {
-          const C zm = my[M - k];
-          const C ev = cscale(cadd(zk, cconj(zm)), 0.5);
-          const C od = cscale(mul_mi(csub(zk, cconj(zm))), 0.5);
-          X = cadd(ev, cmul(od, tb.post[k]));
-        }
-        out[(line0 + ll) * M + k] = X;
+        out[(line0 + ll) * M + k] = r2c_post(my, k, M, tb.post[k]);
       }
     }
   }
+  if (planes) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < LPB * M; i += kScalarThreads) {
+      const int k = i / LPB, j = i - k * LPB;
+      if (line0 + j < nlines) out[(long)k * nlines + line0 + j] = r2c_post(lds + j * (M + PAD), k, M, tb.post[k]);
+    }
+  }
+  if constexpr (OP == 2) return;
   const double s = block_sum(acc, red);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }

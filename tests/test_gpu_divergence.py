@@ -20,7 +20,11 @@ pytestmark = pytest.mark.gpu
 # partial blocks of lines (N1 = 6, 12), half and one-and-a-half patches along
 # N2 (8, 24, 48), one block exactly (8), a plane, node-plane runs that do not
 # divide N0 (48 and 96 planes), blocks padded in the block layout (N0 >= 64)
-SHAPES = [(4, 6, 8), (6, 12, 24), (8, 8, 16), (1, 12, 48), (48, 4, 12), (96, 6, 8), (64, 8, 32), (4, 24, 96)]
+SHAPES = [(4, 6, 8), (6, 12, 24), (8, 8, 16), (1, 12, 48), (48, 4, 12), (96, 6, 8), (64, 8, 32),
+          (4, 24, 96)]
+# largest (N0, N1) planes transformed in LDS as one (96 x 96), the first ones
+# that are not (128 x 96), lines of every shape on both axes; cubic voxels
+PLANES = [(96, 96, 4), (128, 96, 4), (32, 16, 6), (48, 64, 8), (128, 12, 8), (256, 8, 4), (24, 256, 4), (1, 512, 8)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -41,13 +45,13 @@ def test_projection_by_divergence(shape):
 # times larger than their gradients, and their single-precision storage moves
 # the fourth iterate by 2e-5, whichever way the operator is applied)
 @pytest.mark.parametrize("law", ["neo_hookean", "svk"])
-@pytest.mark.parametrize("shape,precision,tol", [(s, "fp64", 1e-11) for s in SHAPES] +
-                         [(s, "mixed", 1e-5) for s in SHAPES[:-1]])
+@pytest.mark.parametrize("shape,precision,tol", [(s, "fp64", 1e-11) for s in SHAPES + PLANES] +
+                         [(s, "mixed", 1e-5) for s in SHAPES[:-1] + PLANES])
 def test_cg_iterates_by_divergence(shape, precision, tol, law):
     """Four CG iterations (2, then 2 more) of the first Newton system of a
     random two-phase cell = the oracle's 9-component CG."""
     print(f"cg {shape} {precision} {law}", flush=True)
-    work = synth.homogeneous_workload(shape)
+    work = synth.homogeneous_workload(shape, tuple(float(n) for n in shape) if shape in PLANES else 1.0)
     rng = np.random.default_rng(5 + shape[2])
     phase = rng.random(shape) < 0.3
     work["E"] = np.where(phase, 100e9, 10e9)
