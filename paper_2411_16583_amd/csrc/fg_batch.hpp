@@ -118,6 +118,7 @@ k_newton_cg_start(const double* __restrict__ partials, Parts parts, KrylovScalar
   k.flag = 0;
   k.beta = 0.0;
   k.done = (s == 0.0) ? 1 : 0;
+  k.publish();
   nc[b].started = 1;
 }
 

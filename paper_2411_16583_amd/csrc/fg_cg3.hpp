@@ -56,7 +56,7 @@ struct Gate {
   const int* p = nullptr;
   int stride = 0;
   __device__ __forceinline__ bool operator()(long item) const { return p && p[item * stride] != 0; }
-  static Gate done(const KrylovScalars* ks) { return Gate{&ks->done, (int)(sizeof(KrylovScalars) / sizeof(int))}; }
+  static Gate done(const KrylovScalars* ks) { return Gate{&ks->stop, (int)(sizeof(KrylovScalars) / sizeof(int))}; }
   static Gate flags(const int* f) { return Gate{f, f ? 1 : 0}; }
 };
 
@@ -185,11 +185,26 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   auto plane_sums = [&](int i0, R (&cs)[3][3][W]) {
     const R* r0 = pi + ((long)i0 * a.n1 + i1) * a.n2;
     const R* r1 = pi + ((long)i0 * a.n1 + i1m) * a.n2;
+    // every load before the first use
+    PV w0[3], w1[3];
+    R h0[3], h1[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      w0[c] = *reinterpret_cast<const PV*>(r0 + c * N + x);
+      w1[c] = *reinterpret_cast<const PV*>(r1 + c * N + x);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      h0[c] = h1[c] = R(0);
+      if (gx == 0) {
+        h0[c] = r0[c * N + xm];
+        h1[c] = r1[c * N + xm];
+      }
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       R u[2][W + 1];
-      const PV v0 = *reinterpret_cast<const PV*>(r0 + c * N + x);
-      const PV v1 = *reinterpret_cast<const PV*>(r1 + c * N + x);
+      const PV v0 = w0[c], v1 = w1[c];
 #pragma unroll
       for (int w = 0; w < W; ++w) {
         u[0][w + 1] = pk_get<R>(v0, w);
@@ -199,8 +214,8 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
       u[0][0] = __shfl_up(u[0][W], 1);
       u[1][0] = __shfl_up(u[1][W], 1);
       if (gx == 0) {
-        u[0][0] = r0[c * N + xm];
-        u[1][0] = r1[c * N + xm];
+        u[0][0] = h0[c];
+        u[1][0] = h1[c];
       }
 #pragma unroll
       for (int w = 0; w < W; ++w) {
@@ -347,6 +362,33 @@ template <typename C> __device__ __forceinline__ C r2c_post(const C* z, int k, i
   return cadd(ev, cmul(od, w));
 }
 
+// Tables of the N2 passes, read into registers with the workgroup's data and
+// put in LDS behind it: one memory latency at the head of the pass, which is
+// most of its time on a small grid.
+template <typename C, int M> struct TwiddleRegs {
+  static constexpr int n = (M + XBLOCK - 1) / XBLOCK;
+  C a[n], b[n];
+  template <typename TB> __device__ __forceinline__ explicit TwiddleRegs(const TB& tb) {
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+      const int k = (int)threadIdx.x + u * XBLOCK;
+      const int i = M % XBLOCK == 0 || k < M ? k : 0;
+      a[u] = tb.twM[i];
+      b[u] = tb.post[i];
+    }
+  }
+  __device__ __forceinline__ void store(C* stw, C* spost) const {
+#pragma unroll
+    for (int u = 0; u < n; ++u) {
+      const int k = (int)threadIdx.x + u * XBLOCK;
+      if (M % XBLOCK == 0 || k < M) {
+        stw[k] = a[u];
+        spost[k] = b[u];
+      }
+    }
+  }
+};
+
 // N2 transform of the 3-component fields q of k_cg_op with the patch edges
 // added on load, into the line layout or (planes) the plane layout.  grid: line blocks of 3 N0 N1 lines per item, blockIdx.y =
 // item.
@@ -363,11 +405,6 @@ k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, 
   __shared__ C stw[M], spost[M];
   __shared__ R ecl[LPB][NP], ecr[LPB][NP];
   const int item = blockIdx.y;
-  if (gate(item)) return;
-  for (int k = threadIdx.x; k < M; k += XBLOCK) {
-    stw[k] = tb.twM[k];
-    spost[k] = tb.post[k];
-  }
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
   const int nlines = n0 * n1;
@@ -395,12 +432,28 @@ k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, 
     for (int e = 0; e < LS::E; ++e) r[e] = mk<C>(R(0), R(0));
   }
   // the line's edge values through LDS (one coalesced read each)
-  if (active) {
-    for (int p = t; p < el.np; p += LS::T) {
-      ecl[ll][p] = ec[el.col + (long)line * el.np + p];
-      ecr[ll][p] = lastl ? ec[el.cor + nb * el.np + p] : R(0);
+  constexpr int NPT = (NP + LS::T - 1) / LS::T;
+  R cl[NPT], cr[NPT];
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const int p = t + u * LS::T;
+    cl[u] = cr[u] = R(0);
+    if (active && p < el.np) {
+      cl[u] = ec[el.col + (long)line * el.np + p];
+      if (lastl) cr[u] = ec[el.cor + nb * el.np + p];
     }
   }
+  TwiddleRegs<C, M> tw(tb);
+  tw.store(stw, spost);
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const int p = t + u * LS::T;
+    if (p < NP) {
+      ecl[ll][p] = cl[u];
+      ecr[ll][p] = cr[u];
+    }
+  }
+  if (gate(item)) return;  // (the mask is read with the data, not before it)
   __syncthreads();
   const int sh = 31 - __clz(el.W8);  // W8 is a power of two
 #pragma unroll
@@ -463,10 +516,15 @@ template <typename R> struct N1Args {
   int M, tile;
   const cplx<R>* tw;
   Gate gate;
-  // forward pass of the CG: one workgroup per item forms alpha from the
+  // forward pass of the CG: a workgroup per item forms alpha from the
   // partial sums of p.Kp (nothing before the N0 pass reads it)
   const double* pap;
   int npap;
+  // inverse pass of the CG: a workgroup per item ends the iteration before
+  // (krylov_close; nothing before the N2 pass reads it but the mask, and z is
+  // not needed once that is set).  As a kernel of its own this took 4-6 us.
+  const double *prr, *prz;
+  Parts parts;
   KrylovScalars* ks;
   int pcg;  // alpha = r.z / p.Ap (preconditioned CG)
   int nc;   // components per item
@@ -477,16 +535,22 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
   using C = cplx<R>;
   using LS = Line<L>;
   extern __shared__ __align__(16) char smem_raw[];
-  __shared__ double red[16];
+  __shared__ double buf[256];
   C* lds = reinterpret_cast<C*>(smem_raw);
-  const int z = blockIdx.z, i0 = blockIdx.y, N0 = gridDim.y;
+  // (with ks, a first row of workgroups for the scalars)
+  const int row0 = a.ks ? 1 : 0, z = blockIdx.z, i0 = (int)blockIdx.y - row0, N0 = (int)gridDim.y - row0;
   if (a.gate(z / a.nc)) return;
-  if constexpr (!INV) {
-    if (a.pap && blockIdx.x == 0 && i0 == 0 && z % a.nc == 0) {
-      const int item = z / a.nc;
-      const double s = sum_partials(a.pap + (long)item * a.npap, a.npap, red);
+  if (i0 < 0) {
+    if (blockIdx.x != 0 || z % a.nc != 0) return;
+    const int item = z / a.nc;
+    if constexpr (INV) {
+      const long o = (long)item * a.parts.stride();
+      krylov_close(a.ks + item, a.prr + o, a.prz ? a.prz + o : nullptr, a.parts, false, buf);
+    } else {
+      const double s = sum_parts_any(a.pap + (long)item * a.npap, Parts(a.npap), buf);
       if (threadIdx.x == 0) krylov_alpha(a.ks + item, s, a.pcg);
     }
+    return;
   }
   const int B = a.tile;
   const C* tw = a.tw;
@@ -870,28 +934,38 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 //   xi = 0,  pi_0 = z                                       (k = 0).
 // grid: line blocks of the item's lines (nlines per component), blockIdx.y =
 // item; in: line or (planes) plane layout.  Without ks: z alone, into pi.
+//
+// With prr (prz of the preconditioned CG), the partial sums of the iteration
+// before that k_plane left (np per item): every workgroup adds them up itself, in
+// the same order, for beta and the end of the solve, and one of them notes
+// what it found for the passes behind.  A kernel of its own between the two
+// took 2.6-4.6 us of an iteration of 30-60.
+template <typename R> struct DirArgs {
+  const cplx<R>* in;
+  cplx<R>*pi, *xi;
+  int nlines, nc, planes;
+  SpecTables<R> tb;
+  KrylovScalars* ks;
+  const double *prr, *prz;
+  int np;
+};
+
 template <typename R, int M>
-__global__ void __launch_bounds__(XBLOCK)
-k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __restrict__ xi, int nlines, int nc,
-          SpecTables<R> tb, const KrylovScalars* __restrict__ ksb, int planes) {
+__global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
   using C = cplx<R>;
   using LS = Line<M>;
   constexpr int LPB = XBLOCK / LS::T;
   constexpr int PAD = (M >= 16) ? 1 : 0;
   __shared__ C lds[LPB * (M + PAD)];
   __shared__ C stw[M], spost[M];
-  const int item = blockIdx.y;
-  const KrylovScalars* ks = ksb + item;
-  if (ksb && ks->done) return;
-  for (int k = threadIdx.x; k < M; k += XBLOCK) {
-    stw[k] = tb.twM[k];
-    spost[k] = tb.post[k];
-  }
-  const bool first = !ksb || ks->iter == 0;
-  const R alpha = first ? R(0) : (R)ks->alpha, beta = first ? R(0) : (R)ks->beta;
+  __shared__ double red[16];
+  const int item = blockIdx.y, nlines = a.nlines, planes = a.planes;
+  const C* __restrict__ in = a.in;
+  C *pi = a.pi, *xi = a.xi;
+  KrylovScalars* ks = a.ks ? a.ks + item : nullptr;
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
-  const int all = nc * nlines;  // lines of the item
+  const int all = a.nc * nlines;  // lines of the item
   const int lin0 = (int)blockIdx.x * LPB, lin = lin0 + ll;
   const bool active = lin < all;
   const long ib = (long)item * all * M;
@@ -929,7 +1003,33 @@ k_c2r_dir(const cplx<R>* __restrict__ in, cplx<R>* __restrict__ pi, cplx<R>* __r
     }
   };
   if constexpr (kAhead) {
-    if (!first && active) vectors();
+    if (ks && active) vectors();  // (not used by the first iteration)
+  }
+  double rr = 0.0, rz = 0.0;
+  if (a.prr) rr = thread_partials(a.prr + (long)item * a.np, a.np);
+  if (a.prz) rz = thread_partials(a.prz + (long)item * a.np, a.np);
+  TwiddleRegs<C, M> tw(a.tb);
+  tw.store(stw, spost);
+  if (ks && ks->done) return;  // (read with the data, not before it)
+  const bool pending = ks && a.prr && !ks->fresh;
+  const bool first = !ks || (!pending && ks->iter == 0);
+  R alpha = R(0), beta = R(0);
+  if (!first) {
+    alpha = (R)ks->alpha;
+    beta = (R)ks->beta;
+  }
+  if (pending) {
+    rr = block_sum_all(rr, red);
+    if (a.prz) rz = block_sum_all(rz, red + 8);
+    const KrylovTest kt = krylov_test(ks, rr, rz, a.prz != nullptr);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ks->run_rr = rr;
+      ks->run_rz = rz;
+      ks->run_iter = kt.iter;
+      ks->stop = kt.done;
+    }
+    if (kt.done) return;
+    beta = (R)kt.beta;
   }
   if (planes) {
 #pragma unroll

@@ -36,6 +36,24 @@ struct KrylovScalars {
   int maxit;
   int done;      // 1 when converged, broken down or out of iterations
   int flag;      // 0 running/converged, 1 breakdown, 2 max iterations
+  // Where the partial sums of an iteration are few, its direction pass
+  // (k_c2r_dir) adds them up in every workgroup instead of waiting for a
+  // kernel of its own.  What it finds is kept apart from what its other
+  // workgroups still read, and taken over by the pass that forms alpha.
+  double run_rr, run_rz;
+  int run_iter;
+  int stop;    // the passes of the running iteration skip the item (set with done, or by the direction pass)
+  int fresh;   // rr ... flag above are those of the last iteration; 0: its partial sums are still to be added up
+  int pad_;
+
+  // rr ... flag are what the next iteration starts from
+  __host__ __device__ __forceinline__ void publish() {
+    run_rr = rr;
+    run_rz = rz;
+    run_iter = iter;
+    stop = done;
+    fresh = 1;
+  }
 };
 
 // Which batch item a workgroup belongs to and whether that item is masked
@@ -55,7 +73,7 @@ struct Skip {
   // skip items whose Krylov solve is done
   static Skip done(const KrylovScalars* ks, long per_item = 1L << 62) {
     Skip s;
-    s.gate = &ks->done;
+    s.gate = &ks->stop;
     s.stride = (int)(sizeof(KrylovScalars) / sizeof(int));
     s.per_item = per_item;
     return s;
@@ -233,6 +251,13 @@ __device__ __forceinline__ double block_sum(double v, double* red /*>= 16 double
     for (int k = 0; k < nw; ++k) s += red[k];
   return s;  // valid in thread 0 only
 }
+// The same, for every thread.
+__device__ __forceinline__ double block_sum_all(double v, double* red) {
+  block_sum(v, red);
+  double s = 0.0;
+  for (int k = 0; k < (int)((blockDim.x + 63) >> 6); ++k) s += red[k];
+  return s;
+}
 
 // Sum of nparts partials in a fixed order by one block (deterministic).
 // Each thread keeps eight independent running sums, so that eight loads are
@@ -246,7 +271,9 @@ __device__ __forceinline__ double thread_partials(const double* __restrict__ par
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] += partials[k + u * bd];
   }
-  for (; k < nparts; k += bd) a[0] += partials[k];
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (k + u * bd < nparts) a[u] += partials[k + u * bd];
   return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 }
 __device__ __forceinline__ double sum_partials(const double* __restrict__ partials, int nparts, double* red) {
@@ -259,23 +286,35 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
 // group's sum does not depend on how many columns a workgroup took).
 struct Parts {
   int groups, head, r;  // sums in all (plain ones and groups)
-  Parts(int n = 0) : groups(n), head(n), r(1) {}
-  Parts(int g, int h, int r_) : groups(g), head(h), r(r_) {}
+  __host__ __device__ Parts(int n = 0) : groups(n), head(n), r(1) {}
+  __host__ __device__ Parts(int g, int h, int r_) : groups(g), head(h), r(r_) {}
   __host__ __device__ __forceinline__ int stride() const { return head + (groups - head) * r; }
 };
 
-__device__ __forceinline__ double sum_parts(const double* __restrict__ partials, const Parts ps, double* red) {
-  if (ps.r == 1) return sum_partials(partials, ps.groups, red);
+// Share of thread t of T.
+__device__ __forceinline__ double thread_parts(const double* __restrict__ partials, const Parts ps, int t, int T) {
   double acc = 0.0;
-  for (int g = threadIdx.x; g < ps.groups; g += blockDim.x) {
+  for (int g = t; g < ps.groups; g += T) {
     if (g < ps.head) {
       acc += partials[g];
       continue;
     }
     const double* p = partials + ps.head + (long)(g - ps.head) * ps.r;
+    if (ps.r == 1) {
+      acc += p[0];
+      continue;
+    }
     double st[9], v = 0.0;  // binary counter of subtree sums (r <= 256)
-    for (int i = 0; i < ps.r; ++i) {
-      v = p[i];
+    const int b = ps.r % 8 == 0 ? 8 : 1;  // leaves read at once
+    for (int i = 0; i < ps.r / b; ++i) {
+      if (b == 8) {
+        double q[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) q[k] = p[8 * i + k];
+        v = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+      } else {
+        v = p[i];
+      }
       bool go = true;
 #pragma unroll
       for (int k = 0; k < 9; ++k)
@@ -290,19 +329,90 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ partials,
     }
     acc += v;
   }
-  return block_sum(acc, red);
+  return acc;
+}
+__device__ __forceinline__ double sum_parts(const double* __restrict__ partials, const Parts ps, double* red) {
+  if (ps.r == 1) return sum_partials(partials, ps.groups, red);
+  return block_sum(thread_parts(partials, ps, threadIdx.x, blockDim.x), red);
+}
+// The same by a workgroup of any size, the same number for every size; buf:
+// 256 doubles of LDS.
+__device__ __forceinline__ double sum_parts_any(const double* __restrict__ partials, const Parts ps, double* buf) {
+  __syncthreads();
+  for (int t = threadIdx.x; t < 256; t += blockDim.x) buf[t] = thread_parts(partials, ps, t, 256);
+  __syncthreads();
+  for (int n = 128; n >= 1; n >>= 1) {
+    for (int t = threadIdx.x; t < n; t += blockDim.x) buf[t] += buf[t + n];
+    __syncthreads();
+  }
+  return buf[0];
 }
 
 // CG step length from s = p.Ap (or p.Aq): alpha = r.r / s (r.z / s
 // preconditioned), or breakdown when s <= 0.  One thread.
 __device__ __forceinline__ void krylov_alpha(KrylovScalars* ks, double s, int pcg) {
+  ks->rr = ks->run_rr;
+  ks->rz = ks->run_rz;
+  ks->iter = ks->run_iter;
+  ks->fresh = 0;
   ks->pAp = s;
   if (!(s > 0.0)) {
     ks->done = 1;
     ks->flag = 1;
+    ks->publish();
   } else {
     ks->alpha = (pcg ? ks->rz : ks->rr) / s;
   }
+}
+
+// An iteration's r.r (and r.z): the direction's beta, and whether the solve
+// ends here.
+struct KrylovTest {
+  double beta;
+  int iter, done, flag;
+};
+__device__ __forceinline__ KrylovTest krylov_test(const KrylovScalars* ks, double rr, double rz, int pcg) {
+  KrylovTest k;
+  k.beta = pcg ? rz / ks->rz : rr / ks->rr;
+  k.iter = ks->iter + 1;
+  k.done = k.flag = 0;
+  if (ks->tol2 > 0.0 && rr <= ks->tol2 * ks->rr0) {
+    k.done = 1;
+  } else if (k.iter >= ks->maxit) {
+    k.done = 1;
+    k.flag = (ks->tol2 > 0.0) ? 2 : 0;
+  }
+  return k;
+}
+// The same taken over by one thread.  beta is kept even when the solve stops
+// here, so that a solve stopped at a fixed iteration count can be continued.
+__device__ __forceinline__ void krylov_take(KrylovScalars* ks, double rr, double rz, int pcg) {
+  const KrylovTest k = krylov_test(ks, rr, rz, pcg);
+  ks->beta = k.beta;
+  ks->iter = k.iter;
+  ks->rr = rr;
+  if (pcg) ks->rz = rz;
+  ks->done = k.done;
+  if (k.done) ks->flag = k.flag;
+  ks->publish();
+}
+
+// End of an iteration from the partial sums of r.r (and r.z) that the N0 pass
+// left, by one workgroup of any size, if that is still to be done.  `few`: the
+// sums of k_plane, added as its direction pass adds them (XBLOCK threads).
+__device__ __forceinline__ void krylov_close(KrylovScalars* ks, const double* __restrict__ prr,
+                                             const double* __restrict__ prz, const Parts parts, bool few,
+                                             double* buf /*256 doubles in LDS*/) {
+  if (ks->done || ks->fresh) return;
+  double rr, rz = 0.0;
+  if (few) {
+    rr = sum_partials(prr, parts.groups, buf);
+    if (prz) rz = sum_partials(prz, parts.groups, buf + 16);
+  } else {
+    rr = sum_parts_any(prr, parts, buf);
+    if (prz) rz = sum_parts_any(prz, parts, buf);
+  }
+  if (threadIdx.x == 0) krylov_take(ks, rr, rz, prz != nullptr);
 }
 
 // Tables of one 3-D plan (device pointers), in the working precision R.

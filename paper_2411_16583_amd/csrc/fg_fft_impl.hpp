@@ -197,7 +197,7 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
   const bool twl = sizeof(R) == 4 && (size_t)(N1 * B + N1) * sizeof(cplx<R>) <= 65536;
   const size_t shm = (size_t)(N1 * B + (twl ? N1 : 0)) * sizeof(cplx<R>);
   a.tile = B;
-  const dim3 grid((unsigned)(a.M / B), (unsigned)N0, (unsigned)(a.nc * nitems));
+  const dim3 grid((unsigned)(a.M / B), (unsigned)(N0 + (a.ks ? 1 : 0)), (unsigned)(a.nc * nitems));
   const dim3 block((unsigned)(T * B / cpt));
   constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
   constexpr bool TW = sizeof(R) == 4;
@@ -230,24 +230,36 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
   throw std::invalid_argument("unsupported N1");
 }
 
-template <typename R, typename RO>
-Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+template <typename R> N0Tile n0_tile(int N0, int N1, int M, int tile, int nc) {
   const int eb = (int)sizeof(cplx<R>);
   const int T = zgrad_threads(N0, eb);
+  N0Tile t;
   // built-in choice: the largest tile, workgroups ky fastest (consecutive
   // blocks in memory)
-  a.kymajor = (a.tile == 0 || (a.tile & kTileKyMajor)) ? 1 : 0;
-  int B = a.tile & ~kTileKyMajor;
-  if (B == 0) B = zgrad_tile(N0, a.M, eb);
+  t.kymajor = (tile == 0 || (tile & kTileKyMajor)) ? 1 : 0;
+  int B = tile & ~kTileKyMajor;
+  if (B == 0) B = zgrad_tile(N0, M, eb);
   auto cpt_of = [&](int b) { return (b % 2 == 0) ? zgrad_cpt(N0, eb) : 1; };
   while (B > 1 && T * B / cpt_of(B) > 256) B /= 2;  // a tile chosen for another line shape
-  const int cpt = cpt_of(B);
+  t.B = B;
+  t.cpt = cpt_of(B);
+  t.T = T;
+  const int bm = M & -M;  // a row of ky in groups of the largest power of two of columns
+  const int ndc = N1 / 2 + 1;
+  t.parts = Parts(nc * (ndc + N1 * (M / bm)), nc * ndc, bm / B);
+  return t;
+}
+
+template <typename R, typename RO>
+Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  const N0Tile t = n0_tile<R>(N0, a.N1, a.M, a.tile, a.nc);
+  const int B = t.B, T = t.T, cpt = t.cpt;
+  const Parts parts = t.parts;
+  a.kymajor = t.kymajor;
   a.tile = B;
   a.ndc = a.N1 / 2 + 1;
   a.nmain = (a.M / B) * a.N1;
   const size_t shm = (size_t)N0 * std::max(B, 4) * sizeof(cplx<R>) + n0_extra_lds<R>(N0);
-  const int bm = a.M & -a.M;  // a row of ky in groups of the largest power of two of columns
-  const Parts parts(a.nc * (a.ndc + a.N1 * (a.M / bm)), a.nc * a.ndc, bm / B);
   const dim3 grid((unsigned)((long)parts.stride() * nitems));
   const dim3 block((unsigned)std::max(T * B / cpt, 2 * T));
   constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
@@ -288,16 +300,13 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
 }
 
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, int nlines, int nc, const SpecTables<R>& tb,
-                    const KrylovScalars* ks, int nitems, int planes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  using C = cplx<R>;
+void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   switch (M) {
 #define FG_CASE(L_)                                                                                              \
   case L_: {                                                                                                     \
     constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
-    const dim3 grid((unsigned)((nc * nlines + LPB - 1) / LPB), (unsigned)nitems);                                \
-    launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, reinterpret_cast<const C*>(in),            \
-              reinterpret_cast<C*>(pi), reinterpret_cast<C*>(xi), nlines, nc, tb, ks, planes);                   \
+    const dim3 grid((unsigned)((a.nc * a.nlines + LPB - 1) / LPB), (unsigned)nitems);                            \
+    launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, a);                                        \
     return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
@@ -309,11 +318,7 @@ void launch_c2r_dir(int M, const R* in, R* pi, R* xi, int nlines, int nc, const 
 template <typename R, typename RO>
 Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hipStream_t s, hipEvent_t ev0,
                    hipEvent_t ev1) {
-  const int plane = a.n0 * a.n1;
-  // one plane per workgroup; several small ones where that leaves 512
-  // workgroups
-  a.P = 1;
-  while (a.M % (2 * a.P) == 0 && 2 * a.P * plane <= 1024 && (long)nc * a.M / (2 * a.P) * nitems >= 512) a.P *= 2;
+  a.P = planes_per_group(a.n0, a.n1, a.M, nc, nitems);
   a.groups = nc * a.M / a.P;
   a.dn1 = FastDiv(a.n1);
   const dim3 grid((unsigned)(a.groups * nitems));
@@ -359,10 +364,10 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
                                     int, hipStream_t, hipEvent_t, hipEvent_t);                          \
   template void launch_n1<R>(int, bool, int, N1Args<R>, int, hipStream_t, hipEvent_t, hipEvent_t);      \
+  template N0Tile n0_tile<R>(int, int, int, int, int);                                                  \
   template Parts launch_n0<R, R>(int, int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
   template Parts launch_plane<R, R>(int, int, PlaneArgs<R, R>, int, int, hipStream_t, hipEvent_t, hipEvent_t); \
-  template void launch_c2r_dir<R>(int, const R*, R*, R*, int, int, const SpecTables<R>&, const KrylovScalars*, int, \
-                                  int, hipStream_t, hipEvent_t, hipEvent_t);                            \
+  template void launch_c2r_dir<R>(int, const DirArgs<R>&, int, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
   template int launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, const C2REpi&, hipStream_t, hipEvent_t, \
                              hipEvent_t);                                                           \

@@ -73,11 +73,21 @@ void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s,
 template <typename R, typename RO>
 Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
               hipEvent_t ev1 = nullptr);
+// How the N0 pass splits an item for a tile (0: its own choice): columns and
+// threads per line of a workgroup, columns per thread, order, partial sums.
+struct N0Tile {
+  int B, T, cpt, kymajor;
+  Parts parts;
+};
+template <typename R> N0Tile n0_tile(int N0, int N1, int M, int tile, int nc);
 // most partial sums per item that launch_n0 writes, for any tile
 inline long n0_max_parts(int N1, int M) { return 3L * ((long)M * N1 + N1 / 2 + 1); }
 // Whether a grid's planes fit k_plane in double precision (the working type
 // of every residual pass).
 bool plane_fits(int n0, int n1);
+// Planes of k_plane per workgroup: one, or several small ones where that
+// leaves 512 workgroups.
+int planes_per_group(int n0, int n1, int M, int nc, int nitems);
 // N1 and N0 passes in one (k_plane), mode and symbol as launch_n0; a: q, z, s,
 // tables, scalars and partial sums.  Returns the partial sums of an item.
 template <typename R, typename RO>
@@ -85,8 +95,8 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
                    hipEvent_t ev1 = nullptr);
 // Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
 template <typename R>
-void launch_c2r_dir(int M, const R* in, R* pi, R* xi, int nlines, int nc, const SpecTables<R>& tb,
-                    const KrylovScalars* ks, int nitems, int planes, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                    hipEvent_t ev1 = nullptr);
 
 template <typename R>
 void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const Skip& skip,

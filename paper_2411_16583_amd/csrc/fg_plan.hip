@@ -114,6 +114,12 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 // 96 x 48 48 / 55, plane 256 x 256 42 / 47, 48 x 96 x 192 123 / 123.
 bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= 160 * 1024 - 1024; }
 
+int planes_per_group(int n0, int n1, int M, int nc, int nitems) {
+  int p = 1;
+  while (M % (2 * p) == 0 && 2 * p * n0 * n1 <= 1024 && (long)nc * M / (2 * p) * nitems >= 512) p *= 2;
+  return p;
+}
+
 int zline_threads(int L) {
   if (L == 256) return Line3<256>::T;
   if (L == 128) return Line3<128>::T;
@@ -555,6 +561,33 @@ template <typename R, typename RO> PlaneArgs<R, RO> plane_args(fg_plan* P, const
   return a;
 }
 
+// Partial sums of r.r that the N0 pass of a CG of nc components leaves in part2.
+template <typename T> Parts rr_parts(fg_plan* P, int nc, int nitems) {
+  if (P->planes) return Parts(nc * P->M / planes_per_group(P->n0, P->n1, P->M, nc, nitems));
+  return n0_tile<T>(P->n0, P->n1, P->M, tile_zproj<T>(P), nc).parts;
+}
+
+// The partial sums that k_plane left in part2 are added up by the direction
+// pass itself.
+template <typename R>
+DirArgs<R> dir_args(fg_plan* P, const void* in, void* pi, void* xi, KrylovScalars* ks, int nc, bool pcg = false) {
+  DirArgs<R> a{};
+  a.in = (const cplx<R>*)in;
+  a.pi = (cplx<R>*)pi;
+  a.xi = (cplx<R>*)xi;
+  a.nlines = P->n0 * P->n1;
+  a.nc = nc;
+  a.planes = P->planes;
+  a.tb = tabs<R>(P).spec();
+  a.ks = ks;
+  if (P->planes && ks) {
+    a.prr = P->part2;
+    if (pcg) a.prz = P->part2 + P->part_n / 2;
+    a.np = rr_parts<R>(P, nc, pcg ? 1 : P->nitems).groups;
+  }
+  return a;
+}
+
 // ----------------------------------------------------------------------------
 // Mechanics.
 void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, double* pparts,
@@ -652,13 +685,22 @@ int next_chunk(const KrylovScalars& h, long launched) {
 // (they return at once); excluded from the profiled launch counts.
 void note_noop_iterations(fg_plan* P, long noop) {
   if (!P->prof_on || noop <= 0) return;
-  for (int pass : {FG_PASS_FRONT, FG_PASS_R2C, FG_PASS_AXIS, FG_PASS_ZPROJ, FG_PASS_AXIS3, FG_PASS_C2R3, FG_PASS_FINALIZE})
+  for (int pass : {FG_PASS_FRONT, FG_PASS_R2C, FG_PASS_AXIS, FG_PASS_ZPROJ, FG_PASS_AXIS3, FG_PASS_C2R3})
     if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
 }
 
 // Grid of a per-item field kernel: up to 256 blocks per item, grid.y = item.
 inline dim3 item_grid(long n, int nitems) {
   return dim3((unsigned)std::min<long>(256, (n + 255) / 256), (unsigned)nitems);
+}
+
+// End of the last CG iteration (r.r, beta, the end of the solve) before the
+// scalars are read; between iterations the next pass does it itself.
+template <typename T> void cg_end(fg_plan* P) {
+  ProfScope ps(P, FG_PASS_FINALIZE, true);
+  launch_ev(k_cg_close, dim3(P->nitems), dim3(P->planes ? XBLOCK : 256), 0, P->stream, ps.start, ps.stop,
+            (const double*)P->part2, (const double*)nullptr, rr_parts<T>(P, 3, P->nitems), P->ks, P->planes);
+  check_launch();
 }
 
 // One CG iteration for every item of the plan (items whose solve is done
@@ -672,12 +714,15 @@ void cg_iteration(fg_plan* P) {
   const Gate gate = Gate::done(ks);
   if (!P->planes) {
     ProfScope ps(P, FG_PASS_AXIS3, true);
-    launch_n1<T>(P->n1, true, P->n0, n1_args<T>(P, P->ln, P->bk, P->dc, gate), nit, P->stream, ps.start, ps.stop);
+    N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
+    a.ks = ks;
+    a.prr = P->part2;
+    a.parts = rr_parts<T>(P, 3, nit);
+    launch_n1<T>(P->n1, true, P->n0, a, nit, P->stream, ps.start, ps.stop);
   }
   {
     ProfScope ps(P, FG_PASS_C2R3, true);
-    launch_c2r_dir<T>(P->M, (const T*)P->ln, (T*)P->p, (T*)P->x, P->n0 * P->n1, 3, tb, ks, nit, P->planes, P->stream,
-                      ps.start, ps.stop);
+    launch_c2r_dir<T>(P->M, dir_args<T>(P, P->ln, P->p, P->x, ks, 3), nit, P->stream, ps.start, ps.stop);
   }
   int nbf;
   {
@@ -690,7 +735,6 @@ void cg_iteration(fg_plan* P) {
     launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->planes,
                         P->stream, ps.start, ps.stop);
   }
-  Parts nbz;
   if (P->planes) {
     ProfScope ps(P, FG_PASS_ZPROJ, true);
     PlaneArgs<T, T> a = plane_args<T, T>(P, gate);
@@ -700,7 +744,7 @@ void cg_iteration(fg_plan* P) {
     a.npap = nbf;
     a.ks = ks;
     a.partials = P->part2;
-    nbz = launch_plane<T, T>(kN0Cg, kSymProj, a, 3, nit, P->stream, ps.start, ps.stop);
+    launch_plane<T, T>(kN0Cg, kSymProj, a, 3, nit, P->stream, ps.start, ps.stop);
   } else {
     {
       // alpha = r.r / p.Kp is formed by the N1 pass (one workgroup per item)
@@ -719,12 +763,7 @@ void cg_iteration(fg_plan* P) {
     a.dcs = (cplx<T>*)P->rdc;
     a.ks = ks;
     a.partials = P->part2;
-    nbz = launch_n0<T, T>(P->n0, kN0Cg, kSymProj, a, nit, P->stream, ps.start, ps.stop);
-  }
-  {
-    ProfScope ps(P, FG_PASS_FINALIZE, true);
-    launch_ev(k_finalize, dim3(nit), dim3(1024), 0, P->stream, ps.start, ps.stop, (const double*)P->part2, nbz, ks,
-              (double*)nullptr, 1);
+    launch_n0<T, T>(P->n0, kN0Cg, kSymProj, a, nit, P->stream, ps.start, ps.stop);
   }
   check_launch();
 }
@@ -770,6 +809,7 @@ void cg_solve(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
   for (int guard = 0; guard < 1000000; ++guard) {
     launched += chunk;
     for (int k = 0; k < chunk; ++k) cg_iteration<T>(P);
+    cg_end<T>(P);
     sync_read(P);
     if (P->hks[0].done) break;
     chunk = next_chunk(P->hks[0], launched);
@@ -1025,6 +1065,8 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   const Gate gate = Gate::done(ks);
   const SpecTables<double> tb = P->t64.spec();
   const Grid3 g{P->n0, P->n1, P->n2, 1.0 / P->h[0], 1.0 / P->h[1], 1.0 / P->h[2]};
+  const double *prr = P->part2, *prz = P->part2 + P->part_n / 2;
+  const DirArgs<double> dir = dir_args<double>(P, P->ln64, v.p, v.x, ks, 1, true);
   // the N1 and N0 passes of q (npap partial sums of p.q) and the inverse N1
   // pass of z
   auto passes = [&](int mode, int npap) {
@@ -1067,10 +1109,15 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
         n = launch_n0<double, double>(P->n0, mode, kSymLap, a, 1, P->stream);
       }
     }
-    hipLaunchKernelGGL(k_pcg_finalize, dim3(1), dim3(1024), 0, P->stream, (const double*)P->part2,
-                       (const double*)(P->part2 + P->part_n / 2), n, ks, mode == kN0Start ? 1 : 0);
-    if (!P->planes)
-      launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1), 1, P->stream);
+    if (mode == kN0Start) hipLaunchKernelGGL(k_pcg_start, dim3(1), dim3(1024), 0, P->stream, prz, n, ks);
+    if (!P->planes) {
+      N1Args<double> b = n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate, 1);
+      b.ks = ks;
+      b.prr = prr;
+      b.prz = prz;
+      b.parts = n;
+      launch_n1<double>(P->n1, true, P->n0, b, 1, P->stream);
+    }
   };
   auto apply = [&](int which, const double* in) {
     return launch_scalar_op(which, P->M, in, op == ScalarOp::FICK ? v.w : v.a, v.A6,
@@ -1084,10 +1131,12 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   int chunk = 4;
   for (int guard = 0; guard < 1000000; ++guard) {
     for (int k = 0; k < chunk; ++k) {
-      launch_c2r_dir<double>(P->M, P->ln64, v.p, v.x, P->n0 * P->n1, 1, tb, ks, 1, P->planes, P->stream);
+      launch_c2r_dir<double>(P->M, dir, 1, P->stream);
       passes(kN0Cg, apply(op == ScalarOp::FICK ? 1 : 0, v.p));
       check_launch();
     }
+    // (without planes the inverse N1 pass has closed the iteration)
+    if (P->planes) hipLaunchKernelGGL(k_cg_close, dim3(1), dim3(XBLOCK), 0, P->stream, prr, prz, Parts(dir.np), ks, 1);
     sync_read(P);
     if (P->hksc[0].done) break;
     chunk = next_chunk(P->hksc[0], 0);
@@ -1411,6 +1460,7 @@ fg_status fg_cg_iterate(fg_plan* P, int n, int apply, fg_stats* stats) {
       h.maxit = h.iter + n;
       h.done = 0;
       h.flag = 0;
+      h.publish();
       FG_HIP(hipMemcpyAsync(P->ks, &h, sizeof(KrylovScalars), hipMemcpyHostToDevice, P->stream));
       for (int left = n; left > 0;) {
         const int chunk = std::min(left, 8);
@@ -1421,6 +1471,7 @@ fg_status fg_cg_iterate(fg_plan* P, int n, int apply, fg_stats* stats) {
             cg_iteration<float>(P);
         }
         left -= chunk;
+        P->prec == FG_FP64 ? cg_end<double>(P) : cg_end<float>(P);
         sync_read(P);
         if (P->hks[0].flag == 1) break;
       }
@@ -1566,8 +1617,7 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
       launch_n0<double, double>(P->n0, kN0Apply, kSymProj, a, 1, P->stream);
       launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
     }
-    launch_c2r_dir<double>(P->M, P->ln64, P->q64, nullptr, P->n0 * P->n1, 3, P->t64.spec(), nullptr, 1, P->planes,
-                           P->stream);
+    launch_c2r_dir<double>(P->M, dir_args<double>(P, P->ln64, P->q64, nullptr, nullptr, 3), 1, P->stream);
     launch_grad_store<double, double>(P->q64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
                                       P->stream);
     check_launch();
@@ -1780,6 +1830,7 @@ template <typename T>
 void batch_tick(fg_plan* P, fg_batch::Group& g, bool newton) {
   cg_iteration<T>(P);
   if (!newton) return;
+  cg_end<T>(P);
   const int nit = P->nitems;
   hipLaunchKernelGGL(k_newton_gate, dim3(1), dim3(1024), 0, P->stream, (const KrylovScalars*)P->ks, g.nc, g.idle,
                      g.active, nit, (int)FG_E_BREAKDOWN, (int)FG_E_NOCONV);
@@ -1870,6 +1921,7 @@ void batch_prologue(fg_batch* B, fg_batch::Group& g, const double* F_macro, cons
     KrylovScalars& k = P->hks[b];
     std::memset(&k, 0, sizeof(KrylovScalars));
     k.done = 1;  // the first tick starts with the Newton step
+    k.publish();
     k.tol2 = (om.fixed_lin > 0) ? 0.0 : om.tol_lin * om.tol_lin;
     k.maxit = (om.fixed_lin > 0) ? om.fixed_lin : om.max_lin;
   }

@@ -192,7 +192,6 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs<R, RO> a) {
   using CO = cplx<RO>;
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ double red[16];
-  __shared__ double s_alpha;
   const int item = (int)(blockIdx.x / (unsigned)a.groups);
   const int g = (int)blockIdx.x - item * a.groups;
   if (a.gate(item)) return;
@@ -231,17 +230,14 @@ __global__ void __launch_bounds__(512) k_plane(PlaneArgs<R, RO> a) {
   }
   R alpha = R(0);
   if constexpr (MODE == kN0Cg) {
-    const double s = block_sum(pap, red);
-    if (threadIdx.x == 0) {
-      KrylovScalars* ks = a.ks + item;
-      s_alpha = s > 0.0 ? (a.pcg ? ks->rz : ks->rr) / s : -1.0;  // p.Kp <= 0: breakdown
-      if (g == 0) krylov_alpha(ks, s, a.pcg);
-    }
-  }
-  __syncthreads();
-  if constexpr (MODE == kN0Cg) {
-    if (!(s_alpha >= 0.0)) return;
-    alpha = (R)s_alpha;
+    const double s = block_sum_all(pap, red);
+    KrylovScalars* ks = a.ks + item;
+    const double rn = a.pcg ? ks->run_rz : ks->run_rr;
+    if (g == 0 && threadIdx.x == 0) krylov_alpha(ks, s, a.pcg);
+    if (!(s > 0.0)) return;  // p.Kp <= 0: breakdown
+    alpha = (R)(rn / s);
+  } else {
+    __syncthreads();
   }
   double acc = 0.0, acc2 = 0.0;
   auto symbol = [&](int kz, int ky, R cx, R sx) {

@@ -296,20 +296,8 @@ k_contract(T* __restrict__ Y, const T* __restrict__ X, const T* __restrict__ st,
   for (int k = 0; k < 9; ++k) yv[k * N2v + i] = mk<V>(Y0[k], Y1[k]);
 }
 
-// mode 1: plain CG: rr_new, iteration count, convergence, beta.
 // mode 2: store the sum into out[0] (norms).
 // mode 5: initialise a Krylov solve from rr0 = sum (b.b): rr = rr0, iter = 0.
-__device__ __forceinline__ void krylov_test(KrylovScalars* ks, double rr) {
-  ks->iter += 1;
-  ks->rr = rr;
-  if (ks->tol2 > 0.0 && rr <= ks->tol2 * ks->rr0) {
-    ks->done = 1;
-  } else if (ks->iter >= ks->maxit) {
-    ks->done = 1;
-    ks->flag = (ks->tol2 > 0.0) ? 2 : 0;
-  }
-}
-
 __global__ void __launch_bounds__(1024)
 k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, double* out, int mode) {
   // one workgroup per batch item: its partials, scalars and output
@@ -317,15 +305,9 @@ k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, 
   partials += (long)blockIdx.x * parts.stride();
   if (ks) ks += blockIdx.x;
   if (out) out += blockIdx.x;
-  if (ks && ks->done && mode != 5 && mode != 2) return;
   const double s = sum_parts(partials, parts, red);
   if (threadIdx.x != 0) return;
-  if (mode == 1) {
-    // beta is kept even when the solve stops here, so that a solve stopped
-    // at a fixed iteration count can be continued
-    ks->beta = s / ks->rr;
-    krylov_test(ks, s);
-  } else if (mode == 2) {
+  if (mode == 2) {
     out[0] = s;
   } else if (mode == 5) {
     ks->rr0 = s;
@@ -334,24 +316,27 @@ k_finalize(const double* __restrict__ partials, Parts parts, KrylovScalars* ks, 
     ks->flag = 0;
     ks->beta = 0.0;
     ks->done = (s == 0.0) ? 1 : 0;
+    ks->publish();
   }
 }
 
-// Preconditioned CG after the N0 pass: r.r (iteration count, convergence) and
-// r.z -> beta = rz_new / rz; with start, r.z of the first residual alone.
-__global__ void __launch_bounds__(1024)
-k_pcg_finalize(const double* __restrict__ prr, const double* __restrict__ prz, Parts parts, KrylovScalars* ks,
-               int start) {
+// r.z of the first residual of a preconditioned CG.
+__global__ void __launch_bounds__(1024) k_pcg_start(const double* __restrict__ prz, Parts parts, KrylovScalars* ks) {
   __shared__ double red[16];
   if (ks->done) return;
   const double rz = sum_parts(prz, parts, red);
-  const double rr = start ? 0.0 : sum_parts(prr, parts, red);
   if (threadIdx.x != 0) return;
-  if (!start) {
-    ks->beta = rz / ks->rz;
-    krylov_test(ks, rr);
-  }
   ks->rz = rz;
+  ks->publish();
+}
+
+// krylov_close as a kernel of its own: before the scalars are read by the
+// host.  One workgroup per item.
+__global__ void __launch_bounds__(256)
+k_cg_close(const double* __restrict__ prr, const double* __restrict__ prz, Parts parts, KrylovScalars* ks, int few) {
+  __shared__ double buf[256];
+  const long o = (long)blockIdx.x * parts.stride();
+  krylov_close(ks + blockIdx.x, prr + o, prz ? prz + o : nullptr, parts, few != 0, buf);
 }
 
 // F += x (F FP64, x in the CG precision), n = 9N.

@@ -73,3 +73,29 @@ def test_cg_iterates_by_divergence(shape, precision, tol, law):
     assert plan.cg_iterate(2, apply=True)["iters"] == 4
     assert rel(host(F, (3, 3) + shape) - F0, dF) <= tol
     plan.close()
+
+
+@pytest.mark.parametrize("shape,precision", [((12, 8, 16), "fp64"), ((64, 8, 32), "mixed"), ((128, 96, 12), "fp64"),
+                                             ((128, 96, 16), "mixed"), ((256, 8, 64), "fp64")])
+def test_cg_ends_alike_wherever_its_scalars_are_read(shape, precision):
+    """r.r and beta are formed by the pass after the N0 pass between iterations
+    (in every workgroup of it, or in one of them), and by a kernel of their own
+    before the host reads them: the same bits, so 9 iterations in one call and
+    in calls of 1, 3 and 5 give the same solution."""
+    print(f"cg in parts {shape} {precision}", flush=True)
+    work = synth.homogeneous_workload(shape, 1.0)
+    phase = np.random.default_rng(3).random(shape) < 0.3
+    work["E"] = np.where(phase, 100e9, 10e9)
+    Fbar = np.eye(3)
+    Fbar[0, 1] += 0.004
+    out = []
+    for parts in ((9,), (1, 3, 5)):
+        plan = plan_for(work, precision)
+        F = dt(mechanics.uniform_field(Fbar, shape))
+        plan.set_state(F, dt(work["c0"]), dt(work["d0"]))
+        plan.newton_linear_begin(Fbar)
+        for k, n in enumerate(parts):
+            plan.cg_iterate(n, apply=k == len(parts) - 1)
+        out.append(host(F, (3, 3) + shape))
+        plan.close()
+    assert np.array_equal(out[0], out[1])
