@@ -55,10 +55,11 @@ k_grad_store(const TI* __restrict__ U, long ucs, long uis, TO* __restrict__ Z, l
 // precision of xi), added to Z (ADD) or stored there.  The deferred step
 // alpha pi is left out after a breakdown (the direction pass had already
 // applied the last valid one); a solve that never iterated has x = 0.
-// xi, pi: 3 N values per item; Z: 9 N.
+// xi, pi: 3 N values per item (pi2: distance of the buffer that odd iterations
+// write, or 0); Z: 9 N.
 template <typename T, bool ADD>
 __global__ void __launch_bounds__(256)
-k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, const KrylovScalars* __restrict__ ksb,
+k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, long pi2, const KrylovScalars* __restrict__ ksb,
             double* __restrict__ Z, const int* __restrict__ idle, int n0, int n1, int n2, double q0, double q1,
             double q2) {
   const int item = blockIdx.y;
@@ -70,7 +71,7 @@ k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, const KrylovScal
   const T alpha = (T)ks->alpha;
   const long N = (long)n0 * n1 * n2;
   xi += (long)item * 3 * N;
-  pi += (long)item * 3 * N;
+  pi += (long)item * 3 * N + (none ? 0 : (ks->iter - 1) & 1) * pi2;
   Z += (long)item * 9 * N;
   const int G = n2 / 2;
   const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -118,11 +119,11 @@ void launch_grad_store(const TI* U, long ucs, long uis, TO* Z, long zis, const i
 }
 
 template <typename T, bool ADD>
-void launch_cg_result(const T* xi, const T* pi, const KrylovScalars* ks, double* Z, const int* idle, int n0, int n1,
+void launch_cg_result(const T* xi, const T* pi, long pi2, const KrylovScalars* ks, double* Z, const int* idle, int n0, int n1,
                       int n2, int nitems, const double h[3], hipStream_t s) {
   const long N = (long)n0 * n1 * n2;
   hipLaunchKernelGGL((k_cg_result<T, ADD>), dim3((unsigned)((N / 2 + 255) / 256), (unsigned)nitems), dim3(256), 0, s, xi,
-                     pi, ks, Z, idle, n0, n1, n2, 0.25 / h[0], 0.25 / h[1], 0.25 / h[2]);
+                     pi, pi2, ks, Z, idle, n0, n1, n2, 0.25 / h[0], 0.25 / h[1], 0.25 / h[2]);
 }
 
 }  // namespace fg

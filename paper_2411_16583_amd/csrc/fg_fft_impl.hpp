@@ -315,6 +315,27 @@ void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEv
   throw std::invalid_argument("unsupported N2/2");
 }
 
+template <typename R>
+int launch_cg_lines(int law, int M, LinesArgs<R> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  a.nb = (a.n1 + a.L - 1) / a.L;
+  a.groups = a.n0 * a.nb;
+  const dim3 grid((unsigned)(a.groups * nitems)), block(kLinesThreads);
+  switch (M) {
+#define FG_CASE(L_)                                                                                               \
+  case L_: {                                                                                                      \
+    const unsigned shm = (unsigned)lines_lds(sizeof(R), L_, a.L);                                                  \
+    if (law == kLawSVK)                                                                                           \
+      launch_ev((k_cg_lines<R, L_, kLawSVK>), grid, block, shm, s, ev0, ev1, a);                                  \
+    else                                                                                                          \
+      launch_ev((k_cg_lines<R, L_, kLawNH>), grid, block, shm, s, ev0, ev1, a);                                   \
+    return a.groups;                                                                                              \
+  }
+    FG_FOR_LINES(FG_CASE)
+#undef FG_CASE
+  }
+  throw std::invalid_argument("unsupported N2/2");
+}
+
 template <typename R, typename RO>
 Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hipStream_t s, hipEvent_t ev0,
                    hipEvent_t ev1) {
@@ -367,6 +388,7 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   template N0Tile n0_tile<R>(int, int, int, int, int);                                                  \
   template Parts launch_n0<R, R>(int, int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \
   template Parts launch_plane<R, R>(int, int, PlaneArgs<R, R>, int, int, hipStream_t, hipEvent_t, hipEvent_t); \
+  template int launch_cg_lines<R>(int, int, LinesArgs<R>, int, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_c2r_dir<R>(int, const DirArgs<R>&, int, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
   template int launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, const C2REpi&, hipStream_t, hipEvent_t, \

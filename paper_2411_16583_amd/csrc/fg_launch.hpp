@@ -6,6 +6,7 @@
 
 #include "fg_cg3.hpp"
 #include "fg_plane.hpp"
+#include "fg_cg_lines.hpp"
 
 namespace fg {
 
@@ -96,6 +97,14 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
 // Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
 template <typename R>
 void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
+                    hipEvent_t ev1 = nullptr);
+
+// Lines per workgroup of k_cg_lines for a plan (0: the grid takes the passes).
+int lines_per_group(int n0, int n1, int M, int nitems);
+// The inverse N2 pass, the operator and the N2 pass of a CG iteration in one
+// (k_cg_lines); returns the partial sums of p.Kp of an item.
+template <typename R>
+int launch_cg_lines(int law, int M, LinesArgs<R> a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
                     hipEvent_t ev1 = nullptr);
 
 template <typename R>

@@ -114,6 +114,19 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 // 96 x 48 48 / 55, plane 256 x 256 42 / 47, 48 x 96 x 192 123 / 123.
 bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= 160 * 1024 - 1024; }
 
+// Up to 32^3 voxels the launches and memory latencies of the separate passes
+// cost more than the transforms and the tangent that the lines kernel repeats.
+// CG iteration with it / with the passes (us, FP64): 16^3 22.9 / 31.2, 24^3
+// 29.9 / 36.1, 32^3 26.6 / 31.1, 64 x 64 plane 23.9 / 30.3, 48^3 102 / 45.
+// Two lines per workgroup, or four where there are more than 256 lines (24^3
+// with 1, 2, 4 lines: 41.8, 32.9, 29.9; 16^3: 23.5, 22.9, 23.3).
+int lines_per_group(int n0, int n1, int M, int nitems) {
+  if (M > 32 || 2L * M * n0 * n1 * nitems > 32768) return 0;
+  int L = (long)n0 * n1 * nitems > 256 ? 4 : 2;
+  while (L > 1 && lines_lds(sizeof(double), M, L) > 64000) L /= 2;
+  return L;
+}
+
 int planes_per_group(int n0, int n1, int M, int nc, int nitems) {
   int p = 1;
   while (M % (2 * p) == 0 && 2 * p * n0 * n1 <= 1024 && (long)nc * M / (2 * p) * nitems >= 512) p *= 2;
@@ -197,6 +210,7 @@ struct fg_plan {
   // [0] N1 pass FP64, [1] N0 projection pass FP64, [2] N1 pass FP32, [3] N0 projection pass FP32
   int tiles[4] = {0, 0, 0, 0};
   int tiles_gen = 0;  // bumped by fg_plan_set_tiles (a captured batch graph is then stale)
+  int lines = 0;        // lines per workgroup of k_cg_lines (0: not taken)
   bool planes = false;  // the N1 and N0 passes of the CG run as one (k_plane)
   int law = ::FG_LAW_NEO_HOOKE;  // material law (fg_set_law, before the workspace)
   double h[3];
@@ -698,16 +712,14 @@ inline dim3 item_grid(long n, int nitems) {
 // scalars are read; between iterations the next pass does it itself.
 template <typename T> void cg_end(fg_plan* P) {
   ProfScope ps(P, FG_PASS_FINALIZE, true);
-  launch_ev(k_cg_close, dim3(P->nitems), dim3(P->planes ? XBLOCK : 256), 0, P->stream, ps.start, ps.stop,
+  launch_ev(k_cg_close, dim3(P->nitems), dim3(P->planes && !P->lines ? XBLOCK : 256), 0, P->stream, ps.start, ps.stop,
             (const double*)P->part2, (const double*)nullptr, rr_parts<T>(P, 3, P->nitems), P->ks, P->planes);
   check_launch();
 }
 
-// One CG iteration for every item of the plan (items whose solve is done
-// skip every kernel): the passes of fg_cg3.hpp.  It starts from z_k in the
-// block layout (left by residual_pass or by the iteration before).
-template <typename T>
-void cg_iteration(fg_plan* P) {
+// The passes of an iteration in front of the spectrum of q: z, the CG vectors,
+// q and its N2 transform.  Returns the partial sums of p.Kp.
+template <typename T> int cg_front_passes(fg_plan* P) {
   const int nit = P->nitems;
   KrylovScalars* ks = P->ks;
   const SpecTables<T> tb = tabs<T>(P).spec();
@@ -735,10 +747,46 @@ void cg_iteration(fg_plan* P) {
     launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->planes,
                         P->stream, ps.start, ps.stop);
   }
+  return nbf;
+}
+// The same in one kernel.
+template <typename T> int cg_front_lines(fg_plan* P) {
+  ProfScope ps(P, FG_PASS_FRONT, true);
+  LinesArgs<T> a{};
+  a.z = (const cplx<T>*)P->ln;
+  a.q = (cplx<T>*)P->q;
+  a.pi = (T*)P->p;
+  a.pi2 = 3 * P->N * P->nitems;
+  a.xi = (T*)P->x;
+  a.st = (const T*)P->st;
+  a.ks = P->ks;
+  a.prr = P->part2;
+  a.np = rr_parts<T>(P, 3, P->nitems).groups;
+  a.partials = P->part;
+  a.n0 = P->n0;
+  a.n1 = P->n1;
+  a.L = P->lines;
+  a.tb = tabs<T>(P).spec();
+  a.q0 = (T)(0.25 / P->h[0]);
+  a.q1 = (T)(0.25 / P->h[1]);
+  a.q2 = (T)(0.25 / P->h[2]);
+  return launch_cg_lines<T>(P->law, P->M, a, P->nitems, P->stream, ps.start, ps.stop);
+}
+
+// One CG iteration for every item of the plan (items whose solve is done
+// skip every kernel): the passes of fg_cg3.hpp.  It starts from z_k in the
+// block layout (left by residual_pass or by the iteration before).
+template <typename T>
+void cg_iteration(fg_plan* P) {
+  const int nit = P->nitems;
+  KrylovScalars* ks = P->ks;
+  const Gate gate = Gate::done(ks);
+  const int nbf = P->lines ? cg_front_lines<T>(P) : cg_front_passes<T>(P);
   if (P->planes) {
     ProfScope ps(P, FG_PASS_ZPROJ, true);
     PlaneArgs<T, T> a = plane_args<T, T>(P, gate);
-    a.q = a.z = (cplx<T>*)P->ln;
+    a.q = (const cplx<T>*)(P->lines ? P->q : P->ln);
+    a.z = (cplx<T>*)P->ln;
     a.s = (cplx<T>*)P->rs;
     a.pap = P->part;
     a.npap = nbf;
@@ -781,10 +829,11 @@ void cg_result(fg_plan* P, double* dst, bool add, const int* idle = nullptr) {
   auto go = [&](auto tag) {
     using T = decltype(tag);
     const T *xi = (const T*)P->x, *pi = (const T*)P->p;
+    const long pi2 = P->lines ? 3 * P->N * P->nitems : 0;
     if (add)
-      launch_cg_result<T, true>(xi, pi, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+      launch_cg_result<T, true>(xi, pi, pi2, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
     else
-      launch_cg_result<T, false>(xi, pi, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+      launch_cg_result<T, false>(xi, pi, pi2, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
   };
   if (P->prec == FG_FP64)
     go(double());
@@ -1297,6 +1346,7 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
   P->nitems = nitems;
   P->prec = prec;
   P->planes = fg::plane_fits(P->n0, P->n1);
+  P->lines = P->planes ? fg::lines_per_group(P->n0, P->n1, P->M, P->nitems) : 0;
   P->stream = (hipStream_t)stream;
   P->need = layout(P, nullptr) + kAlign;
   if (hipHostMalloc((void**)&P->hks, (nitems + 1) * sizeof(KrylovScalars), hipHostMallocDefault) != hipSuccess ||

@@ -50,8 +50,12 @@ def test_projection_by_divergence(shape):
 def test_cg_iterates_by_divergence(shape, precision, tol, law):
     """Four CG iterations (2, then 2 more) of the first Newton system of a
     random two-phase cell = the oracle's 9-component CG."""
+    check_cg_iterates(shape, precision, tol, law, tuple(float(n) for n in shape) if shape in PLANES else 1.0)
+
+
+def check_cg_iterates(shape, precision, tol, law, lengths):
     print(f"cg {shape} {precision} {law}", flush=True)
-    work = synth.homogeneous_workload(shape, tuple(float(n) for n in shape) if shape in PLANES else 1.0)
+    work = synth.homogeneous_workload(shape, lengths)
     rng = np.random.default_rng(5 + shape[2])
     phase = rng.random(shape) < 0.3
     work["E"] = np.where(phase, 100e9, 10e9)
@@ -99,3 +103,17 @@ def test_cg_ends_alike_wherever_its_scalars_are_read(shape, precision):
         out.append(host(F, (3, 3) + shape))
         plan.close()
     assert np.array_equal(out[0], out[1])
+
+
+# the largest grid whose iteration runs as lines (32^3 voxels, 64-long lines) and
+# the first ones that take the passes; odd counts of lines and blocks of lines
+LINES = [(32, 32, 32), (32, 32, 48), (1, 12, 64), (4, 6, 64), (24, 4, 64), (64, 96, 6), (48, 48, 24), (6, 96, 96)]
+
+
+@pytest.mark.parametrize("law", ["neo_hookean", "svk"])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-11), ("mixed", 1e-5)])
+@pytest.mark.parametrize("shape", LINES)
+def test_cg_iterates_as_lines_or_passes(shape, precision, tol, law):
+    """Both sides of the choice between the one-kernel front of a CG iteration
+    and its passes, against the oracle (cubic voxels; the tolerances above)."""
+    check_cg_iterates(shape, precision, tol, law, tuple(float(n) for n in shape))
