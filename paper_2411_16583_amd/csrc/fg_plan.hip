@@ -270,6 +270,8 @@ struct fg_plan {
   KrylovScalars* hksc = nullptr;
   double* hd = nullptr;
   int* hflags = nullptr;
+  hipEvent_t ev_read = nullptr;
+  size_t read_bytes = 0;  // hks, hflags and hd: the image of ks ... dscal
 };
 
 namespace {
@@ -307,6 +309,7 @@ size_t layout(fg_plan* P, char* base) {
   P->ksc = P->ks + P->nitems;
   P->flags = carve<int>(base, off, 4);
   P->dscal = carve<double>(base, off, 64 + 16 * P->nitems);
+  P->read_bytes = base + off - (char*)P->ks;  // ks, flags, dscal: what the host reads
   P->Fu = carve<double>(base, off, 16 + 9 * P->nitems);
   // partial sums of an item: 9 per 256-voxel block, a workgroup per line of
   // k_cg_op or per column of the N0 pass at most, plus slack for the per-item
@@ -450,11 +453,20 @@ inline unsigned grid_stride_blocks(long n) { return (unsigned)std::min<long>(204
 void check_launch() { FG_HIP(hipGetLastError()); }
 
 void sync_read(fg_plan* P) {
-  FG_HIP(hipMemcpyAsync(P->hks, P->ks, (P->nitems + 1) * sizeof(KrylovScalars), hipMemcpyDeviceToHost, P->stream));
-  FG_HIP(hipMemcpyAsync(P->hd, P->dscal, (64 + 16 * P->nitems) * sizeof(double), hipMemcpyDeviceToHost,
-                        P->stream));
-  FG_HIP(hipMemcpyAsync(P->hflags, P->flags, 4 * sizeof(int), hipMemcpyDeviceToHost, P->stream));
+  // Krylov scalars, flags and reduction results in one copy (three took 10 us
+  // more of the stream each time)
+  FG_HIP(hipMemcpyAsync(P->hks, P->ks, P->read_bytes, hipMemcpyDeviceToHost, P->stream));
   FG_HIP(hipStreamSynchronize(P->stream));
+}
+
+// The same with work put behind the copy before the host waits for it: the
+// stream does not run dry while the host reads and launches (an iteration too
+// many costs a few empty launches, a dry stream 10-15 us per read).
+template <typename F> void sync_read_ahead(fg_plan* P, F&& more) {
+  FG_HIP(hipMemcpyAsync(P->hks, P->ks, P->read_bytes, hipMemcpyDeviceToHost, P->stream));
+  FG_HIP(hipEventRecord(P->ev_read, P->stream));
+  more();
+  FG_HIP(hipEventSynchronize(P->ev_read));
 }
 
 void check_domain(fg_plan* P) {
@@ -703,11 +715,6 @@ void note_noop_iterations(fg_plan* P, long noop) {
     if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
 }
 
-// Grid of a per-item field kernel: up to 256 blocks per item, grid.y = item.
-inline dim3 item_grid(long n, int nitems) {
-  return dim3((unsigned)std::min<long>(256, (n + 255) / 256), (unsigned)nitems);
-}
-
 // End of the last CG iteration (r.r, beta, the end of the solve) before the
 // scalars are read; between iterations the next pass does it itself.
 template <typename T> void cg_end(fg_plan* P) {
@@ -842,24 +849,33 @@ void cg_result(fg_plan* P, double* dst, bool add, const int* idle = nullptr) {
   check_launch();
 }
 
+// Tolerance and iteration cap of a solve about to start (tol2, iter = 0 and
+// maxit lie together in KrylovScalars); pinned: 16 bytes of staging.
+void set_limits(fg_plan* P, KrylovScalars* ks, double* pinned, const fg_solver_opts* o) {
+  static_assert(offsetof(KrylovScalars, iter) == offsetof(KrylovScalars, tol2) + 8 &&
+                    offsetof(KrylovScalars, maxit) == offsetof(KrylovScalars, tol2) + 12,
+                "tol2, iter, maxit");
+  pinned[0] = (o->fixed_lin > 0) ? 0.0 : o->tol_lin * o->tol_lin;
+  int* n = (int*)(pinned + 1);
+  n[0] = 0;
+  n[1] = (o->fixed_lin > 0) ? o->fixed_lin : o->max_lin;
+  FG_HIP(hipMemcpyAsync(&ks->tol2, pinned, 16, hipMemcpyHostToDevice, P->stream));
+}
+
 template <typename T>
 void cg_solve(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
   KrylovScalars* ks = P->ks;
-  // s_0, z_0 and ks (rr0, rr, iter = 0, done) were set by residual_pass and cg_begin
-  {
-    // only tol2 / maxit are host-set; the rest was set on the device
-    P->hd[62] = (o->fixed_lin > 0) ? 0.0 : o->tol_lin * o->tol_lin;
-    ((int*)(P->hd + 63))[0] = (o->fixed_lin > 0) ? o->fixed_lin : o->max_lin;
-    FG_HIP(hipMemcpyAsync(&ks->tol2, P->hd + 62, sizeof(double), hipMemcpyHostToDevice, P->stream));
-    FG_HIP(hipMemcpyAsync(&ks->maxit, P->hd + 63, sizeof(int), hipMemcpyHostToDevice, P->stream));
-  }
+  // s_0, z_0 and ks (rr0, rr, iter = 0, done) were set by residual_pass and
+  // cg_begin; only tol2 and maxit come from the host
+  set_limits(P, ks, P->hd + 62, o);
   int chunk = 8;
   long launched = 0;
   for (int guard = 0; guard < 1000000; ++guard) {
     launched += chunk;
     for (int k = 0; k < chunk; ++k) cg_iteration<T>(P);
     cg_end<T>(P);
-    sync_read(P);
+    sync_read_ahead(P, [&]() { cg_iteration<T>(P); });
+    ++launched;
     if (P->hks[0].done) break;
     chunk = next_chunk(P->hks[0], launched);
   }
@@ -1107,10 +1123,7 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
                 fg_stats* stats) {
   ScalarVecs v = scalar_vecs(P);
   KrylovScalars* ks = P->ksc;
-  P->hd[60] = (o->fixed_lin > 0) ? 0.0 : o->tol_lin * o->tol_lin;
-  ((int*)(P->hd + 61))[0] = (o->fixed_lin > 0) ? o->fixed_lin : o->max_lin;
-  FG_HIP(hipMemcpyAsync(&ks->tol2, P->hd + 60, sizeof(double), hipMemcpyHostToDevice, P->stream));
-  FG_HIP(hipMemcpyAsync(&ks->maxit, P->hd + 61, sizeof(int), hipMemcpyHostToDevice, P->stream));
+  set_limits(P, ks, P->hd + 60, o);
   const Gate gate = Gate::done(ks);
   const SpecTables<double> tb = P->t64.spec();
   const Grid3 g{P->n0, P->n1, P->n2, 1.0 / P->h[0], 1.0 / P->h[1], 1.0 / P->h[2]};
@@ -1177,16 +1190,17 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
   apply(2, v.r);
   passes(kN0Start, 0);
   check_launch();
+  auto iteration = [&]() {
+    launch_c2r_dir<double>(P->M, dir, 1, P->stream);
+    passes(kN0Cg, apply(op == ScalarOp::FICK ? 1 : 0, v.p));
+    check_launch();
+  };
   int chunk = 4;
   for (int guard = 0; guard < 1000000; ++guard) {
-    for (int k = 0; k < chunk; ++k) {
-      launch_c2r_dir<double>(P->M, dir, 1, P->stream);
-      passes(kN0Cg, apply(op == ScalarOp::FICK ? 1 : 0, v.p));
-      check_launch();
-    }
+    for (int k = 0; k < chunk; ++k) iteration();
     // (without planes the inverse N1 pass has closed the iteration)
     if (P->planes) hipLaunchKernelGGL(k_cg_close, dim3(1), dim3(XBLOCK), 0, P->stream, prr, prz, Parts(dir.np), ks, 1);
-    sync_read(P);
+    sync_read_ahead(P, iteration);
     if (P->hksc[0].done) break;
     chunk = next_chunk(P->hksc[0], 0);
   }
@@ -1349,12 +1363,13 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
   P->lines = P->planes ? fg::lines_per_group(P->n0, P->n1, P->M, P->nitems) : 0;
   P->stream = (hipStream_t)stream;
   P->need = layout(P, nullptr) + kAlign;
-  if (hipHostMalloc((void**)&P->hks, (nitems + 1) * sizeof(KrylovScalars), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&P->hd, (64 + 16 * nitems) * sizeof(double), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&P->hflags, 4 * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&P->hks, P->read_bytes, hipHostMallocDefault) != hipSuccess ||
+      hipEventCreateWithFlags(&P->ev_read, hipEventDisableTiming) != hipSuccess) {
     plan_delete(P);
     return FG_E_HIP;
   }
+  P->hflags = (int*)((char*)P->hks + ((char*)P->flags - (char*)P->ks));
+  P->hd = (double*)((char*)P->hks + ((char*)P->dscal - (char*)P->ks));
   P->hksc = P->hks + nitems;
   *out = P;
   return FG_OK;
@@ -1798,9 +1813,8 @@ void plan_delete(fg_plan* P) {
       (void)hipEventDestroy(e.first);
       (void)hipEventDestroy(e.second);
     }
+  if (P->ev_read) (void)hipEventDestroy(P->ev_read);
   if (P->hks) (void)hipHostFree(P->hks);
-  if (P->hd) (void)hipHostFree(P->hd);
-  if (P->hflags) (void)hipHostFree(P->hflags);
   delete P;
 }
 
