@@ -244,11 +244,11 @@ fg_status fg_apply_operator(fg_plan* plan, const double* x, double* y);
  * precision (x, y: device, 9 N doubles; y may equal x).  Does not sync. */
 fg_status fg_project(fg_plan* plan, const double* x, double* y);
 
-/* The same projection computed as the CG iteration computes it: the N0
- * pass reduces the 9-component spectrum to the 3-component potential
- * U = -i e^{i Phi} (A r) / |r|^2 (Phi = (q0 + q1 + q2) / 2), only U is
- * transformed back, and y = D U with D the corner-difference stencil of the
- * rotated scheme (its symbol is i e^{-i Phi} r).  Double precision; x, y:
+/* The same projection computed as the CG iteration computes it: y = D U,
+ * U = (D^T D)^+ D^T x, with D the corner-difference stencil of the rotated
+ * scheme (its symbol is i e^{-i Phi} r, Phi = (q0 + q1 + q2) / 2): the
+ * divergence D^T x is formed in real space, so only three components are
+ * transformed, there and back.  Double precision; x, y:
  * device, 9 N doubles (y may equal x).  Does not synchronise. */
 fg_status fg_project_grad(fg_plan* plan, const double* x, double* y);
 
@@ -368,8 +368,10 @@ int fg_batch_group_info(const fg_batch* batch, int group, int grid[3], int* nite
 
 /* ---------------------------------------------------------------------
  * Tile widths of the two column passes, for the autotuner: the complex
- * pass along N1 and the N0 pass fused with the projection of eq. (28) work
- * on `tile` adjacent kx columns per workgroup.  Pass index `which`:
+ * pass along N1 and the N0 pass (of the CG, and fused with the
+ * projection of eq. (28) in fg_project) work on `tile` adjacent kx columns
+ * per workgroup.  (The CG of grids whose (N0, N1) plane fits LDS has no such
+ * passes.)  Pass index `which`:
  * 0 = N1 pass FP64, 1 = N0 projection pass FP64, 2 = N1 pass FP32,
  * 3 = N0 projection pass FP32 (the single-precision passes run in FG_MIXED
  * plans).  Valid tiles are powers of two dividing N2/2 with (threads per
@@ -402,18 +404,20 @@ fg_status fg_plan_time_pass(fg_plan* plan, int which, int tile, int reps, double
 
 /* Kernel classes timed by fg_profile_*: */
 enum {
-  FG_PASS_FRONT = 0,        /* CG front: x, p updates, K:p, p.Kp, N2 pass  */
-  FG_PASS_R2C = 1,          /* real-to-complex pass along N2 (residuals)   */
-  FG_PASS_AXIS = 2,         /* complex pass along N1 (forward and inverse) */
-  FG_PASS_ZPROJ = 3,        /* N0 pass fused with the projection           */
+  FG_PASS_FRONT = 0,        /* CG operator q = D^T K : (D pi) and p.Kp; on
+                               small grids with both N2 passes             */
+  FG_PASS_R2C = 1,          /* real-to-complex pass along N2               */
+  FG_PASS_AXIS = 2,         /* forward complex pass along N1               */
+  FG_PASS_ZPROJ = 3,        /* N0 pass with the residual and its symbol
+                               (small planes: with the N1 passes)          */
   FG_PASS_C2R = 4,          /* N2 complex-to-real pass (9 components)      */
   FG_PASS_CG_UPDATE = 5,    /* vector updates of the scalar PCGs           */
-  FG_PASS_FINALIZE = 6,     /* one-block reductions of the Krylov scalars  */
+  FG_PASS_FINALIZE = 6,     /* Krylov scalars before the host reads them   */
   FG_PASS_CONSTITUTIVE = 7, /* stress and tangent state                    */
   FG_PASS_ZSCALAR = 8,      /* N0 pass fused with a scalar symbol          */
-  FG_PASS_AXIS3 = 9,        /* inverse N1 pass of the 3-component potential */
-  FG_PASS_C2R3 = 10,        /* inverse N2 pass of the potential            */
-  FG_PASS_GRAD = 11,        /* residual update rho -= a U and |D rho|^2    */
+  FG_PASS_AXIS3 = 9,        /* inverse N1 pass of z                        */
+  FG_PASS_C2R3 = 10,        /* inverse N2 pass of z with the CG vectors    */
+  FG_PASS_GRAD = 11,        /* no longer taken                             */
   FG_NPASS = 12
 };
 

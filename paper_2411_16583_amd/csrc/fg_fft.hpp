@@ -70,22 +70,6 @@ struct Skip {
   __device__ __forceinline__ bool operator()(long unit) const {
     return gate && gate[(long)item(unit) * stride] != 0;
   }
-  // skip items whose Krylov solve is done
-  static Skip done(const KrylovScalars* ks, long per_item = 1L << 62) {
-    Skip s;
-    s.gate = &ks->stop;
-    s.stride = (int)(sizeof(KrylovScalars) / sizeof(int));
-    s.per_item = per_item;
-    return s;
-  }
-  // skip items with flags[b] != 0
-  static Skip flags(const int* f, long per_item = 1L << 62) {
-    Skip s;
-    s.gate = f;
-    s.stride = 1;
-    s.per_item = per_item;
-    return s;
-  }
   Skip unit(long per) const {
     Skip s = *this;
     s.per_item = per;
@@ -664,36 +648,23 @@ template <typename R> constexpr size_t zpass_extra_lds(int L) {
 // (ky, -ky), transforms along N0, separates
 //   A(k) = (P(k) + conj P(-k)) / 2,   B(k) = (P(k) - conj P(-k)) / (2i),
 // applies the operator at qx = 0 to A and at qx = pi to B, and recombines.
-// OP = 0: projection, one row per workgroup (grid.y = 3 rows per item);
-// OP = 1: scalar symbol (grid.y = 1);
-// OP = 2: projection to the 3-component potential (see k_fft_z_grad3), one
-//         row per workgroup (grid.y = 3 rows per item), U_i into slot 3 i.
-// Components read per row by k_fft_z_dc, one wave per component (the
-// components' loads and transforms run side by side).
-template <int OP> constexpr int z_dc_groups() { return (OP == 1) ? 1 : 3; }
-// LDS of z_dc_body in complex values: an exchange buffer of the column pair
-// per wave and the spectra of the components read.
-template <int L, int OP> constexpr int z_dc_lds() { return z_dc_groups<OP>() * 2 * L * 2; }
-
-// Body of k_fft_z_dc for the column pair (ky0, -ky0) of row `row` (OP 0, 2)
-// with xbuf (NC 2 L) and spec (NC 2 L complex) in LDS; 64 NC threads, wave g
-// reading component g (lanes with t >= T take part in the barriers only).
-template <typename R, int L, int OP>
-__device__ __forceinline__ void z_dc_body(R* data, int N1, int M, const SpecTables<R>& tb, R scale, double a0,
-                                          double a1, int ky0, int row, cplx<R>* xbuf, cplx<R>* spec,
-                                          const cplx<R>* __restrict__ dcb) {
+// One row per workgroup (grid.y = 3 rows per item), one wave per component: the
+// components' loads and transforms run side by side, and wave j writes output j.
+template <typename R, int L>
+__global__ void __launch_bounds__(192)
+k_fft_z_dc(R* data, int N1, int M, SpecTables<R> tb, R scale, Skip skip) {
+  __shared__ cplx<R> lds[12 * L];  // an exchange buffer of the column pair per wave, and the three spectra
+  if (skip(blockIdx.y)) return;
+  const int ky0 = (int)blockIdx.x, row = (int)blockIdx.y;
   using C = cplx<R>;
   using LS = Line<L>;
-  constexpr int NC = z_dc_groups<OP>();    // components read per row
-  constexpr int NOUT = (OP == 0) ? 3 : 1;  // components written per row
   static_assert(2 * LS::T <= 64, "a column pair of lines per wave");
   const int grp = threadIdx.x / 64;
   const int col = threadIdx.x % 2;
   const int t = (threadIdx.x % 64) / 2;
-  // idle lanes (t >= T, and waves beyond the NC components when the body
-  // runs in a larger workgroup) still take part in every barrier below
-  const bool lane_ok = t < LS::T && grp < NC;
-  xbuf += grp * 2 * L;
+  const bool lane_ok = t < LS::T;  // the other lanes take part in the barriers only
+  C* xbuf = lds + grp * 2 * L;
+  C* spec = lds + 6 * L;
   const int ky1 = (N1 - ky0) % N1;
   const int myky = col ? ky1 : ky0;
   const long plane = (long)N1 * M;
@@ -701,20 +672,13 @@ __device__ __forceinline__ void z_dc_body(R* data, int N1, int M, const SpecTabl
   C* base = reinterpret_cast<C*>(data) + (long)myky * M;  // kx = 0
   const bool store = lane_ok && (col == 0 || ky1 != ky0);
   {
-    // first component read and written by this workgroup's row
-    const int cin = (OP == 1) ? 0 : 3 * row;
-    const int cout = cin;
+    const int c0 = 3 * row;
     {
       const int l = grp;
       C v[LS::E];
 #pragma unroll
       for (int e = 0; e < LS::E; ++e) {
-        if (!lane_ok)
-          v[e] = mk<C>(R(0), R(0));
-        else if (dcb)  // the compact copy of the column: contiguous along N0
-          v[e] = dcb[((long)(cin + l) * N1 + myky) * L + LS::idxA(t, e)];
-        else
-          v[e] = base[(cin + l) * comp + LS::idxA(t, e) * plane];
+        v[e] = lane_ok ? base[(c0 + l) * comp + LS::idxA(t, e) * plane] : mk<C>(R(0), R(0));
       }
       if constexpr (LS::R2 == 1) {
         Dft<LS::R1, 1, false, C>::run(v);
@@ -747,79 +711,44 @@ __device__ __forceinline__ void z_dc_body(R* data, int N1, int M, const SpecTabl
         for (int e = 0; e < LS::E; ++e) spec[(l * 2 + col) * L + LS::idxB(t, e)] = v[e];
     }
     __syncthreads();
-    // separate, apply, recombine: thread (t, col) owns kz = idxB(t, e) of its column.
-    // With one output (OP 1, 2) the recombined value goes straight into v1;
-    // the projection (OP 0, three outputs) keeps tA, tB.
-    constexpr int TE = (NOUT == 1) ? 1 : LS::E;
-    C tA[TE], tB[TE], v1[LS::E];
+    // separate, apply, recombine: thread (t, col) owns kz = idxB(t, e) of its column
+    C tA[LS::E], tB[LS::E];
 #pragma unroll
-    for (int e = 0; e < TE; ++e) {
-      tA[e] = mk<C>(R(0), R(0));
-      tB[e] = mk<C>(R(0), R(0));
-    }
-#pragma unroll
-    for (int e = 0; e < LS::E; ++e) v1[e] = mk<C>(R(0), R(0));
+    for (int e = 0; e < LS::E; ++e) tA[e] = tB[e] = mk<C>(R(0), R(0));
     if (lane_ok) {
 #pragma unroll
       for (int e = 0; e < LS::E; ++e) {
         const int kz = LS::idxB(t, e);
         const int kzm = (L - kz) % L;
         C ta = mk<C>(R(0), R(0)), tbv = mk<C>(R(0), R(0));
-        if constexpr (OP != 1) {
-          const RVec<R> rA = rot_vec(tb, kz, myky, 0);
-          const RVec<R> rB = rot_vec(tb, kz, myky, M);
-          for (int l = 0; l < 3; ++l) {
-            const C P = spec[(l * 2 + col) * L + kz];
-            const C Pm = spec[(l * 2 + (1 - col)) * L + kzm];
-            const C A = cscale(cadd(P, cconj(Pm)), R(0.5));
-            const C Bv = cscale(mul_mi(csub(P, cconj(Pm))), R(0.5));
-            const R ra = rget(rA, l), rb = rget(rB, l);
-            ta = mk<C>(ta.x + A.x * ra, ta.y + A.y * ra);
-            tbv = mk<C>(tbv.x + Bv.x * rb, tbv.y + Bv.y * rb);
-          }
-          const R a2 = rA.x * rA.x + rA.y * rA.y + rA.z * rA.z;
-          const R b2 = rB.x * rB.x + rB.y * rB.y + rB.z * rB.z;
-          ta = cscale(ta, a2 > R(0) ? scale / a2 : R(0));
-          tbv = cscale(tbv, b2 > R(0) ? scale / b2 : R(0));
-        } else {
-          const C P = spec[col * L + kz];
-          const C Pm = spec[(1 - col) * L + kzm];
+        const RVec<R> rA = rot_vec(tb, kz, myky, 0);
+        const RVec<R> rB = rot_vec(tb, kz, myky, M);
+        for (int l = 0; l < 3; ++l) {
+          const C P = spec[(l * 2 + col) * L + kz];
+          const C Pm = spec[(l * 2 + (1 - col)) * L + kzm];
           const C A = cscale(cadd(P, cconj(Pm)), R(0.5));
           const C Bv = cscale(mul_mi(csub(P, cconj(Pm))), R(0.5));
-          const double dA = a0 + a1 * (double)lap_sym(tb, kz, myky, 0);
-          const double dB = a0 + a1 * (double)lap_sym(tb, kz, myky, M);
-          ta = cscale(A, (R)((double)scale / dA));
-          tbv = cscale(Bv, (R)((double)scale / dB));
+          const R ra = rget(rA, l), rb = rget(rB, l);
+          ta = mk<C>(ta.x + A.x * ra, ta.y + A.y * ra);
+          tbv = mk<C>(tbv.x + Bv.x * rb, tbv.y + Bv.y * rb);
         }
-        if constexpr (OP == 2) {
-          // potential U = -i e^{i Phi} w: at qx = 0, U_A = -i e^{i Phi_A} tA;
-          // at qx = pi, e^{i Phi_B} = i e^{i Phi_A}, so U_B = e^{i Phi_A} tB;
-          // packed as U_A + i U_B
-          const C ph = cmul(mk<C>(tb.cz[kz], tb.snz[kz]), mk<C>(tb.cy[myky], tb.sny[myky]));  // e^{i Phi_A}
-          v1[e] = cadd(mul_mi(cmul(ta, ph)), mul_pi(cmul(tbv, ph)));
-        } else if constexpr (OP == 1) {
-          v1[e] = cadd(ta, mul_pi(tbv));
-        } else {
-          tA[e] = ta;
-          tB[e] = tbv;
-        }
+        const R a2 = rA.x * rA.x + rA.y * rA.y + rA.z * rA.z;
+        const R b2 = rB.x * rB.x + rB.y * rB.y + rB.z * rB.z;
+        ta = cscale(ta, a2 > R(0) ? scale / a2 : R(0));
+        tbv = cscale(tbv, b2 > R(0) ? scale / b2 : R(0));
+        tA[e] = ta;
+        tB[e] = tbv;
       }
     }
     {
-      // OP 0: wave j writes output j; OP 1, 2: every wave forms the one
-      // output (in its own exchange buffer), wave 0 stores it
-      const int j = (NOUT == 1) ? 0 : grp;
+      const int j = grp;
       C v[LS::E];
 #pragma unroll
       for (int e = 0; e < LS::E; ++e) {
-        if constexpr (OP == 0) {
-          const int kz = LS::idxB(t, e);
-          const C a = cscale(tA[e], rget(rot_vec(tb, kz, myky, 0), j));
-          const C b = cscale(tB[e], rget(rot_vec(tb, kz, myky, M), j));
-          v[e] = cadd(a, mul_pi(b));  // A' + i B'
-        } else {
-          v[e] = v1[e];
-        }
+        const int kz = LS::idxB(t, e);
+        const C a = cscale(tA[e], rget(rot_vec(tb, kz, myky, 0), j));
+        const C b = cscale(tB[e], rget(rot_vec(tb, kz, myky, M), j));
+        v[e] = cadd(a, mul_pi(b));  // A' + i B'
       }
       if constexpr (LS::R2 == 1) {
         Dft<LS::R1, 1, true, C>::run(v);
@@ -846,20 +775,11 @@ __device__ __forceinline__ void z_dc_body(R* data, int N1, int M, const SpecTabl
         }
         __syncthreads();
       }
-      if (store && (NOUT > 1 || grp == 0))
+      if (store)
 #pragma unroll
-        for (int e = 0; e < LS::E; ++e) base[(cout + j) * comp + LS::idxA(t, e) * plane] = v[e];
+        for (int e = 0; e < LS::E; ++e) base[(c0 + j) * comp + LS::idxA(t, e) * plane] = v[e];
     }
   }
-}
-
-template <typename R, int L, int OP>
-__global__ void __launch_bounds__(64 * z_dc_groups<OP>())
-k_fft_z_dc(R* data, int N1, int M, SpecTables<R> tb, R scale, double a0, double a1, Skip skip, const R* dcb) {
-  __shared__ cplx<R> lds[z_dc_lds<L, OP>()];
-  if (skip(blockIdx.y)) return;
-  z_dc_body<R, L, OP>(data, N1, M, tb, scale, a0, a1, (int)blockIdx.x, (int)blockIdx.y, lds,
-                      lds + z_dc_groups<OP>() * 2 * L, reinterpret_cast<const cplx<R>*>(dcb));
 }
 
 }  // namespace fg

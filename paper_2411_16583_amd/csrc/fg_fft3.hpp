@@ -1,7 +1,7 @@
 // Three-stage line FFT (L = R1 R2 R3) with more threads per line and fewer
-// elements per thread than the two-stage version; used by the N0 pass fused
-// with the projection, whose per-thread accumulator would otherwise double
-// the register footprint.
+// elements per thread than the two-stage version; used by the N0 passes and
+// the long lines of k_plane, which hold a residual or an accumulator beside
+// the line.
 //
 // Forward, with Q = R2 R3:
 //   stage 1: butterfly b in [0, Q):        x[b + Q n1]            -> Y1[b][k1]  * W_L^{b k1}

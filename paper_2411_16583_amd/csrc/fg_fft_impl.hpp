@@ -115,8 +115,7 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
   case L_:                                                                                             \
     hipLaunchKernelGGL((k_fft_z_proj<R, L_>), grid, dim3(T * B), shm, s, data, N1, M, B, tb, scale, skip, \
                        kymajor);                                                                       \
-    hipLaunchKernelGGL((k_fft_z_dc<R, L_, 0>), gdc, dim3(64 * z_dc_groups<0>()), 0, s, data, N1, M, tb, scale, \
-                       0.0, 0.0, skip, (const R*)nullptr);                                            \
+    hipLaunchKernelGGL((k_fft_z_dc<R, L_>), gdc, dim3(192), 0, s, data, N1, M, tb, scale, skip);       \
     return;
     FG_FOR_AXIS(FG_CASE)
 #undef FG_CASE

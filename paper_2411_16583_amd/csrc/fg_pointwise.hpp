@@ -339,13 +339,6 @@ k_cg_close(const double* __restrict__ prr, const double* __restrict__ prz, Parts
   krylov_close(ks + blockIdx.x, prr + o, prz ? prz + o : nullptr, parts, few != 0, buf);
 }
 
-// F += x (F FP64, x in the CG precision), n = 9N.
-template <typename T>
-__global__ void __launch_bounds__(256) k_axpy_into_f64(double* __restrict__ F, const T* __restrict__ x, long n) {
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) F[i] += (double)x[i];
-}
-
 // a -= b (double precision), n values.
 __global__ void __launch_bounds__(256) k_sub_f64(double* __restrict__ a, const double* __restrict__ b, long n) {
   const long stride = (long)gridDim.x * blockDim.x;
