@@ -342,9 +342,11 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   a.groups = nc * a.M / a.P;
   a.dn1 = FastDiv(a.n1);
   const dim3 grid((unsigned)(a.groups * nitems));
-  // a thread per line task where 512 threads are enough
+  // a thread per line task where the bound allows
   const int tasks = a.P * std::max(a.n0 * plane_line_threads(a.n1), a.n1 * plane_line_threads(a.n0));
-  const dim3 block((unsigned)std::min(512, (tasks + 63) / 64 * 64));
+  // (see the kernel's launch bounds)
+  const bool shared = sizeof(R) == 4 && a.groups * nitems > 256;
+  const dim3 block((unsigned)std::min(sizeof(R) == 8 || shared ? 512 : 768, (tasks + 63) / 64 * 64));
   const unsigned shm = (unsigned)plane_lds<R>(a.n0, a.n1, a.P);
   auto go = [&](auto kernel) {
     if (shm > 65536) {
@@ -356,23 +358,31 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
     launch_ev(kernel, grid, block, shm, s, ev0, ev1, a);
   };
   constexpr bool kSame = sizeof(R) == sizeof(RO);
+  constexpr int TH = 512;
   if (sym == kSymLap) {
     if constexpr (sizeof(R) == 8 && kSame) {
       if (mode == kN0Cg)
-        go(k_plane<R, RO, kN0Cg, kSymLap>);
+        go(k_plane<R, RO, kN0Cg, kSymLap, TH>);
       else
-        go(k_plane<R, RO, kN0Start, kSymLap>);
+        go(k_plane<R, RO, kN0Start, kSymLap, TH>);
     }
   } else if (mode == kN0Cg) {
-    if constexpr (kSame) go(k_plane<R, RO, kN0Cg, kSymProj>);
+    if constexpr (kSame && sizeof(R) == 4) {
+      if (shared)
+        go(k_plane<R, RO, kN0Cg, kSymProj, 1024>);
+      else
+        go(k_plane<R, RO, kN0Cg, kSymProj, 768>);
+    } else if constexpr (kSame) {
+      go(k_plane<R, RO, kN0Cg, kSymProj, TH>);
+    }
   } else if constexpr (sizeof(R) == 8) {
     if (mode == kN0Start) {
-      go(k_plane<R, RO, kN0Start, kSymProj>);
+      go(k_plane<R, RO, kN0Start, kSymProj, TH>);
     } else if constexpr (kSame) {
       if (mode == kN0Norm)
-        go(k_plane<R, RO, kN0Norm, kSymProj>);
+        go(k_plane<R, RO, kN0Norm, kSymProj, TH>);
       else
-        go(k_plane<R, RO, kN0Apply, kSymProj>);
+        go(k_plane<R, RO, kN0Apply, kSymProj, TH>);
     }
   }
   return Parts(a.groups);

@@ -186,8 +186,14 @@ __device__ __forceinline__ void plane_cols_inv(C* x, int LD, int n1, FastDiv dn1
   }
 }
 
-template <typename R, typename RO, int MODE, int SYM>
-__global__ void __launch_bounds__(512) k_plane(PlaneArgs<R, RO> a) {
+// TH bounds the registers: 512 threads (256 registers) in double precision;
+// single precision takes a thread per line task up to 768, or, where there are
+// more workgroups than CUs, at most 512 of a build with 128 registers, so that
+// two workgroups share a CU instead of a second round with few of them.
+// (FP32, 512-thread build / chosen, us: 96^3 30.3 / 27.5, 24 x 256 x 64 20.6 /
+// 19.5, 48 x 96 x 192 29.0 / 24.1.)
+template <typename R, typename RO, int MODE, int SYM, int TH>
+__global__ void __launch_bounds__(TH) k_plane(PlaneArgs<R, RO> a) {
   using C = cplx<R>;
   using CO = cplx<RO>;
   extern __shared__ __align__(16) char smem_raw[];

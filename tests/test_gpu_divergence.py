@@ -106,8 +106,10 @@ def test_cg_ends_alike_wherever_its_scalars_are_read(shape, precision):
 
 
 # the largest grid whose iteration runs as lines (32^3 voxels, 64-long lines) and
-# the first ones that take the passes; odd counts of lines and blocks of lines
-LINES = [(32, 32, 32), (32, 32, 48), (1, 12, 64), (4, 6, 64), (24, 4, 64), (64, 96, 6), (48, 48, 24), (6, 96, 96)]
+# the first ones that take the passes; odd counts of lines and blocks of lines;
+# more planes than CUs
+LINES = [(32, 32, 32), (32, 32, 48), (1, 12, 64), (4, 6, 64), (24, 4, 64), (64, 96, 6), (48, 48, 24), (6, 96, 96),
+         (8, 12, 192)]
 
 
 @pytest.mark.parametrize("law", ["neo_hookean", "svk"])
