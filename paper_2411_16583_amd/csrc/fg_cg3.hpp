@@ -11,15 +11,20 @@
 // components through the transforms instead of nine, and with the residual
 // kept where it is needed, in the spectrum (s^ is read and written by the N0
 // pass; no real-space residual update).  Passes of one iteration (words per
-// voxel, 64 in all):
-//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     15
-//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6
-//   k_r2c_edges  N2 pass of q                                                6.6
-//   k_n1         N1 pass into the block layout (+ alpha)                     6
-//   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12
-//   k_n1         inverse N1 pass                                             6
-// (the iteration that carried nine components through the N2 and N1 passes
-// and the residual in real space moved 81).
+// voxel, 64 in all; us at 256^3 in double / single precision):
+//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     15    366 / 186
+//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6  557 / 263
+//   k_r2c_edges  N2 pass of q                                                6.6  153 /  91
+//   k_n1         N1 pass into the block layout (+ alpha)                     6    148 /  77
+//   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12    295 / 156
+//   k_n1         inverse N1 pass (+ beta, the end of the solve)              6    175 /  78
+// 4.9-5.8 TB/s where a plain copy reaches 4.4: bound by HBM.  The iteration
+// that carried nine components through the N2 and N1 passes and the residual
+// in real space moved 81 words: 2180 / 1040 us against 1710 / 860.
+//
+// On small grids the passes are bound by launches and memory latency: k_plane
+// (fg_plane.hpp) takes the N1 and N0 passes in one, k_cg_lines
+// (fg_cg_lines.hpp) the rest.
 #pragma once
 #include "fg_fft.hpp"
 #include "fg_fft3.hpp"
@@ -390,8 +395,9 @@ template <typename C, int M> struct TwiddleRegs {
 };
 
 // N2 transform of the 3-component fields q of k_cg_op with the patch edges
-// added on load, into the line layout or (planes) the plane layout.  grid: line blocks of 3 N0 N1 lines per item, blockIdx.y =
-// item.
+// added on load, into the line layout or (planes) the plane layout.  grid: line
+// blocks of 3 N0 N1 lines per item, blockIdx.y = item.  Every load is issued
+// before the first wait (256^3 FP64 167 -> 153 us, 64^3 8.4 -> 7.0).
 template <typename R, int M>
 __global__ void __launch_bounds__(XBLOCK)
 k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, cplx<R>* __restrict__ out, int n0,

@@ -8,6 +8,8 @@
 // planes of L + 1 lines, and transforms its 3 L lines of q, with nothing but
 // LDS in between.  The neighbours' lines are transformed again by their own
 // workgroups, so pi is kept in two buffers (iteration k writes buffer k mod 2).
+// Bound by latency, a launch and half a dozen dependent waits: 16^3 FP64 11.6 us
+// where the three passes took 8.0 + 5.6 + 6.3 and two more launches.
 #pragma once
 #include "fg_cg3.hpp"
 

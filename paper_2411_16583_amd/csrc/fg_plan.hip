@@ -887,6 +887,8 @@ void cg_solve(fg_plan* P, const fg_solver_opts* o, fg_stats* stats) {
   }
   // Both precisions report a breakdown (p.Ap <= 0) and the iteration cap:
   // a correction from an indefinite or unconverged solve is not handed on.
+  // (nothing is left queued behind a call that fails)
+  if (h.flag != 0) FG_HIP(hipStreamSynchronize(P->stream));
   if (h.flag == 1) throw Status(FG_E_BREAKDOWN, "CG breakdown: p.Ap <= 0");
   if (h.flag == 2) throw Status(FG_E_NOCONV, "CG reached max_lin iterations");
 }
@@ -1210,6 +1212,7 @@ void scalar_pcg(fg_plan* P, ScalarOp op, double a0, double a1, double dt, const 
     stats->lin_relres = h.rr0 > 0 ? std::sqrt(h.rr / h.rr0) : 0.0;
     stats->lin_iters_total += h.iter;
   }
+  if (h.flag != 0) FG_HIP(hipStreamSynchronize(P->stream));
   if (h.flag == 1) throw Status(FG_E_BREAKDOWN, "PCG breakdown: p.Ap <= 0");
   if (h.flag == 2) throw Status(FG_E_NOCONV, "PCG reached max_lin iterations");
 }

@@ -11,6 +11,11 @@
 // plane; the plane passes through LDS only between the N1 and N0 lines, with
 // one workgroup barrier there and one on the way back.  The residual is kept
 // in the order (kz, ky), read ahead of the N0 transform.
+//
+// Bound by its chain of LDS passes and barriers, with one plane per workgroup
+// on 96 (64^3) to 144 (96^3) of 256 CUs: 16.3 and 39 us in double precision.
+// The iteration with the three passes instead took 59.5 / 121 us, with this
+// 54.0 / 113.
 #pragma once
 #include "fg_cg3.hpp"
 
