@@ -49,7 +49,9 @@ WORDS_MOVED = {
     "axis": 6,        # N1 pass: read 3, write 3
     "zproj": 12,      # N0 pass: read q (3) + residual (3), write residual (3) + z (3)
     "axis3": 6,       # inverse N1 pass: read 3, write 3
-    "c2r3": 15,       # inverse N2 pass and CG vectors: read z (3) + pi (3) + xi (3), write pi (3) + xi (3)
+    # inverse N2 pass and CG vectors: read z (3) + pi (3), write pi (3); every second
+    # iteration read pi (3) and xi (3) more and write xi (3)
+    "c2r3": 13.5,
 }
 # The iteration that carried nine components through the N2 and N1 passes and
 # the residual in real space (81 words): the model of profiles that name no

@@ -11,16 +11,16 @@
 // components through the transforms instead of nine, and with the residual
 // kept where it is needed, in the spectrum (s^ is read and written by the N0
 // pass; no real-space residual update).  Passes of one iteration (words per
-// voxel, 64 in all; us at 256^3 in double / single precision):
-//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     15    366 / 186
-//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6  557 / 263
+// voxel, 63 in all; us at 256^3 in double / single precision):
+//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     13.5  344 / 180
+//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6  537 / 252
 //   k_r2c_edges  N2 pass of q                                                6.6  153 /  91
 //   k_n1         N1 pass into the block layout (+ alpha)                     6    148 /  77
 //   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12    295 / 156
 //   k_n1         inverse N1 pass (+ beta, the end of the solve)              6    175 /  78
 // 4.9-5.8 TB/s where a plain copy reaches 4.4: bound by HBM.  The iteration
 // that carried nine components through the N2 and N1 passes and the residual
-// in real space moved 81 words: 2180 / 1040 us against 1710 / 860.
+// in real space moved 81 words: 2180 / 1040 us against 1660 / 840.
 //
 // On small grids the passes are bound by launches and memory latency: k_plane
 // (fg_plane.hpp) takes the N1 and N0 passes in one, k_cg_lines
@@ -130,7 +130,9 @@ template <typename R> inline EdgeLayout edge_layout(int n0, int n1, int n2) {
 template <typename R> struct OpArgs {
   R* q;                // out: 3 N per item
   R* edge;             // out: 3 el.comp per item
-  const R* pi;         // direction potential, 3 N per item (unused by kSrcField)
+  const R* pi;         // direction potential, 3 N per item (unused by kSrcField):
+  long pi2;            // the running iteration's of two buffers pi2 values apart
+  const KrylovScalars* ks;
   const R* st;         // tangent state, or the 9-component field
   double* partials;    // p.Kp per workgroup (unused by kSrcField)
   Gate gate;
@@ -172,6 +174,7 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   const bool active = live && i1 < a.n1 && x < a.n2;
   const long N = (long)a.n0 * a.n1 * a.n2;
   const R* pi = a.pi + (long)item * 3 * N;
+  if constexpr (SRC != kSrcField) pi += (a.ks[item].run_iter & 1) * a.pi2;
   const R* st = a.st + (long)item * (SRC == kSrcField ? 9 : state_words(SRC)) * N;
   R* q = a.q + (long)item * 3 * N;
   R* edge = a.edge + (long)item * 3 * a.el.comp;
@@ -935,9 +938,17 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Inverse N2 pass of z fused with the CG vectors, per line of a component:
-//   xi += alpha_{k-1} pi_{k-1},  pi_k = z + beta pi_{k-1}   (k > 0),
-//   xi = 0,  pi_0 = z                                       (k = 0).
+// Inverse N2 pass of z fused with the CG vectors, per line of a component, in
+// iteration k:
+//   pi_k = z + beta pi_{k-1}  (pi_0 = z), into buffer k mod 2,
+//   xi += alpha_{k-2} pi_{k-2} + alpha_{k-1} pi_{k-1}  for even k > 0 (xi
+//   starts at 0): both steps in one pass over xi, 13.5 words per voxel on
+//   average where a step in every iteration took 15.
+// Without TWO (small grids, whose vectors stay in the last-level cache, and the
+// scalar problems): one buffer, and
+//   xi += alpha_{k-1} pi_{k-1}  (k > 0),  xi = 0  (k = 0).
+// 256^3 iteration with / without TWO: 1653 / 1710 us FP64, 835 / 861 FP32; but
+// 48 x 96 x 192 FP32 17.7 / 15.7 us of this pass, 96^3 FP64 20.2 / 19.2.
 // grid: line blocks of the item's lines (nlines per component), blockIdx.y =
 // item; in: line or (planes) plane layout.  Without ks: z alone, into pi.
 //
@@ -949,6 +960,7 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
 template <typename R> struct DirArgs {
   const cplx<R>* in;
   cplx<R>*pi, *xi;
+  long pi2;  // distance of the second buffer of pi, or 0
   int nlines, nc, planes;
   SpecTables<R> tb;
   KrylovScalars* ks;
@@ -956,7 +968,7 @@ template <typename R> struct DirArgs {
   int np;
 };
 
-template <typename R, int M>
+template <typename R, int M, bool TWO>
 __global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
   using C = cplx<R>;
   using LS = Line<M>;
@@ -967,8 +979,13 @@ __global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
   __shared__ double red[16];
   const int item = blockIdx.y, nlines = a.nlines, planes = a.planes;
   const C* __restrict__ in = a.in;
-  C *pi = a.pi, *xi = a.xi;
   KrylovScalars* ks = a.ks ? a.ks + item : nullptr;
+  const int k = ks ? ks->iter + (a.prr && !ks->fresh ? 1 : 0) : 0;  // this iteration
+  const bool first = k == 0;
+  const bool step = TWO ? (k & 1) == 0 && k > 0 : true;    // xi is taken on
+  C* pi = a.pi + (TWO ? (k & 1) * a.pi2 : 0);              // pi_k (and pi_{k-2} before)
+  const C* p1 = a.pi + (TWO ? ((k + 1) & 1) * a.pi2 : 0);  // pi_{k-1}
+  C* xi = a.xi;
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
   const int all = a.nc * nlines;  // lines of the item
@@ -1000,16 +1017,26 @@ __global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
   // the vectors are read with the spectrum where the registers allow it (one
   // memory latency instead of two: what the pass costs on small grids)
   constexpr bool kAhead = LS::E * sizeof(C) <= 192;
-  C po[LS::E], xo[LS::E];
-  auto vectors = [&]() {
+  constexpr int NV = kAhead ? LS::E : (LS::E % 8 == 0 ? 8 : LS::E);  // elements read together
+  C po[NV], qo[TWO ? NV : 1], xo[NV];
+  auto vectors = [&](int e0) {
 #pragma unroll
-    for (int e = 0; e < LS::E; ++e) {
-      po[e] = pi[base + LS::idxB(t, e)];
-      xo[e] = xi[base + LS::idxB(t, e)];
+    for (int e = 0; e < NV; ++e) {
+      const long n = base + LS::idxB(t, e0 + e);
+      po[e] = p1[n];
+      if constexpr (TWO) {
+        qo[e] = xo[e] = mk<C>(R(0), R(0));
+        if (step) {
+          qo[e] = pi[n];
+          if (k != 2) xo[e] = xi[n];  // (it starts there)
+        }
+      } else {
+        xo[e] = xi[n];
+      }
     }
   };
   if constexpr (kAhead) {
-    if (ks && active) vectors();  // (not used by the first iteration)
+    if ((TWO ? !first : ks != nullptr) && active) vectors(0);  // (not used by the first iteration)
   }
   double rr = 0.0, rz = 0.0;
   if (a.prr) rr = thread_partials(a.prr + (long)item * a.np, a.np);
@@ -1018,10 +1045,10 @@ __global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
   tw.store(stw, spost);
   if (ks && ks->done) return;  // (read with the data, not before it)
   const bool pending = ks && a.prr && !ks->fresh;
-  const bool first = !ks || (!pending && ks->iter == 0);
-  R alpha = R(0), beta = R(0);
+  R alpha = R(0), alpha1 = R(0), beta = R(0);
   if (!first) {
     alpha = (R)ks->alpha;
+    if (TWO) alpha1 = (R)ks->alpha1;
     beta = (R)ks->beta;
   }
   if (pending) {
@@ -1072,16 +1099,23 @@ __global__ void __launch_bounds__(XBLOCK) k_c2r_dir(DirArgs<R> a) {
     for (int e = 0; e < LS::E; ++e) {
       const long n = base + LS::idxB(t, e);
       pi[n] = v[e];
-      if (xi) xi[n] = mk<C>(R(0), R(0));
+      if (xi && !TWO) xi[n] = mk<C>(R(0), R(0));
     }
-  } else {
-    if constexpr (!kAhead) vectors();
+    return;
+  }
 #pragma unroll
-    for (int e = 0; e < LS::E; ++e) {
-      const long n = base + LS::idxB(t, e);
-      const C p = po[e], x = xo[e];
-      xi[n] = mk<C>(x.x + alpha * p.x, x.y + alpha * p.y);
-      pi[n] = mk<C>(v[e].x + beta * p.x, v[e].y + beta * p.y);
+  for (int e0 = 0; e0 < LS::E; e0 += NV) {
+    if constexpr (!kAhead) vectors(e0);
+#pragma unroll
+    for (int e = 0; e < NV; ++e) {
+      const long n = base + LS::idxB(t, e0 + e);
+      const C p = po[e], z = v[e0 + e];
+      if (step) {
+        C x = xo[e];
+        if constexpr (TWO) x = mk<C>(x.x + alpha1 * qo[e].x, x.y + alpha1 * qo[e].y);
+        xi[n] = mk<C>(x.x + alpha * p.x, x.y + alpha * p.y);
+      }
+      pi[n] = mk<C>(z.x + beta * p.x, z.y + beta * p.y);
     }
   }
 }

@@ -56,22 +56,29 @@ k_grad_store(const TI* __restrict__ U, long ucs, long uis, TO* __restrict__ Z, l
 // alpha pi is left out after a breakdown (the direction pass had already
 // applied the last valid one); a solve that never iterated has x = 0.
 // xi, pi: 3 N values per item (pi2: distance of the buffer that odd iterations
-// write, or 0); Z: 9 N.
+// write); pairs: xi takes its steps two at a time.  Z: 9 N.
 template <typename T, bool ADD>
 __global__ void __launch_bounds__(256)
-k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, long pi2, const KrylovScalars* __restrict__ ksb,
+k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, long pi2, int pairs,
+            const KrylovScalars* __restrict__ ksb,
             double* __restrict__ Z, const int* __restrict__ idle, int n0, int n1, int n2, double q0, double q1,
             double q2) {
   const int item = blockIdx.y;
   if (idle && idle[item]) return;
   const KrylovScalars* ks = ksb + item;
-  const bool none = ks->iter == 0;
+  // n steps; the direction pass of iteration `run` was the last, and xi has the
+  // steps before `have` (every step before its own, or, two at a time, before
+  // the last even iteration)
+  const int n = ks->iter, run = ks->flag == 1 ? n : n - 1, have = pairs ? run & ~1 : run;
+  const bool none = n == 0;
   if (ADD && none) return;
-  const bool last = ks->flag != 1;
-  const T alpha = (T)ks->alpha;
+  const int left = n - have;  // steps still to be taken: 0, 1 or (pairs) 2
+  const bool empty = pairs && have == 0;
+  const T alpha = (T)ks->alpha, alpha1 = (T)ks->alpha1;
   const long N = (long)n0 * n1 * n2;
   xi += (long)item * 3 * N;
-  pi += (long)item * 3 * N + (none ? 0 : (ks->iter - 1) & 1) * pi2;
+  pi += (long)item * 3 * N;
+  const T *pl = pi + ((n + 1) & 1) * pi2, *pb = pi + (n & 1) * pi2;  // pi_{n-1}, pi_{n-2}
   Z += (long)item * 9 * N;
   const int G = n2 / 2;
   const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -82,15 +89,25 @@ k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, long pi2, const 
   for (int c = 0; c < 3; ++c) {
     double u[2][2][3] = {};
     if (!none) {
-      T x[2][2][3], p[2][2][3];
-      load_corners<T, 2>(xi + c * N, sl, x);
-      if (last) load_corners<T, 2>(pi + c * N, sl, p);
+      T x[2][2][3] = {}, p[2][2][3];
+      if (!empty) load_corners<T, 2>(xi + c * N, sl, x);
+      auto add = [&](const T* f, T al) {
+        load_corners<T, 2>(f + c * N, sl, p);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) x[a][b][q] = x[a][b][q] + al * p[a][b][q];
+      };
+      if (left == 2) add(pb, alpha1);
+      if (left >= 1) add(pl, alpha);
 #pragma unroll
       for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int q = 0; q < 3; ++q) u[a][b][q] = (double)(last ? (T)(x[a][b][q] + alpha * p[a][b][q]) : x[a][b][q]);
+          for (int q = 0; q < 3; ++q) u[a][b][q] = (double)x[a][b][q];
     }
     double D[3][2];
     corner_grad<double, 2>(u, q0, q1, q2, D);
@@ -119,11 +136,11 @@ void launch_grad_store(const TI* U, long ucs, long uis, TO* Z, long zis, const i
 }
 
 template <typename T, bool ADD>
-void launch_cg_result(const T* xi, const T* pi, long pi2, const KrylovScalars* ks, double* Z, const int* idle, int n0, int n1,
+void launch_cg_result(const T* xi, const T* pi, long pi2, int pairs, const KrylovScalars* ks, double* Z, const int* idle, int n0, int n1,
                       int n2, int nitems, const double h[3], hipStream_t s) {
   const long N = (long)n0 * n1 * n2;
   hipLaunchKernelGGL((k_cg_result<T, ADD>), dim3((unsigned)((N / 2 + 255) / 256), (unsigned)nitems), dim3(256), 0, s, xi,
-                     pi, pi2, ks, Z, idle, n0, n1, n2, 0.25 / h[0], 0.25 / h[1], 0.25 / h[2]);
+                     pi, pi2, pairs, ks, Z, idle, n0, n1, n2, 0.25 / h[0], 0.25 / h[1], 0.25 / h[2]);
 }
 
 }  // namespace fg

@@ -30,6 +30,7 @@ struct KrylovScalars {
   double rz;     // r.z (preconditioned solves)
   double pAp;
   double alpha;
+  double alpha1;  // of the iteration before
   double beta;
   double tol2;   // tol^2 (0: run to maxit)
   int iter;
@@ -345,6 +346,7 @@ __device__ __forceinline__ void krylov_alpha(KrylovScalars* ks, double s, int pc
     ks->flag = 1;
     ks->publish();
   } else {
+    ks->alpha1 = ks->alpha;
     ks->alpha = (pcg ? ks->rz : ks->rr) / s;
   }
 }

@@ -124,7 +124,8 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
 }
 
 template <typename R>
-int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* partials, const Gate& gate, int n0, int n1,
+int launch_cg_op(int src, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
+                 const Gate& gate, int n0, int n1,
                  int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   OpArgs<R> a;
   a.el = edge_layout<R>(n0, n1, n2);
@@ -132,6 +133,8 @@ int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* parti
   a.q = q;
   a.edge = edge;
   a.pi = pi;
+  a.pi2 = pi2;
+  a.ks = ks;
   a.st = st;
   a.partials = partials;
   a.gate = gate;
@@ -305,7 +308,10 @@ void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEv
   case L_: {                                                                                                     \
     constexpr int LPB = XBLOCK / Line<L_>::T;                                                                    \
     const dim3 grid((unsigned)((a.nc * a.nlines + LPB - 1) / LPB), (unsigned)nitems);                            \
-    launch_ev((k_c2r_dir<R, L_>), grid, dim3(XBLOCK), 0, s, ev0, ev1, a);                                        \
+    if (a.pi2 != 0)                                                                                              \
+      launch_ev((k_c2r_dir<R, L_, true>), grid, dim3(XBLOCK), 0, s, ev0, ev1, a);                                \
+    else                                                                                                         \
+      launch_ev((k_c2r_dir<R, L_, false>), grid, dim3(XBLOCK), 0, s, ev0, ev1, a);                               \
     return;                                                                                                      \
   }
     FG_FOR_M(FG_CASE)
@@ -389,7 +395,7 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
 }
 
 #define FG_INSTANTIATE_LAUNCHERS(R)                                                                     \
-  template int launch_cg_op<R>(int, R*, R*, const R*, const R*, double*, const Gate&, int, int, int, const double*, \
+  template int launch_cg_op<R>(int, R*, R*, const R*, long, const KrylovScalars*, const R*, double*, const Gate&, int, int, int, const double*, \
                                int, hipStream_t, hipEvent_t, hipEvent_t);                               \
   template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
                                     int, hipStream_t, hipEvent_t, hipEvent_t);                          \

@@ -56,7 +56,8 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems);
 // fields st (src = kSrcField), as k_cg_op leaves it (q and its patch edges);
 // h: grid spacings.  Returns the number of partial sums of p.Kp per item.
 template <typename R>
-int launch_cg_op(int src, R* q, R* edge, const R* pi, const R* st, double* partials, const Gate& gate, int n0, int n1,
+int launch_cg_op(int src, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
+                 const Gate& gate, int n0, int n1,
                  int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);
 // N2 transform of q with its patch edges added.

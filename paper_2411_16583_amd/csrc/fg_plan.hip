@@ -587,6 +587,9 @@ template <typename R, typename RO> PlaneArgs<R, RO> plane_args(fg_plan* P, const
   return a;
 }
 
+// Distance of the second buffer of the CG's direction potential (0: one buffer).
+long second_pi(const fg_plan* P) { return P->lines || !P->planes ? 3 * P->N * P->nitems : 0; }
+
 // Partial sums of r.r that the N0 pass of a CG of nc components leaves in part2.
 template <typename T> Parts rr_parts(fg_plan* P, int nc, int nitems) {
   if (P->planes) return Parts(nc * P->M / planes_per_group(P->n0, P->n1, P->M, nc, nitems));
@@ -601,6 +604,7 @@ DirArgs<R> dir_args(fg_plan* P, const void* in, void* pi, void* xi, KrylovScalar
   a.in = (const cplx<R>*)in;
   a.pi = (cplx<R>*)pi;
   a.xi = (cplx<R>*)xi;
+  if (ks && !pcg) a.pi2 = second_pi(P) / 2;  // in pairs of reals
   a.nlines = P->n0 * P->n1;
   a.nc = nc;
   a.planes = P->planes;
@@ -638,7 +642,7 @@ void divergence64(fg_plan* P, const double* Y, const Gate& gate) {
   const SpecTables<double> tb = P->t64.spec();
   {
     ProfScope ps(P, FG_PASS_R2C);
-    launch_cg_op<double>(kSrcField, P->q64, P->qe64, nullptr, Y, nullptr, gate, P->n0, P->n1, P->n2, P->h, P->nitems,
+    launch_cg_op<double>(kSrcField, P->q64, P->qe64, nullptr, 0, nullptr, Y, nullptr, gate, P->n0, P->n1, P->n2, P->h, P->nitems,
                          P->stream);
     launch_r2c_edges<double>(P->M, P->q64, P->qe64, P->ln64, gate, P->n0, P->n1, tb, P->nitems, P->planes, P->stream);
   }
@@ -746,7 +750,7 @@ template <typename T> int cg_front_passes(fg_plan* P) {
   int nbf;
   {
     ProfScope ps(P, FG_PASS_FRONT, true);
-    nbf = launch_cg_op<T>(P->law, (T*)P->q, (T*)P->qe, (const T*)P->p, (const T*)P->st, P->part, gate, P->n0, P->n1,
+    nbf = launch_cg_op<T>(P->law, (T*)P->q, (T*)P->qe, (const T*)P->p, second_pi(P), ks, (const T*)P->st, P->part, gate, P->n0, P->n1,
                           P->n2, P->h, nit, P->stream, ps.start, ps.stop);
   }
   {
@@ -763,7 +767,7 @@ template <typename T> int cg_front_lines(fg_plan* P) {
   a.z = (const cplx<T>*)P->ln;
   a.q = (cplx<T>*)P->q;
   a.pi = (T*)P->p;
-  a.pi2 = 3 * P->N * P->nitems;
+  a.pi2 = second_pi(P);
   a.xi = (T*)P->x;
   a.st = (const T*)P->st;
   a.ks = P->ks;
@@ -836,11 +840,12 @@ void cg_result(fg_plan* P, double* dst, bool add, const int* idle = nullptr) {
   auto go = [&](auto tag) {
     using T = decltype(tag);
     const T *xi = (const T*)P->x, *pi = (const T*)P->p;
-    const long pi2 = P->lines ? 3 * P->N * P->nitems : 0;
+    const long pi2 = second_pi(P);
+    const int pairs = pi2 != 0 && P->lines == 0;
     if (add)
-      launch_cg_result<T, true>(xi, pi, pi2, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+      launch_cg_result<T, true>(xi, pi, pi2, pairs, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
     else
-      launch_cg_result<T, false>(xi, pi, pi2, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
+      launch_cg_result<T, false>(xi, pi, pi2, pairs, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
   };
   if (P->prec == FG_FP64)
     go(double());

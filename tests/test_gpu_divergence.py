@@ -53,7 +53,7 @@ def test_cg_iterates_by_divergence(shape, precision, tol, law):
     check_cg_iterates(shape, precision, tol, law, tuple(float(n) for n in shape) if shape in PLANES else 1.0)
 
 
-def check_cg_iterates(shape, precision, tol, law, lengths):
+def check_cg_iterates(shape, precision, tol, law, lengths, parts=(2, 2)):
     print(f"cg {shape} {precision} {law}", flush=True)
     work = synth.homogeneous_workload(shape, lengths)
     rng = np.random.default_rng(5 + shape[2])
@@ -68,13 +68,14 @@ def check_cg_iterates(shape, precision, tol, law, lengths):
     GP, _ = mechanics.residual_rhs(F0, c0, d0, work, work["spacing"])
     b = -spectral.project(GP, work["spacing"])
     K = cm.tangent(F0, c0, d0, work["E"], work["nu"], work["Omega"], law=law)
-    dF, _, _ = krylov.cg(lambda X: mechanics.operator(K, X, work["spacing"]), b, 1e-10, 100, fixed_iters=4)
+    dF, _, _ = krylov.cg(lambda X: mechanics.operator(K, X, work["spacing"]), b, 1e-10, 100, fixed_iters=sum(parts))
     plan = plan_for(work, precision)
     F = dt(F0)
     plan.set_state(F, dt(c0), dt(d0))
     plan.newton_linear_begin(Fbar)
-    plan.cg_iterate(2)
-    assert plan.cg_iterate(2, apply=True)["iters"] == 4
+    for k, n in enumerate(parts):
+        st = plan.cg_iterate(n, apply=k == len(parts) - 1)
+    assert st["iters"] == sum(parts)
     assert rel(host(F, (3, 3) + shape) - F0, dF) <= tol
     plan.close()
 
@@ -119,3 +120,13 @@ def test_cg_iterates_as_lines_or_passes(shape, precision, tol, law):
     """Both sides of the choice between the one-kernel front of a CG iteration
     and its passes, against the oracle (cubic voxels; the tolerances above)."""
     check_cg_iterates(shape, precision, tol, law, tuple(float(n) for n in shape))
+
+
+@pytest.mark.parametrize("parts", [(1,), (2,), (1, 2), (3, 2)])
+@pytest.mark.parametrize("shape,precision,tol", [((128, 96, 4), "fp64", 1e-11), ((128, 96, 4), "mixed", 1e-5),
+                                                 ((32, 32, 48), "fp64", 1e-11), ((8, 8, 16), "fp64", 1e-11)])
+def test_solution_after_any_count_of_iterations(shape, precision, tol, parts):
+    """The solution takes its steps late, two at a time where the direction has
+    two buffers and the passes run: the steps still due are added with the
+    result, after odd and even counts (against the oracle, the tolerances above)."""
+    check_cg_iterates(shape, precision, tol, "neo_hookean", tuple(float(n) for n in shape), parts)
