@@ -1,7 +1,7 @@
 // Real-space stencil kernels around the CG in divergence form (fg_cg3.hpp):
 //   k_grad_store  Z = D U as a 9-component field (the projection itself);
 //   k_cg_result   the CG solution x = D (xi + alpha pi) in double precision
-//                 (the last, deferred step of xi included), stored or added
+//                 (the steps that xi has not taken yet included), stored or added
 //                 to a 9-component field.
 #pragma once
 #include "fg_fft.hpp"
