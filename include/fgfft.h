@@ -244,11 +244,11 @@ fg_status fg_apply_operator(fg_plan* plan, const double* x, double* y);
  * precision (x, y: device, 9 N doubles; y may equal x).  Does not sync. */
 fg_status fg_project(fg_plan* plan, const double* x, double* y);
 
-/* The same projection computed as the CG iteration computes it: y = D U,
+/* The same projection by the route of the Newton residual: y = D U,
  * U = (D^T D)^+ D^T x, with D the corner-difference stencil of the rotated
  * scheme (its symbol is i e^{-i Phi} r, Phi = (q0 + q1 + q2) / 2): the
- * divergence D^T x is formed in real space, so only three components are
- * transformed, there and back.  Double precision; x, y:
+ * spectrum of x is multiplied by the symbol, three components are
+ * transformed back, and D is applied in real space.  Double precision; x, y:
  * device, 9 N doubles (y may equal x).  Does not synchronise. */
 fg_status fg_project_grad(fg_plan* plan, const double* x, double* y);
 

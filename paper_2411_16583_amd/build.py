@@ -18,7 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfgfft.so")
 ARCH = os.environ.get("FGFFT_ARCH", "gfx950")
-SOURCES = ["fg_fft_f64.hip", "fg_fft_f32.hip", "fg_scalar.hip", "fg_plan.hip"]
+SOURCES = ["fg_fft_f64.hip", "fg_fft_f32.hip", "fg_rows.hip", "fg_scalar.hip", "fg_plan.hip"]
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

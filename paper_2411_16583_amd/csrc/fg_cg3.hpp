@@ -95,10 +95,6 @@ template <typename R> inline BlockLayout block_layout(int n0, int n1, int M) {
 }
 
 // ---------------------------------------------------------------------------
-// Source of the tensor field whose divergence is taken: the tangent of either
-// law applied to D pi, or a stored 9-component field.
-constexpr int kSrcField = 2;
-
 // Lines (i1) and lanes along N2 of a wave's patch: 8 x 8 lanes of W voxels,
 // one 128-byte line of each plane per patch row.
 constexpr int kPatch = 8;
@@ -130,11 +126,11 @@ template <typename R> inline EdgeLayout edge_layout(int n0, int n1, int n2) {
 template <typename R> struct OpArgs {
   R* q;                // out: 3 N per item
   R* edge;             // out: 3 el.comp per item
-  const R* pi;         // direction potential, 3 N per item (unused by kSrcField):
+  const R* pi;         // direction potential, 3 N per item:
   long pi2;            // the running iteration's of two buffers pi2 values apart
   const KrylovScalars* ks;
-  const R* st;         // tangent state, or the 9-component field
-  double* partials;    // p.Kp per workgroup (unused by kSrcField)
+  const R* st;         // tangent state
+  double* partials;    // p.Kp per workgroup
   Gate gate;
   EdgeLayout el;
   int n0, n1, n2;
@@ -146,14 +142,14 @@ template <typename R> struct OpArgs {
 
 constexpr int kOpThreads = 256;
 
-// q = D^T Y with Y = K : (D pi) (or a stored field).  A wave owns a patch of
+// q = D^T Y with Y = K : (D pi).  A wave owns a patch of
 // 8 lines x 8 W voxels of a run of K node planes and marches along i0: node
 // plane m takes the voxel planes m and m + 1, so the previous plane's Y stays
 // in registers.  Inside the patch a node's contributions come from the lanes
 // of the next voxels and of the next line; what crosses the patch's edges is
 // stored apart (EdgeLayout), so nothing is computed twice, no workgroup
 // barrier is needed and the waves run freely.
-template <typename R, int W, int SRC>
+template <typename R, int W, int LAW>
 __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   using PV = typename FrontPack<R, W>::type;
   __shared__ double red[16];
@@ -173,9 +169,8 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   const int i1 = blk * kPatch + l, x = patch * a.el.W8 + gx * W;
   const bool active = live && i1 < a.n1 && x < a.n2;
   const long N = (long)a.n0 * a.n1 * a.n2;
-  const R* pi = a.pi + (long)item * 3 * N;
-  if constexpr (SRC != kSrcField) pi += (a.ks[item].run_iter & 1) * a.pi2;
-  const R* st = a.st + (long)item * (SRC == kSrcField ? 9 : state_words(SRC)) * N;
+  const R* pi = a.pi + (long)item * 3 * N + (a.ks[item].run_iter & 1) * a.pi2;
+  const R* st = a.st + (long)item * state_words(LAW) * N;
   R* q = a.q + (long)item * 3 * N;
   R* edge = a.edge + (long)item * 3 * a.el.comp;
   // the next voxels (line) of the patch are in the lane one (eight) above
@@ -235,10 +230,8 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
     }
   };
   R pp[3][3][W];
-  if constexpr (SRC != kSrcField) {
-    if (active) plane_sums(ps == 0 ? a.n0 - 1 : ps - 1, pp);
-  }
-  constexpr int NS = (SRC == kSrcField) ? 1 : (SRC == kLawSVK) ? 17 : 12;
+  if (active) plane_sums(ps == 0 ? a.n0 - 1 : ps - 1, pp);
+  constexpr int NS = (LAW == kLawSVK) ? 17 : 12;
   for (int v = ps; v <= pe; ++v) {
     const int i0 = (v == a.n0) ? 0 : v;
     const long line = (long)i0 * a.n1 + i1;
@@ -249,52 +242,43 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
       for (int w = 0; w < W; ++w) Yc[k][w] = R(0);
     if (active) {
       const R* sp = st + line * a.n2 + x;
-      if constexpr (SRC == kSrcField) {
+      PV A[NS];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          const PV y = *reinterpret_cast<const PV*>(sp + k * N);
+      for (int k = 0; k < NS; ++k) A[k] = pk_load_nt<R, W>(reinterpret_cast<const PV*>(sp + k * N));
+      R X[W][9];
+      R cs[3][3][W];
+      plane_sums(i0, cs);
 #pragma unroll
-          for (int w = 0; w < W; ++w) Yc[k][w] = pk_get<R>(y, w);
-        }
-      } else {
-        PV A[NS];
-#pragma unroll
-        for (int k = 0; k < NS; ++k) A[k] = pk_load_nt<R, W>(reinterpret_cast<const PV*>(sp + k * N));
-        R X[W][9];
-        R cs[3][3][W];
-        plane_sums(i0, cs);
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-          for (int w = 0; w < W; ++w) {
-            X[w][3 * c] = a.q0 * (cs[c][0][w] - pp[c][0][w]);
-            X[w][3 * c + 1] = a.q1 * (cs[c][1][w] + pp[c][1][w]);
-            X[w][3 * c + 2] = a.q2 * (cs[c][2][w] + pp[c][2][w]);
-            pp[c][0][w] = cs[c][0][w];
-            pp[c][1][w] = cs[c][1][w];
-            pp[c][2][w] = cs[c][2][w];
-          }
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          R A0[9], Y0[9];
-#pragma unroll
-          for (int k = 0; k < 9; ++k) A0[k] = pk_get<R>(A[k], w);
-          if constexpr (SRC == kLawSVK) {
-            R S0[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) S0[k] = pk_get<R>(A[9 + k], w);
-            svk_apply<R>(A0, S0, pk_get<R>(A[15], w), pk_get<R>(A[16], w), X[w], Y0);
-          } else {
-            tangent_apply<R>(A0, pk_get<R>(A[9], w), pk_get<R>(A[10], w), pk_get<R>(A[11], w), X[w], Y0);
-          }
-          double d = 0.0;
-#pragma unroll
-          for (int k = 0; k < 9; ++k) {
-            d += (double)X[w][k] * (double)Y0[k];
-            Yc[k][w] = Y0[k];
-          }
-          if (v < pe) acc += d;
+          X[w][3 * c] = a.q0 * (cs[c][0][w] - pp[c][0][w]);
+          X[w][3 * c + 1] = a.q1 * (cs[c][1][w] + pp[c][1][w]);
+          X[w][3 * c + 2] = a.q2 * (cs[c][2][w] + pp[c][2][w]);
+          pp[c][0][w] = cs[c][0][w];
+          pp[c][1][w] = cs[c][1][w];
+          pp[c][2][w] = cs[c][2][w];
         }
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        R A0[9], Y0[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) A0[k] = pk_get<R>(A[k], w);
+        if constexpr (LAW == kLawSVK) {
+          R S0[6];
+#pragma unroll
+          for (int k = 0; k < 6; ++k) S0[k] = pk_get<R>(A[9 + k], w);
+          svk_apply<R>(A0, S0, pk_get<R>(A[15], w), pk_get<R>(A[16], w), X[w], Y0);
+        } else {
+          tangent_apply<R>(A0, pk_get<R>(A[9], w), pk_get<R>(A[10], w), pk_get<R>(A[11], w), X[w], Y0);
+        }
+        double d = 0.0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          d += (double)X[w][k] * (double)Y0[k];
+          Yc[k][w] = Y0[k];
+        }
+        if (v < pe) acc += d;
       }
     }
     if (v > ps) {  // node plane v - 1 is complete
@@ -352,10 +336,8 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
 #pragma unroll
       for (int w = 0; w < W; ++w) Yp[k][w] = Yc[k][w];
   }
-  if constexpr (SRC != kSrcField) {
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) a.partials[(long)item * a.groups + grp] = s;
-  }
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) a.partials[(long)item * a.groups + grp] = s;
 }
 
 // Element k of a real line's half spectrum from its packed transform z (k = 0
@@ -623,9 +605,8 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
 // N0 pass on the block layout: forward N0 transform of q, the CG update of
 // the spectral residual, the norm, the symbol, and the inverse N0 transform.
 //   kN0Cg     s -= alpha q (stored), z = f s, partial sums of r.r
-//   kN0Start  s = sign q (stored, type RO), z = f s (type RO), r.r
+//   kN0Start  s = q (stored), z = f s, r.r
 //   kN0Apply  z = f q
-//   kN0Norm   partial sums of r.r alone
 // SYM = kSymProj: f = 1 / (N |r|^2) with the rotated vector r of eq. (28) (0
 // where r = 0), and r.r = sum over the full spectrum of f |s|^2 (the columns
 // kx > 0 of the half spectrum count twice).  SYM = kSymLap (the scalar
@@ -638,7 +619,7 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
 // B(k) = (P(k) - conj P(-k)) / (2 i), scales each with its own symbol and
 // recombines; the other workgroups leave that column alone.
 constexpr int kSymProj = 0, kSymLap = 1;
-constexpr int kN0Cg = 0, kN0Start = 1, kN0Apply = 2, kN0Norm = 3;
+constexpr int kN0Cg = 0, kN0Start = 1, kN0Apply = 2;
 
 template <typename R, typename RO> struct N0Args {
   const cplx<R>* q;    // blocks
@@ -650,7 +631,7 @@ template <typename R, typename RO> struct N0Args {
   BlockLayout bl, blo;  // of q, and of z and s
   int N1, M, tile, kymajor;
   SpecTables<R> tb;
-  R scale, sign;
+  R scale;
   Gate gate;
   const KrylovScalars* ks;
   double* partials;  // per workgroup: column pairs, then [component][ky][tile]; items consecutive (Parts)
@@ -764,8 +745,6 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       if constexpr (MODE == kN0Cg) {
         const CO s = a.dcs[off + kz];
         v[0][e] = mk<C>((R)s.x - alpha * v[0][e].x, (R)s.y - alpha * v[0][e].y);
-      } else if constexpr (MODE == kN0Start) {
-        v[0][e] = cscale(v[0][e], a.sign);
       }
       sp[col * L + kz] = v[0][e];
     }
@@ -804,12 +783,10 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       }
       v[0][e] = cadd(cscale(A, fa), mul_pi(cscale(Bv, fb)));
     }
-    if constexpr (MODE != kN0Norm) {
-      LS::inv(v[0], lds + col, 2, t, stw);
-      if (store) {
+    LS::inv(v[0], lds + col, 2, t, stw);
+    if (store) {
 #pragma unroll
-        for (int e = 0; e < LS::E; ++e) a.dcz[off + LS::idxA(t, e)] = mk<CO>((RO)v[0][e].x, (RO)v[0][e].y);
-      }
+      for (int e = 0; e < LS::E; ++e) a.dcz[off + LS::idxA(t, e)] = mk<CO>((RO)v[0][e].x, (RO)v[0][e].y);
     }
   } else {
     const int nkx = a.M / B;
@@ -874,8 +851,6 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       for (int c = 0; c < CPT; ++c) {
         if constexpr (MODE == kN0Cg)
           v[c][e] = mk<C>((R)s[c][e].x - alpha * v[c][e].x, (R)s[c][e].y - alpha * v[c][e].y);
-        else if constexpr (MODE == kN0Start)
-          v[c][e] = cscale(v[c][e], a.sign);
       }
       if constexpr (MODE == kN0Cg || MODE == kN0Start) {
         CO* d = a.s + oo + (long)kz * bo;
@@ -907,19 +882,17 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
         v[c][e] = cscale(v[c][e], f);
       }
     }
-    if constexpr (MODE != kN0Norm) {
-      LS::template inv_cols<CPT>(v, lds + col0, B, t, stw);
+    LS::template inv_cols<CPT>(v, lds + col0, B, t, stw);
 #pragma unroll
-      for (int e = 0; e < LS::E; ++e) {
-        CO* d = a.z + oo + (long)LS::idxA(t, e) * bo;
-        if constexpr (CPT == 2) {
-          if (store && kx0 != 0)
-            st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
-          else if (store)
-            d[1] = v[CPT - 1][e];
-        } else {
-          if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
-        }
+    for (int e = 0; e < LS::E; ++e) {
+      CO* d = a.z + oo + (long)LS::idxA(t, e) * bo;
+      if constexpr (CPT == 2) {
+        if (store && kx0 != 0)
+          st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
+        else if (store)
+          d[1] = v[CPT - 1][e];
+      } else {
+        if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
       }
     }
   }

@@ -124,7 +124,7 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
 }
 
 template <typename R>
-int launch_cg_op(int src, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
+int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
                  const Gate& gate, int n0, int n1,
                  int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   OpArgs<R> a;
@@ -150,9 +150,7 @@ int launch_cg_op(int src, R* q, R* edge, const R* pi, long pi2, const KrylovScal
   auto go = [&](auto width) {
     constexpr int W = decltype(width)::value;
     const dim3 grid((unsigned)((long)sp.groups * nitems)), block(kOpThreads);
-    if (src == kSrcField)
-      launch_ev((k_cg_op<R, W, kSrcField>), grid, block, 0, s, ev0, ev1, a);
-    else if (src == kLawSVK)
+    if (law == kLawSVK)
       launch_ev((k_cg_op<R, W, kLawSVK>), grid, block, 0, s, ev0, ev1, a);
     else
       launch_ev((k_cg_op<R, W, kLawNH>), grid, block, 0, s, ev0, ev1, a);
@@ -287,11 +285,6 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
       if constexpr (kSame) FG_N0_GO(L_, kN0Cg, kSymProj);        \
     } else if (mode == kN0Apply) {                               \
       if constexpr (kSame) FG_N0_GO(L_, kN0Apply, kSymProj);     \
-    } else if constexpr (sizeof(R) == 8) {                       \
-      if (mode == kN0Start)                                      \
-        FG_N0_GO(L_, kN0Start, kSymProj);                        \
-      else if constexpr (kSame)                                  \
-        FG_N0_GO(L_, kN0Norm, kSymProj);                         \
     }                                                            \
     return parts;
     FG_FOR_AXIS(FG_CASE)
@@ -380,15 +373,6 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
         go(k_plane<R, RO, kN0Cg, kSymProj, 768>);
     } else if constexpr (kSame) {
       go(k_plane<R, RO, kN0Cg, kSymProj, TH>);
-    }
-  } else if constexpr (sizeof(R) == 8) {
-    if (mode == kN0Start) {
-      go(k_plane<R, RO, kN0Start, kSymProj, TH>);
-    } else if constexpr (kSame) {
-      if (mode == kN0Norm)
-        go(k_plane<R, RO, kN0Norm, kSymProj, TH>);
-      else
-        go(k_plane<R, RO, kN0Apply, kSymProj, TH>);
     }
   }
   return Parts(a.groups);

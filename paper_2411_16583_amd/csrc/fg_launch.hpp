@@ -7,6 +7,7 @@
 #include "fg_cg3.hpp"
 #include "fg_plane.hpp"
 #include "fg_cg_lines.hpp"
+#include "fg_rows.hpp"
 
 namespace fg {
 
@@ -52,11 +53,10 @@ struct OpSplit {
 };
 OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems);
 
-// q = D^T K : (D pi) for all items (src: the law), or D^T of the 9-component
-// fields st (src = kSrcField), as k_cg_op leaves it (q and its patch edges);
+// q = D^T K : (D pi) for all items, as k_cg_op leaves it (q and its patch edges);
 // h: grid spacings.  Returns the number of partial sums of p.Kp per item.
 template <typename R>
-int launch_cg_op(int src, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
+int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
                  const Gate& gate, int n0, int n1,
                  int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);
@@ -95,6 +95,17 @@ int planes_per_group(int n0, int n1, int M, int nc, int nitems);
 template <typename R, typename RO>
 Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
                    hipEvent_t ev1 = nullptr);
+// Passes of the residual and of fg_project_grad on 9-component fields (fg_rows.hpp):
+// the forward N1 pass with the rows merged (tile as for launch_axis), the N0
+// pass in one of its modes (returns the partial sums of r.r of an item), and
+// the inverse N1 pass of the plane layout.
+void launch_rows_n1(int N1, int N0, double* y, double* dc, int M, int tile, const SpecTables<double>& tb,
+                    const Gate& gate, int nitems, hipStream_t s);
+template <typename RO, typename Z>
+Parts launch_rows_n0(int N0, int mode, RowsN0Args<RO, Z> a, int nitems, hipStream_t s);
+template <typename RO>
+void launch_rows_out(int n1, long nlines, const double* z, RO* out, const SpecTables<double>& tb, const Gate& gate,
+                     int nitems, hipStream_t s);
 // Inverse N2 pass fused with the direction and solution updates (k_c2r_dir).
 template <typename R>
 void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,

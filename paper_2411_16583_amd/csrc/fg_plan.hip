@@ -241,8 +241,8 @@ struct fg_plan {
   // and the compact kx = 0 column, and the spectral residual of the CG
   void *ln = nullptr, *bk = nullptr, *dc = nullptr, *rs = nullptr, *rdc = nullptr;
   double *ln64 = nullptr, *bk64 = nullptr, *dc64 = nullptr;  // the first three in double (aliases in FP64 plans)
+  double* rows_dc = nullptr;  // kx = 0 column of the 9 components of S64 (fg_rows.hpp)
   void *q = nullptr, *qe = nullptr;            // divergence q (3N T) and its patch edges
-  double *q64 = nullptr, *qe64 = nullptr;
   double* sc = nullptr;          // scalar solver area, 16N doubles
   size_t part_n = 0;
 
@@ -338,18 +338,15 @@ size_t layout(fg_plan* P, char* base) {
   const size_t ne64 = fg::edge_layout<double>(n0, n1, P->n2).comp, ne32 = fg::edge_layout<float>(n0, n1, P->n2).comp;
   P->q = carve<char>(base, off, 3 * NT * tb);
   P->qe = carve<char>(base, off, 3 * nit * (P->prec == FG_FP64 ? ne64 : ne32) * tb);
+  P->rows_dc = carve<double>(base, off, 18 * nit * n0 * n1);
   if (P->prec == FG_FP64) {
     P->ln64 = (double*)P->ln;
     P->bk64 = (double*)P->bk;
     P->dc64 = (double*)P->dc;
-    P->q64 = (double*)P->q;
-    P->qe64 = (double*)P->qe;
   } else {
     P->ln64 = carve<double>(base, off, 3 * NT);
     P->bk64 = carve<double>(base, off, 6 * nit * cb64);
     P->dc64 = carve<double>(base, off, 6 * nit * n0 * n1);
-    P->q64 = carve<double>(base, off, 3 * NT);
-    P->qe64 = carve<double>(base, off, 3 * nit * ne64);
   }
   // scalar solvers (phase field, Fick) only on single plans; batches keep
   // just the zero fields standing in for c and d
@@ -570,7 +567,6 @@ template <typename R, typename RO> N0Args<R, RO> n0_args(fg_plan* P, const Gate&
   a.tile = tile_zproj<R>(P);
   a.tb = tabs<R>(P).spec();
   a.scale = (R)(1.0 / (double)P->N);
-  a.sign = R(1);
   a.gate = gate;
   return a;
 }
@@ -582,7 +578,6 @@ template <typename R, typename RO> PlaneArgs<R, RO> plane_args(fg_plan* P, const
   a.M = P->M;
   a.tb = tabs<R>(P).spec();
   a.scale = (R)(1.0 / (double)P->N);
-  a.sign = R(1);
   a.gate = gate;
   return a;
 }
@@ -635,54 +630,69 @@ void constitutive(fg_plan* P, const double* Fu, double* Pout, void* state, doubl
   check_launch();
 }
 
-// Spectrum of the divergence D^T Y of the FP64 9-component fields Y of all
-// items not masked: stencil and N2 transform, in the plane layout (ln64) or,
-// after the N1 pass, in the FP64 block layout (bk64, dc64).
-void divergence64(fg_plan* P, const double* Y, const Gate& gate) {
+// Spectra of the rows of the FP64 9-component fields `in` (all items not masked)
+// after their N1 pass, in S64 and rows_dc (k_rows_n1); in may be S64.
+void rows64(fg_plan* P, const double* in, const Gate& gate) {
   const SpecTables<double> tb = P->t64.spec();
+  const long lines = 9L * P->n0 * P->n1;
   {
     ProfScope ps(P, FG_PASS_R2C);
-    launch_cg_op<double>(kSrcField, P->q64, P->qe64, nullptr, 0, nullptr, Y, nullptr, gate, P->n0, P->n1, P->n2, P->h, P->nitems,
-                         P->stream);
-    launch_r2c_edges<double>(P->M, P->q64, P->qe64, P->ln64, gate, P->n0, P->n1, tb, P->nitems, P->planes, P->stream);
+    Skip skip;
+    skip.gate = gate.p;
+    skip.stride = gate.stride;
+    launch_r2c<double>(P->M, in, P->S64, lines * P->nitems, tb, skip.unit(lines), P->stream);
   }
-  if (P->planes) return;
   ProfScope ps(P, FG_PASS_AXIS);
-  launch_n1<double>(P->n1, false, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, gate), P->nitems, P->stream);
+  launch_rows_n1(P->n1, P->n0, P->S64, P->rows_dc, P->M, tile_axis<double>(P), tb, gate, P->nitems, P->stream);
 }
 
-// |G*Y|^2 of the FP64 9-component fields Y of all items not idle (G*Y =
+// The N0 pass of rows64's output, with the inverse N1 pass of the plane layout:
+// s and z of the residual (kRowsStart, in the working precision), their norm
+// alone (kRowsNorm; partial sums of both to P->part), or z alone in double
+// precision (kRowsApply).
+template <typename RO> Parts rows_n0(fg_plan* P, int mode, double sign, const Gate& gate) {
+  ProfScope ps(P, FG_PASS_ZPROJ);
+  auto go = [&](auto z) {
+    using Z = decltype(z);
+    RowsN0Args<RO, Z> a{};
+    a.y = (const double2*)P->S64;
+    a.dc = (const double2*)P->rows_dc;
+    const bool wide = sizeof(Z) == 8;
+    a.z = (cplx<Z>*)(P->planes ? (wide ? P->ln64 : P->ln) : (wide ? P->bk64 : P->bk));
+    a.dcz = (cplx<Z>*)(wide ? P->dc64 : P->dc);
+    a.s = (cplx<RO>*)P->rs;
+    a.dcs = (cplx<RO>*)P->rdc;
+    a.blo = block_layout<RO>(P->n0, P->n1, P->M);
+    a.N1 = P->n1;
+    a.M = P->M;
+    a.tile = tile_zproj<double>(P);
+    a.planes = P->planes;
+    a.tb = P->t64.spec();
+    a.scale = 1.0 / (double)P->N;
+    a.sign = sign;
+    a.gate = gate;
+    a.partials = P->part;
+    return launch_rows_n0<RO, Z>(P->n0, mode, a, P->nitems, P->stream);
+  };
+  if (!P->planes) return go(RO());
+  const Parts n = go(double());
+  if (mode != kRowsNorm)
+    launch_rows_out<RO>(P->n1, 3L * P->M * P->n0, P->ln64, sizeof(RO) == 8 ? (RO*)P->ln64 : (RO*)P->ln,
+                        P->t64.spec(), gate, P->nitems, P->stream);
+  return n;
+}
+
+// |G*Y|^2 of the FP64 9-component fields Y in S64 of all items not idle (G*Y =
 // D (D^T D)^+ D^T Y, normed in the spectrum); partial sums to P->part,
 // described by the result.  With start, the residual of a CG on
 // r_0 = sign G*Y is left ready for cg_iteration: s_0 and z_0 in the working
-// precision.
-Parts residual_pass(fg_plan* P, const double* Y, const int* idle, bool start, double sign = -1.0) {
+// precision.  Y is replaced by its spectrum.
+Parts residual_pass(fg_plan* P, const int* idle, bool start, double sign = -1.0) {
   const Gate gate = Gate::flags(idle);
-  divergence64(P, Y, gate);
-  ProfScope ps(P, FG_PASS_ZPROJ);
-  auto go = [&](auto out, int mode) {
-    using T = decltype(out);
-    if (P->planes) {
-      PlaneArgs<double, T> a = plane_args<double, T>(P, gate);
-      a.q = (const cplx<double>*)P->ln64;
-      a.z = (cplx<T>*)P->ln;
-      a.s = (cplx<T>*)P->rs;
-      a.sign = sign;
-      a.partials = P->part;
-      return launch_plane<double, T>(mode, kSymProj, a, 3, P->nitems, P->stream);
-    }
-    N0Args<double, T> a = n0_args<double, T>(P, gate);
-    a.q = (const cplx<double>*)P->bk64;
-    a.dcq = (const cplx<double>*)P->dc64;
-    a.z = (cplx<T>*)P->bk;
-    a.dcz = (cplx<T>*)P->dc;
-    a.s = (cplx<T>*)P->rs;
-    a.dcs = (cplx<T>*)P->rdc;
-    a.sign = sign;
-    a.partials = P->part;
-    return launch_n0<double, T>(P->n0, mode, kSymProj, a, P->nitems, P->stream);
-  };
-  const Parts nb = !start ? go(double(), kN0Norm) : P->prec == FG_FP64 ? go(double(), kN0Start) : go(float(), kN0Start);
+  rows64(P, P->S64, gate);
+  const Parts nb = !start                ? rows_n0<double>(P, kRowsNorm, sign, gate)
+                   : P->prec == FG_FP64 ? rows_n0<double>(P, kRowsStart, sign, gate)
+                                        : rows_n0<float>(P, kRowsStart, sign, gate);
   check_launch();
   return nb;
 }
@@ -905,7 +915,7 @@ double residual_denominator(fg_plan* P, const double Fmacro[9]) {
   const unsigned nbN = blocks_for(P->N);
   constitutive(P, P->Fu, P->S64, nullptr, P->part2);
   reduce_to(P, P->part2, (int)nbN, 0);                                 // ||P(Fbar)||^2
-  reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);  // ||G*P(Fbar)||^2
+  reduce_to(P, P->part, residual_pass(P, nullptr, false), 1);  // ||G*P(Fbar)||^2
   sync_read(P);
   check_domain(P);
   return std::max(std::max(std::sqrt(P->hd[1]), 1e-14 * std::sqrt(P->hd[0])), 1e-300);
@@ -920,7 +930,7 @@ double newton_residual_norm(fg_plan* P, const double* B = nullptr) {
     hipLaunchKernelGGL(k_sub_f64, dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, P->S64, B, n9);
     check_launch();
   }
-  cg_begin(P, residual_pass(P, P->S64, nullptr, true));
+  cg_begin(P, residual_pass(P, nullptr, true));
   sync_read(P);
   check_domain(P);
   return std::sqrt(P->hks[0].rr0);
@@ -1018,7 +1028,7 @@ void adjoint(fg_plan* P, const double W[9], double* gE, double* gO, const fg_sol
   check_launch();
   static_assert(sizeof(T) == 8, "the single-precision adjoint is adjoint_mixed");
   // b = -G*(K:W)
-  cg_begin(P, residual_pass(P, (double*)S, nullptr, true));
+  cg_begin(P, residual_pass(P, nullptr, true));
   sync_read(P);
   check_domain(P);
   if (!P->hks[0].done) cg_solve<T>(P, o, stats);
@@ -1062,7 +1072,7 @@ void adjoint_mixed(fg_plan* P, const double W[9], double* gE, double* gO, const 
                        (const double*)P->Fu, (const double*)lam, P->S64, P->flags, N, P->law);
     check_launch();
     // the inner CG starts from R_k (rr0 = R.R)
-    cg_begin(P, residual_pass(P, P->S64, nullptr, true));
+    cg_begin(P, residual_pass(P, nullptr, true));
     sync_read(P);
     check_domain(P);
     rr = P->hks[0].rr0;
@@ -1600,9 +1610,9 @@ fg_status fg_residual(fg_plan* P, const double F_macro[9], double* err_res) {
     const unsigned nbN = blocks_for(P->N);
     constitutive(P, P->Fu, P->S64, nullptr, P->part2);
     reduce_to(P, P->part2, (int)nbN, 0);
-    reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);
+    reduce_to(P, P->part, residual_pass(P, nullptr, false), 1);
     constitutive(P, nullptr, P->S64, nullptr, nullptr);
-    reduce_to(P, P->part, residual_pass(P, P->S64, nullptr, false), 2);
+    reduce_to(P, P->part, residual_pass(P, nullptr, false), 2);
     sync_read(P);
     check_domain(P);
     const double den = std::max(std::max(std::sqrt(P->hd[1]), 1e-14 * std::sqrt(P->hd[0])), 1e-300);
@@ -1678,20 +1688,12 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
     if (!P->ws) throw Status(FG_E_STATE, "workspace not set");
     P->lin_open = false;
     const Gate none{};
-    divergence64(P, x, none);
-    if (P->planes) {
-      PlaneArgs<double, double> a = plane_args<double, double>(P, none);
-      a.q = a.z = (cplx<double>*)P->ln64;
-      launch_plane<double, double>(kN0Apply, kSymProj, a, 3, 1, P->stream);
-    } else {
-      N0Args<double, double> a = n0_args<double, double>(P, none);
-      a.q = a.z = (cplx<double>*)P->bk64;
-      a.dcq = a.dcz = (cplx<double>*)P->dc64;
-      launch_n0<double, double>(P->n0, kN0Apply, kSymProj, a, 1, P->stream);
+    rows64(P, x, none);
+    rows_n0<double>(P, kRowsApply, 1.0, none);
+    if (!P->planes)
       launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
-    }
-    launch_c2r_dir<double>(P->M, dir_args<double>(P, P->ln64, P->q64, nullptr, nullptr, 3), 1, P->stream);
-    launch_grad_store<double, double>(P->q64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
+    launch_c2r_dir<double>(P->M, dir_args<double>(P, P->ln64, P->S64, nullptr, nullptr, 3), 1, P->stream);
+    launch_grad_store<double, double>(P->S64, P->N, 9 * P->N, y, 9 * P->N, nullptr, P->n0, P->n1, P->n2, 1, P->h,
                                       P->stream);
     check_launch();
   });
@@ -1909,7 +1911,7 @@ void batch_tick(fg_plan* P, fg_batch::Group& g, bool newton) {
   cg_result(P, P->F, true, g.idle);  // F += D xi
   constitutive(P, nullptr, P->S64, P->st, nullptr, g.idle);
   // err_res of eq. (31), the Newton test, and a fresh CG on b = -G*P
-  const Parts nb = residual_pass(P, P->S64, g.idle, true);
+  const Parts nb = residual_pass(P, g.idle, true);
   hipLaunchKernelGGL(k_newton_check, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, g.nc, g.idle,
                      (int)FG_E_NOCONV);
   hipLaunchKernelGGL(k_newton_cg_start, dim3(nit), dim3(1024), 0, P->stream, (const double*)P->part, nb, P->ks, g.nc,
@@ -1976,7 +1978,7 @@ void batch_prologue(fg_batch* B, fg_batch::Group& g, const double* F_macro, cons
   // ||P(Fbar)||^2 and ||G*P(Fbar)||^2 per item
   constitutive(P, P->Fu, P->S64, nullptr, P->part2);
   reduce_items(P, P->part2, (int)blocks_for(N), 0);
-  reduce_items(P, P->part, residual_pass(P, P->S64, nullptr, false), 1);
+  reduce_items(P, P->part, residual_pass(P, nullptr, false), 1);
   sync_read(P);
   check_domain(P);
   const bool mixed = (P->prec == FG_MIXED);

@@ -40,7 +40,7 @@ template <typename R, typename RO> struct PlaneArgs {
   int groups;        // workgroups per item
   FastDiv dn1;
   SpecTables<R> tb;
-  R scale, sign;
+  R scale;
   double sa0, sa1;  // kSymLap
   Gate gate;
   KrylovScalars* ks;
@@ -274,9 +274,7 @@ __global__ void __launch_bounds__(TH) k_plane(PlaneArgs<R, RO> a) {
   auto update = [&](C& v, int kz, int pl, int ky, CO r) {
     if constexpr (MODE == kN0Cg)
       v = mk<C>((R)r.x - alpha * v.x, (R)r.y - alpha * v.y);
-    else if constexpr (MODE == kN0Start)
-      v = cscale(v, a.sign);
-    if constexpr (MODE == kN0Cg || MODE == kN0Start) res[(pl * n0 + kz) * n1 + ky] = mk<CO>((RO)v.x, (RO)v.y);
+    res[(pl * n0 + kz) * n1 + ky] = mk<CO>((RO)v.x, (RO)v.y);
   };
   const int pid0 = g * a.P;             // first plane (component, kx) of the workgroup
   const bool packed = pid0 % a.M == 0;  // its kx is 0
@@ -286,7 +284,7 @@ __global__ void __launch_bounds__(TH) k_plane(PlaneArgs<R, RO> a) {
       update(v, kz, pl, ky, r);
       const int kx = (pid0 + pl) % a.M;
       const R f = symbol(kz, ky, a.tb.cx[kx], a.tb.sx[kx]);
-      if constexpr (MODE != kN0Apply) norm(v, f, 2.0);
+      norm(v, f, 2.0);
       v = cscale(v, f);
     };
     switch (n0) {
@@ -303,7 +301,7 @@ __global__ void __launch_bounds__(TH) k_plane(PlaneArgs<R, RO> a) {
       if (pl > 0) {
         const int kx = (pid0 + pl) % a.M;
         const R f = symbol(kz, ky, a.tb.cx[kx], a.tb.sx[kx]);
-        if constexpr (MODE != kN0Apply) norm(v, f, 2.0);
+        norm(v, f, 2.0);
         v = cscale(v, f);
       }
     };
@@ -325,41 +323,33 @@ __global__ void __launch_bounds__(TH) k_plane(PlaneArgs<R, RO> a) {
       const C A = cscale(cadd(u, cconj(um)), R(0.5));
       const C B = cscale(mul_mi(csub(u, cconj(um))), R(0.5));
       const R fa = symbol((int)kz, (int)ky, cA, sA), fb = symbol((int)kz, (int)ky, cB, sB);
-      if constexpr (MODE != kN0Apply) {
-        const double w = ip == i ? 1.0 : 2.0;
-        norm(A, fa, w);
-        norm(B, fb, w);
-      }
+      const double w = ip == i ? 1.0 : 2.0;
+      norm(A, fa, w);
+      norm(B, fb, w);
       const C ta = cscale(A, fa), tb = cscale(B, fb);
       x[kz * LD + ky] = cadd(ta, mul_pi(tb));
       if (ip != i) x[q0 * LD + q1] = cadd(cconj(ta), mul_pi(cconj(tb)));
     }
     __syncthreads();
-    if constexpr (MODE != kN0Norm) {
-      switch (n0) {
+    switch (n0) {
 #define FG_CASE(L_) \
   case L_: plane_cols_inv<L_>(x, LD, n1, a.dn1, a.P, tw0); break;
-        FG_PLANE_LINES(FG_CASE)
-#undef FG_CASE
-      }
-    }
-  }
-  if constexpr (MODE != kN0Norm) {
-    __syncthreads();
-    switch (n1) {
-#define FG_CASE(L_) \
-  case L_: plane_rows_inv<L_>(x, dst, nl, tw1); break;
       FG_PLANE_LINES(FG_CASE)
 #undef FG_CASE
     }
   }
-  if constexpr (MODE != kN0Apply) {
-    double s = block_sum(acc, red);
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = s;
-    if constexpr (SYM == kSymLap) {
-      s = block_sum(acc2, red);
-      if (threadIdx.x == 0) a.partials2[blockIdx.x] = s;
-    }
+  __syncthreads();
+  switch (n1) {
+#define FG_CASE(L_) \
+  case L_: plane_rows_inv<L_>(x, dst, nl, tw1); break;
+    FG_PLANE_LINES(FG_CASE)
+#undef FG_CASE
+  }
+  double s = block_sum(acc, red);
+  if (threadIdx.x == 0) a.partials[blockIdx.x] = s;
+  if constexpr (SYM == kSymLap) {
+    s = block_sum(acc2, red);
+    if (threadIdx.x == 0) a.partials2[blockIdx.x] = s;
   }
 }
 
