@@ -371,7 +371,8 @@ int fg_batch_group_info(const fg_batch* batch, int group, int grid[3], int* nite
  * pass along N1 and the N0 pass (of the CG, and fused with the
  * projection of eq. (28) in fg_project) work on `tile` adjacent kx columns
  * per workgroup.  (The CG of grids whose (N0, N1) plane fits LDS has no such
- * passes.)  Pass index `which`:
+ * passes; their residual and fg_project, and fg_apply_operator in single
+ * precision, do.)  Pass index `which`:
  * 0 = N1 pass FP64, 1 = N0 projection pass FP64, 2 = N1 pass FP32,
  * 3 = N0 projection pass FP32 (the single-precision passes run in FG_MIXED
  * plans).  Valid tiles are powers of two dividing N2/2 with (threads per
@@ -395,7 +396,8 @@ fg_status fg_plan_set_tiles(fg_plan* plan, const int tiles[4]);
 /* The four tiles in use (built-in choice resolved). */
 fg_status fg_plan_get_tiles(const fg_plan* plan, int tiles[4]);
 /* Mean time in milliseconds of one launch of pass `which` with `tile`
- * (0 = built-in) over all items of the plan, from reps launches after one
+ * (0 = built-in; of the CG where it has the pass, else of the residual or of
+ * fg_apply_operator) over all items of the plan, from reps launches after one
  * warm-up, HIP events on the plan stream.  Overwrites the plan's spectral
  * work buffer (state and material are untouched).  Synchronises.
  * Errors: FG_E_ARG (bad pass or tile, FP32 pass on an FG_FP64 plan),

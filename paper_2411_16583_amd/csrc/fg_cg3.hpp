@@ -606,7 +606,6 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
 // the spectral residual, the norm, the symbol, and the inverse N0 transform.
 //   kN0Cg     s -= alpha q (stored), z = f s, partial sums of r.r
 //   kN0Start  s = q (stored), z = f s, r.r
-//   kN0Apply  z = f q
 // SYM = kSymProj: f = 1 / (N |r|^2) with the rotated vector r of eq. (28) (0
 // where r = 0), and r.r = sum over the full spectrum of f |s|^2 (the columns
 // kx > 0 of the half spectrum count twice).  SYM = kSymLap (the scalar
@@ -619,7 +618,7 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
 // B(k) = (P(k) - conj P(-k)) / (2 i), scales each with its own symbol and
 // recombines; the other workgroups leave that column alone.
 constexpr int kSymProj = 0, kSymLap = 1;
-constexpr int kN0Cg = 0, kN0Start = 1, kN0Apply = 2;
+constexpr int kN0Cg = 0, kN0Start = 1;
 
 template <typename R, typename RO> struct N0Args {
   const cplx<R>* q;    // blocks
@@ -754,9 +753,7 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
     for (int e = 0; e < LS::E; ++e) {
       const int kz = LS::idxB(t, e);
       const C P = v[0][e], Pm = sp[(1 - col) * L + (kz == 0 ? 0 : L - kz)];
-      if constexpr (MODE == kN0Cg || MODE == kN0Start) {
-        if (store) a.dcs[off + kz] = mk<CO>((RO)P.x, (RO)P.y);
-      }
+      if (store) a.dcs[off + kz] = mk<CO>((RO)P.x, (RO)P.y);
       R fa, fb;
       if constexpr (SYM == kSymProj) {
         // rotated vector at qx = 0: (sz cy, cz sy, 0); at qx = pi: (0, 0, cz cy sx)
@@ -771,7 +768,7 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       }
       const C A = cscale(cadd(P, cconj(Pm)), R(0.5));
       const C Bv = cscale(mul_mi(csub(P, cconj(Pm))), R(0.5));
-      if (MODE != kN0Apply && store) {
+      if (store) {
         const double na = (double)A.x * A.x + (double)A.y * A.y, nb = (double)Bv.x * Bv.x + (double)Bv.y * Bv.y;
         const double d = (double)fa * na + (double)fb * nb;
         if constexpr (SYM == kSymProj) {
@@ -852,16 +849,14 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
         if constexpr (MODE == kN0Cg)
           v[c][e] = mk<C>((R)s[c][e].x - alpha * v[c][e].x, (R)s[c][e].y - alpha * v[c][e].y);
       }
-      if constexpr (MODE == kN0Cg || MODE == kN0Start) {
-        CO* d = a.s + oo + (long)kz * bo;
-        if constexpr (CPT == 2) {
-          if (store && kx0 != 0)
-            st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
-          else if (store)
-            d[1] = v[CPT - 1][e];
-        } else {
-          if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
-        }
+      CO* d = a.s + oo + (long)kz * bo;
+      if constexpr (CPT == 2) {
+        if (store && kx0 != 0)
+          st_stream_f4(d, make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y));
+        else if (store)
+          d[1] = v[CPT - 1][e];
+      } else {
+        if (store && kx0 != 0) st_stream(d, mk<CO>((RO)v[0][e].x, (RO)v[0][e].y));
       }
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
@@ -873,7 +868,7 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
         } else {
           f = (R)((double)a.scale / (a.a0 + a.a1 * (double)(sz * sz + f1[c])));
         }
-        if (MODE != kN0Apply && store && kx0 + c != 0) {
+        if (store && kx0 + c != 0) {
           const double n = __fma_rn((double)v[c][e].x, (double)v[c][e].x, (double)v[c][e].y * (double)v[c][e].y);
           const double w = 2.0 * (double)(SYM == kSymProj ? f : a.scale);
           acc[c] = __fma_rn(w, n, acc[c]);
@@ -896,17 +891,15 @@ __global__ void __launch_bounds__(256) k_n0(N0Args<R, RO> a) {
       }
     }
   }
-  if constexpr (MODE != kN0Apply) {
-    double* cr = reinterpret_cast<double*>(smem_raw);
-    auto emit = [&](double (&v)[CPT], double* out) {
-      const double sum = isdc ? block_sum(v[0], red) : tile_tree<LS::T, CPT>(v, B / CPT, cr);
-      if (threadIdx.x == 0) out[part] = sum;
-    };
-    emit(acc, a.partials);
-    if constexpr (SYM == kSymLap) {
-      __syncthreads();
-      emit(acc2, a.partials2);
-    }
+  double* cr = reinterpret_cast<double*>(smem_raw);
+  auto emit = [&](double (&v)[CPT], double* out) {
+    const double sum = isdc ? block_sum(v[0], red) : tile_tree<LS::T, CPT>(v, B / CPT, cr);
+    if (threadIdx.x == 0) out[part] = sum;
+  };
+  emit(acc, a.partials);
+  if constexpr (SYM == kSymLap) {
+    __syncthreads();
+    emit(acc2, a.partials2);
   }
 }
 

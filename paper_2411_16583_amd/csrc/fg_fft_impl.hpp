@@ -283,8 +283,6 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
       }                                                          \
     } else if (mode == kN0Cg) {                                  \
       if constexpr (kSame) FG_N0_GO(L_, kN0Cg, kSymProj);        \
-    } else if (mode == kN0Apply) {                               \
-      if constexpr (kSame) FG_N0_GO(L_, kN0Apply, kSymProj);     \
     }                                                            \
     return parts;
     FG_FOR_AXIS(FG_CASE)

@@ -650,7 +650,8 @@ void rows64(fg_plan* P, const double* in, const Gate& gate) {
 // s and z of the residual (kRowsStart, in the working precision), their norm
 // alone (kRowsNorm; partial sums of both to P->part), or z alone in double
 // precision (kRowsApply).
-template <typename RO> Parts rows_n0(fg_plan* P, int mode, double sign, const Gate& gate) {
+template <typename RO>
+Parts rows_n0(fg_plan* P, int mode, double sign, const Gate& gate, int tile) {
   ProfScope ps(P, FG_PASS_ZPROJ);
   auto go = [&](auto z) {
     using Z = decltype(z);
@@ -665,7 +666,7 @@ template <typename RO> Parts rows_n0(fg_plan* P, int mode, double sign, const Ga
     a.blo = block_layout<RO>(P->n0, P->n1, P->M);
     a.N1 = P->n1;
     a.M = P->M;
-    a.tile = tile_zproj<double>(P);
+    a.tile = tile;
     a.planes = P->planes;
     a.tb = P->t64.spec();
     a.scale = 1.0 / (double)P->N;
@@ -690,9 +691,10 @@ template <typename RO> Parts rows_n0(fg_plan* P, int mode, double sign, const Ga
 Parts residual_pass(fg_plan* P, const int* idle, bool start, double sign = -1.0) {
   const Gate gate = Gate::flags(idle);
   rows64(P, P->S64, gate);
-  const Parts nb = !start                ? rows_n0<double>(P, kRowsNorm, sign, gate)
-                   : P->prec == FG_FP64 ? rows_n0<double>(P, kRowsStart, sign, gate)
-                                        : rows_n0<float>(P, kRowsStart, sign, gate);
+  const int tile = tile_zproj<double>(P);
+  const Parts nb = !start               ? rows_n0<double>(P, kRowsNorm, sign, gate, tile)
+                   : P->prec == FG_FP64 ? rows_n0<double>(P, kRowsStart, sign, gate, tile)
+                                        : rows_n0<float>(P, kRowsStart, sign, gate, tile);
   check_launch();
   return nb;
 }
@@ -1689,7 +1691,7 @@ fg_status fg_project_grad(fg_plan* P, const double* x, double* y) {
     P->lin_open = false;
     const Gate none{};
     rows64(P, x, none);
-    rows_n0<double>(P, kRowsApply, 1.0, none);
+    rows_n0<double>(P, kRowsApply, 1.0, none, tile_zproj<double>(P));
     if (!P->planes)
       launch_n1<double>(P->n1, true, P->n0, n1_args<double>(P, P->ln64, P->bk64, P->dc64, none), 1, P->stream);
     launch_c2r_dir<double>(P->M, dir_args<double>(P, P->ln64, P->S64, nullptr, nullptr, 3), 1, P->stream);
@@ -2331,37 +2333,68 @@ struct TilePass {
 TilePass tile_pass(int which) { return TilePass{(which & 1) != 0, (which < 2) ? 16 : 8}; }
 int tile_len(const fg_plan* P, int which) { return (which & 1) ? P->n0 : P->n1; }
 
-template <typename R>
-void time_pass_impl(fg_plan* P, bool zproj, int tile, int reps, double* ms) {
-  R *ln = (R*)P->ln, *bk = (R*)P->bk, *dc = (R*)P->dc;
-  if (sizeof(R) == 8) {
-    ln = (R*)P->ln64;
-    bk = (R*)P->bk64;
-    dc = (R*)P->dc64;
-  }
-  auto fill = [&](R* p, long n) {
-    hipLaunchKernelGGL((k_fill<R>), dim3(grid_stride_blocks(n)), dim3(256), 0, P->stream, p, (R)1e-3, n);
-  };
-  fill(ln, 3 * P->N * P->nitems);
-  fill(bk, 6 * block_layout<R>(P->n0, P->n1, P->M).cstr * P->nitems);
-  fill(dc, 6L * P->n0 * P->n1 * P->nitems);
-  check_launch();
+// One pass of precision R as the plan runs it with `tile`: the N0 or N1 pass of
+// a CG iteration where the plan has one (the working precision of a grid that
+// does not take k_plane), else the passes that read the same tile, of the residual
+// (double) or of fg_apply_operator (single).
+template <typename R> void tile_pass_launch(fg_plan* P, bool zproj, int tile) {
   const Gate none{};
-  auto launch = [&]() {
+  const bool working = (sizeof(R) == 8) == (P->prec == FG_FP64);
+  if (working && !P->planes) {
     if (zproj) {
       N0Args<R, R> a = n0_args<R, R>(P, none);
-      a.q = a.z = (cplx<R>*)bk;
-      a.dcq = a.dcz = (cplx<R>*)dc;
+      a.q = a.z = (cplx<R>*)P->bk;
+      a.dcq = a.dcz = (cplx<R>*)P->dc;
+      a.s = (cplx<R>*)P->rs;
+      a.dcs = (cplx<R>*)P->rdc;
+      a.ks = P->ks;
+      a.partials = P->part2;
       a.tile = tile;
-      launch_n0<R, R>(P->n0, kN0Apply, kSymProj, a, P->nitems, P->stream);
+      launch_n0<R, R>(P->n0, kN0Cg, kSymProj, a, P->nitems, P->stream);
     } else {
-      // the N1 work of a CG iteration: the forward and the inverse pass
-      N1Args<R> a = n1_args<R>(P, ln, bk, dc, none);
+      N1Args<R> a = n1_args<R>(P, P->ln, P->bk, P->dc, none);
       a.tile = tile;
       launch_n1<R>(P->n1, false, P->n0, a, P->nitems, P->stream);
       launch_n1<R>(P->n1, true, P->n0, a, P->nitems, P->stream);
     }
+  } else if constexpr (sizeof(R) == 8) {
+    if (zproj)
+      rows_n0<double>(P, kRowsNorm, 1.0, none, tile);
+    else
+      launch_rows_n1(P->n1, P->n0, P->S64, P->rows_dc, P->M, tile, P->t64.spec(), none, P->nitems, P->stream);
+  } else {
+    const SpecTables<R> tb = tabs<R>(P).spec();
+    if (zproj)
+      launch_zproj<R>(P->n0, (R*)P->S, P->n1, P->M, tb, (R)(1.0 / (double)P->N), Skip{}, P->stream, P->nitems, tile);
+    else
+      launch_axis<R>(P->n1, false, (R*)P->S, P->M, (long)P->n1 * P->M, (long)P->n0 * P->n1 * P->M, P->M, P->n0,
+                     9 * P->nitems, tb.tw1, Skip{}, P->stream, tile);
+  }
+}
+
+template <typename R>
+void time_pass_impl(fg_plan* P, bool zproj, int tile, int reps, double* ms) {
+  auto fill = [&](auto* p, long n) {
+    using T = std::remove_pointer_t<decltype(p)>;
+    hipLaunchKernelGGL((k_fill<T>), dim3(grid_stride_blocks(n)), dim3(256), 0, P->stream, p, (T)1e-3, n);
   };
+  // ordinary numbers wherever the passes read
+  fill(P->S64, 9 * P->N * P->nitems);
+  fill(P->rows_dc, 18L * P->n0 * P->n1 * P->nitems);
+  auto working = [&](auto zero) {
+    using T = decltype(zero);
+    const long nb = 6 * block_layout<T>(P->n0, P->n1, P->M).cstr * P->nitems, nd = 6L * P->n0 * P->n1 * P->nitems;
+    if (sizeof(T) == 4) fill((T*)P->S, 9 * P->N * P->nitems);
+    fill((T*)P->ln, 3 * P->N * P->nitems);
+    for (void* p : {P->bk, P->rs}) fill((T*)p, nb);
+    for (void* p : {P->dc, P->rdc}) fill((T*)p, nd);
+  };
+  if (P->prec == FG_FP64)
+    working(0.0);
+  else
+    working(0.0f);
+  check_launch();
+  auto launch = [&]() { tile_pass_launch<R>(P, zproj, tile); };
   hipEvent_t e0, e1;
   FG_HIP(hipEventCreate(&e0));
   FG_HIP(hipEventCreate(&e1));
