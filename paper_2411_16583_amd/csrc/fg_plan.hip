@@ -232,17 +232,18 @@ struct fg_plan {
   double* part = nullptr;        // partial sums
   double* part2 = nullptr;
   double* Fu = nullptr;          // uniform tensor (9)
-  double* S64 = nullptr;         // 9N doubles: stress / FP64 spectra
-  void* S = nullptr;             // 9N T (aliases S64 in FP64 plans)
-  void* p = nullptr;             // 9N T: direction potential pi (3N); scratch outside the CG
+  double* S64 = nullptr;         // 9N doubles: stress / FP64 spectra; within a CG iteration q and its edges
+  void* p = nullptr;             // direction potential pi: 3N T, or two buffers of it
   void* x = nullptr;             // 3N T: solution potential xi
   void* st = nullptr;            // tangent state, state_words(law) N T
-  // spectra of 3-component fields (fg_cg3.hpp): line layout, block layout
-  // and the compact kx = 0 column, and the spectral residual of the CG
+  // spectra of 3-component fields (fg_cg3.hpp): line (or plane) layout, block
+  // layout and the compact kx = 0 column, and the spectral residual of the CG;
+  // with planes there are no blocks
   void *ln = nullptr, *bk = nullptr, *dc = nullptr, *rs = nullptr, *rdc = nullptr;
-  double *ln64 = nullptr, *bk64 = nullptr, *dc64 = nullptr;  // the first three in double (aliases in FP64 plans)
+  // the first three in double (bk64 and dc64 outside the CG of a mixed plan)
+  double *ln64 = nullptr, *bk64 = nullptr, *dc64 = nullptr;
   double* rows_dc = nullptr;  // kx = 0 column of the 9 components of S64 (fg_rows.hpp)
-  void *q = nullptr, *qe = nullptr;            // divergence q (3N T) and its patch edges
+  void *q = nullptr, *qe = nullptr;  // divergence q (3N T) and its patch edges, in S64
   double* sc = nullptr;          // scalar solver area, 16N doubles
   size_t part_n = 0;
 
@@ -282,6 +283,9 @@ template <typename T> T* carve(char* base, size_t& off, size_t count) {
   return ptr;
 }
 
+// Distance of the second buffer of the CG's direction potential (0: one buffer).
+long second_pi(const fg_plan* P) { return P->lines || !P->planes ? 3 * P->N * P->nitems : 0; }
+
 size_t layout(fg_plan* P, char* base) {
   const long N = P->N;
   const long NT = P->N * P->nitems;
@@ -312,42 +316,36 @@ size_t layout(fg_plan* P, char* base) {
   P->read_bytes = base + off - (char*)P->ks;  // ks, flags, dscal: what the host reads
   P->Fu = carve<double>(base, off, 16 + 9 * P->nitems);
   // partial sums of an item: 9 per 256-voxel block, a workgroup per line of
-  // k_cg_op or per column of the N0 pass at most, plus slack for the per-item
+  // k_cg_op or per column of the N0 pass at most (three components of them, or
+  // the scalar problems' one in each half), plus slack for the per-item
   // rounding of the line passes
-  P->part_n = (size_t)P->nitems * std::max({9 * (N / 256 + 2), (long)n0 * n1, 2 * fg::n0_max_parts(n1, M)}) + 8192;
+  P->part_n = (size_t)P->nitems * std::max({9 * (N / 256 + 2), (long)n0 * n1, fg::n0_max_parts(n1, M)}) + 8192;
   P->part = carve<double>(base, off, P->part_n);
   P->part2 = carve<double>(base, off, P->part_n);
   const size_t tb = (P->prec == FG_FP64) ? sizeof(double) : sizeof(float);
-  P->S64 = carve<double>(base, off, 9 * NT);
-  if (P->prec == FG_FP64) {
-    P->S = P->S64;
-  } else {
-    P->S = carve<char>(base, off, 9 * NT * tb);
-  }
-  P->p = carve<char>(base, off, 9 * NT * tb);
+  const size_t nit = (size_t)P->nitems;
+  const size_t ne = (P->prec == FG_FP64 ? fg::edge_layout<double>(n0, n1, P->n2).comp
+                                        : fg::edge_layout<float>(n0, n1, P->n2).comp);
+  P->S64 = carve<double>(base, off, std::max((size_t)9 * NT, (3 * NT + 3 * nit * ne) * tb / sizeof(double) + 1));
+  P->q = P->S64;
+  P->qe = (char*)P->q + 3 * NT * tb;
+  P->p = carve<char>(base, off, (3 * NT + second_pi(P)) * tb);
   P->x = carve<char>(base, off, 3 * NT * tb);
   P->st = carve<char>(base, off, (size_t)fg::state_words(P->law) * NT * tb);
-  const size_t nit = (size_t)P->nitems;
-  const size_t cb64 = fg::block_layout<double>(n0, n1, M).cstr, cb32 = fg::block_layout<float>(n0, n1, M).cstr;
-  const size_t cb = (P->prec == FG_FP64) ? cb64 : cb32;
+  // (in the plane layout a component takes N, in blocks a little more)
+  const size_t cb = std::max(fg::block_layout<double>(n0, n1, M).cstr, fg::block_layout<float>(n0, n1, M).cstr);
+  const size_t nbk = P->planes ? 0 : 6 * nit * cb, ndc = P->planes ? 0 : 6 * nit * n0 * n1;
   P->ln = carve<char>(base, off, 3 * NT * tb);
-  P->bk = carve<char>(base, off, 3 * nit * cb * 2 * tb);
-  P->dc = carve<char>(base, off, 3 * nit * n0 * n1 * 2 * tb);
-  P->rs = carve<char>(base, off, 3 * nit * cb * 2 * tb);
-  P->rdc = carve<char>(base, off, 3 * nit * n0 * n1 * 2 * tb);
-  const size_t ne64 = fg::edge_layout<double>(n0, n1, P->n2).comp, ne32 = fg::edge_layout<float>(n0, n1, P->n2).comp;
-  P->q = carve<char>(base, off, 3 * NT * tb);
-  P->qe = carve<char>(base, off, 3 * nit * (P->prec == FG_FP64 ? ne64 : ne32) * tb);
+  P->bk = carve<char>(base, off, nbk * tb);
+  P->rs = carve<char>(base, off, (P->planes ? 3 * NT : nbk) * tb);
+  P->dc = carve<char>(base, off, ndc * tb);
+  P->rdc = carve<char>(base, off, ndc * tb);
   P->rows_dc = carve<double>(base, off, 18 * nit * n0 * n1);
-  if (P->prec == FG_FP64) {
-    P->ln64 = (double*)P->ln;
-    P->bk64 = (double*)P->bk;
-    P->dc64 = (double*)P->dc;
-  } else {
-    P->ln64 = carve<double>(base, off, 3 * NT);
-    P->bk64 = carve<double>(base, off, 6 * nit * cb64);
-    P->dc64 = carve<double>(base, off, 6 * nit * n0 * n1);
-  }
+  // in double: the blocks of both precisions hold the same number of values, so
+  // those of z and s together are one of z (no CG is open where these are used)
+  P->bk64 = (double*)P->bk;
+  P->dc64 = (double*)P->dc;
+  P->ln64 = (P->prec == FG_FP64) ? (double*)P->ln : carve<double>(base, off, 3 * NT);
   // scalar solvers (phase field, Fick) only on single plans; batches keep
   // just the zero fields standing in for c and d
   P->sc = carve<double>(base, off, P->nitems == 1 ? 16 * N : NT);
@@ -581,9 +579,6 @@ template <typename R, typename RO> PlaneArgs<R, RO> plane_args(fg_plan* P, const
   a.gate = gate;
   return a;
 }
-
-// Distance of the second buffer of the CG's direction potential (0: one buffer).
-long second_pi(const fg_plan* P) { return P->lines || !P->planes ? 3 * P->N * P->nitems : 0; }
 
 // Partial sums of r.r that the N0 pass of a CG of nc components leaves in part2.
 template <typename T> Parts rr_parts(fg_plan* P, int nc, int nitems) {
@@ -1020,8 +1015,8 @@ template <typename T>
 void adjoint(fg_plan* P, const double W[9], double* gE, double* gO, const fg_solver_opts* o, fg_stats* stats,
              double* Tout = nullptr) {
   const long N = P->N;
-  T* S = (T*)P->S;
-  T* pbuf = (T*)P->p;
+  T* S = (T*)P->S64;
+  T* pbuf = (T*)P->sc;
   constitutive(P, nullptr, nullptr, P->st, nullptr);
   FG_HIP(hipMemcpyAsync(P->Fu, W, 9 * sizeof(double), hipMemcpyHostToDevice, P->stream));
   hipLaunchKernelGGL((k_fill_uniform9<T>), dim3(blocks_for(N)), dim3(256), 0, P->stream, pbuf, (const double*)P->Fu,
@@ -1658,8 +1653,8 @@ fg_status fg_apply_operator(fg_plan* P, const double* x, double* y) {
       project9<double>(P, y, y, y, epi);
     } else {
       constitutive(P, nullptr, nullptr, P->st, nullptr);
-      float* xf = (float*)P->p;
-      float* yf = (float*)P->S;
+      float* xf = (float*)P->S64;
+      float* yf = xf + n9;
       hipLaunchKernelGGL((k_convert<double, float>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, xf, x,
                          n9);
       launch_contract<float>(P, yf, (const float*)xf);
@@ -2365,9 +2360,9 @@ template <typename R> void tile_pass_launch(fg_plan* P, bool zproj, int tile) {
   } else {
     const SpecTables<R> tb = tabs<R>(P).spec();
     if (zproj)
-      launch_zproj<R>(P->n0, (R*)P->S, P->n1, P->M, tb, (R)(1.0 / (double)P->N), Skip{}, P->stream, P->nitems, tile);
+      launch_zproj<R>(P->n0, (R*)P->S64, P->n1, P->M, tb, (R)(1.0 / (double)P->N), Skip{}, P->stream, P->nitems, tile);
     else
-      launch_axis<R>(P->n1, false, (R*)P->S, P->M, (long)P->n1 * P->M, (long)P->n0 * P->n1 * P->M, P->M, P->n0,
+      launch_axis<R>(P->n1, false, (R*)P->S64, P->M, (long)P->n1 * P->M, (long)P->n0 * P->n1 * P->M, P->M, P->n0,
                      9 * P->nitems, tb.tw1, Skip{}, P->stream, tile);
   }
 }
@@ -2384,7 +2379,8 @@ void time_pass_impl(fg_plan* P, bool zproj, int tile, int reps, double* ms) {
   auto working = [&](auto zero) {
     using T = decltype(zero);
     const long nb = 6 * block_layout<T>(P->n0, P->n1, P->M).cstr * P->nitems, nd = 6L * P->n0 * P->n1 * P->nitems;
-    if (sizeof(T) == 4) fill((T*)P->S, 9 * P->N * P->nitems);
+    if (sizeof(R) == 4) fill((T*)P->S64, 9 * P->N * P->nitems);
+    if (P->planes) return;
     fill((T*)P->ln, 3 * P->N * P->nitems);
     for (void* p : {P->bk, P->rs}) fill((T*)p, nb);
     for (void* p : {P->dc, P->rdc}) fill((T*)p, nd);

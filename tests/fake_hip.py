@@ -61,6 +61,9 @@ int hipEventRecord(void*, void*) { return 0; }
 int hipEventSynchronize(void*) { return fail_wait; }
 int hipEventElapsedTime(float* t, void*, void*) { *t = 1.0f; return 0; }
 int hipStreamSynchronize(void*) { return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned) { *s = (void*)8; return 0; }
+int hipStreamDestroy(void*) { return 0; }
+int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
 int hipGetLastError() { return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 const char* hipGetErrorString(int) { return "fake"; }
