@@ -347,9 +347,11 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   const unsigned shm = (unsigned)plane_lds<R>(a.n0, a.n1, a.P);
   auto go = [&](auto kernel) {
     if (shm > 65536) {
-      // (the attribute is per kernel and device; setting it again is cheap)
+      // the limit belongs to the kernel and the device, not to this launch: every
+      // launch sets the same one, so that plans of other planes in other
+      // threads do not lower it between the two (setting it again is cheap)
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPlaneLds);
       if (e != hipSuccess) throw std::runtime_error(std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
     }
     launch_ev(kernel, grid, block, shm, s, ev0, ev1, a);

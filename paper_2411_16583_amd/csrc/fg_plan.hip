@@ -108,11 +108,11 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 }
 
 // The largest plane that fits LDS in double precision is 96 x 96 (one
-// workgroup per CU), with a margin for the kernel's static LDS.  One CG
+// workgroup per CU).  One CG
 // iteration with k_plane / with the three separate passes (us): 16^3 32.7 /
 // 37.0, 64^3 54.0 / 59.5 (single precision 43.7 / 49.2), 96^3 113 / 121, 24 x
 // 96 x 48 48 / 55, plane 256 x 256 42 / 47, 48 x 96 x 192 123 / 123.
-bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= 160 * 1024 - 1024; }
+bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= kPlaneLds; }
 
 // Up to 32^3 voxels the launches and memory latencies of the separate passes
 // cost more than the transforms and the tangent that the lines kernel repeats.

@@ -49,6 +49,9 @@ template <typename R, typename RO> struct PlaneArgs {
   double *partials, *partials2;  // one per workgroup, items consecutive
 };
 
+// Most dynamic LDS that a workgroup takes: 160 KiB, with a margin for the
+// kernel's static LDS.
+constexpr size_t kPlaneLds = 160 * 1024 - 1024;
 // LDS: the planes (odd line stride), the stage twiddles and the symbol tables.
 template <typename R> inline size_t plane_lds(int n0, int n1, int P) {
   return ((size_t)P * n0 * (n1 | 1) + n0 + n1) * sizeof(cplx<R>) + 2 * (size_t)(n0 + n1) * sizeof(R);
