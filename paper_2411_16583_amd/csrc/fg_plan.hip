@@ -719,11 +719,17 @@ int next_chunk(const KrylovScalars& h, long launched) {
 }
 
 // Kernel launches of the CG loop that found the solve already converged
-// (they return at once); excluded from the profiled launch counts.
+// (they return at once); excluded from the profiled launch counts of the
+// classes that an iteration of this plan launches (cg_iteration).
 void note_noop_iterations(fg_plan* P, long noop) {
   if (!P->prof_on || noop <= 0) return;
-  for (int pass : {FG_PASS_FRONT, FG_PASS_R2C, FG_PASS_AXIS, FG_PASS_ZPROJ, FG_PASS_AXIS3, FG_PASS_C2R3})
-    if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
+  auto note = [&](std::initializer_list<int> passes) {
+    for (int pass : passes)
+      if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
+  };
+  note({FG_PASS_FRONT, FG_PASS_ZPROJ});
+  if (!P->lines) note({FG_PASS_R2C, FG_PASS_C2R3});
+  if (!P->planes) note({FG_PASS_AXIS, FG_PASS_AXIS3});
 }
 
 // End of the last CG iteration (r.r, beta, the end of the solve) before the
