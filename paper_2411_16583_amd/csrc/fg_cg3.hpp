@@ -498,7 +498,7 @@ k_r2c_edges(const R* __restrict__ q, const R* __restrict__ edge, EdgeLayout el, 
 // ---------------------------------------------------------------------------
 // N1 pass between the line layout (component, i0, i1, kx) and the block
 // layout: forward line -> block, inverse block -> line.  Grid (M / tile, N0,
-// components).  CPT = 2 (single precision): two adjacent columns per thread.
+// components).
 template <typename R> struct N1Args {
   cplx<R>* lines;
   cplx<R>* blocks;
@@ -521,7 +521,7 @@ template <typename R> struct N1Args {
   int nc;   // components per item
 };
 
-template <typename R, int L, bool INV, int CPT, bool TWL>
+template <typename R, int L, bool INV, bool TWL>
 __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
   using C = cplx<R>;
   using LS = Line<L>;
@@ -551,53 +551,34 @@ __global__ void __launch_bounds__(256) k_n1(N1Args<R> a) {
     __syncthreads();
     tw = stw;
   }
-  const int BC = B / CPT;
-  const int cg = threadIdx.x % BC;
-  const int t = threadIdx.x / BC;
-  const int kx = blockIdx.x * B + CPT * cg;
+  const int col = threadIdx.x % B;
+  const int t = threadIdx.x / B;
+  const int kx = blockIdx.x * B + col;
   C* ln = a.lines + (((long)z * N0 + i0) * L) * a.M + kx;            // + n M
   C* bk = a.blocks + (long)z * a.bl.cstr + a.bl.at(L, 0, kx) + (long)i0 * a.bl.B;  // + ky bstr
   C* dc = a.dc + (long)z * L * N0 + i0;                              // + ky N0
   const bool col0 = kx == 0;
-  C v[CPT][LS::E];
+  C v[LS::E];
 #pragma unroll
   for (int e = 0; e < LS::E; ++e) {
     const int n = LS::idxA(t, e);
-    if constexpr (CPT == 2) {
-      const float4 w = *reinterpret_cast<const float4*>(INV ? bk + n * a.bl.bstr : ln + (long)n * a.M);
-      v[0][e] = mk<C>(w.x, w.y);
-      v[CPT - 1][e] = mk<C>(w.z, w.w);
-      if (INV && col0) v[0][e] = dc[(long)n * N0];
-    } else {
-      if (INV && col0)
-        v[0][e] = dc[(long)n * N0];
-      else if constexpr (INV)
-        v[0][e] = bk[n * a.bl.bstr];
-      else  // the N2 pass streamed it out; double precision streams it in too (168 -> 147 us at 256^3)
-        v[0][e] = sizeof(R) == 8 ? ld_stream(ln + (long)n * a.M) : ln[(long)n * a.M];
-    }
+    if (INV && col0)
+      v[e] = dc[(long)n * N0];
+    else if constexpr (INV)
+      v[e] = bk[n * a.bl.bstr];
+    else  // the N2 pass streamed it out; double precision streams it in too (168 -> 147 us at 256^3)
+      v[e] = sizeof(R) == 8 ? ld_stream(ln + (long)n * a.M) : ln[(long)n * a.M];
   }
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) line_fft_AB<L, INV>(v[c], lds + CPT * cg + c, B, t, tw);
+  line_fft_AB<L, INV>(v, lds + col, B, t, tw);
 #pragma unroll
   for (int e = 0; e < LS::E; ++e) {
     const int n = LS::idxB(t, e);
-    if constexpr (CPT == 2) {
-      C* dst = INV ? ln + (long)n * a.M : bk + n * a.bl.bstr;
-      if (!INV && col0) {
-        dc[(long)n * N0] = v[0][e];
-        dst[1] = v[CPT - 1][e];
-      } else {
-        *reinterpret_cast<float4*>(dst) = make_float4(v[0][e].x, v[0][e].y, v[CPT - 1][e].x, v[CPT - 1][e].y);
-      }
-    } else if constexpr (INV) {
-      ln[(long)n * a.M] = v[0][e];
-    } else {
-      if (col0)
-        dc[(long)n * N0] = v[0][e];
-      else
-        bk[n * a.bl.bstr] = v[0][e];
-    }
+    if constexpr (INV)
+      ln[(long)n * a.M] = v[e];
+    else if (col0)
+      dc[(long)n * N0] = v[e];
+    else
+      bk[n * a.bl.bstr] = v[e];
   }
 }
 

@@ -317,7 +317,8 @@ __device__ __forceinline__ double thread_parts(const double* __restrict__ partia
   return acc;
 }
 __device__ __forceinline__ double sum_parts(const double* __restrict__ partials, const Parts ps, double* red) {
-  if (ps.r == 1) return sum_partials(partials, ps.groups, red);
+  // (plain sums with more loads in flight; groups in one order whatever r is)
+  if (ps.groups == ps.head) return sum_partials(partials, ps.groups, red);
   return block_sum(thread_parts(partials, ps, threadIdx.x, blockDim.x), red);
 }
 // The same by a workgroup of any size, the same number for every size; buf:

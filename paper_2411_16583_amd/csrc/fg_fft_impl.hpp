@@ -186,42 +186,32 @@ void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate
 
 template <typename R>
 void launch_n1(int N1, bool inv, int N0, N1Args<R> a, int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  int tile = a.tile;
-  int cpt = (sizeof(R) == 4 && (tile & kTileColumnPairs)) ? 2 : 1;
-  tile &= ~kTileColumnPairs;
   const int T = line_threads(N1);
-  const int B = tile > 0 ? tile : column_tile_cpt(N1, a.M, (int)sizeof(cplx<R>), cpt);
-  if (B % cpt != 0) cpt = 1;
+  int B = a.tile & ~kTileColumnPairs;
+  if (B == 0) B = column_tile(N1, a.M, (int)sizeof(cplx<R>));
+  while (B > 1 && T * B > 256) B /= 2;  // a tile of column pairs: one column per thread here
   // single precision reads the stage twiddles from LDS where they fit beside
   // the exchange buffer (as launch_axis)
   const bool twl = sizeof(R) == 4 && (size_t)(N1 * B + N1) * sizeof(cplx<R>) <= 65536;
   const size_t shm = (size_t)(N1 * B + (twl ? N1 : 0)) * sizeof(cplx<R>);
   a.tile = B;
   const dim3 grid((unsigned)(a.M / B), (unsigned)(N0 + (a.ks ? 1 : 0)), (unsigned)(a.nc * nitems));
-  const dim3 block((unsigned)(T * B / cpt));
-  constexpr int CP = (sizeof(R) == 4) ? 2 : 1;
+  const dim3 block((unsigned)(T * B));
   constexpr bool TW = sizeof(R) == 4;
   switch (N1) {
-#define FG_N1_GO(L_, INV_, CPT_)                                                               \
-  do {                                                                                         \
-    if (twl)                                                                                   \
-      launch_ev((k_n1<R, L_, INV_, CPT_, TW>), grid, block, (unsigned)shm, s, ev0, ev1, a);    \
-    else                                                                                       \
-      launch_ev((k_n1<R, L_, INV_, CPT_, false>), grid, block, (unsigned)shm, s, ev0, ev1, a); \
+#define FG_N1_GO(L_, INV_)                                                                \
+  do {                                                                                    \
+    if (twl)                                                                              \
+      launch_ev((k_n1<R, L_, INV_, TW>), grid, block, (unsigned)shm, s, ev0, ev1, a);     \
+    else                                                                                  \
+      launch_ev((k_n1<R, L_, INV_, false>), grid, block, (unsigned)shm, s, ev0, ev1, a);  \
   } while (0)
-#define FG_CASE(L_)                \
-  case L_:                         \
-    if (cpt == 2) {                \
-      if (inv)                     \
-        FG_N1_GO(L_, true, CP);    \
-      else                         \
-        FG_N1_GO(L_, false, CP);   \
-    } else {                       \
-      if (inv)                     \
-        FG_N1_GO(L_, true, 1);     \
-      else                         \
-        FG_N1_GO(L_, false, 1);    \
-    }                              \
+#define FG_CASE(L_)          \
+  case L_:                   \
+    if (inv)                 \
+      FG_N1_GO(L_, true);    \
+    else                     \
+      FG_N1_GO(L_, false);   \
     return;
     FG_FOR_N1(FG_CASE)
 #undef FG_CASE
@@ -239,6 +229,9 @@ template <typename R> N0Tile n0_tile(int N0, int N1, int M, int tile, int nc) {
   t.kymajor = (tile == 0 || (tile & kTileKyMajor)) ? 1 : 0;
   int B = tile & ~kTileKyMajor;
   if (B == 0) B = zgrad_tile(N0, M, eb);
+  // two columns per thread round differently from one (other contractions): no
+  // single column where there are pairs
+  if (B == 1 && zgrad_cpt(N0, eb) == 2 && M % 2 == 0) B = 2;
   auto cpt_of = [&](int b) { return (b % 2 == 0) ? zgrad_cpt(N0, eb) : 1; };
   while (B > 1 && T * B / cpt_of(B) > 256) B /= 2;  // a tile chosen for another line shape
   t.B = B;
