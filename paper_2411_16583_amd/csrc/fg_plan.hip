@@ -108,10 +108,16 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 }
 
 // The largest plane that fits LDS in double precision is 96 x 96 (one
-// workgroup per CU).  One CG
-// iteration with k_plane / with the three separate passes (us): 16^3 32.7 /
-// 37.0, 64^3 54.0 / 59.5 (single precision 43.7 / 49.2), 96^3 113 / 121, 24 x
-// 96 x 48 48 / 55, plane 256 x 256 42 / 47, 48 x 96 x 192 123 / 123.
+// workgroup per CU).  Whether its 3 M workgroups fill the chip or not, one CG
+// iteration with k_plane / with the three separate passes took (us, FP64 |
+// single precision):
+//   64 x 64 x 4 27 / 44 | 23 / 49, x 16 40 / 42 | 35 / 40, x 64 50 / 54 | 41 / 46, x 128 66 / 74 | 51 / 57
+//   96 x 96 x 4 55 / 64 | 44 / 67, x 8 57 / 56 | 45 / 61, x 16 66 / 59 | 50 / 53, x 32 74 / 67 | 53 / 56,
+//     x 48 88 / 95 | 67 / 78, x 96 110 / 112 | 76 / 85, x 192 213 / 219 | 122 / 124
+//   48 x 96 x 192 122 / 117 | 79 / 81, 24 x 256 x 64 70 / 70 | 52 / 54, plane 256 x 256 40 / 43 | 37 / 38
+// so the plane alone decides: its length N2 moves the two by less than 12%
+// (the worst, 96 x 96 x 16 in double precision, against 1.2 to 2 times on short
+// small planes).
 bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= kPlaneLds; }
 
 // Up to 32^3 voxels the launches and memory latencies of the separate passes
