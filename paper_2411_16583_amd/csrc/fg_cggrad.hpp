@@ -50,6 +50,9 @@ k_grad_store(const TI* __restrict__ U, long ucs, long uis, TO* __restrict__ Z, l
   }
 }
 
+// Two doubles of a caller's field, which is aligned to 8 bytes and no more.
+typedef double Pair8 __attribute__((ext_vector_type(2), aligned(8)));
+
 // x = D (xi + alpha pi) of every item not idle, evaluated in double
 // precision (a discrete gradient: compatible to rounding whatever the
 // precision of xi), added to Z (ADD) or stored there.  The deferred step
@@ -113,13 +116,12 @@ k_cg_result(const T* __restrict__ xi, const T* __restrict__ pi, long pi2, int pa
     corner_grad<double, 2>(u, q0, q1, q2, D);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      double2* z = reinterpret_cast<double2*>(Z + (3 * c + j) * N) + g;
-      if constexpr (ADD) {
-        const double2 f = *z;
-        *z = make_double2(f.x + D[j][0], f.y + D[j][1]);
-      } else {
-        *z = make_double2(D[j][0], D[j][1]);
-      }
+      Pair8* z = reinterpret_cast<Pair8*>(Z + (3 * c + j) * N) + g;
+      const Pair8 d = {D[j][0], D[j][1]};
+      if constexpr (ADD)
+        *z = *z + d;
+      else
+        *z = d;
     }
   }
 }
