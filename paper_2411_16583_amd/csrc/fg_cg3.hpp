@@ -56,6 +56,19 @@ template <typename R, int W, typename PV> __device__ __forceinline__ PV pk_load_
   return v;
 }
 
+// W consecutive values in 16-byte stores (one of 8 where that is all).
+template <int W, typename R> __device__ __forceinline__ void store_run(R* p, const R (&v)[W]) {
+  constexpr int n = (W * (int)sizeof(R) > 16) ? 16 / (int)sizeof(R) : W;
+  using PV = typename FrontPack<R, n>::type;
+#pragma unroll
+  for (int w = 0; w < W; w += n) {
+    PV o;
+#pragma unroll
+    for (int k = 0; k < n; ++k) pk_set<R>(o, k, v[w + k]);
+    reinterpret_cast<PV*>(p)[w / n] = o;
+  }
+}
+
 // Per-item mask of a launch: items with a nonzero word are left alone.
 struct Gate {
   const int* p = nullptr;
@@ -123,9 +136,9 @@ template <typename R> inline EdgeLayout edge_layout(int n0, int n1, int n2) {
   return e;
 }
 
-template <typename R> struct OpArgs {
-  R* q;                // out: 3 N per item
-  R* edge;             // out: 3 el.comp per item
+template <typename R, typename RQ> struct OpArgs {
+  RQ* q;               // out: 3 N per item
+  RQ* edge;            // out: 3 el.comp per item
   const R* pi;         // direction potential, 3 N per item:
   long pi2;            // the running iteration's of two buffers pi2 values apart
   const KrylovScalars* ks;
@@ -148,9 +161,10 @@ constexpr int kOpThreads = 256;
 // in registers.  Inside the patch a node's contributions come from the lanes
 // of the next voxels and of the next line; what crosses the patch's edges is
 // stored apart (EdgeLayout), so nothing is computed twice, no workgroup
-// barrier is needed and the waves run freely.
-template <typename R, int W, int LAW>
-__global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
+// barrier is needed and the waves run freely.  RQ: precision of the divergence
+// (the sums, q and its edges).
+template <typename R, typename RQ, int W, int LAW>
+__global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R, RQ> a) {
   using PV = typename FrontPack<R, W>::type;
   __shared__ double red[16];
   const unsigned lb = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -171,8 +185,9 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
   const long N = (long)a.n0 * a.n1 * a.n2;
   const R* pi = a.pi + (long)item * 3 * N + (a.ks[item].run_iter & 1) * a.pi2;
   const R* st = a.st + (long)item * state_words(LAW) * N;
-  R* q = a.q + (long)item * 3 * N;
-  R* edge = a.edge + (long)item * 3 * a.el.comp;
+  RQ* q = a.q + (long)item * 3 * N;
+  RQ* edge = a.edge + (long)item * 3 * a.el.comp;
+  const RQ h0 = a.q0, h1 = a.q1, h2 = a.q2;
   // the next voxels (line) of the patch are in the lane one (eight) above
   const bool lastx = gx == kPatch - 1 || x + W >= a.n2;
   const bool lastl = l == kPatch - 1 || i1 + 1 >= a.n1;
@@ -285,49 +300,46 @@ __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R> a) {
       const long nline = (long)(v - 1) * a.n1 + i1;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        R f0[W], f1[W], c0[W], c1[W];  // to node i2 / node i2 - 1, of node line i1 (0) and i1 - 1 (1)
+        RQ f0[W], f1[W], c0[W], c1[W];  // to node i2 / node i2 - 1, of node line i1 (0) and i1 - 1 (1)
 #pragma unroll
         for (int w = 0; w < W; ++w) {
           // no contraction: the contributions of equal neighbours cancel
           // exactly (a uniform field has zero divergence, not rounding)
 #pragma clang fp contract(off)
-          const R d0 = a.q0 * (Yp[3 * i][w] - Yc[3 * i][w]);
-          const R s1 = a.q1 * (Yp[3 * i + 1][w] + Yc[3 * i + 1][w]);
-          const R s2 = a.q2 * (Yp[3 * i + 2][w] + Yc[3 * i + 2][w]);
-          const R u0 = d0 + s1, u1 = d0 - s1;
+          const RQ d0 = h0 * ((RQ)Yp[3 * i][w] - (RQ)Yc[3 * i][w]);
+          const RQ s1 = h1 * ((RQ)Yp[3 * i + 1][w] + (RQ)Yc[3 * i + 1][w]);
+          const RQ s2 = h2 * ((RQ)Yp[3 * i + 2][w] + (RQ)Yc[3 * i + 2][w]);
+          const RQ u0 = d0 + s1, u1 = d0 - s1;
           f0[w] = u0 + s2;
           c0[w] = u0 - s2;
           f1[w] = u1 + s2;
           c1[w] = u1 - s2;
         }
-        const R n0 = __shfl_down(c0[0], 1), n1 = __shfl_down(c1[0], 1);
-        const R cl = __shfl_down(c1[0], kPatch);
-        R Tp[W];
+        const RQ n0 = __shfl_down(c0[0], 1), n1 = __shfl_down(c1[0], 1);
+        const RQ cl = __shfl_down(c1[0], kPatch);
+        RQ Tp[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          const R cp = (w + 1 < W) ? c0[w + 1 < W ? w + 1 : w] : (lastx ? R(0) : n0);
-          const R cm = (w + 1 < W) ? c1[w + 1 < W ? w + 1 : w] : (lastx ? R(0) : n1);
+          const RQ cp = (w + 1 < W) ? c0[w + 1 < W ? w + 1 : w] : (lastx ? RQ(0) : n0);
+          const RQ cm = (w + 1 < W) ? c1[w + 1 < W ? w + 1 : w] : (lastx ? RQ(0) : n1);
           Tp[w] = f0[w] + cp;
           f1[w] += cm;  // the whole contribution to node line i1 - 1
         }
-        PV out;
+        RQ out[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          const R t = __shfl_down(f1[w], kPatch);
-          pk_set<R>(out, w, Tp[w] + (lastl ? R(0) : t));
+          const RQ t = __shfl_down(f1[w], kPatch);
+          out[w] = Tp[w] + (lastl ? RQ(0) : t);
         }
         if (active) {
-          *reinterpret_cast<PV*>(q + i * N + nline * a.n2 + x) = out;
-          R* ec = edge + i * a.el.comp;
+          store_run<W>(q + i * N + nline * a.n2 + x, out);
+          RQ* ec = edge + i * a.el.comp;
           if (l == 0) {
-            PV r;
-#pragma unroll
-            for (int w = 0; w < W; ++w) pk_set<R>(r, w, f1[w]);
             const long b = (long)(v - 1) * a.el.nb + blk;
-            *reinterpret_cast<PV*>(ec + a.el.row + b * a.n2 + x) = r;
+            store_run<W>(ec + a.el.row + b * a.n2 + x, f1);
             if (gx == 0) ec[a.el.cor + b * a.el.np + patch] = c1[0];
           }
-          if (gx == 0) ec[a.el.col + nline * a.el.np + patch] = c0[0] + (lastl ? R(0) : cl);
+          if (gx == 0) ec[a.el.col + nline * a.el.np + patch] = c0[0] + (lastl ? RQ(0) : cl);
         }
       }
     }

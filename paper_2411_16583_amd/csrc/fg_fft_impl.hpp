@@ -123,11 +123,11 @@ void launch_zproj(int N0, R* data, int N1, int M, const SpecTables<R>& tb, R sca
   throw std::invalid_argument("unsupported N0");
 }
 
-template <typename R>
-int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
-                 const Gate& gate, int n0, int n1,
-                 int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  OpArgs<R> a;
+template <typename R, typename RQ>
+int launch_cg_op(int law, RQ* q, RQ* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st,
+                 double* partials, const Gate& gate, int n0, int n1, int n2, const double h[3], int nitems,
+                 hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+  OpArgs<R, RQ> a;
   a.el = edge_layout<R>(n0, n1, n2);
   const OpSplit sp = op_split(n0, n1, n2, a.el, nitems);
   a.q = q;
@@ -151,9 +151,9 @@ int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScal
     constexpr int W = decltype(width)::value;
     const dim3 grid((unsigned)((long)sp.groups * nitems)), block(kOpThreads);
     if (law == kLawSVK)
-      launch_ev((k_cg_op<R, W, kLawSVK>), grid, block, 0, s, ev0, ev1, a);
+      launch_ev((k_cg_op<R, RQ, W, kLawSVK>), grid, block, 0, s, ev0, ev1, a);
     else
-      launch_ev((k_cg_op<R, W, kLawNH>), grid, block, 0, s, ev0, ev1, a);
+      launch_ev((k_cg_op<R, RQ, W, kLawNH>), grid, block, 0, s, ev0, ev1, a);
   };
   if constexpr (sizeof(R) == 4) {
     if (a.el.W8 == 4 * kPatch) {
@@ -166,9 +166,8 @@ int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScal
 }
 
 template <typename R>
-void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
+void launch_r2c_edges(int M, const R* q, const R* edge, const EdgeLayout& el, R* out, const Gate& gate, int n0, int n1,
                       const SpecTables<R>& tb, int nitems, int planes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  const EdgeLayout el = edge_layout<R>(n0, n1, 2 * M);
   switch (M) {
 #define FG_CASE(L_)                                                                                              \
   case L_: {                                                                                                     \
@@ -275,7 +274,7 @@ Parts launch_n0(int N0, int mode, int sym, N0Args<R, RO> a, int nitems, hipStrea
           FG_N0_GO(L_, kN0Start, kSymLap);                       \
       }                                                          \
     } else if (mode == kN0Cg) {                                  \
-      if constexpr (kSame) FG_N0_GO(L_, kN0Cg, kSymProj);        \
+      FG_N0_GO(L_, kN0Cg, kSymProj);                             \
     }                                                            \
     return parts;
     FG_FOR_AXIS(FG_CASE)
@@ -359,12 +358,12 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
         go(k_plane<R, RO, kN0Start, kSymLap, TH>);
     }
   } else if (mode == kN0Cg) {
-    if constexpr (kSame && sizeof(R) == 4) {
+    if constexpr (sizeof(R) == 4) {
       if (shared)
         go(k_plane<R, RO, kN0Cg, kSymProj, 1024>);
       else
         go(k_plane<R, RO, kN0Cg, kSymProj, 768>);
-    } else if constexpr (kSame) {
+    } else {
       go(k_plane<R, RO, kN0Cg, kSymProj, TH>);
     }
   }
@@ -372,10 +371,10 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
 }
 
 #define FG_INSTANTIATE_LAUNCHERS(R)                                                                     \
-  template int launch_cg_op<R>(int, R*, R*, const R*, long, const KrylovScalars*, const R*, double*, const Gate&, int, int, int, const double*, \
-                               int, hipStream_t, hipEvent_t, hipEvent_t);                               \
-  template void launch_r2c_edges<R>(int, const R*, const R*, R*, const Gate&, int, int, const SpecTables<R>&, int, \
-                                    int, hipStream_t, hipEvent_t, hipEvent_t);                          \
+  template int launch_cg_op<R, R>(int, R*, R*, const R*, long, const KrylovScalars*, const R*, double*, const Gate&,  \
+                                  int, int, int, const double*, int, hipStream_t, hipEvent_t, hipEvent_t); \
+  template void launch_r2c_edges<R>(int, const R*, const R*, const EdgeLayout&, R*, const Gate&, int, int,            \
+                                    const SpecTables<R>&, int, int, hipStream_t, hipEvent_t, hipEvent_t);  \
   template void launch_n1<R>(int, bool, int, N1Args<R>, int, hipStream_t, hipEvent_t, hipEvent_t);      \
   template N0Tile n0_tile<R>(int, int, int, int, int);                                                  \
   template Parts launch_n0<R, R>(int, int, int, N0Args<R, R>, int, hipStream_t, hipEvent_t, hipEvent_t);       \

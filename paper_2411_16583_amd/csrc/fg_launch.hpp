@@ -53,16 +53,16 @@ struct OpSplit {
 };
 OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems);
 
-// q = D^T K : (D pi) for all items, as k_cg_op leaves it (q and its patch edges);
+// q = D^T K : (D pi) for all items, as k_cg_op leaves it (q and its patch edges,
+// in precision RQ);
 // h: grid spacings.  Returns the number of partial sums of p.Kp per item.
+template <typename R, typename RQ>
+int launch_cg_op(int law, RQ* q, RQ* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st,
+                 double* partials, const Gate& gate, int n0, int n1, int n2, const double h[3], int nitems,
+                 hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// N2 transform of q with its patch edges added (el: the operator's).
 template <typename R>
-int launch_cg_op(int law, R* q, R* edge, const R* pi, long pi2, const KrylovScalars* ks, const R* st, double* partials,
-                 const Gate& gate, int n0, int n1,
-                 int n2, const double h[3], int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
-                 hipEvent_t ev1 = nullptr);
-// N2 transform of q with its patch edges added.
-template <typename R>
-void launch_r2c_edges(int M, const R* q, const R* edge, R* out, const Gate& gate, int n0, int n1,
+void launch_r2c_edges(int M, const R* q, const R* edge, const EdgeLayout& el, R* out, const Gate& gate, int n0, int n1,
                       const SpecTables<R>& tb, int nitems, int planes, hipStream_t s, hipEvent_t ev0 = nullptr,
                       hipEvent_t ev1 = nullptr);
 // N1 pass between the line layout and the block layout (k_n1), 3 components
@@ -111,6 +111,9 @@ template <typename R>
 void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEvent_t ev0 = nullptr,
                     hipEvent_t ev1 = nullptr);
 
+// Whether the open system of a mixed plan keeps the divergence of an iteration and
+// its spectrum in double precision.
+bool divergence_wide(const int n[3], const double h[3]);
 // Lines per workgroup of k_cg_lines for a plan (0: the grid takes the passes).
 int lines_per_group(int n0, int n1, int M, int nitems);
 // The inverse N2 pass, the operator and the N2 pass of a CG iteration in one

@@ -120,6 +120,32 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 // small planes).
 bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= kPlaneLds; }
 
+// Whether the iterates of a mixed plan's open system (fg_cg_iterate), which
+// nothing refines, keep q in double precision.  The rounding of q = D^T Y and of
+// its transforms is white, and the projection amplifies it on long waves, the
+// more the further the grid is from a cube.  Error of 12 CG iterates over that
+// of an iteration whose nine components are projected in the spectrum, with q
+// in single precision, the worst of six loads on a white two-phase material:
+//   64^3 1.01, 128^3 1.00, sides 2:1 1.14 (128 x 128 x 64 1.22), 3:1 1.41, 4:1
+//   1.51, 128 x 96 x 8 2.6, voxels 1.25:1 1.07, 1.5:1 1.14, 2:1 1.27, 16:1 2.5
+// (an inclusion: 0.1 to 0.5 up to 4:1); with q in double 0.04 to 0.46 on every
+// grid.  So the line is at sides of 2:1 and voxels of 1.5:1, within which single
+// precision is as often better as worse.  Double costs an iteration, single |
+// double (us): 64^3 41 | 47, 96 x 96 x 192 122 | 163, 48 x 96 x 192 79 | 97,
+// 128 x 8 x 16 24 | 34 (with nine components 85, 202, 139, 77).  Solves that
+// refine their correction by a double-precision residual (Newton, the adjoint,
+// a batch) take single precision on every grid: their results are the same.
+bool divergence_wide(const int n[3], const double h[3]) {
+  int lo = 1 << 30, hi = 0;
+  for (int k = 0; k < 3; ++k) {
+    if (n[k] == 1) continue;  // (a plane)
+    lo = std::min(lo, n[k]);
+    hi = std::max(hi, n[k]);
+  }
+  const double hmin = std::min({h[0], h[1], h[2]}), hmax = std::max({h[0], h[1], h[2]});
+  return hi > 2 * lo || hmax > 1.5 * hmin;
+}
+
 // Up to 32^3 voxels the launches and memory latencies of the separate passes
 // cost more than the transforms and the tangent that the lines kernel repeats.
 // CG iteration with it / with the passes (us, FP64): 16^3 22.9 / 31.2, 24^3
@@ -218,6 +244,8 @@ struct fg_plan {
   int tiles_gen = 0;  // bumped by fg_plan_set_tiles (a captured batch graph is then stale)
   int lines = 0;        // lines per workgroup of k_cg_lines (0: not taken)
   bool planes = false;  // the N1 and N0 passes of the CG run as one (k_plane)
+  bool far = false;     // mixed form, far from cubic: an open system runs wide
+  bool wide = false;    // this CG keeps q and its spectrum in double precision
   int law = ::FG_LAW_NEO_HOOKE;  // material law (fg_set_law, before the workspace)
   double h[3];
   fg_precision prec;
@@ -249,7 +277,8 @@ struct fg_plan {
   // the first three in double (bk64 and dc64 outside the CG of a mixed plan)
   double *ln64 = nullptr, *bk64 = nullptr, *dc64 = nullptr;
   double* rows_dc = nullptr;  // kx = 0 column of the 9 components of S64 (fg_rows.hpp)
-  void *q = nullptr, *qe = nullptr;  // divergence q (3N T) and its patch edges, in S64
+  void *q = nullptr, *qe = nullptr;    // divergence q (3N) and its patch edges, in S64
+  void *wbk = nullptr, *wdc = nullptr;  // wide: spectrum of q after its N1 pass, in S64
   double* sc = nullptr;          // scalar solver area, 16N doubles
   size_t part_n = 0;
 
@@ -289,8 +318,10 @@ template <typename T> T* carve(char* base, size_t& off, size_t count) {
   return ptr;
 }
 
+// Whether an iteration runs as k_cg_lines and k_plane.
+bool as_lines(const fg_plan* P) { return P->lines && !P->wide; }
 // Distance of the second buffer of the CG's direction potential (0: one buffer).
-long second_pi(const fg_plan* P) { return P->lines || !P->planes ? 3 * P->N * P->nitems : 0; }
+long second_pi(const fg_plan* P) { return as_lines(P) || !P->planes ? 3 * P->N * P->nitems : 0; }
 
 size_t layout(fg_plan* P, char* base) {
   const long N = P->N;
@@ -332,15 +363,28 @@ size_t layout(fg_plan* P, char* base) {
   const size_t nit = (size_t)P->nitems;
   const size_t ne = (P->prec == FG_FP64 ? fg::edge_layout<double>(n0, n1, P->n2).comp
                                         : fg::edge_layout<float>(n0, n1, P->n2).comp);
-  P->S64 = carve<double>(base, off, std::max((size_t)9 * NT, (3 * NT + 3 * nit * ne) * tb / sizeof(double) + 1));
-  P->q = P->S64;
-  P->qe = (char*)P->q + 3 * NT * tb;
+  const size_t cb = std::max(fg::block_layout<double>(n0, n1, M).cstr, fg::block_layout<float>(n0, n1, M).cstr);
+  const size_t nbk = P->planes ? 0 : 6 * nit * cb, ndc = P->planes ? 0 : 6 * nit * n0 * n1;
+  // the stress field, and what lives within a CG iteration: q, its edges and
+  // (wide) the spectrum of q after its N1 pass
+  {
+    const size_t tq = P->far ? sizeof(double) : tb;
+    size_t in = 0;
+    char* at = nullptr;
+    auto sub = [&](size_t n) { return (size_t)(carve<char>(at, in, n) - at); };
+    const size_t oq = sub(3 * NT * tq), oe = sub(3 * nit * ne * tq), ob = sub(P->far ? nbk * tq : 0),
+                 od = sub(P->far ? ndc * tq : 0);
+    P->S64 = (double*)carve<char>(base, off, std::max(9 * NT * sizeof(double), in));
+    char* S = (char*)P->S64;
+    P->q = S + oq;
+    P->qe = S + oe;
+    P->wbk = S + ob;
+    P->wdc = S + od;
+  }
   P->p = carve<char>(base, off, (3 * NT + second_pi(P)) * tb);
   P->x = carve<char>(base, off, 3 * NT * tb);
   P->st = carve<char>(base, off, (size_t)fg::state_words(P->law) * NT * tb);
   // (in the plane layout a component takes N, in blocks a little more)
-  const size_t cb = std::max(fg::block_layout<double>(n0, n1, M).cstr, fg::block_layout<float>(n0, n1, M).cstr);
-  const size_t nbk = P->planes ? 0 : 6 * nit * cb, ndc = P->planes ? 0 : 6 * nit * n0 * n1;
   P->ln = carve<char>(base, off, 3 * NT * tb);
   P->bk = carve<char>(base, off, nbk * tb);
   P->rs = carve<char>(base, off, (P->planes ? 3 * NT : nbk) * tb);
@@ -734,32 +778,40 @@ void note_noop_iterations(fg_plan* P, long noop) {
       if (P->prof_mask >> pass & 1u) P->prof_noop[pass] += noop;
   };
   note({FG_PASS_FRONT, FG_PASS_ZPROJ});
-  if (!P->lines) note({FG_PASS_R2C, FG_PASS_C2R3});
+  if (!as_lines(P)) note({FG_PASS_R2C, FG_PASS_C2R3});
   if (!P->planes) note({FG_PASS_AXIS, FG_PASS_AXIS3});
+}
+
+// N2 spectrum of q in precision RQ (that of z in the same place where RQ is the
+// working precision).
+template <typename RQ> void* line_spectrum(fg_plan* P) { return sizeof(RQ) == 8 ? (void*)P->ln64 : P->ln; }
+
+// Partial sums of r.r of an iteration.
+template <typename T> Parts cg_parts(fg_plan* P) {
+  return P->wide ? rr_parts<double>(P, 3, P->nitems) : rr_parts<T>(P, 3, P->nitems);
 }
 
 // End of the last CG iteration (r.r, beta, the end of the solve) before the
 // scalars are read; between iterations the next pass does it itself.
 template <typename T> void cg_end(fg_plan* P) {
   ProfScope ps(P, FG_PASS_FINALIZE, true);
-  launch_ev(k_cg_close, dim3(P->nitems), dim3(P->planes && !P->lines ? XBLOCK : 256), 0, P->stream, ps.start, ps.stop,
-            (const double*)P->part2, (const double*)nullptr, rr_parts<T>(P, 3, P->nitems), P->ks, P->planes);
+  launch_ev(k_cg_close, dim3(P->nitems), dim3(P->planes && !as_lines(P) ? XBLOCK : 256), 0, P->stream, ps.start, ps.stop,
+            (const double*)P->part2, (const double*)nullptr, cg_parts<T>(P), P->ks, P->planes);
   check_launch();
 }
 
 // The passes of an iteration in front of the spectrum of q: z, the CG vectors,
-// q and its N2 transform.  Returns the partial sums of p.Kp.
-template <typename T> int cg_front_passes(fg_plan* P) {
+// q and its N2 transform (in precision RQ).  Returns the partial sums of p.Kp.
+template <typename T, typename RQ> int cg_front_passes(fg_plan* P) {
   const int nit = P->nitems;
   KrylovScalars* ks = P->ks;
-  const SpecTables<T> tb = tabs<T>(P).spec();
   const Gate gate = Gate::done(ks);
   if (!P->planes) {
     ProfScope ps(P, FG_PASS_AXIS3, true);
     N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
     a.ks = ks;
     a.prr = P->part2;
-    a.parts = rr_parts<T>(P, 3, nit);
+    a.parts = cg_parts<T>(P);
     launch_n1<T>(P->n1, true, P->n0, a, nit, P->stream, ps.start, ps.stop);
   }
   {
@@ -769,13 +821,14 @@ template <typename T> int cg_front_passes(fg_plan* P) {
   int nbf;
   {
     ProfScope ps(P, FG_PASS_FRONT, true);
-    nbf = launch_cg_op<T>(P->law, (T*)P->q, (T*)P->qe, (const T*)P->p, second_pi(P), ks, (const T*)P->st, P->part, gate, P->n0, P->n1,
-                          P->n2, P->h, nit, P->stream, ps.start, ps.stop);
+    nbf = launch_cg_op<T, RQ>(P->law, (RQ*)P->q, (RQ*)P->qe, (const T*)P->p, second_pi(P), ks, (const T*)P->st,
+                              P->part, gate, P->n0, P->n1, P->n2, P->h, nit, P->stream, ps.start, ps.stop);
   }
   {
     ProfScope ps(P, FG_PASS_R2C, true);
-    launch_r2c_edges<T>(P->M, (const T*)P->q, (const T*)P->qe, (T*)P->ln, gate, P->n0, P->n1, tb, nit, P->planes,
-                        P->stream, ps.start, ps.stop);
+    launch_r2c_edges<RQ>(P->M, (const RQ*)P->q, (const RQ*)P->qe, edge_layout<T>(P->n0, P->n1, P->n2),
+                         (RQ*)line_spectrum<RQ>(P), gate, P->n0, P->n1, tabs<RQ>(P).spec(), nit, P->planes, P->stream,
+                         ps.start, ps.stop);
   }
   return nbf;
 }
@@ -791,7 +844,7 @@ template <typename T> int cg_front_lines(fg_plan* P) {
   a.st = (const T*)P->st;
   a.ks = P->ks;
   a.prr = P->part2;
-  a.np = rr_parts<T>(P, 3, P->nitems).groups;
+  a.np = cg_parts<T>(P).groups;
   a.partials = P->part;
   a.n0 = P->n0;
   a.n1 = P->n1;
@@ -804,46 +857,56 @@ template <typename T> int cg_front_lines(fg_plan* P) {
 }
 
 // One CG iteration for every item of the plan (items whose solve is done
-// skip every kernel): the passes of fg_cg3.hpp.  It starts from z_k in the
-// block layout (left by residual_pass or by the iteration before).
-template <typename T>
-void cg_iteration(fg_plan* P) {
+// skip every kernel): the passes of fg_cg3.hpp, the forward ones in precision
+// RQ.  It starts from z_k in the block layout (left by residual_pass or by the
+// iteration before).
+template <typename T, typename RQ> void cg_passes(fg_plan* P) {
   const int nit = P->nitems;
   KrylovScalars* ks = P->ks;
   const Gate gate = Gate::done(ks);
-  const int nbf = P->lines ? cg_front_lines<T>(P) : cg_front_passes<T>(P);
+  const int nbf = as_lines(P) ? cg_front_lines<T>(P) : cg_front_passes<T, RQ>(P);
   if (P->planes) {
     ProfScope ps(P, FG_PASS_ZPROJ, true);
-    PlaneArgs<T, T> a = plane_args<T, T>(P, gate);
-    a.q = (const cplx<T>*)(P->lines ? P->q : P->ln);
+    PlaneArgs<RQ, T> a = plane_args<RQ, T>(P, gate);
+    a.q = (const cplx<RQ>*)(as_lines(P) ? P->q : line_spectrum<RQ>(P));
     a.z = (cplx<T>*)P->ln;
     a.s = (cplx<T>*)P->rs;
     a.pap = P->part;
     a.npap = nbf;
     a.ks = ks;
     a.partials = P->part2;
-    launch_plane<T, T>(kN0Cg, kSymProj, a, 3, nit, P->stream, ps.start, ps.stop);
+    launch_plane<RQ, T>(kN0Cg, kSymProj, a, 3, nit, P->stream, ps.start, ps.stop);
   } else {
+    void* bq = sizeof(RQ) > sizeof(T) ? P->wbk : P->bk;
+    void* dq = sizeof(RQ) > sizeof(T) ? P->wdc : P->dc;
     {
       // alpha = r.r / p.Kp is formed by the N1 pass (one workgroup per item)
       ProfScope ps(P, FG_PASS_AXIS, true);
-      N1Args<T> a = n1_args<T>(P, P->ln, P->bk, P->dc, gate);
+      N1Args<RQ> a = n1_args<RQ>(P, line_spectrum<RQ>(P), bq, dq, gate);
       a.pap = P->part;
       a.npap = nbf;
       a.ks = ks;
-      launch_n1<T>(P->n1, false, P->n0, a, nit, P->stream, ps.start, ps.stop);
+      launch_n1<RQ>(P->n1, false, P->n0, a, nit, P->stream, ps.start, ps.stop);
     }
     ProfScope ps(P, FG_PASS_ZPROJ, true);
-    N0Args<T, T> a = n0_args<T, T>(P, gate);
-    a.q = a.z = (cplx<T>*)P->bk;
-    a.dcq = a.dcz = (cplx<T>*)P->dc;
+    N0Args<RQ, T> a = n0_args<RQ, T>(P, gate);
+    a.q = (const cplx<RQ>*)bq;
+    a.dcq = (const cplx<RQ>*)dq;
+    a.z = (cplx<T>*)P->bk;
+    a.dcz = (cplx<T>*)P->dc;
     a.s = (cplx<T>*)P->rs;
     a.dcs = (cplx<T>*)P->rdc;
     a.ks = ks;
     a.partials = P->part2;
-    launch_n0<T, T>(P->n0, kN0Cg, kSymProj, a, nit, P->stream, ps.start, ps.stop);
+    launch_n0<RQ, T>(P->n0, kN0Cg, kSymProj, a, nit, P->stream, ps.start, ps.stop);
   }
   check_launch();
+}
+template <typename T> void cg_iteration(fg_plan* P) {
+  if (sizeof(T) == 4 && P->wide)
+    cg_passes<T, double>(P);
+  else
+    cg_passes<T, T>(P);
 }
 
 // Krylov scalars of a single-item CG whose start residual_pass left the
@@ -860,7 +923,7 @@ void cg_result(fg_plan* P, double* dst, bool add, const int* idle = nullptr) {
     using T = decltype(tag);
     const T *xi = (const T*)P->x, *pi = (const T*)P->p;
     const long pi2 = second_pi(P);
-    const int pairs = pi2 != 0 && P->lines == 0;
+    const int pairs = pi2 != 0 && !as_lines(P);
     if (add)
       launch_cg_result<T, true>(xi, pi, pi2, pairs, P->ks, dst, idle, P->n0, P->n1, P->n2, P->nitems, P->h, P->stream);
     else
@@ -1387,6 +1450,7 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
   P->nitems = nitems;
   P->prec = prec;
   P->planes = fg::plane_fits(P->n0, P->n1);
+  P->far = prec == FG_MIXED && nitems == 1 && fg::divergence_wide(grid, spacing);
   P->lines = P->planes ? fg::lines_per_group(P->n0, P->n1, P->M, P->nitems) : 0;
   P->stream = (hipStream_t)stream;
   P->need = layout(P, nullptr) + kAlign;
@@ -1405,6 +1469,7 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
 void need_ready(fg_plan* P, bool need_state) {
   if (P->batch_group) throw Status(FG_E_ARG, "a batch group plan takes only the tile calls");
   P->lin_open = false;  // every solver call reuses the CG workspace
+  P->wide = false;
   if (!P->ws) throw Status(FG_E_STATE, "workspace not set");
   if (!P->have_material) throw Status(FG_E_STATE, "material not set");
   if (need_state && !P->F) throw Status(FG_E_STATE, "state not set");
@@ -1537,6 +1602,7 @@ fg_status fg_newton_linear_begin(fg_plan* P, const double F_macro[9], double* er
     const double err = newton_residual(P, residual_denominator(P, F_macro));
     if (err_res) *err_res = err;
     P->lin_open = true;
+    P->wide = P->far;  // (nothing refines the iterates)
   });
 }
 
