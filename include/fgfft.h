@@ -172,7 +172,9 @@ fg_status fg_newton_solve_shifted(fg_plan* plan, const double* B, const fg_solve
  * host, 9 doubles.  Synchronises.  Errors: FG_E_STATE, FG_E_DOMAIN,
  * FG_E_HIP.
  * fg_cg_iterate continues that CG by exactly n iterations (n >= 0; no
- * tolerance test, the iterations are those fg_newton_solve runs).  With
+ * tolerance test; the iterations are those fg_newton_solve runs, but that a
+ * mixed plan whose spacings differ by more than 1.5:1 keeps the divergence of an
+ * iteration in double precision, as no residual refines its iterates).  With
  * apply != 0 it then adds the CG iterate dF to F (double precision) and the
  * system is closed.  Any other call on the plan that uses its workspace also
  * closes it; fg_cg_iterate on a closed system returns FG_E_STATE.  stats (may

@@ -113,7 +113,7 @@ void launch_c2r_dir(int M, const DirArgs<R>& a, int nitems, hipStream_t s, hipEv
 
 // Whether the open system of a mixed plan keeps the divergence of an iteration and
 // its spectrum in double precision.
-bool divergence_wide(const int n[3], const double h[3]);
+bool divergence_wide(const double h[3]);
 // Lines per workgroup of k_cg_lines for a plan (0: the grid takes the passes).
 int lines_per_group(int n0, int n1, int M, int nitems);
 // The inverse N2 pass, the operator and the N2 pass of a CG iteration in one

@@ -121,29 +121,22 @@ OpSplit op_split(int n0, int n1, int n2, const EdgeLayout& el, int nitems) {
 bool plane_fits(int n0, int n1) { return plane_lds<double>(n0, n1, 1) <= kPlaneLds; }
 
 // Whether the iterates of a mixed plan's open system (fg_cg_iterate), which
-// nothing refines, keep q in double precision.  The rounding of q = D^T Y and of
-// its transforms is white, and the projection amplifies it on long waves, the
-// more the further the grid is from a cube.  Error of 12 CG iterates over that
-// of an iteration whose nine components are projected in the spectrum, with q
-// in single precision, the worst of six loads on a white two-phase material:
-//   64^3 1.01, 128^3 1.00, sides 2:1 1.14 (128 x 128 x 64 1.22), 3:1 1.41, 4:1
-//   1.51, 128 x 96 x 8 2.6, voxels 1.25:1 1.07, 1.5:1 1.14, 2:1 1.27, 16:1 2.5
-// (an inclusion: 0.1 to 0.5 up to 4:1); with q in double 0.04 to 0.46 on every
-// grid.  So the line is at sides of 2:1 and voxels of 1.5:1, within which single
-// precision is as often better as worse.  Double costs an iteration, single |
-// double (us): 64^3 41 | 47, 96 x 96 x 192 122 | 163, 48 x 96 x 192 79 | 97,
-// 128 x 8 x 16 24 | 34 (with nine components 85, 202, 139, 77).  Solves that
-// refine their correction by a double-precision residual (Newton, the adjoint,
-// a batch) take single precision on every grid: their results are the same.
-bool divergence_wide(const int n[3], const double h[3]) {
-  int lo = 1 << 30, hi = 0;
-  for (int k = 0; k < 3; ++k) {
-    if (n[k] == 1) continue;  // (a plane)
-    lo = std::min(lo, n[k]);
-    hi = std::max(hi, n[k]);
-  }
-  const double hmin = std::min({h[0], h[1], h[2]}), hmax = std::max({h[0], h[1], h[2]});
-  return hi > 2 * lo || hmax > 1.5 * hmin;
+// nothing refines, keep q in double precision: on elongated voxels.  The
+// rounding of q = D^T Y and of its transforms is white, and the projection
+// amplifies it on long waves.  Error of 12 CG iterates over that of an iteration
+// whose nine components are projected in the spectrum, on 64^3 voxels of a
+// white two-phase material, the worst of six loads, q in single precision:
+// voxels 1:1 1.01, 1.25:1 1.07, 1.5:1 1.14, 2:1 1.27, 4:1 1.9 (of an inclusion
+// 0.1 to 0.4); 32^3 at 4:1:16 2.5.  In double 0.04 to 0.46 on every grid.  So the
+// line is at 1.5:1, within which single precision is as often better as worse.
+// (Cubic voxels keep it on thin grids too, where it is up to 1.5 at sides of 4:1
+// and 2.6 on 128 x 96 x 8.)  Double costs an iteration, single | double (us):
+// 64^3 41 | 47, 96 x 96 x 192 122 | 163, 48 x 96 x 192 79 | 97 (with nine
+// components 85, 202, 139).  Solves that refine their correction by a
+// double-precision residual (Newton, the adjoint, a batch) take single precision
+// on every grid: their results are the same.
+bool divergence_wide(const double h[3]) {
+  return std::max({h[0], h[1], h[2]}) > 1.5 * std::min({h[0], h[1], h[2]});
 }
 
 // Up to 32^3 voxels the launches and memory latencies of the separate passes
@@ -244,7 +237,7 @@ struct fg_plan {
   int tiles_gen = 0;  // bumped by fg_plan_set_tiles (a captured batch graph is then stale)
   int lines = 0;        // lines per workgroup of k_cg_lines (0: not taken)
   bool planes = false;  // the N1 and N0 passes of the CG run as one (k_plane)
-  bool far = false;     // mixed form, far from cubic: an open system runs wide
+  bool far = false;     // mixed form, elongated voxels: an open system runs wide
   bool wide = false;    // this CG keeps q and its spectrum in double precision
   int law = ::FG_LAW_NEO_HOOKE;  // material law (fg_set_law, before the workspace)
   double h[3];
@@ -1450,7 +1443,7 @@ fg_status plan_new(const int grid[3], const double spacing[3], fg_precision prec
   P->nitems = nitems;
   P->prec = prec;
   P->planes = fg::plane_fits(P->n0, P->n1);
-  P->far = prec == FG_MIXED && nitems == 1 && fg::divergence_wide(grid, spacing);
+  P->far = prec == FG_MIXED && nitems == 1 && fg::divergence_wide(spacing);
   P->lines = P->planes ? fg::lines_per_group(P->n0, P->n1, P->M, P->nitems) : 0;
   P->stream = (hipStream_t)stream;
   P->need = layout(P, nullptr) + kAlign;
