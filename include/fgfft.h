@@ -411,11 +411,12 @@ enum {
   FG_PASS_FRONT = 0,        /* CG operator q = D^T K : (D pi) and p.Kp; on
                                small grids with both N2 passes             */
   FG_PASS_R2C = 1,          /* real-to-complex pass along N2               */
-  FG_PASS_AXIS = 2,         /* forward complex pass along N1               */
+  FG_PASS_AXIS = 2,         /* forward complex pass along N1 (fg_project:
+                               both)                                       */
   FG_PASS_ZPROJ = 3,        /* N0 pass with the residual and its symbol
                                (small planes: with the N1 passes)          */
   FG_PASS_C2R = 4,          /* N2 complex-to-real pass (9 components)      */
-  FG_PASS_CG_UPDATE = 5,    /* vector updates of the scalar PCGs           */
+  FG_PASS_CG_UPDATE = 5,    /* no longer taken                             */
   FG_PASS_FINALIZE = 6,     /* Krylov scalars before the host reads them   */
   FG_PASS_CONSTITUTIVE = 7, /* stress and tangent state                    */
   FG_PASS_ZSCALAR = 8,      /* N0 pass fused with a scalar symbol          */

@@ -33,11 +33,6 @@
 
 namespace fg {
 
-// W consecutive voxels of one plane in one 16-byte (or 8-byte) access.
-template <typename R, int W> struct FrontPack;
-template <> struct FrontPack<double, 2> { using type = double2; };
-template <> struct FrontPack<float, 2> { using type = float2; };
-template <> struct FrontPack<float, 4> { using type = float4; };
 template <typename R, typename PV> __device__ __forceinline__ R pk_get(const PV& v, int w) {
   return reinterpret_cast<const R*>(&v)[w];
 }
@@ -59,7 +54,7 @@ template <typename R, int W, typename PV> __device__ __forceinline__ PV pk_load_
 // W consecutive values in 16-byte stores (one of 8 where that is all).
 template <int W, typename R> __device__ __forceinline__ void store_run(R* p, const R (&v)[W]) {
   constexpr int n = (W * (int)sizeof(R) > 16) ? 16 / (int)sizeof(R) : W;
-  using PV = typename FrontPack<R, n>::type;
+  using PV = typename VecW<R, n>::type;
 #pragma unroll
   for (int w = 0; w < W; w += n) {
     PV o;
@@ -165,7 +160,7 @@ constexpr int kOpThreads = 256;
 // (the sums, q and its edges).
 template <typename R, typename RQ, int W, int LAW>
 __global__ void __launch_bounds__(kOpThreads) k_cg_op(OpArgs<R, RQ> a) {
-  using PV = typename FrontPack<R, W>::type;
+  using PV = typename VecW<R, W>::type;
   __shared__ double red[16];
   const unsigned lb = xcd_contiguous(blockIdx.x, gridDim.x);
   const int item = (int)(lb / (unsigned)a.groups);

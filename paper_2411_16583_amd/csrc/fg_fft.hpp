@@ -65,8 +65,6 @@ struct Skip {
   const int* gate = nullptr;  // nullptr: never skip
   int stride = 0;             // ints between the words of consecutive items
   long per_item = 1L << 62;   // grid units (lines, planes or rows) per item
-  long item_stride = 0;       // real passes: lines between the first lines of consecutive items (0: per_item)
-  int sub = 1;                // real passes: per_item counts sub-items, sub of them per gated item
   __host__ __device__ int item(long unit) const { return (int)(unit / per_item); }
   __device__ __forceinline__ bool operator()(long unit) const {
     return gate && gate[(long)item(unit) * stride] != 0;
@@ -76,7 +74,7 @@ struct Skip {
     s.per_item = per;
     return s;
   }
-  __device__ __forceinline__ bool masked(int item) const { return gate && gate[(long)(item / sub) * stride] != 0; }
+  __device__ __forceinline__ bool masked(int item) const { return gate && gate[(long)item * stride] != 0; }
   // Workgroups of lpb lines over nlines lines (per_item lines per item) that
   // never straddle two items: ceil(lines per item / lpb) workgroups per item.
   __host__ __device__ long item_lines(long nlines) const { return per_item < nlines ? per_item : nlines; }
@@ -97,7 +95,7 @@ __device__ __forceinline__ LineMap map_line(const Skip& sk, long nlines, int lpb
   const long bpi = (lpi + lpb - 1) / lpb;
   const long it = (long)blockIdx.x / bpi;
   const long lin = ((long)blockIdx.x - it * bpi) * lpb + ll;
-  return LineMap{it * (sk.item_stride > 0 ? sk.item_stride : lpi) + lin, lin < lpi, (int)it};
+  return LineMap{it * lpi + lin, lin < lpi, (int)it};
 }
 static_assert(sizeof(KrylovScalars) % sizeof(int) == 0, "gate stride");
 
@@ -465,27 +463,15 @@ k_fft_x_r2c(const R* in, R* out, long nlines, SpecTables<R> tb, Skip skip) {
   }
 }
 
-// Epilogue of the inverse real pass: y = scale * x_out is stored (type R,
-// into out) and sum(y * dotv) (or sum(y*y) when dotv == nullptr) is reduced
-// per block into partials[blockIdx.x] (FP64).  A block skips everything when
-// *skip is nonzero.
-struct C2REpi {
-  double scale;
-  const void* dotv;  // same type R as the output, or nullptr
-  bool self_dot;     // sum y*y
-  double* partials;  // nullptr: no reduction
-  Skip skip;         // per-item early exit (units: lines)
-};
-
+// Inverse real pass: y = scale * x_out (type R, into out).
 template <typename R, int M>
 __global__ void __launch_bounds__(XBLOCK)
-k_fft_x_c2r(const R* in, R* out, long nlines, SpecTables<R> tb, C2REpi epi) {
+k_fft_x_c2r(const R* in, R* out, long nlines, SpecTables<R> tb, double scale, Skip skip) {
   using C = cplx<R>;
   using LS = Line<M>;
   constexpr int LPB = XBLOCK / LS::T;
   constexpr int PAD = (M >= 16) ? 1 : 0;
   __shared__ C lds[LPB * (M + PAD)];
-  __shared__ double red[16];
   // the line's stage twiddles and the C2R pre-processing factors, read once
   // per workgroup (the barrier after the line load orders them); from the
   // caches they cost the pass 71 -> 65 us in single precision at 256^3
@@ -496,8 +482,8 @@ k_fft_x_c2r(const R* in, R* out, long nlines, SpecTables<R> tb, C2REpi epi) {
   }
   const int t = threadIdx.x % LS::T;
   const int ll = threadIdx.x / LS::T;
-  const LineMap lm = map_line(epi.skip, nlines, LPB, ll);
-  if (epi.skip.masked(lm.item)) return;
+  const LineMap lm = map_line(skip, nlines, LPB, ll);
+  if (skip.masked(lm.item)) return;
   const long line = lm.line;
   const bool active = lm.active;
   const C* src = reinterpret_cast<const C*>(in) + line * M;
@@ -529,9 +515,7 @@ k_fft_x_c2r(const R* in, R* out, long nlines, SpecTables<R> tb, C2REpi epi) {
   line_fft_AB<M, true>(v, my, 1, t, stw);
   // v[e] = N2 * (x[2n] + i x[2n+1]) with n = idxB(t, e)
   C* dst = reinterpret_cast<C*>(out) + line * M;
-  const C* dv = reinterpret_cast<const C*>(epi.dotv) + line * M;
-  const R sg = (R)epi.scale;
-  double acc = 0.0;
+  const R sg = (R)scale;
 #pragma unroll
   for (int e = 0; e < LS::E; ++e) {
     const int n = LS::idxB(t, e);
@@ -541,19 +525,7 @@ k_fft_x_c2r(const R* in, R* out, long nlines, SpecTables<R> tb, C2REpi epi) {
         st_stream(dst + n, y);
       else
         dst[n] = y;
-      if (epi.partials) {
-        if (epi.self_dot) {
-          acc += (double)y.x * (double)y.x + (double)y.y * (double)y.y;
-        } else {
-          const C q = dv[n];
-          acc += (double)y.x * (double)q.x + (double)y.y * (double)q.y;
-        }
-      }
     }
-  }
-  if (epi.partials) {
-    const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) epi.partials[blockIdx.x] = s;
   }
 }
 

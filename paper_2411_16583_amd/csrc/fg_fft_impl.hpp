@@ -31,16 +31,16 @@ void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb
 }
 
 template <typename R>
-int launch_c2r(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const C2REpi& epi,
-               hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+void launch_c2r(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, double scale, const Skip& skip,
+                hipStream_t s) {
   switch (M) {
-#define FG_CASE(L_)                                                                        \
-  case L_: {                                                                               \
-    constexpr int LPB = XBLOCK / Line<L_>::T;                                              \
-    const long blocks = epi.skip.line_blocks(nlines, LPB);                                 \
-    launch_ev((k_fft_x_c2r<R, L_>), dim3((unsigned)blocks), dim3(XBLOCK), 0, s, ev0, ev1, in, out, \
-              nlines, tb, epi);                                                            \
-    return (int)blocks;                                                                    \
+#define FG_CASE(L_)                                                                                      \
+  case L_: {                                                                                             \
+    constexpr int LPB = XBLOCK / Line<L_>::T;                                                            \
+    const long blocks = skip.line_blocks(nlines, LPB);                                                   \
+    hipLaunchKernelGGL((k_fft_x_c2r<R, L_>), dim3((unsigned)blocks), dim3(XBLOCK), 0, s, in, out, nlines, \
+                       tb, scale, skip);                                                                 \
+    return;                                                                                              \
   }
     FG_FOR_M(FG_CASE)
 #undef FG_CASE
@@ -332,7 +332,7 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   a.dn1 = FastDiv(a.n1);
   const dim3 grid((unsigned)(a.groups * nitems));
   // a thread per line task where the bound allows
-  const int tasks = a.P * std::max(a.n0 * plane_line_threads(a.n1), a.n1 * plane_line_threads(a.n0));
+  const int tasks = a.P * std::max(a.n0 * zline_threads(a.n1), a.n1 * zline_threads(a.n0));
   // (see the kernel's launch bounds)
   const bool shared = sizeof(R) == 4 && a.groups * nitems > 256;
   const dim3 block((unsigned)std::min(sizeof(R) == 8 || shared ? 512 : 768, (tasks + 63) / 64 * 64));
@@ -382,8 +382,7 @@ Parts launch_plane(int mode, int sym, PlaneArgs<R, RO> a, int nc, int nitems, hi
   template int launch_cg_lines<R>(int, int, LinesArgs<R>, int, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_c2r_dir<R>(int, const DirArgs<R>&, int, hipStream_t, hipEvent_t, hipEvent_t);     \
   template void launch_r2c<R>(int, const R*, R*, long, const SpecTables<R>&, const Skip&, hipStream_t); \
-  template int launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, const C2REpi&, hipStream_t, hipEvent_t, \
-                             hipEvent_t);                                                           \
+  template void launch_c2r<R>(int, const R*, R*, long, const SpecTables<R>&, double, const Skip&, hipStream_t); \
   template void launch_axis<R>(int, bool, R*, long, long, long, int, int, int, const cplx<R>*, const Skip&, \
                                hipStream_t, int, hipEvent_t, hipEvent_t);                               \
   template void launch_zproj<R>(int, R*, int, int, const SpecTables<R>&, R, const Skip&, hipStream_t, int, int);

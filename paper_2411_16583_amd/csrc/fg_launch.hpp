@@ -125,10 +125,9 @@ int launch_cg_lines(int law, int M, LinesArgs<R> a, int nitems, hipStream_t s, h
 template <typename R>
 void launch_r2c(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const Skip& skip,
                 hipStream_t s);
-// returns the number of blocks (= partials written when epi.partials != nullptr)
 template <typename R>
-int launch_c2r(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, const C2REpi& epi,
-               hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_c2r(int M, const R* in, R* out, long nlines, const SpecTables<R>& tb, double scale, const Skip& skip,
+                hipStream_t s);
 // tile: columns per workgroup (0: column_tile).
 template <typename R>
 void launch_axis(int L, bool inv, R* data, long estride, long ystride, long zstride, int M, int gy, int gz,

@@ -539,48 +539,39 @@ template <typename R> int tile_axis(const fg_plan* P) { return P->tiles[sizeof(R
 template <typename R> int tile_zproj(const fg_plan* P) { return P->tiles[sizeof(R) == 8 ? 1 : 3]; }
 
 // Forward passes 1 and 2 (N2 real-to-complex, N1 complex) of ncomp fields,
-// in -> data (in may equal data).  In a batch the ncomp fields are
-// ncomp / nitems per item, item-major; skip masks whole items.
-template <typename R>
-void fwd_xy(fg_plan* P, const R* in, R* data, int ncomp, const Skip& skip) {
+// in -> data (in may equal data).
+template <typename R> void fwd_xy(fg_plan* P, const R* in, R* data, int ncomp) {
   const SpecTables<R> tb = tabs<R>(P).spec();
-  const long cpi = ncomp / P->nitems;
   {
     ProfScope ps(P, FG_PASS_R2C);
-    launch_r2c<R>(P->M, in, data, (long)ncomp * P->n0 * P->n1, tb, skip.unit(cpi * P->n0 * P->n1), P->stream);
+    launch_r2c<R>(P->M, in, data, (long)ncomp * P->n0 * P->n1, tb, Skip{}, P->stream);
   }
   ProfScope ps(P, FG_PASS_AXIS);
-  launch_axis<R>(P->n1, false, data, P->M, (long)P->n1 * P->M, 0, P->M, ncomp * P->n0, 1, tb.tw1,
-                 skip.unit(cpi * P->n0), P->stream, tile_axis<R>(P));
+  launch_axis<R>(P->n1, false, data, P->M, (long)P->n1 * P->M, 0, P->M, ncomp * P->n0, 1, tb.tw1, Skip{}, P->stream,
+                 tile_axis<R>(P));
 }
 
-// Inverse passes 2 and 1, data -> out with the C2R epilogue; returns #partials.
-template <typename R>
-int inv_yx(fg_plan* P, R* data, R* out, int ncomp, const C2REpi& epi) {
+// Inverse passes 2 and 1, data -> out, times scale.
+template <typename R> void inv_yx(fg_plan* P, R* data, R* out, int ncomp, double scale) {
   const SpecTables<R> tb = tabs<R>(P).spec();
-  const long cpi = ncomp / P->nitems;
   {
     ProfScope ps(P, FG_PASS_AXIS);
-    launch_axis<R>(P->n1, true, data, P->M, (long)P->n1 * P->M, 0, P->M, ncomp * P->n0, 1, tb.tw1,
-                   epi.skip.unit(cpi * P->n0), P->stream, tile_axis<R>(P));
+    launch_axis<R>(P->n1, true, data, P->M, (long)P->n1 * P->M, 0, P->M, ncomp * P->n0, 1, tb.tw1, Skip{}, P->stream,
+                   tile_axis<R>(P));
   }
   ProfScope ps(P, FG_PASS_C2R);
-  C2REpi e = epi;
-  e.skip = epi.skip.unit(cpi * P->n0 * P->n1);
-  return launch_c2r<R>(P->M, data, out, (long)ncomp * P->n0 * P->n1, tb, e, P->stream);
+  launch_c2r<R>(P->M, data, out, (long)ncomp * P->n0 * P->n1, tb, scale, Skip{}, P->stream);
 }
 
-// y = G * x for the 9-component fields of all items (projection); returns
-// the number of partials (all items; nitems divides it).
-template <typename R>
-int project9(fg_plan* P, const R* in, R* work, R* out, const C2REpi& epi) {
-  fwd_xy<R>(P, in, work, 9 * P->nitems, epi.skip);
+// out = G * in for a 9-component field (projection).
+template <typename R> void project9(fg_plan* P, const R* in, R* work, R* out) {
+  fwd_xy<R>(P, in, work, 9);
   {
     ProfScope ps(P, FG_PASS_ZPROJ);
-    launch_zproj<R>(P->n0, work, P->n1, P->M, tabs<R>(P).spec(), (R)(1.0 / (double)P->N), epi.skip.unit(3),
-                    P->stream, P->nitems, tile_zproj<R>(P));
+    launch_zproj<R>(P->n0, work, P->n1, P->M, tabs<R>(P).spec(), (R)(1.0 / (double)P->N), Skip{}, P->stream, 1,
+                    tile_zproj<R>(P));
   }
-  return inv_yx<R>(P, work, out, 9 * P->nitems, epi);
+  inv_yx<R>(P, work, out, 9, 1.0);
 }
 
 // Arguments of the N1 and N0 passes of nc-component fields.
@@ -1720,8 +1711,7 @@ fg_status fg_apply_operator(fg_plan* P, const double* x, double* y) {
       constitutive(P, nullptr, nullptr, P->st, nullptr);
       launch_contract<double>(P, y, x);
       check_launch();
-      C2REpi epi{1.0, nullptr, true, nullptr, Skip{}};
-      project9<double>(P, y, y, y, epi);
+      project9<double>(P, y, y, y);
     } else {
       constitutive(P, nullptr, nullptr, P->st, nullptr);
       float* xf = (float*)P->S64;
@@ -1730,8 +1720,7 @@ fg_status fg_apply_operator(fg_plan* P, const double* x, double* y) {
                          n9);
       launch_contract<float>(P, yf, (const float*)xf);
       check_launch();
-      C2REpi epi{1.0, nullptr, true, nullptr, Skip{}};
-      project9<float>(P, yf, yf, yf, epi);
+      project9<float>(P, yf, yf, yf);
       hipLaunchKernelGGL((k_convert<float, double>), dim3(grid_stride_blocks(n9)), dim3(256), 0, P->stream, y,
                          (const float*)yf, n9);
     }
@@ -1744,8 +1733,7 @@ fg_status fg_project(fg_plan* P, const double* x, double* y) {
   return run(P, [&]() {
     if (!P->ws) throw Status(FG_E_STATE, "workspace not set");
     P->lin_open = false;
-    C2REpi epi{1.0, nullptr, true, nullptr, Skip{}};
-    project9<double>(P, x, P->S64, y, epi);
+    project9<double>(P, x, P->S64, y);
     check_launch();
   });
 }
@@ -1773,7 +1761,7 @@ fg_status fg_fft_r2c(fg_plan* P, double* data, int ncomp) {
     if (!P->ws) throw Status(FG_E_STATE, "workspace not set");
     P->lin_open = false;
     const SpecTables<double> tb = P->t64.spec();
-    fwd_xy<double>(P, data, data, ncomp, Skip{});
+    fwd_xy<double>(P, data, data, ncomp);
     launch_axis<double>(P->n0, false, data, (long)P->n1 * P->M, P->M, (long)P->n0 * P->n1 * P->M, P->M, P->n1,
                         ncomp, tb.tw0, Skip{}, P->stream);
     check_launch();
@@ -1788,8 +1776,7 @@ fg_status fg_fft_c2r(fg_plan* P, double* data, int ncomp) {
     const SpecTables<double> tb = P->t64.spec();
     launch_axis<double>(P->n0, true, data, (long)P->n1 * P->M, P->M, (long)P->n0 * P->n1 * P->M, P->M, P->n1,
                         ncomp, tb.tw0, Skip{}, P->stream);
-    C2REpi epi{1.0 / (double)P->N, nullptr, true, nullptr, Skip{}};
-    inv_yx<double>(P, data, data, ncomp, epi);
+    inv_yx<double>(P, data, data, ncomp, 1.0 / (double)P->N);
     check_launch();
   });
 }
@@ -1941,8 +1928,9 @@ struct fg_batch {
 
 namespace {
 
-// Items per group: bounded by the grid limits of the N1 pass (9 N0 planes
-// per item on grid.y) and the N0 pass (3 rows per item on grid.z).
+// Items per group.  The N1 passes of a batch take three per item on grid.z, which
+// would allow 65535 / 3; the cap is lower (455 items at 16^3), and larger groups
+// have not been measured against several of this size.
 int max_items_per_group(const int grid[3]) { return std::max(1, 65535 / (9 * grid[0])); }
 
 fg_status batch_run(fg_batch* B, const std::function<void()>& fn) {
@@ -2669,8 +2657,7 @@ fg_status fg_project_noalloc(const int grid[3], const double spacing[3], const d
     const int nt = std::max(std::max(P.n0, P.n1), P.M + 1);
     hipLaunchKernelGGL(k_tables_f64, dim3((nt + 255) / 256), dim3(256), 0, P.stream, t, P.n0, P.n1, P.n2, P.h[0],
                        P.h[1], P.h[2]);
-    C2REpi epi{1.0, nullptr, true, nullptr, Skip{}};
-    project9<double>(&P, x, P.S64, y, epi);
+    project9<double>(&P, x, P.S64, y);
     return hipGetLastError() == hipSuccess ? FG_OK : FG_E_HIP;
   } catch (...) {
     return FG_E_HIP;

@@ -57,41 +57,12 @@ template <typename R> inline size_t plane_lds(int n0, int n1, int P) {
   return ((size_t)P * n0 * (n1 | 1) + n0 + n1) * sizeof(cplx<R>) + 2 * (size_t)(n0 + n1) * sizeof(R);
 }
 
-// Line of the plane kernel: lines within a wave.
-template <int L> struct PlaneLineSel {
-  using type = Line2Ops<L>;
-};
-template <> struct PlaneLineSel<96> {
-  using type = Line3<96>;
-};
-template <> struct PlaneLineSel<128> {
-  using type = Line3<128>;
-};
-template <> struct PlaneLineSel<256> {
-  using type = Line3<256>;
-};
-template <> struct PlaneLineSel<512> {
-  using type = Line3<512>;
-};
-template <int L> using PlaneLine = typename PlaneLineSel<L>::type;
-inline int plane_line_threads(int L) {
-  switch (L) {
-    case 16: case 32: case 48: return 4;
-    case 24: return 2;
-    case 64: case 96: return 8;
-    case 128: return 16;
-    case 256: return 32;
-    case 512: return 64;
-    default: return 1;
-  }
-}
-
 #define FG_PLANE_LINES(X) X(1) X(4) X(6) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256) X(512)
 
 // Forward N1 lines: global rows -> LDS rows (natural ky).
 template <int L, typename C>
 __device__ __forceinline__ void plane_rows_fwd(const C* __restrict__ src, C* x, int nl, const C* tw) {
-  using LS = PlaneLine<L>;
+  using LS = ZLine<L>;
   static_assert(64 % LS::T == 0, "lines within one wave");
   constexpr int LD = L | 1;
   for (int task = threadIdx.x; task < nl * LS::T; task += blockDim.x) {
@@ -108,7 +79,7 @@ __device__ __forceinline__ void plane_rows_fwd(const C* __restrict__ src, C* x, 
 // Inverse N1 lines: LDS rows -> global rows.
 template <int L, typename C, typename CO>
 __device__ __forceinline__ void plane_rows_inv(C* x, CO* __restrict__ dst, int nl, const C* tw) {
-  using LS = PlaneLine<L>;
+  using LS = ZLine<L>;
   using RO = decltype(CO::x);
   constexpr int LD = L | 1;
   for (int task = threadIdx.x; task < nl * LS::T; task += blockDim.x) {
@@ -138,7 +109,7 @@ template <int T> __device__ __forceinline__ void plane_col(int task, int& col, i
 template <int L, bool LOADS, bool INV, typename C, typename CO, typename F>
 __device__ __forceinline__ void plane_cols(C* x, int LD, int n1, FastDiv dn1, int P, const CO* __restrict__ s,
                                            const C* tw, F op) {
-  using LS = PlaneLine<L>;
+  using LS = ZLine<L>;
   const int ncol = P * n1, tasks = (ncol * LS::T + 63) / 64 * 64;
   for (int task = threadIdx.x; task < tasks; task += blockDim.x) {
     int col, t;
@@ -175,7 +146,7 @@ __device__ __forceinline__ void plane_cols(C* x, int LD, int n1, FastDiv dn1, in
 // Inverse N0 lines alone (natural kz in LDS).
 template <int L, typename C>
 __device__ __forceinline__ void plane_cols_inv(C* x, int LD, int n1, FastDiv dn1, int P, const C* tw) {
-  using LS = PlaneLine<L>;
+  using LS = ZLine<L>;
   const int ncol = P * n1, tasks = (ncol * LS::T + 63) / 64 * 64;
   for (int task = threadIdx.x; task < tasks; task += blockDim.x) {
     int col, t;

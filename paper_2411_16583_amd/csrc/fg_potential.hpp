@@ -82,13 +82,4 @@ __device__ __forceinline__ unsigned xcd_contiguous(unsigned flat, unsigned total
   return (x < r) ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-// Storage of the CG potentials of one item: rho (residual), pi (direction)
-// and xi (solution), 3 components of N values each, at the start of the
-// item's 9 N-value regions of the r, p and x buffers.  rho and pi alternate
-// between the halves [0, 3N) and [3N, 6N) by iteration parity: a kernel
-// reads its neighbours' corners of the old values while it writes new ones,
-// so old and new never share memory.  At iteration k (KrylovScalars::iter):
-//   rho_k in half k % 2, pi_k in half k % 2 (pi_{k-1} in the other half).
-__host__ __device__ constexpr long pot_half(int iter, long N) { return (long)(iter & 1) * 3 * N; }
-
 }  // namespace fg
