@@ -42,7 +42,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 
 # Algorithmic bytes per voxel and launch for each kernel class of the
 # mechanics CG iteration, in words of the working precision (the spectrum
-# occupies the same bytes as the real field): 63 in all.
+# occupies the same bytes as the real field): 61.5 in all.
 WORDS_MOVED = {
     "front": 18,      # read pi (3) + state (12); write the divergence q (3)
     "r2c": 6,         # N2 pass of q: read 3, write 3
@@ -54,8 +54,8 @@ WORDS_MOVED = {
     "c2r3": 13.5,
 }
 # The iteration that carried nine components through the N2 and N1 passes and
-# the residual in real space (81 words): the model of profiles that name no
-# model of their own, and the unit of the older records.
+# the residual in real space (81 words): the model of results that name none,
+# as the older records do.
 WORDS_PER_VOXEL = {
     "front": 36,      # read rho, pi, xi (9) + state (12); write xi, pi (6), spectrum (9)
     "axis": 15,       # N1 pass of the 9-component spectrum: read 9, write 6 (2 merged fields per row)

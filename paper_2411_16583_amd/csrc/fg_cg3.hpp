@@ -11,16 +11,18 @@
 // components through the transforms instead of nine, and with the residual
 // kept where it is needed, in the spectrum (s^ is read and written by the N0
 // pass; no real-space residual update).  Passes of one iteration (words per
-// voxel, 63 in all; us at 256^3 in double / single precision):
-//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     13.5  344 / 180
-//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6  537 / 252
-//   k_r2c_edges  N2 pass of q                                                6.6  153 /  91
-//   k_n1         N1 pass into the block layout (+ alpha)                     6    148 /  77
-//   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12    295 / 156
-//   k_n1         inverse N1 pass (+ beta, the end of the solve)              6    175 /  78
-// 4.9-5.8 TB/s where a plain copy reaches 4.4: bound by HBM.  The iteration
-// that carried nine components through the N2 and N1 passes and the residual
-// in real space moved 81 words: 2180 / 1040 us against 1660 / 840.
+// voxel, 62.7 in all; us at 256^3 in double / single precision):
+//   k_c2r_dir    inverse N2 pass of z; xi += alpha pi, pi = z + beta pi     13.5  338 / 184
+//   k_cg_op      q = D^T K : (D pi) by the stencils, p.Kp                   18.6  535 / 251
+//   k_r2c_edges  N2 pass of q                                                6.6  152 /  91
+//   k_n1         N1 pass into the block layout (+ alpha)                     6    146 /  76
+//   k_n0         N0 pass: s^ -= alpha q^, r.r, z^ = s^ / |r|^2, and back    12    294 / 156
+//   k_n1         inverse N1 pass (+ beta, the end of the solve)              6    175 /  79
+// Bound by HBM: 5.4-5.8 TB/s in double precision (the operator 4.7, the inverse
+// N1 pass 4.6) and 4.9-5.3 in single, where a plain copy reaches 4.4.  The
+// iteration that carried nine components through the N2 and N1 passes and the
+// residual in real space moved 81 words: 2180 / 1040 us against 1640 / 837 (sums
+// of the passes; 1.66 / 0.86 ms an iteration with the gaps between them).
 //
 // On small grids the passes are bound by launches and memory latency: k_plane
 // (fg_plane.hpp) takes the N1 and N0 passes in one, k_cg_lines

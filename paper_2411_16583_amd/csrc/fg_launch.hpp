@@ -84,8 +84,8 @@ struct N0Tile {
 template <typename R> N0Tile n0_tile(int N0, int N1, int M, int tile, int nc);
 // most partial sums per item that launch_n0 writes, for any tile
 inline long n0_max_parts(int N1, int M) { return 3L * ((long)M * N1 + N1 / 2 + 1); }
-// Whether a grid's planes fit k_plane in double precision (the working type
-// of every residual pass).
+// Whether a grid's planes fit k_plane in double precision (which a mixed plan's
+// scalar problems and wide iterations take too).
 bool plane_fits(int n0, int n1);
 // Planes of k_plane per workgroup: one, or several small ones where that
 // leaves 512 workgroups.

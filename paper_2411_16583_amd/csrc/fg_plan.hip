@@ -72,7 +72,7 @@ int column_tile_cpt(int L, int M, int elem_bytes, int cpt) {
   return B;
 }
 
-// Built-in tile of the potential-form N0 pass: the largest power of two
+// Built-in tile of the CG's N0 pass: the largest power of two
 // dividing M whose workgroup (two columns per thread in single precision)
 // and LDS fit.
 int zgrad_tile(int L, int M, int elem_bytes) {
@@ -84,12 +84,10 @@ int zgrad_tile(int L, int M, int elem_bytes) {
   return B;
 }
 
-// The potential-form N0 pass in single precision at L = 256 uses the
-// two-stage 16 x 16 line with one column per thread (one LDS exchange per
-// transform instead of two; the pass with its kx = 0 kernel 162 -> 154 us at
-// 256^3);
-// elsewhere the line of zline_threads, two columns per thread in single
-// precision.
+// The CG's N0 pass in single precision at L = 256 uses the two-stage 16 x 16 line
+// with one column per thread (one LDS exchange per transform instead of two;
+// the pass of the nine-component iteration, 162 -> 154 us at 256^3); elsewhere
+// the line of zline_threads, two columns per thread in single precision.
 int zgrad_threads(int L, int elem_bytes) { return (elem_bytes == 8 && L == 256) ? Line<256>::T : zline_threads(L); }
 int zgrad_cpt(int L, int elem_bytes) { return (elem_bytes == 8 && L != 256) ? 2 : 1; }
 
@@ -431,7 +429,7 @@ template <typename R> void host_tables(const fg_plan* P, std::vector<char>& blob
     put(dev.post, w.data(), P->M * sizeof(cplx<R>));
   }
   // cos(q/2), (2/h) sin(q/2) and sin(q/2) at q = 2 pi m / n (the rotated
-  // vector and the half-voxel phase e^{i q/2} of the potential form)
+  // vector and the half-voxel phase e^{i q/2} of D)
   auto half = [&](int n, int count, double h, void* cptr, void* sptr, void* nptr) {
     std::vector<R> cc(count), ss(count), sn(count);
     for (int m = 0; m < count; ++m) {

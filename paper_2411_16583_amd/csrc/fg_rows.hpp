@@ -11,9 +11,15 @@
 // (c* = cos(q/2), s* = (2/h) sin(q/2), Phi = (q0 + q1 + q2) / 2) and keeps
 // eps |Y| whatever the voxel.
 //
-// Passes (words per voxel): N2 transform of nine components (18), k_rows_n1
-// (15: the two terms of a row that share the N0 factor cz are merged), k_rows_n0
-// (6 in, 3 to 6 out), once per Newton iteration.
+// Passes (words per voxel; us at 256^3): N2 transform of nine components (18;
+// 436), k_rows_n1 (15: the two terms of a row that share the N0 factor cz are
+// merged; 420), k_rows_n0 (6 in, 3 to 6 out; 324 into double, 260 into single),
+// bound by HBM at 4.8-5.5 TB/s, once per Newton iteration.  fg_residual (two
+// residuals and two stresses, us) with the differences in real space | here:
+// 256^3 2470 | 2910, 128^3 361 | 374, 96^3 182 | 202, 64^3 100 | 116, 16^3 84 | 84
+// (before the divergence form 3970, 552, 331, 169, 123).  |G*Y| of an equilibrated
+// field, which is rounding: 0.9e-15 to 3e-15 |Y| on voxels of 8:1 to 32:1 | 2.0e-16
+// to 2.5e-16 on every grid.
 #pragma once
 #include "fg_plane.hpp"
 
